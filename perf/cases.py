@@ -269,3 +269,150 @@ def tolerance(case):
     # 2.6e-7 in norm and 2.5e-6 of the root mean square in a single value; another order of the fp32 operations may
     # show a few times that.
     return {"rel": 2e-6, "max": 2e-5}
+
+
+# ---- the same results in 64 bits: the inputs of prepare(), the iteration written out in plain torch
+
+_MASK = 0xFFFFFFFF
+
+
+def _philox_normals(quads, a, b, tag, seed):
+    """Counter-addressed normals (Philox4x32-10, Box-Muller): (..., 4 * quads); a, b broadcast against the quads."""
+    c = [quads, a, b, torch.full_like(quads, tag)]
+    k0, k1 = seed & _MASK, (seed >> 32) & _MASK
+    for _ in range(10):
+        p0, p1 = c[0] * 0xD2511F53, c[2] * 0xCD9E8D57
+        c = [((p1 >> 32) & _MASK) ^ c[1] ^ k0, p1 & _MASK, ((p0 >> 32) & _MASK) ^ c[3] ^ k1, p0 & _MASK]
+        k0, k1 = (k0 + 0x9E3779B9) & _MASK, (k1 + 0xBB67AE85) & _MASK
+    u = [((w >> 9).double() + 0.5) * 2.0 ** -23 for w in c]
+    out = []
+    for r, t in ((u[0], u[1]), (u[2], u[3])):
+        radius, angle = torch.sqrt(-2.0 * torch.log(r)), 2.0 * math.pi * t
+        out += [radius * torch.cos(angle), radius * torch.sin(angle)]
+    return torch.stack(out, dim=-1).flatten(-2)
+
+
+def _normals_row(d, node, j, tag, seed):
+    """d normals of one node for counter word j, or (len(j), d) for a tensor of counter words."""
+    quads = torch.arange((d + 3) // 4, device="cuda")
+    if torch.is_tensor(j):
+        quads, j = quads.expand(j.numel(), -1), j.long()[:, None]
+    else:
+        j = torch.full_like(quads, j)
+    return _philox_normals(quads, torch.full_like(quads, node), j, tag, seed)[..., :d]
+
+
+def _mixed(y, topology, k):
+    n = y.shape[0]
+    tau = max(1, math.ceil(math.log2(n)))
+    rows = torch.arange(n, device=y.device)
+    if topology == "ring":
+        taps = [rows - 1, rows, rows + 1]
+    elif topology == "expo1":
+        taps = [rows, rows + 2 ** (k % tau)]
+    elif topology == "expo":
+        taps = [rows] + [rows + 2 ** j for j in range(tau)]
+    elif topology == "grid":   # a torus on the most nearly square factorisation
+        r = max(q for q in range(1, math.isqrt(n) + 1) if n % q == 0)
+        w = n // r
+        up, col = rows // w, rows % w
+        taps = [rows, up * w + (col + 1) % w, up * w + (col - 1) % w, (up + 1) % r * w + col, (up - 1) % r * w + col]
+    else:
+        return y
+    out = y[taps[0] % n]
+    for t in taps[1:]:
+        out += y[t % n]
+    return out.div_(len(taps))
+
+
+def _step64(case, x, m, g, k, average):
+    """x and momentum after iteration k's update and averaging; m is None without momentum."""
+    lr, mu = (float(torch.tensor(case[v], dtype=torch.float32)) for v in ("lr", "momentum"))
+    if m is None:
+        y = x - lr * g
+    else:
+        m = mu * m + g
+        y = x - lr * (g + mu * m if case.get("nesterov") else m)
+    if average:
+        return y.mean(0, keepdim=True).expand_as(y).contiguous(), m
+    return _mixed(y, case["topology"], k), m
+
+
+def _averages(case, k):
+    return case["topology"] == "full" or (case["H"] > 0 and (k + 1) % case["H"] == 0)
+
+
+def _spread(x):
+    return (x - x.mean(0, keepdim=True)).norm()
+
+
+def _terms(problem, z, target, count):
+    """Per-sample gradient coefficients and loss terms from margins z."""
+    if problem == "lsq":
+        return (z - target) / count, 0.5 * (z - target) ** 2 / count
+    return -target * torch.sigmoid(-target * z) / count, torch.nn.functional.softplus(-target * z) / count
+
+
+def _stored_grad(problem, feat, tgt, x, idx):
+    """Gradients and losses of all nodes over the rows idx (n, B), or over all rows."""
+    g, loss = torch.empty_like(x), torch.empty(x.shape[0], dtype=torch.float64, device=x.device)
+    for i in range(x.shape[0]):
+        h, t = (feat[i], tgt[i]) if idx is None else (feat[i][idx[i].long()], tgt[i][idx[i].long()])
+        h, t = h.double(), t.double()
+        coef, terms = _terms(problem, (h * x[i]).sum(1), t, h.shape[0])
+        g[i], loss[i] = (coef[:, None] * h).sum(0), terms.sum()
+    return g, loss
+
+
+def exact(case, seed):
+    state = prepare(case, seed)
+    sim, kind, n, d = state["sim"], case["kind"], case["n"], case["d"]
+    x = sim.X.double()
+    if kind == "metrics":
+        mean = x.mean(0)
+        return {"consensus": float(x.sub_(mean).norm()), "mean": mean}
+    m, g, more = None if sim.m is None else sim.M.double(), sim.G.double(), {}
+    if kind == "step":
+        x, m = _step64(case, x, m, g, 0, _averages(case, 0))
+    elif kind in ("calls", "loop"):
+        for k in range(case.get("iters", 1)):
+            for i in range(n):
+                g[i] = math.sqrt(_SYNTH_VAR) * _normals_row(d, i, k, 1, seed)
+            x, m = _step64(case, x, m, g, k, _averages(case, k))
+    elif kind == "virtual":
+        y, idx = state["y"], state["idx"][0].long()
+        for i in range(n):
+            h = _normals_row(d, i, idx[i], 2, seed) + math.sqrt(_MU_VAR) * _normals_row(d, i, 0, 3, seed)
+            coef, _ = _terms("logreg", (h * x[i]).sum(1), y[i][idx[i]].double(), case["B"])
+            g[i] = (coef[:, None] * h).sum(0)
+        x, m = _step64(case, x, m, g, 0, _averages(case, 0))
+        more["trace"] = _spread(x).reshape(1)
+    elif kind == "simulation":
+        trace = torch.empty(case["iters"], dtype=torch.float64, device="cuda")
+        for k in range(case["iters"]):
+            g, _ = _stored_grad("logreg", state["feat"], state["y"], x, state["idx"][k])
+            x, m = _step64(case, x, m, g, k, _averages(case, k))
+            trace[k] = _spread(x)
+        xbar = x.mean(0)
+        losses = _stored_grad("logreg", state["feat"], state["y"], xbar.expand(n, d).contiguous(), None)[1]
+        more.update(trace=trace, xbar=xbar, losses=losses, objective=losses.mean().reshape(1))
+    else:
+        period, since, first_loss = case["H"], 0, 0.0   # Algorithm 2, as prepare() enables it
+        for k in range(case["iters"]):
+            g, loss = _stored_grad(case["problem"], state["feat"], state["tgt"], x,
+                                   None if state["idx"] is None else state["idx"][k])
+            average = _averages(case, k)
+            if case["aga"]:
+                since += 1
+                average = since == period
+            x, m = _step64(case, x, m, g, k, average)
+            if case["aga"] and average:
+                since, mean_loss = 0, float(loss.mean())
+                if k < 8:
+                    first_loss = 0.5 * (first_loss + mean_loss)
+                else:
+                    period = min(64, max(1, math.ceil(first_loss / mean_loss * case["H"])))
+    out = {"x": x, "g": g, **more}
+    if m is not None:
+        out["m"] = m
+    return out
