@@ -503,39 +503,38 @@ static gpga_status run_step(gpga_ctx* c, bool global) {
     if (csr && !c->csr_ready)
         return fail(c, GPGA_ESTATE, "no mixing matrix attached (gpga_set_mixing_csr)");
 
-    const bool vec = aligned(c->x, 16) && aligned(c->x_new, 16) && aligned(c->g, 16) &&
-                     (!c->m || aligned(c->m, 16)) && (c->ld % 4 == 0);
     StepGeom ge;
     ge.x = c->x;
     ge.x_new = c->x_new;
     ge.m = c->m;
     ge.g = c->g;
     ge.ld = c->ld;
+    ge.d = c->d;
+    ge.ncols = 0;
+    ge.lead = 0;
     ge.n = c->n;
     ge.lr = scheduled_lr(c, c->k);
     ge.mu = c->mu;
-    const int64_t nv = vec ? c->d / 4 : 0;
-    const int64_t tail = c->d - nv * 4;
+    // 16-byte lanes whatever the alignment of the rows; only rows of fewer than 4 columns take 4-byte lanes.
+    // Rows that are not 16-byte aligned, 4-byte lanes and a pass of their own for the last columns against
+    // this: ring n = 64, d = 25 000 001 10.7 -> 5.9 ms (4-byte lanes are not paced); n = 16, d = 1 000 003
+    // 85 -> 65 us; grid n = 64, d = 4 100 001 2.60 -> 1.23 ms; W = I n = 64, d = 1 000 001 447 -> 219 us.
+    const int vec = c->d >= 4 ? 4 : 1;
     // Consensus trace of this iteration: 0 after a global average (all rows get the same
-    // bits); sums produced by the fused kernel itself when it stores whole columns in
-    // one vector pass; else one reduction pass over the new X.  Nothing here waits.
+    // bits); sums produced by the fused kernel itself when it stores whole columns once
+    // (no unit overlaps another: d is a multiple of the lane width); else one reduction
+    // pass over the new X.  Nothing here waits.
     const bool trace = c->trace && c->k < c->trace_cap;
     int64_t spread_count = 0;
     c->last_path = PATH_NONE;
     c->last_paced = 0;
     c->last_trace_fused = 0;
-    hipError_t e = hipSuccess;
-    for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
-        ge.col0 = pass == 0 ? 0 : nv * 4;
-        ge.ncols = pass == 0 ? nv : tail;
-        if (ge.ncols == 0) continue;
-        const int v = pass == 0 ? 4 : 1;
-        const bool fuse = trace && !global && tail == 0;
-        e = global ? launch_step_global(c, ge, v)
-                   : csr ? launch_step_csr(c, ge, v, fuse ? c->partials + 1 : nullptr, fuse ? &spread_count : nullptr)
-                         : launch_step_walk(c, ge, mode, S, v, fuse ? c->partials + 1 : nullptr,
-                                            fuse ? &spread_count : nullptr);
-    }
+    const bool fuse = trace && !global && c->d % 4 == 0;
+    double* const spread = fuse ? c->partials + 1 : nullptr;
+    int64_t* const count = fuse ? &spread_count : nullptr;
+    hipError_t e = global ? launch_step_global(c, ge, vec)
+                          : csr ? launch_step_csr(c, ge, vec, spread, count)
+                                : launch_step_walk(c, ge, mode, S, vec, spread, count);
     if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
     float* t = c->x;
     c->x = c->x_new;

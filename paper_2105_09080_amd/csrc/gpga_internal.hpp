@@ -100,7 +100,7 @@ struct gpga_ctx {
     int opt_xcd_swizzle = 0;
     int opt_mix_lane_bytes = 0;  // sparse-W tile kernel: widest lane type allowed (0 = automatic, 4, 8, 16)
     // what the most recent step ran as (gpga_query "step_path" ...): written by the launchers
-    mutable int last_path = 0;        // StepPath; the vector pass of a step decides, a scalar tail pass does not overwrite it
+    mutable int last_path = 0;        // StepPath; the first kernel of a step decides (the second pass of a two-pass step does not overwrite it)
     mutable int last_paced = 0;       // 1 = that launch was paced
     mutable int last_lane_bytes = 0;  // bytes per lane of that launch (16, 8, 4)
     int last_trace_fused = 0;         // 1 = the step kernel itself produced the consensus sums of the trace entry
@@ -152,15 +152,16 @@ struct gpga_ctx {
     char err[256] = {0};
 };
 
-// Description of one fused step launch over columns [col0, col0 + ncols*V).
+// Description of one fused step launch over all d columns (column units: gpga_unit.hpp).
 struct StepGeom {
     const float* x;
     float* x_new;
     float* m;
     const float* g;
     int64_t ld;     // floats
-    int64_t col0;   // first column of this pass (floats)
-    int64_t ncols;  // columns of this pass in units of the vector type
+    int64_t d;      // columns (floats)
+    int64_t ncols;  // column units: d / V rounded up; set by the launcher of the kernel that runs
+    int32_t lead;   // lanes the units are shifted to the right (0 or 1)
     int32_t n;
     float lr, mu;
 };
@@ -209,6 +210,12 @@ hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B,
 // small_run_fits tells whether the context's problem and sizes qualify.
 bool small_run_fits(const gpga_ctx* c, const int32_t* idx, int32_t B);
 hipError_t launch_small_run(const gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, const float* lr);
+// How the global-average kernel adds the rows of a column on this context: RL row lanes x wpb wavefronts share the
+// rows, each in batches of U.
+struct GlobalOrder {
+    int32_t RL, wpb, U;
+};
+GlobalOrder global_order(const gpga_ctx* c);
 // Column chunks per node of the virtual-feature margin pass; it needs n * B * chunks doubles in c->partials.
 int64_t virtual_margin_chunks(const gpga_ctx* c);
 

@@ -25,17 +25,9 @@
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_spread.hpp"
+#include "gpga_unit.hpp"
 
 namespace {
-
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
-    return __builtin_nontemporal_load(p);
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(T* p, T v) {
-    __builtin_nontemporal_store(v, p);
-}
 
 // x^(k+1/2) from x, g and the new momentum value (MOM: 0 none, 1 heavy-ball, 2 Nesterov).
 template <int MOM, typename T>
@@ -103,7 +95,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
             s_val[p] = a.w.val[p];
         }
     }
-    const int64_t ldT = a.ge.ld / V;
+    const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     constexpr uint32_t kLoadUnits = MOM ? 4u : 2u;  // 4-byte streams per row in phase 1 (reads + the m store)
     const PaceRun run = pace_begin(a.pace, lane);
@@ -114,30 +106,30 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
     // A paced launch has exactly the resident workgroups: they then read the same row group
     // of their tiles at the same time and later store the same output rows.
     for (int64_t tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
-        const int64_t col = tile * kWave + lane;
-        const bool on = col < a.ge.ncols;
+        const int64_t col = unit_column<T>(a.ge, tile, kWave, lane);
+        const bool on = unit_on(a.ge, tile, kWave, lane);
 
-        const T* __restrict__ xp = reinterpret_cast<const T*>(a.ge.x + a.ge.col0) + col;
-        const T* __restrict__ gp = reinterpret_cast<const T*>(a.ge.g + a.ge.col0) + col;
-        T* __restrict__ mp = MOM ? reinterpret_cast<T*>(a.ge.m + a.ge.col0) + col : nullptr;
-        T* __restrict__ xnp = reinterpret_cast<T*>(a.ge.x_new + a.ge.col0) + col;
+        const float* __restrict__ xp = a.ge.x + col;
+        const float* __restrict__ gp = a.ge.g + col;
+        float* __restrict__ mp = MOM ? a.ge.m + col : nullptr;
+        float* __restrict__ xnp = a.ge.x_new + col;
 
         // Phase 1: rows wave, wave + W, ... : local update, y into LDS.
         // Whole row groups of a whole tile first, in a loop of their own without lane or row
         // predicates: all the loads of a group are issued back to back before the first use,
         // and nothing makes them wait for the stores of the group before.
         int base = wave;
-        if ((tile + 1) * kWave <= a.ge.ncols) {  // every lane has a column
+        if (whole_units(a.ge, tile, kWave)) {  // every lane has a column
             for (; base + (kTileUnroll - 1) * kTileWaves < n; base += kTileWaves * kTileUnroll) {
                 T xv[kTileUnroll], mv[kTileUnroll], gv[kTileUnroll];
                 pace_wait(run, units_done);
                 units_done += kTileUnroll * kLoadUnits;
 #pragma unroll
                 for (int u = 0; u < kTileUnroll; ++u) {
-                    const int64_t off = (int64_t)(base + u * kTileWaves) * ldT;
-                    xv[u] = ld_stream(xp + off);
-                    if (MOM) mv[u] = ld_stream(mp + off);
-                    gv[u] = ld_stream(gp + off);
+                    const int64_t off = (int64_t)(base + u * kTileWaves) * ld;
+                    xv[u] = ld_unit<T>(xp + off);
+                    if (MOM) mv[u] = ld_unit<T>(mp + off);
+                    gv[u] = ld_unit<T>(gp + off);
                 }
 #pragma unroll
                 for (int u = 0; u < kTileUnroll; ++u) {
@@ -145,7 +137,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
                     T mom = gv[u];
                     if (MOM) {
                         mom = mu * mv[u] + gv[u];
-                        st_stream(mp + (int64_t)row * ldT, mom);
+                        st_unit<T>(mp + (int64_t)row * ld, mom);
                     }
                     sy[row * kWave + lane] = half_step<MOM>(xv[u], gv[u], mom, lr, mu);
                 }
@@ -160,10 +152,10 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
             for (int u = 0; u < kTileUnroll; ++u) {
                 const int row = base + u * kTileWaves;
                 if (row < n && on) {
-                    const int64_t off = (int64_t)row * ldT;
-                    xv[u] = ld_stream(xp + off);
-                    if (MOM) mv[u] = ld_stream(mp + off);
-                    gv[u] = ld_stream(gp + off);
+                    const int64_t off = (int64_t)row * ld;
+                    xv[u] = ld_unit<T>(xp + off);
+                    if (MOM) mv[u] = ld_unit<T>(mp + off);
+                    gv[u] = ld_unit<T>(gp + off);
                 }
             }
 #pragma unroll
@@ -175,7 +167,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
                         T mom = gv[u];
                         if (MOM) {
                             mom = mu * mv[u] + gv[u];
-                            st_stream(mp + (int64_t)row * ldT, mom);
+                            st_unit<T>(mp + (int64_t)row * ld, mom);
                         }
                         y = half_step<MOM>(xv[u], gv[u], mom, lr, mu);
                     }
@@ -226,7 +218,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
             }
             pace_wait(run, units_done);
             units_done += 1u;
-            if (on) st_stream(xnp + (int64_t)i * ldT, acc);
+            if (on) st_unit<T>(xnp + (int64_t)i * ld, acc);
             if (TRACE) spread.add(acc);  // lanes without a column hold zeros throughout
         }
         __syncthreads();  // the next tile's phase 1 overwrites the staged y
@@ -290,7 +282,7 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NW = blockDim.x >> 6;
     const int n = a.ge.n, band = a.band, RB = a.ring_rows;
-    const int64_t ldT = a.ge.ld / V;
+    const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     constexpr uint32_t kRowUnits = MOM ? 5u : 3u;
     const PaceRun run = pace_begin(a.pace, lane);
@@ -308,19 +300,19 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
     };
 
     for (int64_t tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
-        const int64_t col = tile * kWave + lane;
-        const bool on = col < a.ge.ncols;
-        const T* __restrict__ xp = reinterpret_cast<const T*>(a.ge.x + a.ge.col0) + col;
-        const T* __restrict__ gp = reinterpret_cast<const T*>(a.ge.g + a.ge.col0) + col;
-        T* __restrict__ mp = MOM ? reinterpret_cast<T*>(a.ge.m + a.ge.col0) + col : nullptr;
-        T* __restrict__ xnp = reinterpret_cast<T*>(a.ge.x_new + a.ge.col0) + col;
+        const int64_t col = unit_column<T>(a.ge, tile, kWave, lane);
+        const bool on = unit_on(a.ge, tile, kWave, lane);
+        const float* __restrict__ xp = a.ge.x + col;
+        const float* __restrict__ gp = a.ge.g + col;
+        float* __restrict__ mp = MOM ? a.ge.m + col : nullptr;
+        float* __restrict__ xnp = a.ge.x_new + col;
 
         auto load_row = [&](Row& r, int row) {  // row is the same for the whole wavefront
             if (row < n && on) {
-                const int64_t o = (int64_t)row * ldT;
-                r.xv = ld_stream(xp + o);
-                if (MOM) r.mv = ld_stream(mp + o);
-                r.gv = ld_stream(gp + o);
+                const int64_t o = (int64_t)row * ld;
+                r.xv = ld_unit<T>(xp + o);
+                if (MOM) r.mv = ld_unit<T>(mp + o);
+                r.gv = ld_unit<T>(gp + o);
             }
         };
         auto load_taps = [&](Taps& t, int i) {  // i uniform; rows outside [0, n) have no taps
@@ -377,10 +369,10 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
                 tp.cnt = a.K;
                 pace_wait(run, units_done);
                 units_done += kRowUnits;
-                const int64_t o = (int64_t)row * ldT;
-                r.xv = ld_stream(xp + o);
-                if (MOM) r.mv = ld_stream(mp + o);
-                r.gv = ld_stream(gp + o);
+                const int64_t o = (int64_t)row * ld;
+                r.xv = ld_unit<T>(xp + o);
+                if (MOM) r.mv = ld_unit<T>(mp + o);
+                r.gv = ld_unit<T>(gp + o);
             } else if (t < nb) {
                 load_taps(tp, t * NW + wave - band);
                 pace_wait(run, units_done);
@@ -400,7 +392,7 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
                     T mom = cur.gv;
                     if (MOM) {
                         mom = mu * cur.mv + cur.gv;
-                        st_stream(mp + (int64_t)row * ldT, mom);
+                        st_unit<T>(mp + (int64_t)row * ld, mom);
                     }
                     y = half_step<MOM>(cur.xv, cur.gv, mom, lr, mu);
                 }
@@ -419,13 +411,13 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
                     if (slot >= RB) slot -= RB;
                     return ring[slot * kWave + lane];
                 });
-                if (HOT || on) st_stream(xnp + (int64_t)i * ldT, acc);
+                if (HOT || on) st_unit<T>(xnp + (int64_t)i * ld, acc);
                 if (TRACE) spread.add(acc);  // lanes without a column hold zeros throughout
             }
             sb += NW;
             if (sb >= RB) sb -= RB;
         };
-        const bool whole_tile = (tile + 1) * kWave <= a.ge.ncols;
+        const bool whole_tile = whole_units(a.ge, tile, kWave);
         const int nb_full = n / NW;                        // batches whose rows all exist
         const int t_hot = (2 * band + NW - 1) / NW;        // from this batch on every wavefront has an output row
 #pragma unroll
@@ -474,7 +466,7 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
                 if (j < 0) return ring_row(j + n);
                 return k < band ? ring_row(j) : head[j * kWave + lane];
             });
-            if (on) st_stream(xnp + (int64_t)i * ldT, acc);
+            if (on) st_unit<T>(xnp + (int64_t)i * ld, acc);
             if (TRACE) spread.add(acc);
         }
         __syncthreads();  // the next tile overwrites the ring and the kept rows
@@ -502,12 +494,9 @@ __global__ void __launch_bounds__(kWave* 8) k_step_band(const BandArgs a) {
 // rows.  That only works while the tile's y (n x LANES x lane bytes) is well below the 4 MiB of an
 // L2, so tiles get narrower as n grows.
 template <typename T, int LANES>
-__global__ void __launch_bounds__(256) k_spmm_rows(const float* __restrict__ y, float* __restrict__ x_new,
-                                                   int64_t ld, int64_t col0, int64_t ncols, int32_t n,
-                                                   int64_t tiles, const CsrDev w) {
-    constexpr int V = sizeof(T) / sizeof(float);
+__global__ void __launch_bounds__(256) k_spmm_rows(const StepGeom ge, int64_t tiles, const CsrDev w) {
     constexpr int R = 256 / LANES;                   // rows per workgroup
-    const int64_t ldT = ld / V;
+    const int32_t n = ge.n;
     const int64_t bid = blockIdx.x;
     const int64_t ng = (n + R - 1) / R;              // row groups per tile
     const int64_t full = (tiles >> 3) << 3;          // tiles covered by whole groups of 8
@@ -524,22 +513,24 @@ __global__ void __launch_bounds__(256) k_spmm_rows(const float* __restrict__ y, 
     }
     // a row per wavefront or more: the row index is uniform in a wavefront (scalar loads of the neighbour list)
     const int i = g * R + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / LANES));
-    const int64_t col = tile * LANES + (threadIdx.x % LANES);
-    if (col >= ncols || i >= n) return;
-    const T* __restrict__ yb = reinterpret_cast<const T*>(y + col0) + col;
+    const int lane = threadIdx.x % LANES;
+    if (!unit_on(ge, tile, LANES, lane) || i >= n) return;
+    const int64_t col = unit_column<T>(ge, tile, LANES, lane);
+    const float* __restrict__ yb = ge.x + col;       // y = x^(k+1/2), left there by the first pass
     const int p0 = w.ptr[i], p1 = w.ptr[i + 1];
     T acc = T(0);
-    for (int p = p0; p < p1; ++p) acc += w.val[p] * yb[(int64_t)w.col[p] * ldT];
-    st_stream(reinterpret_cast<T*>(x_new + col0) + col + (int64_t)i * ldT, acc);
+    for (int p = p0; p < p1; ++p) acc += w.val[p] * ld_unit_cached<T>(yb + (int64_t)w.col[p] * ge.ld);
+    st_unit<T>(ge.x_new + col + (int64_t)i * ge.ld, acc);
 }
 
 template <typename T, int LANES>
-hipError_t launch_spmm(const gpga_ctx* c, const StepGeom& ge, const CsrDev& w) {
-    const int64_t tiles = (ge.ncols + LANES - 1) / LANES;
+hipError_t launch_spmm(const gpga_ctx* c, const StepGeom& geom, const CsrDev& w) {
+    StepGeom ge = geom;
+    set_units(&ge, (int)(sizeof(T) / sizeof(float)), LANES);
+    const int64_t tiles = unit_tiles(ge, LANES);
     const int64_t ng = ((int64_t)ge.n + 256 / LANES - 1) / (256 / LANES);
     if (tiles * ng > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_spmm_rows<T, LANES>), dim3((unsigned)(tiles * ng)), dim3(256), 0, c->stream, ge.x, ge.x_new,
-                       ge.ld, ge.col0, ge.ncols, ge.n, tiles, w);
+    hipLaunchKernelGGL((k_spmm_rows<T, LANES>), dim3((unsigned)(tiles * ng)), dim3(256), 0, c->stream, ge, tiles, w);
     return hipGetLastError();
 }
 
@@ -606,8 +597,9 @@ hipError_t launch_tile(const gpga_ctx* c, const StepGeom& ge, const CsrDev& w, i
     c->note_path(PATH_TILE, (int)sizeof(T));
     TileArgs a;
     a.ge = ge;
+    set_units(&a.ge, (int)(sizeof(T) / sizeof(float)), kWave);
     a.w = w;
-    a.tiles = (ge.ncols + kWave - 1) / kWave;
+    a.tiles = unit_tiles(a.ge, kWave);
     a.spread_partials = nullptr;
     if (a.tiles > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.nnz = (int32_t)c->csr.col.size();
@@ -695,10 +687,11 @@ hipError_t launch_band(const gpga_ctx* c, const StepGeom& ge, int mom, int waves
     c->note_path(PATH_BAND, (int)sizeof(T));
     BandArgs a;
     a.ge = ge;
+    set_units(&a.ge, (int)(sizeof(T) / sizeof(float)), kWave);
     a.off = c->csr_off_d;
     a.val = c->csr_ellval_d;
     a.K = c->csr_max_row;
-    a.tiles = (ge.ncols + kWave - 1) / kWave;
+    a.tiles = unit_tiles(a.ge, kWave);
     a.band = c->csr_band;
     a.ring_rows = 2 * c->csr_band + 2 * waves;
     a.spread_partials = nullptr;
@@ -730,7 +723,6 @@ int band_lane_bytes(const gpga_ctx* c, int vec, int waves) {
 hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, double* spread_partials,
                            int64_t* spread_count) {
     if (spread_count) *spread_count = 0;
-    if (ge.ncols <= 0) return hipSuccess;
     if (!c->csr_ready) return hipErrorInvalidValue;
     const CsrDev w{c->csr_ptr_d, c->csr_col_d, c->csr_val_d};
     const int mom = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
@@ -754,31 +746,15 @@ hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, doubl
     const int band_bytes = (!two_pass && c->opt_mix_band != 0 && (c->opt_mix_band == 1 || (big && !wide_tile_fits)))
                                ? band_lane_bytes(c, vec, band_waves) : 0;
     if (band_bytes) {
-        StepGeom g2 = ge;
-        if (vec == 4 && band_bytes == 16) return launch_band<v4f>(c, ge, mom, band_waves, spread_partials, spread_count);
-        if (vec == 4 && band_bytes == 8) {
-            g2.ncols = ge.ncols * 2;
-            return launch_band<v2f>(c, g2, mom, band_waves, spread_partials, spread_count);
-        }
-        if (vec == 4) g2.ncols = ge.ncols * 4;
-        return launch_band<float>(c, g2, mom, band_waves, spread_partials, spread_count);
+        if (band_bytes == 16) return launch_band<v4f>(c, ge, mom, band_waves, spread_partials, spread_count);
+        if (band_bytes == 8) return launch_band<v2f>(c, ge, mom, band_waves, spread_partials, spread_count);
+        return launch_band<float>(c, ge, mom, band_waves, spread_partials, spread_count);
     }
-    if (vec == 4) {
-        // 16-byte aligned rows also satisfy the narrower lane types.  8-byte lanes only on request
-        // ("mix_lane_bytes" = 8): they were the slowest of the three wherever two of them fit.
-        StepGeom g2 = ge;
-        if (!two_pass && lane_cap >= 16 && n * kWave * sizeof(v4f) <= cap)
-            return launch_tile<v4f>(c, ge, w, mom, spread_partials, spread_count);
-        if (!two_pass && lane_cap == 8 && n * kWave * sizeof(v2f) <= cap) {
-            g2.ncols = ge.ncols * 2;
-            return launch_tile<v2f>(c, g2, w, mom, spread_partials, spread_count);
-        }
-        if (!two_pass && n * kWave * sizeof(float) <= cap) {
-            g2.ncols = ge.ncols * 4;
-            return launch_tile<float>(c, g2, w, mom, spread_partials, spread_count);
-        }
-        return launch_two_pass<v4f>(c, ge, w, 4);
-    }
+    // 8-byte lanes only on request ("mix_lane_bytes" = 8): they were the slowest of the three wherever two of them fit.
+    if (!two_pass && vec == 4 && lane_cap >= 16 && n * kWave * sizeof(v4f) <= cap)
+        return launch_tile<v4f>(c, ge, w, mom, spread_partials, spread_count);
+    if (!two_pass && vec == 4 && lane_cap == 8 && n * kWave * sizeof(v2f) <= cap)
+        return launch_tile<v2f>(c, ge, w, mom, spread_partials, spread_count);
     if (!two_pass && n * kWave * sizeof(float) <= cap) return launch_tile<float>(c, ge, w, mom, spread_partials, spread_count);
-    return launch_two_pass<float>(c, ge, w, 1);
+    return vec == 4 ? launch_two_pass<v4f>(c, ge, w, 4) : launch_two_pass<float>(c, ge, w, 1);
 }

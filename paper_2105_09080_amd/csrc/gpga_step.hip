@@ -41,31 +41,9 @@
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_spread.hpp"
+#include "gpga_unit.hpp"
 
 namespace {
-
-#ifndef GPGA_NT_LOAD
-#define GPGA_NT_LOAD 1
-#endif
-#ifndef GPGA_NT_STORE
-#define GPGA_NT_STORE 1
-#endif
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
-#if GPGA_NT_LOAD
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(T* p, T v) {
-#if GPGA_NT_STORE
-    __builtin_nontemporal_store(v, p);
-#else
-    *p = v;
-#endif
-}
 
 __device__ __forceinline__ float shfl_xor_t(float v, int off) { return __shfl_xor(v, off, kWave); }
 __device__ __forceinline__ v4f shfl_xor_t(v4f v, int off) {
@@ -125,7 +103,6 @@ __device__ __forceinline__ int64_t logical_block(int64_t bid, int64_t gx, int xc
 // walker covers whole columns (one cycle, one segment), which the launcher checks.
 template <typename T, int MODE, int MOM, int U, bool TRACE = false>
 __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a) {
-    constexpr int V = sizeof(T) / sizeof(float);
     __shared__ T s_first[kMaxWaves][kWave];
     __shared__ T s_last[kMaxWaves][kWave];
     __shared__ double s_spread[kMaxWaves];
@@ -140,7 +117,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a
     const int walk_l = wave - tile_l * wpb;
     const int n = a.ge.n;
     const int S = a.S;
-    const int64_t ldT = a.ge.ld / V;  // row stride in units of T
+    const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     const float third = 1.0f / 3.0f;
     constexpr uint32_t kRowUnits = MOM ? 5u : 3u;  // 4-byte streams touched per row
@@ -171,16 +148,15 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a
         const int row_first = (int)(((int64_t)cyc + (int64_t)p0 * S) % n);
 
         const int64_t tile = logical_block(bx, a.gx, a.xcd) * a.tpb + tile_l;
-        const int64_t col = tile * kWave + lane;
-        const bool on = walker_on && (col < a.ge.ncols);
-        const int64_t coff = col;
+        const bool on = walker_on && unit_on(a.ge, tile, kWave, lane);
+        const int64_t col = unit_column<T>(a.ge, tile, kWave, lane);
 
-        const T* __restrict__ xp = reinterpret_cast<const T*>(a.ge.x + a.ge.col0) + coff;
-        const T* __restrict__ gp = reinterpret_cast<const T*>(a.ge.g + a.ge.col0) + coff;
-        T* __restrict__ mp = MOM ? reinterpret_cast<T*>(a.ge.m + a.ge.col0) + coff : nullptr;
-        T* __restrict__ xnp = reinterpret_cast<T*>(a.ge.x_new + a.ge.col0) + coff;
+        const float* __restrict__ xp = a.ge.x + col;
+        const float* __restrict__ gp = a.ge.g + col;
+        float* __restrict__ mp = MOM ? a.ge.m + col : nullptr;
+        float* __restrict__ xnp = a.ge.x_new + col;
         auto put = [&](int rw, const T& v) {
-            st_stream(xnp + (int64_t)rw * ldT, v);
+            st_unit<T>(xnp + (int64_t)rw * ld, v);
             if (TRACE) spread.add(v);
         };
 
@@ -191,10 +167,10 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a
         // One row: issue its three loads / turn loaded values into y (and store m).
         auto load_row = [&](T& xv, T& mv, T& gv, int& rw) {
             rw = row;
-            const int64_t off = (int64_t)row * ldT;
-            xv = ld_stream(xp + off);
-            if (MOM) mv = ld_stream(mp + off);
-            gv = ld_stream(gp + off);
+            const int64_t off = (int64_t)row * ld;
+            xv = ld_unit<T>(xp + off);
+            if (MOM) mv = ld_unit<T>(mp + off);
+            gv = ld_unit<T>(gp + off);
             row += S;
             if (row >= n) row -= n;
         };
@@ -202,7 +178,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a
             T mom = gv;
             if (MOM) {
                 mom = mu * mv + gv;
-                st_stream(mp + (int64_t)rw * ldT, mom);
+                st_unit<T>(mp + (int64_t)rw * ld, mom);
             }
             return half_step<MOM>(xv, gv, mom, lr, mu);
         };
@@ -241,16 +217,16 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_walk(const WalkArgs a
                 if (len >= 2) load_row(x1, m1, g1, r1);
                 if (TRACE && cc == 0) spread.reset(x0);
                 yf = y_of(x0, m0, g0, r0);
-                if (MODE == MODE_SELF) st_stream(xnp + (int64_t)r0 * ldT, yf);
+                if (MODE == MODE_SELF) st_unit<T>(xnp + (int64_t)r0 * ld, yf);
                 // in place: over the old iterate, through a pointer derived from the one it was read with
-                if (MODE == MODE_INPLACE) st_stream(const_cast<T*>(xp) + (int64_t)r0 * ldT, yf);
+                if (MODE == MODE_INPLACE) st_unit<T>(const_cast<float*>(xp) + (int64_t)r0 * ld, yf);
                 pc = yf;
                 row_prev = r0;
                 if (len >= 2) {
                     ys = y_of(x1, m1, g1, r1);
                     if (MODE == MODE_PEER) put(r0, (yf + ys) * 0.5f);
-                    if (MODE == MODE_SELF) st_stream(xnp + (int64_t)r1 * ldT, ys);
-                    if (MODE == MODE_INPLACE) st_stream(const_cast<T*>(xp) + (int64_t)r1 * ldT, ys);
+                    if (MODE == MODE_SELF) st_unit<T>(xnp + (int64_t)r1 * ld, ys);
+                    if (MODE == MODE_INPLACE) st_unit<T>(const_cast<float*>(xp) + (int64_t)r1 * ld, ys);
                     pp = yf;
                     pc = ys;
                     row_prev = r1;
@@ -373,20 +349,20 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_cycles(const CycleArg
     const int waves = blockDim.x >> 6;
     const int n = a.ge.n;
     const int S = a.S;
-    const int64_t ldT = a.ge.ld / 4;
+    const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     constexpr uint32_t kRowUnits = MOM ? 5u : 3u;
     const PaceRun run = pace_begin(a.pace, lane);
     uint32_t units_done = 0;
 
     for (int64_t w = blockIdx.x; w < a.gx; w += gridDim.x) {
-        const int64_t col = (w * waves + wave) * kWave + lane;
-        if (col >= a.ge.ncols) continue;
-        if (TRACE) spread.reset(reinterpret_cast<const T*>(a.ge.x + a.ge.col0)[col]);  // row 0 of the old iterate
-        const T* __restrict__ xp = reinterpret_cast<const T*>(a.ge.x + a.ge.col0) + col;
-        const T* __restrict__ gp = reinterpret_cast<const T*>(a.ge.g + a.ge.col0) + col;
-        T* __restrict__ mp = MOM ? reinterpret_cast<T*>(a.ge.m + a.ge.col0) + col : nullptr;
-        T* __restrict__ xnp = reinterpret_cast<T*>(a.ge.x_new + a.ge.col0) + col;
+        if (!unit_on(a.ge, w * waves + wave, kWave, lane)) continue;
+        const int64_t col = unit_column<T>(a.ge, w * waves + wave, kWave, lane);
+        if (TRACE) spread.reset(ld_unit_cached<T>(a.ge.x + col));  // row 0 of the old iterate
+        const float* __restrict__ xp = a.ge.x + col;
+        const float* __restrict__ gp = a.ge.g + col;
+        float* __restrict__ mp = MOM ? a.ge.m + col : nullptr;
+        float* __restrict__ xnp = a.ge.x_new + col;
 
         struct Row {
             T xv, mv, gv;
@@ -398,10 +374,10 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_cycles(const CycleArg
             pace_wait(run, units_done);
             units_done += kRowUnits;
             b.rw = next_row;
-            const int64_t off = (int64_t)next_row * ldT;
-            b.xv = ld_stream(xp + off);
-            if (MOM) b.mv = ld_stream(mp + off);
-            b.gv = ld_stream(gp + off);
+            const int64_t off = (int64_t)next_row * ld;
+            b.xv = ld_unit<T>(xp + off);
+            if (MOM) b.mv = ld_unit<T>(mp + off);
+            b.gv = ld_unit<T>(gp + off);
             if (++next_pos == L) {  // on to the first row of the next cycle
                 next_pos = 0;
                 next_row = ++next_cyc;
@@ -416,19 +392,19 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_cycles(const CycleArg
             T mom = b.gv;
             if (MOM) {
                 mom = mu * b.mv + b.gv;
-                st_stream(mp + (int64_t)b.rw * ldT, mom);
+                st_unit<T>(mp + (int64_t)b.rw * ld, mom);
             }
             const T y = half_step<MOM>(b.xv, b.gv, mom, lr, mu);
             if (pos == 0) {
                 yf = y;
             } else {
                 const T v = (pc + y) * 0.5f;
-                st_stream(xnp + (int64_t)row_prev * ldT, v);
+                st_unit<T>(xnp + (int64_t)row_prev * ld, v);
                 if (TRACE) spread.add(v);
             }
             if (pos == L - 1) {
                 const T v = (y + yf) * 0.5f;
-                st_stream(xnp + (int64_t)b.rw * ldT, v);
+                st_unit<T>(xnp + (int64_t)b.rw * ld, v);
                 if (TRACE) spread.add(v);
             }
             pc = y;
@@ -490,7 +466,6 @@ struct GlobalArgs {
 
 template <typename T, int MOM, int U>
 __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalArgs a) {
-    constexpr int V = sizeof(T) / sizeof(float);
     __shared__ T s_part[kMaxWaves][kWave];
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -505,7 +480,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
     const int n = a.ge.n;
     const int RS = a.RL * wpb;            // row splitters per column
     const int r0 = wrow * a.RL + lane_r;  // this lane's first row
-    const int64_t ldT = a.ge.ld / V;  // row stride in units of T
+    const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     constexpr uint32_t kReadUnits = MOM ? 4u : 2u;  // 4-byte streams per row in the read phase
     const PaceRun run = pace_begin(a.pace, lane);
@@ -513,7 +488,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
 
     // deferred mean of the previous whole tile of this wavefront (see below)
     T prev_mean = T(0);
-    T* prev_xnp = nullptr;
+    float* prev_xnp = nullptr;
     bool have_prev = false;  // wave-uniform
     auto flush_prev = [&]() {
         for (int row = 0; row < n; row += U) {
@@ -521,20 +496,19 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
             units_done += U;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (row + u < n) st_stream(prev_xnp + (int64_t)(row + u) * ldT, prev_mean);
+                if (row + u < n) st_unit<T>(prev_xnp + (int64_t)(row + u) * ld, prev_mean);
         }
     };
 
     for (int64_t bx = blockIdx.x; bx < a.gx; bx += gridDim.x) {
         const int64_t tile = logical_block(bx, a.gx, a.xcd) * a.tpb + tile_l;
-        const int64_t col = tile * CL + lane_c;
-        const bool on = col < a.ge.ncols;
-        const int64_t coff = col;
+        const bool on = unit_on(a.ge, tile, CL, lane_c);
+        const int64_t col = unit_column<T>(a.ge, tile, CL, lane_c);
 
-        const T* __restrict__ xp = reinterpret_cast<const T*>(a.ge.x + a.ge.col0) + coff;
-        const T* __restrict__ gp = reinterpret_cast<const T*>(a.ge.g + a.ge.col0) + coff;
-        T* __restrict__ mp = MOM ? reinterpret_cast<T*>(a.ge.m + a.ge.col0) + coff : nullptr;
-        T* __restrict__ xnp = reinterpret_cast<T*>(a.ge.x_new + a.ge.col0) + coff;
+        const float* __restrict__ xp = a.ge.x + col;
+        const float* __restrict__ gp = a.ge.g + col;
+        float* __restrict__ mp = MOM ? a.ge.m + col : nullptr;
+        float* __restrict__ xnp = a.ge.x_new + col;
 
         T sum = T(0);
         // One lane walks all n rows of its column group (large problems).  The n copies of
@@ -542,7 +516,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
         // stored row by row while the next tile of this wavefront is being read, so that
         // the chip sees the same steady 3-read : 2-write mix as in the gossip walk.  Only
         // whole tiles take this path (the ragged last tile falls through to the plain one).
-        const bool whole_tile = (tile + 1) * CL <= a.ge.ncols;  // wave-uniform
+        const bool whole_tile = whole_units(a.ge, tile, CL);  // wave-uniform
         if (RS == 1 && whole_tile) {
             // Same software pipeline as the gossip walk: next batch's loads are issued
             // ahead of this batch's stores; branch-free hot loop.
@@ -558,10 +532,10 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                     units_done += U * kUnits;
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int64_t off = (int64_t)(row + u) * ldT;
-                        b.xv[u] = ld_stream(xp + off);
-                        if (MOM) b.mv[u] = ld_stream(mp + off);
-                        b.gv[u] = ld_stream(gp + off);
+                        const int64_t off = (int64_t)(row + u) * ld;
+                        b.xv[u] = ld_unit<T>(xp + off);
+                        if (MOM) b.mv[u] = ld_unit<T>(mp + off);
+                        b.gv[u] = ld_unit<T>(gp + off);
                     }
                     row += U;
                 };
@@ -572,9 +546,9 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                         T mom = b.gv[u];
                         if (MOM) {
                             mom = mu * b.mv[u] + b.gv[u];
-                            st_stream(mp + (int64_t)(first_row + u) * ldT, mom);
+                            st_unit<T>(mp + (int64_t)(first_row + u) * ld, mom);
                         }
-                        if (WP) st_stream(prev_xnp + (int64_t)(first_row + u) * ldT, prev_mean);
+                        if (WP) st_unit<T>(prev_xnp + (int64_t)(first_row + u) * ld, prev_mean);
                         part += half_step<MOM>(b.xv[u], b.gv[u], mom, lr, mu);
                     }
                     sum += part;
@@ -608,15 +582,15 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                     }
                 }
                 for (; done < n; ++done) {
-                    const int64_t off = (int64_t)done * ldT;
-                    const T xv = ld_stream(xp + off);
-                    const T gv = ld_stream(gp + off);
+                    const int64_t off = (int64_t)done * ld;
+                    const T xv = ld_unit<T>(xp + off);
+                    const T gv = ld_unit<T>(gp + off);
                     T mom = gv;
                     if (MOM) {
-                        mom = mu * ld_stream(mp + off) + gv;
-                        st_stream(mp + off, mom);
+                        mom = mu * ld_unit<T>(mp + off) + gv;
+                        st_unit<T>(mp + off, mom);
                     }
-                    if (WP) st_stream(prev_xnp + off, prev_mean);
+                    if (WP) st_unit<T>(prev_xnp + off, prev_mean);
                     units_done += kUnits;
                     sum += half_step<MOM>(xv, gv, mom, lr, mu);
                 }
@@ -640,10 +614,10 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                 for (int u = 0; u < U; ++u) {
                     const int row = base + u * RS;
                     if (row < n) {
-                        const int64_t off = (int64_t)row * ldT;
-                        xv[u] = ld_stream(xp + off);
-                        if (MOM) mv[u] = ld_stream(mp + off);
-                        gv[u] = ld_stream(gp + off);
+                        const int64_t off = (int64_t)row * ld;
+                        xv[u] = ld_unit<T>(xp + off);
+                        if (MOM) mv[u] = ld_unit<T>(mp + off);
+                        gv[u] = ld_unit<T>(gp + off);
                     }
                 }
                 T part = T(0);
@@ -654,7 +628,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                         T mom = gv[u];
                         if (MOM) {
                             mom = mu * mv[u] + gv[u];
-                            st_stream(mp + (int64_t)row * ldT, mom);
+                            st_unit<T>(mp + (int64_t)row * ld, mom);
                         }
                         part += half_step<MOM>(xv[u], gv[u], mom, lr, mu);
                     }
@@ -685,7 +659,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int row = base + u * RS;
-                    if (row < n) st_stream(xnp + (int64_t)row * ldT, mean);
+                    if (row < n) st_unit<T>(xnp + (int64_t)row * ld, mean);
                 }
             }
         }
@@ -838,10 +812,11 @@ LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool w
 
 }  // namespace
 
-hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& ge, int mode, int32_t S, int vec,
+hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, int32_t S, int vec,
                             double* spread_partials, int64_t* spread_count) {
     if (spread_count) *spread_count = 0;
-    if (ge.ncols <= 0) return hipSuccess;
+    StepGeom ge = geom;
+    set_units(&ge, vec, kWave);
     const int n = ge.n;
     WalkArgs a;
     a.ge = ge;
@@ -855,11 +830,11 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& ge, int mode, int
         a.L = n / a.C;
     }
     const int waves = c->opt_waves ? c->opt_waves : 4;
-    const int64_t tiles = (ge.ncols + kWave - 1) / kWave;
+    const int64_t tiles = unit_tiles(ge, kWave);
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
     // persistent and paced.
-    if (mode == MODE_PEER && vec == 4 && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
+    if (mode == MODE_PEER && vec == 4 && ge.d % 4 == 0 && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
         c->opt_cycle_kernel != 0 && (tiles >= kPacedWaves || c->opt_cycle_kernel == 1)) {
         CycleArgs ca;
         ca.ge = ge;
@@ -953,17 +928,11 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& ge, int mode, int
                : launch_walk_mode<float, 0>(mode, U, lp, c->stream, a);
 }
 
-hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& ge, int vec) {
-    if (ge.ncols <= 0) return hipSuccess;
-    c->note_path(PATH_GLOBAL, vec * 4);
-    const int n = ge.n;
-    GlobalArgs a;
-    a.ge = ge;
-    a.inv_n = 1.0f / (float)n;
-    const int waves = c->opt_waves ? c->opt_waves : 4;
-
+GlobalOrder global_order(const gpga_ctx* c) {
+    const int n = c->n, waves = c->opt_waves ? c->opt_waves : 4;
+    const int vec = c->d >= 4 ? 4 : 1;
     // Spread rows over lanes and waves only when columns alone cannot fill the chip.
-    const int64_t tiles64 = (ge.ncols + kWave - 1) / kWave;
+    const int64_t tiles64 = ((c->d + vec - 1) / vec + kWave - 1) / kWave;
     int RL = 1, wpb = 1;
     if (c->opt_row_lanes) {
         RL = c->opt_row_lanes;
@@ -978,16 +947,29 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& ge, int vec) {
     }
     if (wpb > waves) wpb = waves;
     while (wpb > 1 && RL * wpb > n) wpb >>= 1;
-    a.RL = RL;
-    a.tpb = waves / wpb;
-    const int CL = kWave / RL;
-    const int64_t tiles = (ge.ncols + CL - 1) / CL;
+    const LaunchPlan plan = make_plan(c, 1, waves, vec, RL == 1 && wpb == 1 && n >= 8, PACE_GLOBAL);
+    return {RL, wpb, c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : 4)};
+}
+
+hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& geom, int vec) {
+    c->note_path(PATH_GLOBAL, vec * 4);
+    GlobalArgs a;
+    a.ge = geom;
+    const int n = a.ge.n;
+    const GlobalOrder go = global_order(c);
+    const int waves = c->opt_waves ? c->opt_waves : 4;
+    const int CL = kWave / go.RL;
+    set_units(&a.ge, vec, CL);
+    a.inv_n = 1.0f / (float)n;
+    a.RL = go.RL;
+    a.tpb = waves / go.wpb;
+    const int64_t tiles = unit_tiles(a.ge, CL);
     const int64_t gx = (tiles + a.tpb - 1) / a.tpb;
     if (gx > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.gx = gx;
     a.xcd = c->opt_xcd_swizzle;
-    const LaunchPlan plan = make_plan(c, gx, waves, vec, RL == 1 && wpb == 1 && n >= 8, PACE_GLOBAL);
-    const int U = c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : 4);
+    const LaunchPlan plan = make_plan(c, gx, waves, vec, go.RL == 1 && go.wpb == 1 && n >= 8, PACE_GLOBAL);
+    const int U = go.U;
     const int mom = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
     if (vec == 4) {
         if (mom == 2) return launch_global_u<v4f, 2>(U, plan, c->stream, a);

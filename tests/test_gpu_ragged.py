@@ -1,0 +1,58 @@
+"""Rows that no vector width divides: leading dimensions and column counts with every remainder modulo the
+16-byte lane, tiles whose last unit stands alone (64 and 16 lanes a tile), every step kernel."""
+import numpy as np
+import pytest
+
+from oracle import gpga_oracle as orc
+from paper_2105_09080_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5   # of the array: a few fp32 roundings per element (the step tests' own bound)
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_09080_amd import harness
+    return harness
+
+
+def host(t):
+    return t.detach().cpu().numpy().astype(np.float64)
+
+
+# one unit and a bit, a lone unit behind 64 / 16 whole ones (257, 65), behind 128 and 63, and an aligned width on
+# an unaligned leading dimension
+WIDTHS = [(3, 3), (4, 5), (5, 5), (6, 7), (7, 7), (65, 65), (66, 66), (255, 255), (256, 257), (257, 257), (258, 259),
+          (259, 260), (513, 513), (4099, 4099)]
+
+
+@pytest.mark.parametrize("d,ld", WIDTHS)
+@pytest.mark.parametrize("n,topology,opts", [
+    (8, "ring", {}), (40, "ring", {"row_split": 4}), (8, "ring", {"row_split": 1, "blocks_per_cu": 1, "pace_gbs": 4000}),
+    (12, "expo1", {}), (8, "none", {}), (9, "full", {}), (64, "full", {"row_lanes": 1}), (40, "full", {"row_lanes": 2}),
+    (20, "grid", {}), (20, "grid", {"mix_lane_bytes": 8}), (20, "expo", {"mix_two_pass": 1}), (200, "grid", {}),
+    (48, "grid", {"mix_band": 1}), (48, "grid", {"mix_band": 1, "mix_lane_bytes": 8}),
+])
+def test_step_on_ragged_rows(hx, n, topology, opts, d, ld):
+    X, M, G = inputs.random_state(n, d, seed=d + n)
+    sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=0.9, ld=ld)
+    for name, v in opts.items():
+        sim.set_option(name, v)
+    for buf in (*sim._bufs, sim.m, sim.g):
+        buf.fill_(7.0)
+    sim.set_state(X=X, M=M, G=G, k=0)
+    k = 0
+    for _ in range(2):   # both directions of the ping-pong
+        sim.step()
+        X, M = orc.gossip_pga_step(X, M, G, k, topology=topology, H=0, lr=0.1, momentum=0.9)
+        k += 1
+    for got, want in ((host(sim.X), X), (host(sim.M), M)):
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    assert np.array_equal(host(sim.G), G.astype(np.float32))
+    for buf in (*sim._bufs, sim.m, sim.g):   # nothing beyond a row's d columns is written
+        assert (host(buf)[:, d:] == 7.0).all()
+    sim.close()
