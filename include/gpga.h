@@ -299,6 +299,9 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * lanes where they fit, else 4), "mix_tile_kb" (sparse-W tile kernel: largest tile in KiB of
  * LDS, 0 = automatic (all a workgroup may have: 160 on this chip), 1..160), "small_run" (gpga_run on small problems: 1 = whole
  * iterations in single-workgroup launches (default), 0 = one kernel per stage),
+ * "column_run" (gpga_run on synthetic gradients with up to 256 nodes: 1 = several iterations a
+ * launch with the columns on chip (default; not while a trace is being recorded, and not while
+ * the stream is being captured), 0 = one iteration at a time),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
  * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always),
@@ -336,7 +339,8 @@ gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
  *       (the sizes and W decide; every path has the same semantics): 0 none yet, 1 stencil walk
  *       (ring, one-peer, W = I), 2 row-streaming one-peer kernel (short cycles), 3 global average,
  *       4 sparse W with the whole column tile in LDS, 5 sparse banded W with a sliding window,
- *       6 sparse W in two passes, 7 whole iterations in one workgroup (small problems, gpga_run);
+ *       6 sparse W in two passes, 7 whole iterations in one workgroup (small problems, gpga_run),
+ *       8 several iterations with the columns on chip (synthetic gradients, gpga_run);
  *   "step_paced" (1 = that launch was a paced persistent launch), "step_lane_bytes" (16, 8 or 4),
  *   "trace_fused" (1 = the consensus-trace entry of that step came from the step kernel's own
  *       sums, 0 = a reduction pass followed or no trace is attached).  These four do not synchronise.

@@ -682,6 +682,22 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         }
         return GPGA_OK;
     }
+    if (column_run_fits(c, T)) {
+        // synthetic gradients: whole columns stay on chip for up to kColumnRunMaxIters iterations a launch
+        for (int64_t j = 0; j < T;) {
+            const int32_t chunk = (int32_t)(T - j < kColumnRunMaxIters ? T - j : kColumnRunMaxIters);
+            const hipError_t e = launch_column_run(c, chunk);
+            if (e != hipSuccess) return hip_fail(c, e, "trajectory kernel launch");
+            c->last_path = PATH_COLUMN_RUN;
+            c->last_paced = 0;
+            c->last_lane_bytes = 16;
+            c->last_trace_fused = 0;
+            if (chunk % 2) std::swap(c->x, c->x_new);  // X is where `chunk` separate steps would have left it
+            c->k += chunk;
+            j += chunk;
+        }
+        return GPGA_OK;
+    }
     for (int64_t j = 0; j < T; ++j) {
         gpga_status s = run_grad(c, batch_table_dev ? batch_table_dev + j * stride : nullptr, B, nullptr);
         if (s != GPGA_OK) return s;
@@ -825,6 +841,9 @@ gpga_status gpga_set_option(gpga_ctx* c, const char* name, int64_t value) {
     } else if (!strcmp(name, "mix_band")) {
         if (value < -1 || value > 1) return fail(c, GPGA_EINVAL, "mix_band must be -1 (automatic), 0 or 1");
         c->opt_mix_band = (int)value;
+    } else if (!strcmp(name, "column_run")) {
+        if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "column_run must be 0 or 1");
+        c->opt_column_run = (int)value;
     } else if (!strcmp(name, "small_run")) {
         if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "small_run must be 0 or 1");
         c->opt_small_run = (int)value;

@@ -12,75 +12,9 @@
 //  * virtual rows logistic regression whose feature rows are regenerated from
 //                 the counter RNG inside both passes (the array would not fit).
 #include "gpga_internal.hpp"
+#include "gpga_rng.hpp"
 
 namespace {
-
-// ---------------------------------------------------------------- counter RNG
-
-constexpr uint32_t kPhiloxM0 = 0xD2511F53u;
-constexpr uint32_t kPhiloxM1 = 0xCD9E8D57u;
-constexpr uint32_t kPhiloxW0 = 0x9E3779B9u;
-constexpr uint32_t kPhiloxW1 = 0xBB67AE85u;
-
-constexpr uint32_t TAG_GRAD = 1u;
-constexpr uint32_t TAG_FEAT = 2u;
-constexpr uint32_t TAG_MU = 3u;
-
-struct u32x4 {
-    uint32_t a, b, c, d;
-};
-
-// Philox4x32 with 10 rounds (Salmon et al., SC'11): two 32x32->64 multiplies per
-// round, outputs permuted and xor-ed with the round key; key += Weyl constants.
-__device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                               uint32_t k0, uint32_t k1) {
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
-        const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
-        const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        // three-input xor in one instruction (v_bitop3_b32, truth table 0x96 = a ^ b ^ c)
-        const uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);
-        const uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
-        c0 = n0;
-        c1 = lo1;
-        c2 = n2;
-        c3 = lo0;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    return {c0, c1, c2, c3};
-}
-
-// 32 random bits -> uniform in (0,1), exactly representable in fp32: u = ((r >> 9) + 0.5) * 2^-23.
-// Built without an integer-to-float conversion: the 23 bits become the mantissa of a float in
-// [1, 2) (one funnel shift puts the exponent 0x7F above them), and subtracting 1 - 2^-24 leaves
-// (k + 0.5) * 2^-23 exactly (it has at most 24 significant bits, so the subtraction does not round).
-__device__ __forceinline__ float uniform23(uint32_t r) {
-    const uint32_t bits = __builtin_amdgcn_alignbit(0x7Fu, r, 9u);  // ({0x7F, r} >> 9) = 0x3F800000 | (r >> 9)
-    return __uint_as_float(bits) - 0x1.fffffep-1f;
-}
-
-// Four standard normals for one column quad: Box-Muller on (u0,u1) and (u2,u3).
-// The transcendental part uses the hardware units directly: v_log_f32 (log2),
-// v_sqrt_f32, and v_sin_f32 / v_cos_f32, whose argument is in revolutions, so
-// sin(2 pi u) is one instruction on u itself with no range reduction.  Measured
-// over all 2^23 possible u: |sin|, |cos| error <= 1.3e-7, ln relative error
-// <= 1.7e-7, radius error <= 4.9e-7 (radius <= 5.7).
-__device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uint32_t tag,
-                                        uint32_t k0, uint32_t k1) {
-    const u32x4 r = philox4x32_10(c4, a, b, tag, k0, k1);
-    constexpr float kMinus2Ln2 = -1.3862943611198906f;  // -2 ln u = (-2 ln 2) log2 u
-    const float ra = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.a)));
-    const float rb = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.c)));
-    const float ub = uniform23(r.b), ud = uniform23(r.d);
-    v4f z;
-    z.x = ra * __builtin_amdgcn_cosf(ub);
-    z.y = ra * __builtin_amdgcn_sinf(ub);
-    z.z = rb * __builtin_amdgcn_cosf(ud);
-    z.w = rb * __builtin_amdgcn_sinf(ud);
-    return z;
-}
 
 // ---------------------------------------------------------------- synthetic
 

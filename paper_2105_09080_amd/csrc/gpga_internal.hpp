@@ -37,6 +37,8 @@ constexpr int kSmallRunThreads = 1024;   // workgroup of the single-workgroup tr
 constexpr int kSmallRunPasses = 4;     // (node, sample) pairs a lane group keeps in registers for the next iteration
 constexpr int kSmallRunMaxIters = 256;   // iterations per launch (their step sizes travel in the kernel arguments)
 
+constexpr int kColumnRunMaxIters = 64;   // iterations per launch of the column-resident trajectory kernel
+
 enum LrSchedule : int { SCHED_NONE = 0, SCHED_STEP, SCHED_MILESTONES, SCHED_POLY };
 constexpr int kMaxMilestones = 16;
 
@@ -48,7 +50,7 @@ struct PaceState;  // gpga_pace.hpp
 constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
-                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7 };
+                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8 };
 
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
@@ -110,6 +112,7 @@ struct gpga_ctx {
     int opt_mix_two_pass = 0;  // 1 = sparse-W steps always take the two-pass path
     int opt_mix_band = -1;     // sliding-window kernel for banded W: -1 = automatic (large problems), 0 = never, 1 = whenever W qualifies
     int opt_mix_csr_lds = 1;   // 0 = the tile kernel reads W from global memory even when it fits in LDS
+    int opt_column_run = 1;    // 0 = gpga_run takes synthetic gradients one iteration at a time
     int opt_small_run = 1;     // 0 = gpga_run never takes the single-workgroup path for small problems
     int opt_blocks_per_cu = -1;  // -1 = automatic, 0 = one workgroup per tile group, k = persistent
     int num_cus = 256;
@@ -216,6 +219,10 @@ struct GlobalOrder {
     int32_t RL, wpb, U;
 };
 GlobalOrder global_order(const gpga_ctx* c);
+// Synthetic gradients: T <= kColumnRunMaxIters whole iterations with the columns on chip, same conventions as
+// launch_small_run.  column_run_fits tells whether a gpga_run of T iterations qualifies.
+bool column_run_fits(const gpga_ctx* c, int64_t T);
+hipError_t launch_column_run(const gpga_ctx* c, int32_t T);
 // Column chunks per node of the virtual-feature margin pass; it needs n * B * chunks doubles in c->partials.
 int64_t virtual_margin_chunks(const gpga_ctx* c);
 

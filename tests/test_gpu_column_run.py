@@ -1,0 +1,70 @@
+"""Trajectories of synthetic gradients with the columns on chip against the same iterations one step at a time: the same
+bits, over node counts around the tile sizes, ragged widths, every graph, both momentum forms and several launches."""
+import numpy as np
+import pytest
+
+from paper_2105_09080_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_09080_amd import harness
+    return harness
+
+
+def final_state(hx, case, column_run, trace=False):
+    import torch
+    n, d, topology, H, momentum, nesterov, T, ld = case
+    sim = hx.Simulation(n, d, topology=topology, H=H, lr=0.1, momentum=momentum, ld=ld)
+    if nesterov:
+        sim.set_nesterov(True)
+    sim.set_option("column_run", column_run)
+    sim.problem_synthetic(11, 1e-2)
+    for buf in sim._bufs:
+        buf.fill_(7.0)
+    X, M, _ = inputs.random_state(n, d, seed=n + d)
+    sim.set_state(X=X, M=M if momentum else None, k=3)
+    tr = sim.attach_trace(3 + T) if trace else None
+    sim.run(T)
+    torch.cuda.synchronize()
+    path = int(sim.query("step_path"))
+    out = [t.clone() for t in (sim.X, sim.G)] + ([sim.M.clone()] if momentum else []) + ([tr.clone()] if trace else [])
+    edge = sim._addr[sim.X.data_ptr()][:, d:].clone()
+    assert sim.k == 3 + T
+    sim.close()
+    return out, path, edge
+
+
+CASES = [(n, d, topology, H, 0.9, False, 5, d + pad)
+         for n, topology, H in [(1, "ring", 2), (2, "ring", 0), (3, "expo1", 3), (5, "expo", 2), (16, "grid", 4), (33, "ring", 4),
+                                (64, "expo1", 6), (65, "grid", 3), (128, "none", 4), (129, "ring", 4), (256, "expo", 3)]
+         for d, pad in [(4, 0), (257, 1), (1031, 0)]]
+CASES += [(64, 1000, "full", 0, 0.0, False, 4, 1000), (64, 130, "ring", 4, 0.0, False, 64, 130), (20, 515, "expo1", 4, 0.9, True, 65, 515),
+          (40, 129, "grid", 7, 0.9, True, 130, 129), (8, 600_001, "expo1", 4, 0.9, False, 8, 600_001),
+          (64, 2_200_000, "ring", 4, 0.9, False, 8, 2_200_000)]   # the wide, paced step kernels on the other side
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
+def test_columns_on_chip_give_the_bits_of_separate_steps(hx, case):
+    import torch
+    a, path_a, edge_a = final_state(hx, case, 1)
+    b, path_b, _ = final_state(hx, case, 0)
+    assert path_a == 8 and path_b != 8
+    for u, v in zip(a, b):
+        assert torch.equal(u, v)
+    assert (edge_a == 7.0).all()   # nothing beyond a row's d columns is written
+
+
+def test_a_recorded_trace_and_a_single_iteration_take_the_step_kernels(hx):
+    import torch
+    case = (16, 1000, "ring", 4, 0.9, False, 6, 1000)
+    (xa, ga, ma, ta), path, _ = final_state(hx, case, 1, trace=True)
+    (xb, gb, mb), _, _ = final_state(hx, case, 1)
+    assert path != 8 and np.isfinite(ta.cpu().numpy()[3:]).all()
+    assert torch.equal(xa, xb) and torch.equal(ga, gb) and torch.equal(ma, mb)
+    assert final_state(hx, case[:6] + (1, 1000), 1)[1] != 8
