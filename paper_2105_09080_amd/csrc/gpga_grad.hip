@@ -13,6 +13,8 @@
 //                 the counter RNG inside both passes (the array would not fit).
 #include "gpga_internal.hpp"
 #include "gpga_rng.hpp"
+#include "gpga_schedule.hpp"
+#include "gpga_unit.hpp"
 
 namespace {
 
@@ -261,6 +263,56 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float* __restrict__ loss
     if (threadIdx.x == 0) loss[i] = (float)t;
 }
 
+// Losses alone on short rows (d <= 32): one thread per sample, the 256 rows of a workgroup staged through LDS with
+// coalesced loads when they are consecutive (full batch), one fp64 partial sum per workgroup; k_loss_chunks adds
+// them.  Bound: reading the rows and two double-precision transcendentals a sample.  n = 100, M = 8000, d = 10 (35 MB):
+// 12.0 + 4.6 us, where a coefficient and a loss term stored per sample and summed by one workgroup a node took
+// 18.3 + 9.7; with room for the widest rows in every workgroup (32 KiB instead of 10) the first kernel takes 22.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict__ feat, const float* __restrict__ tgt,
+                                                         const float* __restrict__ x, int64_t ld,
+                                                         const int32_t* __restrict__ idx, int32_t B, int32_t M,
+                                                         int32_t d, double* __restrict__ partials) {
+    extern __shared__ __align__(16) unsigned char s_raw[];  // 256 rows (full batch)
+    float* __restrict__ s_rows = reinterpret_cast<float*>(s_raw);
+    __shared__ double s_buf[4];
+    const int64_t i = blockIdx.y;
+    const int32_t b0 = blockIdx.x * 256, b = b0 + (int32_t)threadIdx.x;
+    const float* __restrict__ xi = x + i * ld;
+    const int32_t r = idx ? (b < B ? idx[i * B + b] : 0) : b;
+    const bool ok = b < B && r >= 0 && r < M;
+    const float target = ok ? tgt[i * M + r] : 0.f;
+    if (!idx) {
+        const float* __restrict__ rows = feat + (i * M + b0) * d;
+        const int32_t count = (B - b0 < 256 ? B - b0 : 256) * d;
+        for (int32_t e = threadIdx.x * 4; e + 4 <= count; e += 1024)
+            *reinterpret_cast<v4f*>(s_rows + e) = ld_unit<v4f>(rows + e);
+        for (int32_t e = (count & ~3) + (int32_t)threadIdx.x; e < count; e += 256) s_rows[e] = rows[e];
+        __syncthreads();
+    }
+    double term = 0.0;
+    if (ok) {
+        const float* __restrict__ f = idx ? feat + (i * M + r) * d : s_rows + threadIdx.x * d;
+        double z = 0.0;
+        for (int c = 0; c < d; ++c) z += (double)f[c] * xi[c];
+        float cf, ls;
+        sample_terms<KIND>(z, target, 1.0f / (float)B, &cf, &ls);
+        term = ls;
+    } else if (b < B) {
+        term = __builtin_nan("");  // a sample index outside [0, M): no access, the node's loss becomes NaN
+    }
+    const double t = block_sum(term, s_buf);
+    if (threadIdx.x == 0) partials[i * gridDim.x + blockIdx.x] = t;
+}
+
+__global__ void __launch_bounds__(kWave) k_loss_chunks(const double* __restrict__ partials, int32_t chunks,
+                                                       float* __restrict__ loss) {
+    double v = 0.0;
+    for (int32_t ch = threadIdx.x; ch < chunks; ch += kWave) v += partials[(int64_t)blockIdx.x * chunks + ch];
+    v = wave_sum(v);
+    if (threadIdx.x == 0) loss[blockIdx.x] = (float)v;
+}
+
 // ---------------------------------------------------------------- virtual rows
 
 // Feature quad h_{i,m}[4c4 .. 4c4+3] = mu_i + zeta_{i,m}, rounded to fp32 like a
@@ -425,7 +477,10 @@ struct SmallArgs {
     const float* wval;
     double* trace;  // trace[k] = consensus distance after iteration k, for k < trace_cap
     int64_t trace_cap;
+    int32_t nnz;          // entries of W
+    int32_t worker_waves;  // k_node_run: wavefronts that hold nodes (the others take the trace)
     float lr[kSmallRunMaxIters];  // step size of each iteration of this launch
+    int32_t shift[kSmallRunMaxIters];  // its one-peer offset; -1 = it ends in a global average
 };
 
 template <int KIND, int MOM>
@@ -671,6 +726,285 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
     }
 }
 
+// The same trajectories for short rows (d <= 20), up to four samples a node and iteration and up to 128 nodes - the
+// shapes of Sec. 5.1.  Bound: the latency of one iteration's dependent chain (margin, double-precision sigmoid,
+// update, exchange), so everything off that chain is taken off it:
+//  * four neighbouring lanes own a node, C columns each; x, m and the sample's row stay in registers, the margin is C
+//    multiply-adds and two lane exchanges within the quad, lane b of the quad evaluates the sigmoid of sample b;
+//  * rows and labels are fetched three iterations ahead, two with several samples a node, and their row numbers as
+//    many again (both lie in HBM: about 1 us away, more than an iteration takes), and the gradient uses the registers the margin used;
+//  * x^(k+1/2) is exchanged through two LDS arrays in turn, so an iteration has ONE barrier;
+//  * the consensus distance of iteration t is formed by wavefronts of its own while the nodes do iteration
+//    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.
+// Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 49.6 us here
+// (71 us with loads the compiler could not count).
+constexpr int node_trace_waves(int NB) { return NB == 1 ? 8 : 4; }  // fewer leave the registers that several samples take
+constexpr int kNodeLanes = 4, kNodeSamples = 4, kNodeMaxNodes = 128, kNodeMaxCols = 20;
+
+__device__ __forceinline__ double quad_sum(double v) {
+    v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
+    return v;
+}
+template <int B>
+__device__ __forceinline__ float quad_bcast(float v) {  // the value of lane B of the quad
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), B * 0x55, 0xf, 0xf, true));
+}
+
+template <int KIND, int MOM, int C, int NB>
+__global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trace_waves(NB)) k_node_run(const SmallArgs a) {
+    constexpr int DP = kNodeLanes * C;            // padded row
+    constexpr int LG = DP <= 16 ? 16 : 32;        // lanes over columns in the trace wavefronts
+    constexpr int kNodeTraceWaves = node_trace_waves(NB);
+    constexpr int kNodeDepth = NB == 1 ? 3 : 2;   // iterations the samples are fetched ahead
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    const int n = a.n, d = a.d, B = a.B;
+    double* __restrict__ sMean = reinterpret_cast<double*>(s_raw);      // [DP]
+    double* __restrict__ sP = sMean + DP;                               // [2][trace waves][2][DP]
+    float* __restrict__ sY = reinterpret_cast<float*>(sP + 2 * kNodeTraceWaves * 2 * DP);  // [2][n][DP]
+    float* __restrict__ sX = sY + 2 * n * DP;                           // [2][n][DP]
+    int32_t* __restrict__ sCol = reinterpret_cast<int32_t*>(sX + 2 * n * DP);  // W: [nnz] columns, [nnz] weights
+    float* __restrict__ sVal = reinterpret_cast<float*>(sCol + a.nnz);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const bool worker = wave < a.worker_waves;
+    const int tw = wave - a.worker_waves;         // trace wavefront
+    const int i = tid / kNodeLanes, l = tid & (kNodeLanes - 1);
+    const bool have = worker && i < n;
+    const float invB = 1.0f / (float)B, third = 1.0f / 3.0f, mu = a.mu;
+    const double inv_n = 1.0 / (double)n;
+    const bool sparse = a.topo == GPGA_TOPO_GRID || a.topo == GPGA_TOPO_EXPO || a.topo == GPGA_TOPO_CUSTOM;
+
+    float x[C], m[C];
+    bool real[C];                                 // columns below d; the padding stays 0
+    int w0 = 0, w1 = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        real[c] = have && l * C + c < d;
+        x[c] = real[c] ? a.x[(int64_t)i * a.ld + l * C + c] : 0.f;
+        m[c] = MOM && real[c] ? a.m[(int64_t)i * a.ld + l * C + c] : 0.f;
+    }
+    if (sparse) {
+        for (int p = tid; p < a.nnz; p += blockDim.x) {
+            sCol[p] = a.wcol[p];
+            sVal[p] = a.wval[p];
+        }
+        if (have) {
+            w0 = a.wptr[i];
+            w1 = a.wptr[i + 1];
+        }
+    }
+
+    // All loads of the pipeline are unconditional (clamped addresses, values checked when used): a load under a
+    // condition would make every later wait one for all loads in flight.
+    struct Slot {
+        float f[NB][C];
+        float y;          // label of this lane's sample (sample l of the node)
+        int32_t r;        // its row as given
+        int32_t rows[NB]; // row numbers, kNodeDepth iterations ahead of f
+    };
+    Slot slots[kNodeDepth];
+    const int in = i < n ? i : n - 1;
+    const float* __restrict__ feat_i = a.feat + (int64_t)in * a.M * d;
+    const float* __restrict__ tgt_i = a.tgt + (int64_t)in * a.M;
+    const int32_t* __restrict__ idx = a.idx ? a.idx : reinterpret_cast<const int32_t*>(a.tgt);  // full batch: not used
+    int cols[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) cols[c] = l * C + c < d ? l * C + c : d - 1;
+    auto valid = [&](int32_t r) { return r >= 0 && r < a.M; };
+    auto fetch_rows = [&](Slot& s, int t) {
+        const int tc = t < a.T ? t : a.T - 1;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int bc = b < B ? b : 0;
+            s.rows[b] = idx[a.idx ? ((int64_t)tc * n + in) * B + bc : 0];
+        }
+    };
+    auto fetch = [&](Slot& s) {
+        if (!a.idx) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) s.rows[b] = b < B ? b : 0;
+        }
+        s.r = s.rows[0];
+#pragma unroll
+        for (int b = 1; b < NB; ++b) s.r = l == b ? s.rows[b] : s.r;
+        s.y = tgt_i[valid(s.r) ? s.r : 0];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const float* __restrict__ f = feat_i + (int64_t)(valid(s.rows[b]) ? s.rows[b] : 0) * d;
+#pragma unroll
+            for (int c = 0; c < C; ++c) s.f[b][c] = f[cols[c]];
+        }
+    };
+    if (worker) {
+#pragma unroll
+        for (int s = 0; s < kNodeDepth; ++s) fetch_rows(slots[s], s);
+#pragma unroll
+        for (int s = 0; s < kNodeDepth; ++s) fetch(slots[s]);
+#pragma unroll
+        for (int s = 0; s < kNodeDepth; ++s) fetch_rows(slots[s], kNodeDepth + s);
+    }
+
+    auto traced = [&](int t) { return a.trace && t >= 0 && t < a.T && a.k0 + t < a.trace_cap; };
+    // shifted sums of iteration t's rows, this wavefront's share of them
+    auto trace_columns = [&](int t) {
+        const int c = lane & (LG - 1), group = tw * (kWave / LG) + lane / LG;
+        double s1 = 0.0, s2 = 0.0;
+        if (c < DP) {
+            const float* __restrict__ X = sX + (t & 1) * n * DP + c;
+            const double ref = X[0];
+            for (int r = group; r < n; r += kNodeTraceWaves * (kWave / LG)) {
+                const double v = (double)X[r * DP] - ref;
+                s1 += v;
+                s2 += v * v;
+            }
+        }
+#pragma unroll
+        for (int o = LG; o < kWave; o <<= 1) {
+            s1 += __shfl_xor(s1, o, kWave);
+            s2 += __shfl_xor(s2, o, kWave);
+        }
+        if (lane < DP) {
+            double* __restrict__ p = sP + ((t & 1) * kNodeTraceWaves + tw) * 2 * DP + lane;
+            p[0] = s1;
+            p[DP] = s2;
+        }
+    };
+    auto trace_entry = [&](int t) {
+        double ss = 0.0;
+        if (lane < DP) {
+            double s1 = 0.0, s2 = 0.0;
+            const double* __restrict__ p = sP + (t & 1) * kNodeTraceWaves * 2 * DP + lane;
+#pragma unroll
+            for (int w = 0; w < kNodeTraceWaves; ++w) {
+                s1 += p[w * 2 * DP];
+                s2 += p[w * 2 * DP + DP];
+            }
+            const double v = s2 - s1 * s1 * inv_n;
+            ss = v > 0.0 ? v : 0.0;
+        }
+        ss = group_sum_last(ss, kWave);
+        if (lane == 0) a.trace[a.k0 + t] = sqrt(ss);
+    };
+
+    auto column_means = [&](int t) {              // every wavefront takes columns, lanes over rows
+        const float* __restrict__ Y = sY + (t & 1) * n * DP;
+        for (int c = wave; c < d; c += nw) {
+            double v = 0.0;
+            for (int r = lane; r < n; r += kWave) v += (double)Y[r * DP + c];
+            v = group_sum_last(v, kWave);
+            if (lane == 0) sMean[c] = v * inv_n;
+        }
+        __syncthreads();
+    };
+    float g[C];                                   // gradient of the latest iteration
+#pragma unroll
+    for (int c = 0; c < C; ++c) g[c] = 0.f;
+    auto iteration = [&](int t, Slot& s) {
+        const float lr = a.lr[t];
+        const int shift = a.shift[t];
+        float y[C];
+        float* __restrict__ Y = sY + (t & 1) * n * DP;
+        double z = 0.0;                           // margin of this lane's sample
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            double acc = 0.0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc += (double)s.f[b][c] * (double)x[c];
+            acc = quad_sum(acc);
+            if (b == 0 || l == b) z = acc;
+        }
+        float cf = __builtin_nanf(""), ls;        // no valid sample: the node's gradient becomes NaN
+        if (valid(s.r)) sample_terms<KIND>(z, s.y, invB, &cf, &ls);
+        const float cb[4] = {quad_bcast<0>(cf), quad_bcast<1>(cf), quad_bcast<2>(cf), quad_bcast<3>(cf)};
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            double acc = 0.0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if (b < B) acc += (double)cb[b] * (double)s.f[b][c];
+            g[c] = real[c] ? (float)acc : 0.f;
+            float mom = g[c];
+            if (MOM) m[c] = mom = mu * m[c] + g[c];
+            y[c] = MOM == 2 ? x[c] - lr * (g[c] + mu * mom) : x[c] - lr * mom;
+            if (have) Y[i * DP + l * C + c] = y[c];
+        }
+        fetch(s);                                 // for iteration t + kNodeDepth
+        fetch_rows(s, t + 2 * kNodeDepth);
+        __syncthreads();
+        if (shift < 0) column_means(t);
+        if (!have) return;
+        const float* __restrict__ Yl = Y + l * C;
+        if (n == 1) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = y[c];
+        } else if (shift < 0) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = real[c] ? (float)sMean[l * C + c] : 0.f;
+        } else if (a.topo == GPGA_TOPO_RING) {
+            const float* __restrict__ lo = Yl + (i == 0 ? n - 1 : i - 1) * DP;
+            const float* __restrict__ hi = Yl + (i == n - 1 ? 0 : i + 1) * DP;
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = (lo[c] + y[c] + hi[c]) * third;
+        } else if (a.topo == GPGA_TOPO_EXPO1) {
+            const float* __restrict__ peer = Yl + (i + shift >= n ? i + shift - n : i + shift) * DP;
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = shift ? (y[c] + peer[c]) * 0.5f : y[c];
+        } else if (sparse) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = 0.f;
+            for (int p = w0; p < w1; ++p) {
+                const float* __restrict__ row = Yl + sCol[p] * DP;
+                const float wt = sVal[p];
+#pragma unroll
+                for (int c = 0; c < C; ++c) x[c] += wt * row[c];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < C; ++c) x[c] = y[c];
+        }
+        if (a.trace) {
+            float* __restrict__ X = sX + (t & 1) * n * DP + i * DP + l * C;
+#pragma unroll
+            for (int c = 0; c < C; ++c) X[c] = x[c];
+        }
+    };
+    // The two kinds of wavefront run loops of their own that meet at the same barriers: one loop with both roles in
+    // it, or one that leaves in the middle of a round, blurs the count of loads in flight.
+    if (worker) {
+        int t = 0;
+        for (; t + kNodeDepth <= a.T; t += kNodeDepth) {
+#pragma unroll
+            for (int s = 0; s < kNodeDepth; ++s) iteration(t + s, slots[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < kNodeDepth - 1; ++s)
+            if (t + s < a.T) iteration(t + s, slots[s]);
+    } else {
+        for (int t = 0; t < a.T; ++t) {
+            __syncthreads();
+            if (a.shift[t] < 0) column_means(t);
+            if (traced(t - 1)) trace_columns(t - 1);
+            if (tw == 0 && traced(t - 2)) trace_entry(t - 2);
+        }
+    }
+    __syncthreads();
+    if (!worker) {
+        if (traced(a.T - 1)) trace_columns(a.T - 1);
+        if (tw == 0 && traced(a.T - 2)) trace_entry(a.T - 2);
+    }
+    __syncthreads();
+    if (!worker && tw == 0 && traced(a.T - 1)) trace_entry(a.T - 1);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        if (real[c]) {
+            a.x_out[(int64_t)i * a.ld + l * C + c] = x[c];
+            a.g[(int64_t)i * a.ld + l * C + c] = g[c];
+            if (MOM) a.m[(int64_t)i * a.ld + l * C + c] = m[c];
+        }
+    }
+}
+
 size_t small_run_lds(const gpga_ctx* c, int32_t Beff) {
     const size_t nd = (size_t)c->n * (size_t)c->d;
     return ((size_t)c->d + 2 * (kSmallRunThreads / kWave) + (size_t)c->n * (size_t)Beff) * sizeof(double) +
@@ -697,6 +1031,22 @@ hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, fl
     const int vec_x = vec_feat && aligned16(c->x) && (c->ld % 4 == 0);
     dim3 grid1((unsigned)Beff, (unsigned)c->n), block(256);
     const int64_t pairs = (int64_t)c->n * Beff;
+    if (loss_out && c->d <= 32) {
+        // the partial sums (one double per 256 samples) take the place of the per-sample terms
+        double* partials = reinterpret_cast<double*>(c->coef);
+        const dim3 grid_loss((unsigned)((Beff + 255) / 256), (unsigned)c->n);
+        const size_t lds = idx ? 0 : (size_t)256 * c->d * sizeof(float);
+        if (c->problem == PROB_LSQ) {
+            hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ>), grid_loss, block, lds, c->stream, c->feat, c->tgt, c->x,
+                               c->ld, idx, Beff, c->M, (int32_t)c->d, partials);
+        } else {
+            hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG>), grid_loss, block, lds, c->stream, c->feat, c->tgt,
+                               c->x, c->ld, idx, Beff, c->M, (int32_t)c->d, partials);
+        }
+        hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials,
+                           (int32_t)grid_loss.x, loss_out);
+        return hipGetLastError();
+    }
     if (c->d <= 32 && (pairs + 255) / 256 <= 0x7fffffffLL) {
         const dim3 grid_short((unsigned)((pairs + 255) / 256));
         if (c->problem == PROB_LSQ) {
@@ -788,6 +1138,41 @@ bool small_run_fits(const gpga_ctx* c, const int32_t* idx, int32_t B) {
     return small_run_lds(c, (int32_t)Beff) <= 100 * 1024 && small_run_lds(c, (int32_t)Beff) <= (size_t)c->max_lds_block;
 }
 
+template <int KIND, int MOM, int C, int NB>
+static hipError_t launch_node(const gpga_ctx* c, SmallArgs a) {
+    constexpr size_t DP = kNodeLanes * C, trace_waves = node_trace_waves(NB);
+    a.worker_waves = (a.n * kNodeLanes + kWave - 1) / kWave;
+    const int threads = kWave * (a.worker_waves + (a.trace ? (int)trace_waves : 0));
+    const size_t lds = (DP + 4 * trace_waves * DP) * sizeof(double) + 4 * (size_t)a.n * DP * sizeof(float) +
+                       2 * (size_t)a.nnz * sizeof(int32_t);
+    hipLaunchKernelGGL((k_node_run<KIND, MOM, C, NB>), dim3(1), dim3(threads), lds, c->stream, a);
+    return hipGetLastError();
+}
+
+template <int KIND, int MOM, int C>
+static hipError_t launch_node_samples(const gpga_ctx* c, const SmallArgs& a) {
+    if (a.B == 1) return launch_node<KIND, MOM, C, 1>(c, a);
+    return a.B == 2 ? launch_node<KIND, MOM, C, 2>(c, a) : launch_node<KIND, MOM, C, kNodeSamples>(c, a);
+}
+
+template <int KIND, int MOM>
+static hipError_t launch_node_cols(const gpga_ctx* c, const SmallArgs& a) {
+    return a.d <= 12 ? launch_node_samples<KIND, MOM, 3>(c, a) : launch_node_samples<KIND, MOM, 5>(c, a);
+}
+
+template <int KIND>
+static hipError_t launch_node_kind(const gpga_ctx* c, const SmallArgs& a) {
+    if (c->mu == 0.f) return launch_node_cols<KIND, 0>(c, a);
+    return c->nesterov ? launch_node_cols<KIND, 2>(c, a) : launch_node_cols<KIND, 1>(c, a);
+}
+
+// Which small problems run with four lanes a node: rows and batches that fit its registers, nodes that fit 512
+// threads, and a W of at most 20 entries a node in LDS (54 KiB in all).
+static bool node_run_fits(const gpga_ctx* c, int32_t Beff) {
+    return c->n <= kNodeMaxNodes && c->d <= kNodeMaxCols && Beff <= kNodeSamples &&
+           (c->csr.col.empty() || c->csr.col.size() <= (size_t)20 * kNodeMaxNodes);
+}
+
 template <int KIND>
 static hipError_t launch_small_kind(const gpga_ctx* c, const SmallArgs& a, size_t lds) {
     const dim3 grid(1), block(kSmallRunThreads);
@@ -826,7 +1211,15 @@ hipError_t launch_small_run(const gpga_ctx* c, int32_t T, const int32_t* idx, in
     a.wval = c->csr_val_d;
     a.trace = c->trace;
     a.trace_cap = c->trace_cap;
-    for (int t = 0; t < T; ++t) a.lr[t] = lr[t];
+    a.nnz = a.wptr ? (int32_t)c->csr.col.size() : 0;
+    a.worker_waves = 0;
+    for (int t = 0; t < T; ++t) {
+        a.lr[t] = lr[t];
+        a.shift[t] = is_global_iteration(c->topo, c->H, c->k + t) ? -1 : one_peer_shift(c->n, c->k + t);
+    }
+    if (node_run_fits(c, a.B)) {
+        return c->problem == PROB_LSQ ? launch_node_kind<PROB_LSQ>(c, a) : launch_node_kind<PROB_LOGREG>(c, a);
+    }
     const size_t lds = small_run_lds(c, a.B);
     return c->problem == PROB_LSQ ? launch_small_kind<PROB_LSQ>(c, a, lds) : launch_small_kind<PROB_LOGREG>(c, a, lds);
 }
