@@ -14,6 +14,7 @@
 // step across waves and one partial per workgroup; a last single-workgroup
 // kernel adds the partials in a fixed order (bitwise reproducible).
 #include "gpga_internal.hpp"
+#include "gpga_unit.hpp"
 
 namespace {
 
@@ -23,8 +24,7 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
+__device__ __forceinline__ v4f ld_stream(const v4f* p) {
     return __builtin_nontemporal_load(p);
 }
 
@@ -54,13 +54,14 @@ __device__ __forceinline__ v4f to_mean(const d4& a, double inv_n) {
     r.w = (float)(a.w * inv_n);
     return r;
 }
-__device__ __forceinline__ double col_ss(double s1, double s2, double inv_n) {
+// Squared deviations of a unit's columns; the first `dup` of them are counted with the unit before.
+__device__ __forceinline__ double col_ss(double s1, double s2, double inv_n, int) {
     const double v = s2 - s1 * s1 * inv_n;
     return v > 0.0 ? v : 0.0;
 }
-__device__ __forceinline__ double col_ss(const d4& s1, const d4& s2, double inv_n) {
-    return col_ss(s1.x, s2.x, inv_n) + col_ss(s1.y, s2.y, inv_n) + col_ss(s1.z, s2.z, inv_n) +
-           col_ss(s1.w, s2.w, inv_n);
+__device__ __forceinline__ double col_ss(const d4& s1, const d4& s2, double inv_n, int dup) {
+    return (dup > 0 ? 0.0 : col_ss(s1.x, s2.x, inv_n, 0)) + (dup > 1 ? 0.0 : col_ss(s1.y, s2.y, inv_n, 0)) +
+           (dup > 2 ? 0.0 : col_ss(s1.z, s2.z, inv_n, 0)) + col_ss(s1.w, s2.w, inv_n, 0);
 }
 
 template <typename T>
@@ -78,59 +79,112 @@ struct AccOf<v4f> {
 
 constexpr int U = 4;
 
+// Column unit number u of a reduction: its first column, moved left at a ragged end (reads only, so overlapping units
+// need not share a wavefront), and how many of its columns belong to the unit before.
 template <typename T>
-__global__ void __launch_bounds__(256) k_col_mean(const float* __restrict__ x, int64_t ld,
-                                                  int64_t col0, int64_t ncols, int32_t n,
-                                                  float* __restrict__ xbar) {
+__device__ __forceinline__ int64_t reduce_column(int64_t u, int64_t d, int* dup) {
     constexpr int V = sizeof(T) / sizeof(float);
-    const int64_t col = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= ncols) return;
-    const int64_t ldT = ld / V;
-    const T* __restrict__ xp = reinterpret_cast<const T*>(x + col0) + col;
-    typename AccOf<T>::type acc = AccOf<T>::zero();
-    for (int base = 0; base < n; base += U) {
-        T v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (base + u < n) v[u] = ld_stream(xp + (int64_t)(base + u) * ldT);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (base + u < n) acc_add(acc, v[u]);
-    }
-    reinterpret_cast<T*>(xbar + col0)[col] = to_mean(acc, 1.0 / (double)n);
+    const int64_t c = u * V > d - V ? d - V : u * V;
+    *dup = (int)(u * V - c);
+    return c;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_consensus(const float* __restrict__ x, int64_t ld,
-                                                   int64_t col0, int64_t ncols, int32_t n,
-                                                   double* __restrict__ partials) {
-    constexpr int V = sizeof(T) / sizeof(float);
-    __shared__ double s_buf[4];
-    const int64_t col = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double ss = 0.0;
-    if (col < ncols) {
-        const int64_t ldT = ld / V;
-        const T* __restrict__ xp = reinterpret_cast<const T*>(x + col0) + col;
-        const T x0 = xp[0];
-        typename AccOf<T>::type s1 = AccOf<T>::zero(), s2 = AccOf<T>::zero();
-        for (int base = 1; base < n; base += U) {
-            T v[U];
+__device__ __forceinline__ void acc_add(double& a, const double& b) { a += b; }
+__device__ __forceinline__ void acc_add(d4& a, const d4& b) {
+    a.x += b.x;
+    a.y += b.y;
+    a.z += b.z;
+    a.w += b.w;
+}
+
+// Both reductions: a workgroup shares the rows of its column units among RS groups of lanes (rows group, group + RS,
+// ...), whose fp64 sums meet in LDS in group order.  RS = 1 (256 units a workgroup) streams wide arrays at the memory's
+// rate; narrow ones would leave most of the chip idle and a few lanes with all the rows, so they get 4 or 16 groups of
+// a wavefront each (64 units a workgroup).  Consensus distance + mean,
+// against one lane a column throughout: n = 256, d = 1172 62.5 -> 26.5 us, n = 100, d = 50 000 56.7 -> 27.7, n = 64,
+// d = 100 000 44.9 -> 29.1; rows without 16-byte alignment (n = 64, d = 5 000 001) 517 -> 466.
+constexpr int reduce_lanes(int RS) { return RS == 1 ? 256 : kWave; }
+template <typename T, int RS>
+__global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_col_mean(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
+                                                  int32_t n, float* __restrict__ xbar) {
+    typedef typename AccOf<T>::type Acc;
+    constexpr int CL = reduce_lanes(RS);
+    __shared__ Acc s_acc[RS > 1 ? RS - 1 : 1][CL];
+    const int lane = threadIdx.x % CL, grp = threadIdx.x / CL;
+    const int64_t u = (int64_t)blockIdx.x * CL + lane;
+    const bool on = u < units;
+    int dup;
+    const int64_t c = reduce_column<T>(on ? u : 0, d, &dup);
+    const float* __restrict__ xp = x + c;
+    Acc acc = AccOf<T>::zero();
+    for (int base = grp; base < n; base += U * RS) {
+        T v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (base + u < n) v[u] = ld_stream(xp + (int64_t)(base + u) * ldT);
+        for (int k = 0; k < U; ++k)
+            if (base + k * RS < n) v[k] = ld_unit<T>(xp + (int64_t)(base + k * RS) * ld);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (base + u < n) {
-                    const T dlt = v[u] - x0;
-                    acc_add(s1, dlt);
-                    acc_sq(s2, dlt);
-                }
-        }
-        ss = col_ss(s1, s2, 1.0 / (double)n);
+        for (int k = 0; k < U; ++k)
+            if (base + k * RS < n) acc_add(acc, v[k]);
     }
+    if (RS > 1) {
+        if (grp > 0) s_acc[grp - 1][lane] = acc;
+        __syncthreads();
+        if (grp > 0) return;
+#pragma unroll
+        for (int k = 0; k < RS - 1; ++k) acc_add(acc, s_acc[k][lane]);
+    }
+    if (on) *reinterpret_cast<typename Unit<T>::mem*>(xbar + c) = to_mean(acc, 1.0 / (double)n);
+}
+
+template <typename T, int RS>
+__global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_consensus(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
+                                                   int32_t n, double* __restrict__ partials) {
+    typedef typename AccOf<T>::type Acc;
+    constexpr int CL = reduce_lanes(RS);
+    __shared__ Acc s_acc[2][RS > 1 ? RS - 1 : 1][CL];
+    __shared__ double s_buf[4];
+    const int lane = threadIdx.x % CL, grp = threadIdx.x / CL;
+    const int64_t u = (int64_t)blockIdx.x * CL + lane;
+    const bool on = u < units;
+    int dup;
+    const float* __restrict__ xp = x + reduce_column<T>(on ? u : 0, d, &dup);
+    const T x0 = ld_unit_cached<T>(xp);
+    Acc s1 = AccOf<T>::zero(), s2 = AccOf<T>::zero();
+    for (int base = RS == 1 ? 1 : grp; base < n; base += U * RS) {
+        T v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (base + k * RS < n) v[k] = ld_unit<T>(xp + (int64_t)(base + k * RS) * ld);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (base + k * RS < n) {
+                const T dlt = v[k] - x0;
+                acc_add(s1, dlt);
+                acc_sq(s2, dlt);
+            }
+    }
+    if (RS > 1) {
+        if (grp > 0) {
+            s_acc[0][grp - 1][lane] = s1;
+            s_acc[1][grp - 1][lane] = s2;
+        }
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int k = 0; k < RS - 1; ++k) {
+                acc_add(s1, s_acc[0][k][lane]);
+                acc_add(s2, s_acc[1][k][lane]);
+            }
+        }
+    }
+    double ss = on && grp == 0 ? col_ss(s1, s2, 1.0 / (double)n, dup) : 0.0;
     ss = wave_sum(ss);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    if (lane == 0) s_buf[wave] = ss;
+    if (RS > 1) {  // the first wavefront has all the columns
+        if (threadIdx.x == 0) partials[blockIdx.x] = ss;
+        return;
+    }
+    const int wl = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    if (wl == 0) s_buf[wave] = ss;
     __syncthreads();
     if (threadIdx.x == 0) partials[blockIdx.x] = (s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3]);
 }
@@ -174,17 +228,17 @@ __global__ void __launch_bounds__(256) k_mean_f32(const float* __restrict__ v, i
     if (threadIdx.x == 0) out[0] = ((s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3])) / (double)count;
 }
 
+constexpr int kFillRows = 16;  // rows a lane fills: short chains of stores, and a grid that narrow arrays fill too
 template <typename T>
-__global__ void __launch_bounds__(256) k_fill_rows(float* __restrict__ dst, int64_t ld,
-                                                   int64_t col0, int64_t ncols, int32_t n,
-                                                   const float* __restrict__ src) {
-    constexpr int V = sizeof(T) / sizeof(float);
-    const int64_t col = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= ncols) return;
-    const int64_t ldT = ld / V;
-    const T v = src ? reinterpret_cast<const T*>(src + col0)[col] : T(0);
-    T* __restrict__ dp = reinterpret_cast<T*>(dst + col0) + col;
-    for (int row = 0; row < n; ++row) dp[(int64_t)row * ldT] = v;
+__global__ void __launch_bounds__(256) k_fill_rows(float* __restrict__ dst, int64_t ld, int64_t d, int64_t units,
+                                                   int32_t n, const float* __restrict__ src) {
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= units) return;
+    int dup;
+    const int64_t c = reduce_column<T>(u, d, &dup);
+    const T v = src ? ld_unit_cached<T>(src + c) : T(0);
+    const int32_t r0 = blockIdx.y * kFillRows, r1 = r0 + kFillRows < n ? r0 + kFillRows : n;
+    for (int32_t row = r0; row < r1; ++row) *reinterpret_cast<typename Unit<T>::mem*>(dst + c + (int64_t)row * ld) = v;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -243,38 +297,57 @@ size_t consensus_partials_used(const gpga_ctx* c) {
     return (size_t)((nv + 255) / 256 + (c->d - nv * 4 + 255) / 256);
 }
 
+// Row groups per workgroup of the two reductions over `units` column units: as few as give the chip (256 compute
+// units) about a thousand lanes each, and rows enough for every group to keep its loads in flight.
+static int reduce_split(int64_t units, int32_t n) {
+    constexpr int64_t kLanes = 256 * 1024;
+    return units >= kLanes ? 1 : units * 4 >= kLanes || n <= 32 ? 4 : 16;
+}
+
 size_t consensus_partials_needed(const gpga_ctx* c) {
-    // vector pass workgroups + scalar tail workgroup + 1 result slot
+    // at most one per 256 columns (64 units) and a narrow last one, + 1 result slot
     return (size_t)((c->d / 4 + 255) / 256) + (size_t)((c->d + 255) / 256) + 2;
 }
 
-hipError_t launch_fill_rows(const gpga_ctx* c, float* dst, const float* src) {
-    const bool vec = aligned16(dst) && (!src || aligned16(src)) && (c->ld % 4 == 0);
-    const int64_t nv = vec ? c->d / 4 : 0;
-    if (nv > 0) {
-        hipLaunchKernelGGL((k_fill_rows<v4f>), dim3((unsigned)((nv + 255) / 256)), dim3(256), 0,
-                           c->stream, dst, c->ld, (int64_t)0, nv, c->n, src);
-    }
-    const int64_t tail = c->d - nv * 4;
-    if (tail > 0) {
-        hipLaunchKernelGGL((k_fill_rows<float>), dim3((unsigned)((tail + 255) / 256)), dim3(256), 0,
-                           c->stream, dst, c->ld, nv * 4, tail, c->n, src);
+template <typename T>
+static hipError_t launch_fill(const gpga_ctx* c, float* dst, const float* src) {
+    constexpr int V = sizeof(T) / sizeof(float);
+    const int64_t units = (c->d + V - 1) / V;
+    for (int64_t row = 0; row < c->n; row += (int64_t)kFillRows * 65535) {
+        const int64_t rows = c->n - row < (int64_t)kFillRows * 65535 ? c->n - row : (int64_t)kFillRows * 65535;
+        hipLaunchKernelGGL((k_fill_rows<T>), dim3((unsigned)((units + 255) / 256), (unsigned)((rows + kFillRows - 1) / kFillRows)),
+                           dim3(256), 0, c->stream, dst + row * c->ld, c->ld, c->d, units, (int32_t)rows, src);
     }
     return hipGetLastError();
 }
 
+hipError_t launch_fill_rows(const gpga_ctx* c, float* dst, const float* src) {
+    return c->d >= 4 ? launch_fill<v4f>(c, dst, src) : launch_fill<float>(c, dst, src);
+}
+
+template <typename T, int RS>
+static hipError_t launch_mean_split(const gpga_ctx* c, int64_t units, float* xbar) {
+    const int64_t blocks = (units + reduce_lanes(RS) - 1) / reduce_lanes(RS);
+    hipLaunchKernelGGL((k_col_mean<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
+                       c->n, xbar);
+    return hipGetLastError();
+}
+
 hipError_t launch_col_mean(const gpga_ctx* c, float* xbar) {
-    const bool vec = aligned16(c->x) && aligned16(xbar) && (c->ld % 4 == 0);
-    const int64_t nv = vec ? c->d / 4 : 0;
-    if (nv > 0) {
-        hipLaunchKernelGGL((k_col_mean<v4f>), dim3((unsigned)((nv + 255) / 256)), dim3(256), 0,
-                           c->stream, c->x, c->ld, (int64_t)0, nv, c->n, xbar);
-    }
-    const int64_t tail = c->d - nv * 4;
-    if (tail > 0) {
-        hipLaunchKernelGGL((k_col_mean<float>), dim3((unsigned)((tail + 255) / 256)), dim3(256), 0,
-                           c->stream, c->x, c->ld, nv * 4, tail, c->n, xbar);
-    }
+    if (c->d < 4) return launch_mean_split<float, 16>(c, c->d, xbar);
+    const int64_t units = (c->d + 3) / 4;
+    const int split = reduce_split(units, c->n);
+    if (split == 1) return launch_mean_split<v4f, 1>(c, units, xbar);
+    return split == 4 ? launch_mean_split<v4f, 4>(c, units, xbar) : launch_mean_split<v4f, 16>(c, units, xbar);
+}
+
+template <typename T, int RS>
+static hipError_t launch_consensus_split(const gpga_ctx* c, int64_t units, double* parts, size_t cap, int64_t* count) {
+    const int64_t blocks = (units + reduce_lanes(RS) - 1) / reduce_lanes(RS);
+    if ((size_t)blocks > cap) return hipErrorOutOfMemory;
+    hipLaunchKernelGGL((k_consensus<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
+                       c->n, parts);
+    *count = blocks;
     return hipGetLastError();
 }
 
@@ -282,21 +355,12 @@ hipError_t launch_col_mean(const gpga_ctx* c, float* xbar) {
 // `cap` doubles); *count receives their number.
 static hipError_t launch_consensus_partials(const gpga_ctx* c, double* parts, size_t cap, int64_t* count) {
     *count = 0;
-    const bool vec = aligned16(c->x) && (c->ld % 4 == 0);
-    const int64_t nv = vec ? c->d / 4 : 0;
-    const int64_t tail = c->d - nv * 4;
-    const int64_t b1 = (nv + 255) / 256, b2 = (tail + 255) / 256;
-    if ((size_t)(b1 + b2) > cap) return hipErrorOutOfMemory;
-    if (b1 > 0) {
-        hipLaunchKernelGGL((k_consensus<v4f>), dim3((unsigned)b1), dim3(256), 0, c->stream, c->x,
-                           c->ld, (int64_t)0, nv, c->n, parts);
-    }
-    if (b2 > 0) {
-        hipLaunchKernelGGL((k_consensus<float>), dim3((unsigned)b2), dim3(256), 0, c->stream, c->x,
-                           c->ld, nv * 4, tail, c->n, parts + b1);
-    }
-    *count = b1 + b2;
-    return hipGetLastError();
+    if (c->d < 4) return launch_consensus_split<float, 16>(c, c->d, parts, cap, count);
+    const int64_t units = (c->d + 3) / 4;
+    const int split = reduce_split(units, c->n);
+    if (split == 1) return launch_consensus_split<v4f, 1>(c, units, parts, cap, count);
+    return split == 4 ? launch_consensus_split<v4f, 4>(c, units, parts, cap, count)
+                      : launch_consensus_split<v4f, 16>(c, units, parts, cap, count);
 }
 
 hipError_t launch_consensus_sq(gpga_ctx* c, size_t* partials_needed) {
