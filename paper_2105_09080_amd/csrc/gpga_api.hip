@@ -191,7 +191,8 @@ gpga_status check_batch(gpga_ctx* c, const int32_t* idx, int32_t B, int32_t* Bef
     return GPGA_OK;
 }
 
-gpga_status run_grad(gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out) {
+// Losses into loss_out if it is not NULL, gradients into c->g if `grad`; both share one margin pass.
+gpga_status run_grad(gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out, bool grad) {
     int32_t Beff = 0;
     gpga_status s = check_batch(c, idx, B, &Beff);
     if (s != GPGA_OK) return s;
@@ -210,9 +211,9 @@ gpga_status run_grad(gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out
             if (need < cons) need = cons;
             s = grow_f64(c, &c->partials, &c->partials_cap, need);
             if (s != GPGA_OK) return s;
-            e = launch_virtual_grad(c, idx, Beff, loss_out);
+            e = launch_virtual_grad(c, idx, Beff, loss_out, grad);
         } else {
-            e = launch_rows_grad(c, idx, idx ? Beff : 0, loss_out);
+            e = launch_rows_grad(c, idx, idx ? Beff : 0, loss_out, grad);
         }
     }
     if (e != hipSuccess) return hip_fail(c, e, "gradient kernel launch");
@@ -476,17 +477,19 @@ gpga_status gpga_problem_synthetic(gpga_ctx* c, uint64_t seed, float grad_var) {
 
 gpga_status gpga_local_grad(gpga_ctx* c, const int32_t* batch_idx, int32_t B) {
     if (!c) return GPGA_EINVAL;
-    return run_grad(c, batch_idx, B, nullptr);
+    return run_grad(c, batch_idx, B, nullptr, true);
 }
 
 gpga_status gpga_local_loss(gpga_ctx* c, const int32_t* batch_idx, int32_t B, float* loss_dev) {
     if (!c) return GPGA_EINVAL;
     if (!loss_dev || !aligned(loss_dev, 4)) return fail(c, GPGA_EINVAL, "loss_dev must be a 4-byte aligned device pointer");
-    return run_grad(c, batch_idx, B, loss_dev);
+    return run_grad(c, batch_idx, B, loss_dev, false);
 }
 
 // One fused iteration; `global` selects the all-node mean instead of the gossip mix.
-static gpga_status run_step(gpga_ctx* c, bool global) {
+// With rows_B > 0 the gradients are not in g yet: the step also forms them, from the coefficients of rows_B samples a node
+// (row numbers rows_idx), and stores them if want_g.
+static gpga_status run_step(gpga_ctx* c, bool global, int32_t rows_B = 0, const int32_t* rows_idx = nullptr, bool want_g = true) {
     int mode = MODE_SELF;
     int32_t S = 0;
     if (!global && c->n > 1) {
@@ -529,10 +532,11 @@ static gpga_status run_step(gpga_ctx* c, bool global) {
     c->last_path = PATH_NONE;
     c->last_paced = 0;
     c->last_trace_fused = 0;
-    const bool fuse = trace && !global && c->d % 4 == 0;
+    const bool fuse = trace && !global && c->d % 4 == 0 && rows_B == 0;
     double* const spread = fuse ? c->partials + 1 : nullptr;
     int64_t* const count = fuse ? &spread_count : nullptr;
-    hipError_t e = global ? launch_step_global(c, ge, vec)
+    hipError_t e = rows_B > 0 ? launch_rows_step(c, ge, rows_idx, rows_B, global, mode, S, csr, want_g)
+                   : global ? launch_step_global(c, ge, vec)
                           : csr ? launch_step_csr(c, ge, vec, spread, count)
                                 : launch_step_walk(c, ge, mode, S, vec, spread, count);
     if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
@@ -633,6 +637,46 @@ gpga_status gpga_check_mixing_csr(int32_t n, const int64_t* row_ptr_host, const 
     return GPGA_OK;
 }
 
+// One whole iteration of gpga_run; the losses go to loss_out if it is not NULL, g need only be left if want_g.
+static gpga_status run_iteration(gpga_ctx* c, const int32_t* idx, int32_t B, bool global, float* loss_out, bool want_g) {
+    int32_t Beff = 0;
+    gpga_status s = check_batch(c, idx, B, &Beff);
+    if (s != GPGA_OK) return s;
+    if (!rows_step_fits(c, Beff)) {
+        s = run_grad(c, idx, B, loss_out, true);
+        return s == GPGA_OK ? run_step(c, global) : s;
+    }
+    s = grow_f32(c, &c->coef, &c->coef_cap, (size_t)2 * c->n * Beff);
+    if (s != GPGA_OK) return s;
+    const hipError_t e = launch_rows_margin(c, idx, idx ? Beff : 0, loss_out);
+    if (e != hipSuccess) return hip_fail(c, e, "margin kernel launch");
+    return run_step(c, global, Beff, idx, want_g);
+}
+
+// Algorithm 2 after the global average of iteration k: the period that follows from that iteration's minibatch losses.
+static gpga_status aga_average(gpga_ctx* c, int64_t k, const float* loss_dev) {
+    c->aga_C = 0;
+    // F = (1/n) sum_i F_i of this iteration's minibatches: one scalar back to the host
+    hipError_t e = launch_mean_f32(c, loss_dev, c->n, c->partials);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(c->host_scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "loss average");
+    const double F = *c->host_scalar;
+    if (k < c->aga_warmup) {
+        c->aga_F_init = 0.5 * (c->aga_F_init + F);
+    } else {
+        int64_t H_new = c->aga_H_max;
+        if (F > 0.0) {
+            const double h = std::ceil(c->aga_F_init / F * (double)c->aga_H_init);
+            if (std::isfinite(h) && h < (double)c->aga_H_max) H_new = (int64_t)h;
+        }
+        if (H_new < 1) H_new = 1;
+        c->H = H_new;
+    }
+    return GPGA_OK;
+}
+
 gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int32_t B) {
     if (!c) return GPGA_EINVAL;
     if (T < 0) return fail(c, GPGA_EINVAL, "T must be >= 0");
@@ -647,12 +691,12 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         if (s != GPGA_OK) return s;
         for (int64_t j = 0; j < T; ++j) {
             const int32_t* idx = batch_table_dev ? batch_table_dev + j * stride : nullptr;
-            if (c->aga_C + 1 == c->H) {
-                s = run_grad(c, idx, B, c->aga_loss);
-                if (s != GPGA_OK) return s;
-            }
-            s = run_grad(c, idx, B, nullptr);
-            if (s == GPGA_OK) s = gpga_aga_step(c, c->aga_loss);
+            const int64_t k = c->k;
+            const bool global = c->aga_C + 1 == c->H;
+            s = run_iteration(c, idx, B, global, global ? c->aga_loss : nullptr, j == T - 1);
+            if (s != GPGA_OK) return s;
+            c->aga_C += 1;
+            if (global) s = aga_average(c, k, c->aga_loss);
             if (s != GPGA_OK) return s;
         }
         return GPGA_OK;
@@ -699,9 +743,8 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         return GPGA_OK;
     }
     for (int64_t j = 0; j < T; ++j) {
-        gpga_status s = run_grad(c, batch_table_dev ? batch_table_dev + j * stride : nullptr, B, nullptr);
-        if (s != GPGA_OK) return s;
-        s = run_step(c, is_global_iteration(c->topo, c->H, c->k));
+        const gpga_status s = run_iteration(c, batch_table_dev ? batch_table_dev + j * stride : nullptr, B,
+                                            is_global_iteration(c->topo, c->H, c->k), nullptr, j == T - 1);
         if (s != GPGA_OK) return s;
     }
     return GPGA_OK;
@@ -730,28 +773,8 @@ gpga_status gpga_aga_step(gpga_ctx* c, const float* loss_dev) {
     const int64_t k = c->k;
     c->aga_C += 1;
     const bool global = (c->aga_C == c->H);
-    gpga_status s = run_step(c, global);
-    if (s != GPGA_OK || !global) return s;
-    c->aga_C = 0;
-    // F = (1/n) sum_i F_i of this iteration's minibatches: one scalar back to the host
-    hipError_t e = launch_mean_f32(c, loss_dev, c->n, c->partials);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->host_scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "loss average");
-    const double F = *c->host_scalar;
-    if (k < c->aga_warmup) {
-        c->aga_F_init = 0.5 * (c->aga_F_init + F);
-    } else {
-        int64_t H_new = c->aga_H_max;
-        if (F > 0.0) {
-            const double h = std::ceil(c->aga_F_init / F * (double)c->aga_H_init);
-            if (std::isfinite(h) && h < (double)c->aga_H_max) H_new = (int64_t)h;
-        }
-        if (H_new < 1) H_new = 1;
-        c->H = H_new;
-    }
-    return GPGA_OK;
+    const gpga_status s = run_step(c, global);
+    return s != GPGA_OK || !global ? s : aga_average(c, k, loss_dev);
 }
 
 int64_t gpga_period(const gpga_ctx* c) { return c ? c->H : -1; }

@@ -14,6 +14,7 @@
 // A thread owns R consecutive rows of one 16-byte column unit: with R = 2 the state takes 24 registers, so that
 // two workgroups of 16 wavefronts fit on a compute unit and one loads or stores while the other computes.
 #include "gpga_internal.hpp"
+#include "gpga_order.hpp"
 #include "gpga_rng.hpp"
 #include "gpga_schedule.hpp"
 #include "gpga_unit.hpp"
@@ -39,44 +40,6 @@ struct ColumnArgs {
 };
 
 enum ColumnMix : int { MIX_SELF = 0, MIX_RING = 1, MIX_PEER = 2, MIX_CSR = 3 };
-
-// Sum over all rows (stride `step` units apart) of one column unit in the order k_step_global takes, so that a
-// trajectory and separate steps give the same bits: the rows are dealt to RL x wpb splitters, each adds batches of U
-// rows, and the splitters' sums meet in a binary tree (butterfly over lanes, then over wavefronts).
-__device__ __forceinline__ v4f ordered_sum(const GlobalOrder& o, int n, bool whole, const v4f* __restrict__ y, int step) {
-    const int RS = o.RL * o.wpb;
-    v4f level[5], sum = v4f(0.f);
-#pragma unroll
-    for (int l = 0; l < 5; ++l) level[l] = v4f(0.f);
-#pragma unroll 1
-    for (int r0 = 0; r0 < RS; ++r0) {
-        sum = v4f(0.f);
-        // a whole tile of the unsplit kernel adds the rows behind the last full batch one by one
-        const int batched = RS == 1 && whole ? n - n % o.U : n;
-        int base = r0;
-#pragma unroll 1
-        for (; base < batched; base += RS * o.U) {
-            v4f part = v4f(0.f);
-#pragma unroll 1
-            for (int u = 0; u < o.U && base + u * RS < n; ++u) part += y[(base + u * RS) * step];
-            sum += part;
-        }
-#pragma unroll 1
-        for (; RS == 1 && base < n; ++base) sum += y[base * step];
-        // binary counter over the splitters
-        bool carry = true;
-#pragma unroll
-        for (int l = 0; l < 5; ++l) {
-            if (carry && (r0 >> l) & 1) {
-                sum = level[l] + sum;
-            } else if (carry) {
-                level[l] = sum;
-                carry = false;
-            }
-        }
-    }
-    return sum;
-}
 
 template <int MOM, int R, int QT>
 __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const ColumnArgs a) {
@@ -135,7 +98,11 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
         __syncthreads();
         if (shift < 0) {
             v4f mean = v4f(0.f);
-            if (rs == 0) mean = ordered_sum(a.go, n, whole, sy + q, QT) * a.inv_n;
+            if (rs == 0) {
+                SplitterTree tree;
+                for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0) tree.add(r0, splitter_sum(a.go, r0, n, whole, sy + q, QT));
+                mean = tree.sum * a.inv_n;
+            }
             __syncthreads();
             if (rs == 0) sy[q] = mean;
             __syncthreads();
@@ -207,7 +174,7 @@ hipError_t launch_column_rows(const gpga_ctx* c, const ColumnArgs& a) {
 }  // namespace
 
 bool column_run_fits(const gpga_ctx* c, int64_t T) {
-    if (c->opt_column_run == 0 || c->problem != PROB_SYNTH || c->aga || T < 2) return false;
+    if (c->opt_column_run == 0 || !c->default_geometry() || c->problem != PROB_SYNTH || c->aga || T < 2) return false;
     if (c->n > 256 || c->d < 4) return false;
     if (c->trace && c->k < c->trace_cap) return false;  // the trace wants every iterate
     if ((c->topo == GPGA_TOPO_GRID || c->topo == GPGA_TOPO_EXPO || c->topo == GPGA_TOPO_CUSTOM) && !c->csr_ready) return false;

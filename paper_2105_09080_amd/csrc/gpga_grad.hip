@@ -114,16 +114,18 @@ __device__ __forceinline__ void sample_terms(double z, float target, float invB,
 
 // ---------------------------------------------------------------- stored rows
 
-// Pass 1: one workgroup per (sample slot b, node i): z = <row, x_i> in fp64.
+// Pass 1: one workgroup per (sample slot b, node i): z = <row, x_i> in fp64.  16-byte lanes at any alignment, the last
+// d % 4 columns on lanes of their own.  Bound by latency (sample index, then the row) on the sizes of a minibatch, so
+// rows_margin_threads gives a row lanes enough to have it in flight at once.
 template <int KIND>
-__global__ void __launch_bounds__(256) k_rows_margin(const float* __restrict__ feat,
+__global__ void __launch_bounds__(1024) k_rows_margin(const float* __restrict__ feat,
                                                      const float* __restrict__ tgt,
                                                      const float* __restrict__ x, int64_t ld,
                                                      const int32_t* __restrict__ idx, int32_t B,
-                                                     int32_t M, int64_t d, int vec_ok,
+                                                     int32_t M, int64_t d,
                                                      float* __restrict__ coef,
                                                      float* __restrict__ lossterm) {
-    __shared__ double s_buf[4];
+    __shared__ double s_buf[16];
     const int b = blockIdx.x, i = blockIdx.y;
     const int32_t r = idx ? idx[(int64_t)i * B + b] : b;
     if (r < 0 || r >= M) {  // a sample index outside [0, M): no access, the node's gradient and loss become NaN
@@ -137,19 +139,14 @@ __global__ void __launch_bounds__(256) k_rows_margin(const float* __restrict__ f
     const float* __restrict__ xi = x + (int64_t)i * ld;
     const float target = tgt[(int64_t)i * M + r];  // fetched with the row, not after the reduction
     double acc = 0.0;
-    if (vec_ok) {
-        const int64_t d4 = d >> 2;
-        const v4f* f4 = reinterpret_cast<const v4f*>(f);
-        const v4f* x4 = reinterpret_cast<const v4f*>(xi);
+    const int64_t d4 = d >> 2;
 #pragma unroll 4
-        for (int64_t c = threadIdx.x; c < d4; c += blockDim.x) {
-            const v4f fv = f4[c], xv = x4[c];
-            acc += (double)fv.x * xv.x + (double)fv.y * xv.y + (double)fv.z * xv.z +
-                   (double)fv.w * xv.w;
-        }
-    } else {
-        for (int64_t c = threadIdx.x; c < d; c += blockDim.x) acc += (double)f[c] * xi[c];
+    for (int64_t c = threadIdx.x; c < d4; c += blockDim.x) {
+        const v4f fv = ld_unit_cached<v4f>(f + 4 * c), xv = ld_unit_cached<v4f>(xi + 4 * c);
+        acc += (double)fv.x * xv.x + (double)fv.y * xv.y + (double)fv.z * xv.z +
+               (double)fv.w * xv.w;
     }
+    if ((int64_t)threadIdx.x < d - 4 * d4) acc += (double)f[4 * d4 + threadIdx.x] * xi[4 * d4 + threadIdx.x];
     const double z = block_sum(acc, s_buf);
     if (threadIdx.x == 0) {
         float cf, ls;
@@ -195,7 +192,7 @@ template <int W>
 __global__ void __launch_bounds__(kWave* W) k_rows_accum(const float* __restrict__ feat,
                                                     const float* __restrict__ coef,
                                                     const int32_t* __restrict__ idx, int32_t B,
-                                                    int32_t M, int64_t d, int vec_ok,
+                                                    int32_t M, int64_t d,
                                                     float* __restrict__ g, int64_t ld) {
     __shared__ double s_part[W - 1][4][kWave];
     const int i = blockIdx.y;
@@ -205,22 +202,25 @@ __global__ void __launch_bounds__(kWave* W) k_rows_accum(const float* __restrict
     const float* __restrict__ ci = coef + (int64_t)i * B;
     const int32_t* __restrict__ ii = idx ? idx + (int64_t)i * B : nullptr;
     float* __restrict__ gi = g + (int64_t)i * ld;
-    const int64_t t = (int64_t)blockIdx.x * kWave + lane;          // column quad (vector path) or column
-    const bool on = vec_ok ? t * 4 < d : t < d;
+    // column quad; the last one of a ragged width is moved left and overlaps its neighbour (both store the same sums).
+    // Rows of fewer than four columns: one column a lane.
+    const int64_t t = (int64_t)blockIdx.x * kWave + lane;
+    const bool quads = d >= 4, on = quads ? t * 4 < d : t < d;
+    const int64_t col = !quads ? t : t * 4 > d - 4 ? d - 4 : t * 4;
     double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
     if (on) {
         for (int b = wave; b < B; b += W) {
             int32_t r = ii ? ii[b] : b;
             if (r < 0 || r >= M) r = 0;  // its coefficient is NaN (set by the margin pass): row 0 is only a safe address
             const double cb = ci[b];
-            if (vec_ok) {
-                const v4f fv = reinterpret_cast<const v4f*>(fi + (int64_t)r * d)[t];
+            if (quads) {
+                const v4f fv = ld_unit_cached<v4f>(fi + (int64_t)r * d + col);
                 a0 += cb * fv.x;
                 a1 += cb * fv.y;
                 a2 += cb * fv.z;
                 a3 += cb * fv.w;
             } else {
-                a0 += cb * fi[(int64_t)r * d + t];
+                a0 += cb * fi[(int64_t)r * d + col];
             }
         }
     }
@@ -239,15 +239,15 @@ __global__ void __launch_bounds__(kWave* W) k_rows_accum(const float* __restrict
             a2 += s_part[w][2][lane];
             a3 += s_part[w][3][lane];
         }
-        if (vec_ok) {
+        if (quads) {
             v4f out;
             out.x = (float)a0;
             out.y = (float)a1;
             out.z = (float)a2;
             out.w = (float)a3;
-            __builtin_nontemporal_store(out, reinterpret_cast<v4f*>(gi) + t);
+            st_unit<v4f>(gi + col, out);
         } else {
-            gi[t] = (float)a0;
+            gi[col] = (float)a0;
         }
     }
 }
@@ -1023,30 +1023,22 @@ hipError_t launch_synth_grad(const gpga_ctx* c) {
     return hipGetLastError();
 }
 
-hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out) {
+// Lanes a row of the margin pass: one quad each up to 256 lanes; more, of five quads each, where there are too few rows
+// to fill the chip (1024 rows of 10 000: 14.0 us with 256 lanes, 12.7 with 512).
+static int rows_margin_threads(int64_t d, int64_t rows) {
+    int t = kWave;
+    while (t < 256 && d / 4 > t) t *= 2;
+    while (t < 1024 && d / 4 > (int64_t)5 * t && rows * t < 256 * 2048) t *= 2;
+    return t;
+}
+
+// Pass 1: coefficients and loss terms of every sample, and the losses if they are wanted.
+hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out) {
     const int32_t Beff = idx ? B : c->M;
     float* coef = c->coef;
     float* lossterm = c->coef + (size_t)c->n * Beff;
-    const int vec_feat = aligned16(c->feat) && (c->d % 4 == 0);
-    const int vec_x = vec_feat && aligned16(c->x) && (c->ld % 4 == 0);
-    dim3 grid1((unsigned)Beff, (unsigned)c->n), block(256);
+    dim3 grid1((unsigned)Beff, (unsigned)c->n), block(256), block1(rows_margin_threads(c->d, (int64_t)c->n * Beff));
     const int64_t pairs = (int64_t)c->n * Beff;
-    if (loss_out && c->d <= 32) {
-        // the partial sums (one double per 256 samples) take the place of the per-sample terms
-        double* partials = reinterpret_cast<double*>(c->coef);
-        const dim3 grid_loss((unsigned)((Beff + 255) / 256), (unsigned)c->n);
-        const size_t lds = idx ? 0 : (size_t)256 * c->d * sizeof(float);
-        if (c->problem == PROB_LSQ) {
-            hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ>), grid_loss, block, lds, c->stream, c->feat, c->tgt, c->x,
-                               c->ld, idx, Beff, c->M, (int32_t)c->d, partials);
-        } else {
-            hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG>), grid_loss, block, lds, c->stream, c->feat, c->tgt,
-                               c->x, c->ld, idx, Beff, c->M, (int32_t)c->d, partials);
-        }
-        hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials,
-                           (int32_t)grid_loss.x, loss_out);
-        return hipGetLastError();
-    }
     if (c->d <= 32 && (pairs + 255) / 256 <= 0x7fffffffLL) {
         const dim3 grid_short((unsigned)((pairs + 255) / 256));
         if (c->problem == PROB_LSQ) {
@@ -1057,28 +1049,47 @@ hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, fl
                                c->x, c->ld, idx, Beff, c->M, (int32_t)c->d, pairs, coef, lossterm);
         }
     } else if (c->problem == PROB_LSQ) {
-        hipLaunchKernelGGL((k_rows_margin<PROB_LSQ>), grid1, block, 0, c->stream, c->feat, c->tgt,
-                           c->x, c->ld, idx, Beff, c->M, c->d, vec_x, coef, lossterm);
+        hipLaunchKernelGGL((k_rows_margin<PROB_LSQ>), grid1, block1, 0, c->stream, c->feat, c->tgt,
+                           c->x, c->ld, idx, Beff, c->M, c->d, coef, lossterm);
     } else {
-        hipLaunchKernelGGL((k_rows_margin<PROB_LOGREG>), grid1, block, 0, c->stream, c->feat,
-                           c->tgt, c->x, c->ld, idx, Beff, c->M, c->d, vec_x, coef, lossterm);
+        hipLaunchKernelGGL((k_rows_margin<PROB_LOGREG>), grid1, block1, 0, c->stream, c->feat,
+                           c->tgt, c->x, c->ld, idx, Beff, c->M, c->d, coef, lossterm);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     if (loss_out) {
-        hipLaunchKernelGGL(k_loss_sum, dim3((unsigned)c->n), block, 0, c->stream, lossterm, Beff,
-                           loss_out);
-        return hipGetLastError();
+        hipLaunchKernelGGL(k_loss_sum, dim3((unsigned)c->n), block, 0, c->stream, lossterm, Beff, loss_out);
     }
-    const int vec_g = vec_feat && aligned16(c->g) && (c->ld % 4 == 0);
-    const int64_t cols = vec_g ? c->d / 4 : c->d;
+    return hipGetLastError();
+}
+
+static hipError_t launch_rows_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
+    // the partial sums (one double per 256 samples) take the place of the per-sample terms
+    double* partials = reinterpret_cast<double*>(c->coef);
+    const dim3 grid((unsigned)((Beff + 255) / 256), (unsigned)c->n), block(256);
+    const size_t lds = idx ? 0 : (size_t)256 * c->d * sizeof(float);
+    if (c->problem == PROB_LSQ) {
+        hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx,
+                           Beff, c->M, (int32_t)c->d, partials);
+    } else {
+        hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld,
+                           idx, Beff, c->M, (int32_t)c->d, partials);
+    }
+    hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials, (int32_t)grid.x, loss_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out, bool grad) {
+    const int32_t Beff = idx ? B : c->M;
+    if (!grad && c->d <= 32) return launch_rows_loss_short(c, idx, Beff, loss_out);
+    const hipError_t e = launch_rows_margin(c, idx, B, loss_out);
+    if (e != hipSuccess || !grad) return e;
+    const int64_t cols = c->d >= 4 ? (c->d + 3) / 4 : c->d;
     dim3 grid2((unsigned)((cols + kWave - 1) / kWave), (unsigned)c->n);
     if (Beff >= 64) {
-        hipLaunchKernelGGL(k_rows_accum<16>, grid2, dim3(kWave * 16), 0, c->stream, c->feat, coef, idx, Beff, c->M,
-                           c->d, vec_g, c->g, c->ld);
+        hipLaunchKernelGGL(k_rows_accum<16>, grid2, dim3(kWave * 16), 0, c->stream, c->feat, c->coef, idx, Beff, c->M,
+                           c->d, c->g, c->ld);
     } else {
-        hipLaunchKernelGGL(k_rows_accum<4>, grid2, block, 0, c->stream, c->feat, coef, idx, Beff, c->M,
-                           c->d, vec_g, c->g, c->ld);
+        hipLaunchKernelGGL(k_rows_accum<4>, grid2, dim3(256), 0, c->stream, c->feat, c->coef, idx, Beff, c->M,
+                           c->d, c->g, c->ld);
     }
     return hipGetLastError();
 }
@@ -1095,7 +1106,7 @@ int64_t virtual_margin_chunks(const gpga_ctx* c) {
     return (d4 + qpb - 1) / qpb;
 }
 
-hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out) {
+hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out, bool grad) {
     constexpr int BMAX = 32;
     if (B > BMAX) return hipErrorInvalidValue;
     float* coef = c->coef;
@@ -1116,8 +1127,8 @@ hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B,
     if (loss_out) {
         hipLaunchKernelGGL(k_loss_sum, dim3((unsigned)c->n), block, 0, c->stream, lossterm, B,
                            loss_out);
-        return hipGetLastError();
     }
+    if (!grad) return hipGetLastError();
     const int vec_ok = aligned16(c->g) && (c->ld % 4 == 0);
     dim3 grid2((unsigned)((d4 + 255) / 256), (unsigned)c->n);
     hipLaunchKernelGGL((k_virtual_accum<BMAX>), grid2, block, 0, c->stream, coef, idx, B, c->d, k0,

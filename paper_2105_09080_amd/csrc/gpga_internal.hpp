@@ -50,7 +50,7 @@ struct PaceState;  // gpga_pace.hpp
 constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
-                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8 };
+                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9 };
 
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
@@ -58,6 +58,13 @@ struct gpga_ctx {
             last_path = path;
             last_lane_bytes = lane_bytes;
         }
+    }
+    // No launch-geometry override is set: gpga_run may take the forms that replace the step kernels.
+    bool default_geometry() const {
+        return !opt_unroll && !opt_waves && !opt_row_split && !opt_row_lanes && !opt_xcd_swizzle && opt_blocks_per_cu == -1 &&
+               opt_pace_gbs == -1 && opt_cycle_kernel == -1 && !opt_pace_min_cycle && !opt_mix_lane_bytes &&
+               !opt_mix_spmm_lanes && !opt_mix_tile_kb && !opt_mix_waves && !opt_mix_two_pass && opt_mix_band == -1 &&
+               opt_mix_csr_lds == 1;
     }
     int32_t n = 0;
     int64_t d = 0;
@@ -204,8 +211,15 @@ double mixing_beta(int32_t n, const HostCsr& w);
 
 // Gradients.
 hipError_t launch_synth_grad(const gpga_ctx* c);
-hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
-hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
+// Stored and virtual features: the losses if loss_out is not NULL, the gradients if `grad` (one margin pass for both).
+hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out, bool grad);
+hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out, bool grad);
+// Stored features, small problems: what follows the margin pass of an iteration - gradient sums, update, mixing - in
+// one launch; g is stored only if want_g.  rows_step_fits tells whether the context and Beff samples a node qualify.
+bool rows_step_fits(const gpga_ctx* c, int32_t Beff);
+hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
+hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32_t* idx, int32_t Beff, bool global, int mode,
+                            int32_t shift, bool csr, bool want_g);
 // Small problems: T <= kSmallRunMaxIters whole iterations (stored-feature gradients, update,
 // mix or average, consensus trace) in one single-workgroup launch; the final iterates go to the
 // array T separate steps would leave them in (c->x for even T, c->x_new for odd T: the caller
