@@ -116,6 +116,8 @@ gpga_status upload_csr(gpga_ctx* c) {
     if (e == hipSuccess && nz) e = hipMemcpy(c->csr_val_d, c->csr.val.data(), nz * sizeof(float), hipMemcpyHostToDevice);
     // For the band kernel: circular offsets j - i of the neighbours and their weights, csr_max_row entries
     // per row (padded with weight 0), so that a row's list is one address computation away.
+    c->csr_circ_k = 0;
+    (void)circulant_rows(c->n, c->csr, kMaxCirculant, &c->csr_circ_k, c->csr_circ_off, c->csr_circ_val);
     c->csr_band = 0;
     c->csr_max_row = 0;
     for (int32_t i = 0; i < c->n; ++i) c->csr_max_row = std::max(c->csr_max_row, c->csr.ptr[i + 1] - c->csr.ptr[i]);

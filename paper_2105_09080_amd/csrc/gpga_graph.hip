@@ -85,6 +85,31 @@ double tridiag_max_eig(const std::vector<double>& alpha, const std::vector<doubl
 
 }  // namespace
 
+// Whether all rows of W are the same up to rotation: k (offset, weight) pairs, offsets j - i mod n ascending, at most max_k.
+bool circulant_rows(int32_t n, const HostCsr& w, int32_t max_k, int32_t* k, int32_t* off, float* val) {
+    const int32_t K = w.ptr[1];
+    if (K < 1 || K > max_k) return false;
+    std::vector<std::pair<int32_t, float>> row(K);
+    for (int32_t i = 0; i < n; ++i) {
+        if (w.ptr[i + 1] - w.ptr[i] != K) return false;
+        for (int32_t p = 0; p < K; ++p) {
+            const int32_t j = w.col[w.ptr[i] + p];
+            row[p] = {j >= i ? j - i : j - i + n, w.val[w.ptr[i] + p]};
+        }
+        std::sort(row.begin(), row.end());
+        for (int32_t p = 0; p < K; ++p) {
+            if (i == 0) {
+                off[p] = row[p].first;
+                val[p] = row[p].second;
+            } else if (row[p].first != off[p] || row[p].second != val[p]) {
+                return false;
+            }
+        }
+    }
+    *k = K;
+    return true;
+}
+
 void build_ring_csr(int32_t n, HostCsr* out) {
     std::vector<std::map<int32_t, double>> rows(n);
     for (int32_t i = 0; i < n; ++i)

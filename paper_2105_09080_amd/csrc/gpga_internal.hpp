@@ -37,6 +37,7 @@ constexpr int kSmallRunThreads = 1024;   // workgroup of the single-workgroup tr
 constexpr int kSmallRunPasses = 4;     // (node, sample) pairs a lane group keeps in registers for the next iteration
 constexpr int kSmallRunMaxIters = 256;   // iterations per launch (their step sizes travel in the kernel arguments)
 
+constexpr int kMaxCirculant = 16;        // entries a row of a circulant W may have for the kernel made for it
 constexpr int kColumnRunMaxIters = 64;   // iterations per launch of the column-resident trajectory kernel
 
 enum LrSchedule : int { SCHED_NONE = 0, SCHED_STEP, SCHED_MILESTONES, SCHED_POLY };
@@ -139,6 +140,9 @@ struct gpga_ctx {
     float* csr_ellval_d = nullptr; // band kernel: the weights in the same padded layout (padding has weight 0)
     int32_t csr_band = 0;          // largest circular distance between a node and a neighbour: W is banded (mod n) with this half width
     int32_t csr_max_row = 0;       // most entries in one row
+    int32_t csr_circ_k = 0;        // circulant W: entries of every row, else 0; offsets j - i mod n in ascending order, weights
+    int32_t csr_circ_off[kMaxCirculant] = {0};
+    float csr_circ_val[kMaxCirculant] = {0.f};
     bool csr_ready = false;
 
     // step-size schedule gamma_k (evaluated on the host in double, stored as float)
@@ -195,7 +199,13 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& ge, int vec);
 hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, double* spread_partials = nullptr,
                            int64_t* spread_count = nullptr);
 
+// Circulant W on up to 1024 nodes, more than the tile kernel takes with wide lanes: the whole column tile in LDS, the next one loaded meanwhile.  circulant_fits tells
+// whether the context qualifies.
+bool circulant_fits(const gpga_ctx* c);
+hipError_t launch_step_circulant(const gpga_ctx* c, const StepGeom& geom);
+
 // Host-side graph construction and analysis.
+bool circulant_rows(int32_t n, const HostCsr& w, int32_t max_k, int32_t* k, int32_t* off, float* val);
 void build_ring_csr(int32_t n, HostCsr* out);
 void build_one_peer_csr(int32_t n, int32_t shift, HostCsr* out);
 void build_grid_csr(int32_t n, HostCsr* out);

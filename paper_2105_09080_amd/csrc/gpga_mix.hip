@@ -97,9 +97,12 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
     }
     const int64_t ld = a.ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
+    // Pacing counts rows of the WORKGROUP, so that all its wavefronts have the same deadlines whatever the remainder of
+    // n by the wavefronts: counted per wavefront, those with a row less measured themselves as late at every rate, and
+    // the controller went down to its limit (n = 100, d = 2M: 4.8 ms instead of 0.85).
     constexpr uint32_t kLoadUnits = MOM ? 4u : 2u;  // 4-byte streams per row in phase 1 (reads + the m store)
     const PaceRun run = pace_begin(a.pace, lane);
-    uint32_t units_done = 0;
+    uint32_t tile_units = 0;                        // of the tiles before this one
     double wg_spread = 0.0;  // TRACE: lane 0 of wavefront 0 adds up the workgroup's tiles
 
     // Workgroups stride over the column tiles (one tile each in the default one-shot launch).
@@ -122,8 +125,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
         if (whole_units(a.ge, tile, kWave)) {  // every lane has a column
             for (; base + (kTileUnroll - 1) * kTileWaves < n; base += kTileWaves * kTileUnroll) {
                 T xv[kTileUnroll], mv[kTileUnroll], gv[kTileUnroll];
-                pace_wait(run, units_done);
-                units_done += kTileUnroll * kLoadUnits;
+                pace_wait(run, tile_units + (uint32_t)(base - wave) * kLoadUnits);
 #pragma unroll
                 for (int u = 0; u < kTileUnroll; ++u) {
                     const int64_t off = (int64_t)(base + u * kTileWaves) * ld;
@@ -146,8 +148,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
         // Ragged row groups and the last, partial tile: predicated per row and per lane.
         for (; base < n; base += kTileWaves * kTileUnroll) {
             T xv[kTileUnroll], mv[kTileUnroll], gv[kTileUnroll];
-            pace_wait(run, units_done);
-            units_done += kTileUnroll * kLoadUnits;
+            pace_wait(run, tile_units + (uint32_t)(base - wave) * kLoadUnits);
 #pragma unroll
             for (int u = 0; u < kTileUnroll; ++u) {
                 const int row = base + u * kTileWaves;
@@ -216,11 +217,11 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
                     }
                 }
             }
-            pace_wait(run, units_done);
-            units_done += 1u;
+            pace_wait(run, tile_units + (uint32_t)n * kLoadUnits + (uint32_t)(i - wave));
             if (on) st_unit<T>(xnp + (int64_t)i * ld, acc);
             if (TRACE) spread.add(acc);  // lanes without a column hold zeros throughout
         }
+        tile_units += (uint32_t)n * (kLoadUnits + 1u);
         __syncthreads();  // the next tile's phase 1 overwrites the staged y
         if (TRACE) {
             // the wavefronts' sums meet in LDS ([wave][2V][lane] doubles over the y tile, which is
@@ -238,7 +239,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
         }
     }
     if (TRACE && a.spread_partials && threadIdx.x == 0) a.spread_partials[blockIdx.x] = wg_spread;
-    pace_end(a.pace, run, units_done, lane, pace_now(a.pace));
+    pace_end(a.pace, run, tile_units, lane, pace_now(a.pace));
 }
 
 // Banded W (every neighbour within circular distance `band` of its node: rings with more taps, the
@@ -563,12 +564,9 @@ hipError_t launch_tile_mom(const gpga_ctx* c, TileArgs a, int waves, size_t lds,
         }
     }
     if (want > 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_step_tile<T, MOM, LCSR, TRACE>, threads, lds) != hipSuccess || occ < 1)
-            occ = 1;
-        const int64_t resident = (int64_t)c->num_cus * (want < occ ? want : occ);
+        const int64_t resident = (int64_t)c->num_cus * resident_per_cu(c, k_step_tile<T, MOM, LCSR, TRACE>, threads, lds, want);
         if (resident < blocks) blocks = balanced_blocks(a.tiles, resident);
-        pace_setup(const_cast<gpga_ctx*>(c), gbs, PACE_TILE, (double)blocks * waves, (int)sizeof(T), &a.pace);
+        pace_setup(const_cast<gpga_ctx*>(c), gbs, PACE_TILE, (double)blocks, (int)sizeof(T), &a.pace);
     }
     if (TRACE) {
         if (spread_count && a.spread_partials && spread_slots_fit(c, blocks)) *spread_count = blocks;
@@ -660,9 +658,7 @@ hipError_t launch_band_mom(const gpga_ctx* c, BandArgs a, int waves, size_t lds,
         attr_set[dev] = true;
     }
     if (want > 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_step_band<T, MOM, TRACE>, threads, lds) != hipSuccess || occ < 1) occ = 1;
-        const int64_t resident = (int64_t)c->num_cus * (want < occ ? want : occ);
+        const int64_t resident = (int64_t)c->num_cus * resident_per_cu(c, k_step_band<T, MOM, TRACE>, threads, lds, want);
         if (resident < blocks) blocks = balanced_blocks(a.tiles, resident);
         pace_setup(const_cast<gpga_ctx*>(c), gbs, PACE_BAND, (double)blocks * waves, (int)sizeof(T), &a.pace);
     }
@@ -749,6 +745,10 @@ hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, doubl
         if (band_bytes == 16) return launch_band<v4f>(c, ge, mom, band_waves, spread_partials, spread_count);
         if (band_bytes == 8) return launch_band<v2f>(c, ge, mom, band_waves, spread_partials, spread_count);
         return launch_band<float>(c, ge, mom, band_waves, spread_partials, spread_count);
+    }
+    if (!wide_tile_fits && c->default_geometry() && circulant_fits(c)) {
+        c->note_path(ge.n <= 640 ? PATH_TILE : PATH_TWO_PASS, 16);
+        return launch_step_circulant(c, ge);
     }
     // 8-byte lanes only on request ("mix_lane_bytes" = 8): they were the slowest of the three wherever two of them fit.
     if (!two_pass && vec == 4 && lane_cap >= 16 && n * kWave * sizeof(v4f) <= cap)

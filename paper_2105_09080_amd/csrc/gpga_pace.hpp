@@ -289,6 +289,20 @@ inline int64_t balanced_blocks(int64_t work, int64_t resident) {
     return (work + rounds - 1) / rounds;
 }
 
+// Host side: workgroups of a kernel with dynamic LDS that are resident on a compute unit at once, at most `want`.  LDS is
+// handed out in granules, which the occupancy query leaves out of account for the last workgroup that just fits (54216
+// bytes: three by the query, two on the chip); a paced launch with a workgroup too many waits for a whole round, measures
+// that as lateness and slows down to the controller's limit, so sizes are rounded up to 2 KiB here.
+template <typename Kernel>
+inline int resident_per_cu(const gpga_ctx* c, Kernel kernel, int threads, size_t lds, int want) {
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, lds) != hipSuccess || occ < 1) occ = 1;
+    const size_t granted = (lds + 2047) / 2048 * 2048;
+    const int fit = granted ? (int)((size_t)c->max_lds_block / granted) : occ;
+    if (fit < occ) occ = fit < 1 ? 1 : fit;
+    return want < occ ? want : occ;
+}
+
 // Host side: pacing arguments of one launch whose `wavefronts` resident wavefronts each move
 // 64 lanes x lane_bytes per stream row.  gbs > 0 paces at exactly that rate (GB/s); gbs < 0 lets
 // the controller of PaceState `key` choose; gbs == 0, or a context without pacing state, or a
