@@ -788,6 +788,11 @@ hipError_t launch_global_u(int U, const LaunchPlan& plan, hipStream_t st, const 
 // all its rows, which is the shape the paced launch needs; below it the rows
 // are split over lanes / wavefronts of a workgroup instead.
 constexpr int64_t kPacedWaves = 2048;
+// Walks along cycles of 32 rows and more keep one wavefront per cycle and column tile down to five of them a compute unit
+// (shorter cycles are as fast either way: n = 16, 1563 tiles 25.4 us split, 25.7 whole): split rows have every
+// row open at once (ring, 1832 tiles: n = 64 157 us split, 126 whole; n = 32, 1954 tiles 58.2 / 55.7; with 489 tiles
+// n = 64 34.9 / 39.0, n = 256 111 / 128).
+constexpr int64_t kSplitWaves = 1280;
 
 // Default policy: large launches whose wavefronts each walk many rows run
 // persistent and paced, at the rate the controller of their kind has found;
@@ -860,7 +865,7 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     if (mode != MODE_SELF && mode != MODE_INPLACE) {
         if (c->opt_row_split) {
             Q = c->opt_row_split;
-        } else if (tiles * a.C < kPacedWaves) {
+        } else if (tiles * a.C < (a.L >= 32 ? kSplitWaves : kPacedWaves)) {
             // too few column tiles to occupy the chip with one walker per cycle:
             // split each cycle over the wavefronts of a workgroup (LDS exchange)
             Q = pow2_floor(a.L / 4 > 0 ? a.L / 4 : 1);  // keep segments of >= 4 rows
