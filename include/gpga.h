@@ -288,7 +288,8 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * sharing one column tile along the node axis, 0 = automatic, else 1, 2, 4, 8;
  * must not exceed "waves"), "row_lanes" (global-average kernel: lanes of a
  * wavefront spread over rows: 0 = automatic, 1, 2, 4), "xcd_swizzle" (0/1),
- * "mix_two_pass" (1 = sparse-W gossip steps always take the two-pass path),
+ * "mix_two_pass" (1 = sparse-W gossip steps always take the two-pass path; any override that is set
+ * also keeps gpga_run and circulant W on the step kernels the overrides are for),
  * "mix_spmm_lanes" (two-pass path, second pass: lanes per column tile, 0 = automatic
  * (narrower as n grows, so that a tile's rows stay in one L2), 64, 128, 256),
  * "mix_band" (sliding-window kernel for banded W: -1 = automatic (large problems whose
@@ -339,7 +340,8 @@ gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
  *       (the sizes and W decide; every path has the same semantics): 0 none yet, 1 stencil walk
  *       (ring, one-peer, W = I), 2 row-streaming one-peer kernel (short cycles), 3 global average,
  *       4 sparse W with the whole column tile in LDS, 5 sparse banded W with a sliding window,
- *       6 sparse W in two passes, 7 whole iterations in one workgroup (small problems, gpga_run),
+ *       6 sparse W on more nodes than 4 and 5 take (two passes, or one when W is circulant),
+ *       7 whole iterations in one workgroup (small problems, gpga_run),
  *       8 several iterations with the columns on chip (synthetic gradients, gpga_run),
  *       9 gradient sums, update and mixing in one launch (stored features, small problems, gpga_run);
  *   "step_paced" (1 = that launch was a paced persistent launch), "step_lane_bytes" (16, 8 or 4),

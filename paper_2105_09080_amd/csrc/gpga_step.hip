@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                     }
                     row += U;
                 };
-                auto process_full = [&](const Batch& b, int first_row) {
+                auto process_full = [&](const Batch& b, int first_row, T& into) {
                     T part = T(0);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -551,9 +551,11 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                         if (WP) st_unit<T>(prev_xnp + (int64_t)(first_row + u) * ld, prev_mean);
                         part += half_step<MOM>(b.xv[u], b.gv[u], mom, lr, mu);
                     }
-                    sum += part;
+                    into += part;
                 };
                 const int nfull = n / U;
+                // even and odd batches have a sum each: half the length of either chain of roundings
+                T odd = T(0);
                 Batch A, B;
                 int done = 0;
                 if (nfull >= 1) {
@@ -562,22 +564,22 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                     for (; b + 3 <= nfull; b += 2) {
                         load_full(B);
                         __builtin_amdgcn_sched_barrier(0);
-                        process_full(A, done);
+                        process_full(A, done, sum);
                         __builtin_amdgcn_sched_barrier(0);
                         load_full(A);
                         __builtin_amdgcn_sched_barrier(0);
-                        process_full(B, done + U);
+                        process_full(B, done + U, odd);
                         __builtin_amdgcn_sched_barrier(0);
                         done += 2 * U;
                     }
                     if (nfull - b == 2) {
                         load_full(B);
                         __builtin_amdgcn_sched_barrier(0);
-                        process_full(A, done);
-                        process_full(B, done + U);
+                        process_full(A, done, sum);
+                        process_full(B, done + U, odd);
                         done += 2 * U;
                     } else {
-                        process_full(A, done);
+                        process_full(A, done, sum);
                         done += U;
                     }
                 }
@@ -594,6 +596,7 @@ __global__ void __launch_bounds__(kWave* kMaxWaves) k_step_global(const GlobalAr
                     units_done += kUnits;
                     sum += half_step<MOM>(xv, gv, mom, lr, mu);
                 }
+                sum += odd;
             };
             if (have_prev) rows_pass(std::true_type{}); else rows_pass(std::false_type{});
             prev_mean = sum * a.inv_n;
