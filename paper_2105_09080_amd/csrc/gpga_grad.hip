@@ -315,9 +315,13 @@ __global__ void __launch_bounds__(kWave) k_loss_chunks(const double* __restrict_
 
 // ---------------------------------------------------------------- virtual rows
 
-// Virtual features are bound by vector issue: 57 instructions per (quad, sample) in either pass (16 wide products, 19
-// xors).  n = 1024, d = 1M, B = 16: margin 8.0 -> 7.2 ms, accumulate with no coefficient 0 8.0 -> 7.3 ms against features
-// formed one by one (64 instructions and two more products).
+// Feature quad h_{i,m}[4c4 .. 4c4+3] = mu_i + zeta_{i,m}, rounded to fp32 like a
+// stored feature would be.
+__device__ __forceinline__ v4f virtual_quad(v4f mu, uint32_t c4, uint32_t i, uint32_t m,
+                                            uint32_t k0, uint32_t k1) {
+    return mu + normals4(c4, i, m, TAG_FEAT, k0, k1);
+}
+
 // Pass 1: grid (column chunks, node).  Each lane owns column quads and keeps B
 // partial margins; the node shift mu_i is generated once per quad and reused for
 // all B samples.  Partial margins are combined per workgroup and stored as
@@ -335,10 +339,7 @@ __global__ void __launch_bounds__(256) k_virtual_margin(const float* __restrict_
     const int64_t q_begin = (int64_t)blockIdx.x * quads_per_block;
     const int64_t q_end = (q_begin + quads_per_block < d4) ? q_begin + quads_per_block : d4;
     const float* __restrict__ xi = x + (int64_t)i * ld;
-    // Features h = mu + kNormalScale * polar: the node shift's part of a margin is the same for all samples of the node
-    // and is summed once, the scale is applied once at the end.  Products of a quad are summed in fp32 (relative
-    // roundings of 6e-8 of the quad's own terms, random in sign over the d/4 quads of a margin), quads in fp64.
-    double acc[BMAX], shift = 0.0;
+    double acc[BMAX];
 #pragma unroll
     for (int b = 0; b < BMAX; ++b) acc[b] = 0.0;
     for (int64_t q = q_begin + threadIdx.x; q < q_end; q += blockDim.x) {
@@ -349,14 +350,14 @@ __global__ void __launch_bounds__(256) k_virtual_margin(const float* __restrict_
         xv.z = (c + 2 < d) ? xi[c + 2] : 0.f;
         xv.w = (c + 3 < d) ? xi[c + 3] : 0.f;
         const v4f mu = mu_sigma * normals4((uint32_t)q, i, 0u, TAG_MU, k0, k1);
-        shift += (double)(mu.x * xv.x + mu.y * xv.y + mu.z * xv.z + mu.w * xv.w);
-        const PhiloxQuad pq((uint32_t)q, TAG_FEAT, k1);
 #pragma unroll
         for (int b = 0; b < BMAX; ++b) {
             if (b < B) {
-                const PhiloxPair pp(i, (uint32_t)idx[(int64_t)i * B + b], k0, k1);
-                const PolarQuad z = polar4(pq, pp, k0, k1);
-                const float t = z.ra * (z.ca * xv.x + z.sa * xv.y) + z.rb * (z.cb * xv.z + z.sb * xv.w);
+                const v4f h = virtual_quad(mu, (uint32_t)q, i, (uint32_t)idx[(int64_t)i * B + b], k0, k1);
+                // the four products of a quad are summed in fp32 (three roundings of ~6e-8 relative to
+                // the quad's own terms, random in sign over the d/4 quads of a margin), the quads in fp64:
+                // 6 issue slots per sample where four conversions and four fp64 operations took 12
+                const float t = h.x * xv.x + h.y * xv.y + h.z * xv.z + h.w * xv.w;
                 acc[b] += (double)t;
             }
         }
@@ -364,39 +365,36 @@ __global__ void __launch_bounds__(256) k_virtual_margin(const float* __restrict_
 #pragma unroll
     for (int b = 0; b < BMAX; ++b) {
         if (b < B) {
-            const double t = block_sum(kNormalScale * acc[b] + shift, s_buf);
+            const double t = block_sum(acc[b], s_buf);
             if (threadIdx.x == 0) zpart[((int64_t)i * B + b) * gridDim.x + blockIdx.x] = t;
             __syncthreads();
         }
     }
 }
 
-// Coefficients and loss terms from the margins, one wavefront per node (B <= 32), and the sum of the coefficients in fp64:
-// what the node shift is multiplied with.
-__global__ void __launch_bounds__(256) k_virtual_coef(const double* __restrict__ zpart, int32_t chunks, const float* __restrict__ y,
+__global__ void k_virtual_coef(const double* __restrict__ zpart, int32_t chunks, const float* __restrict__ y,
                                const int32_t* __restrict__ idx, int32_t B, int32_t M, int32_t n,
-                               float* __restrict__ coef, float* __restrict__ lossterm, double* __restrict__ coef_sum) {
-    const int i = blockIdx.x * (256 / kWave) + (threadIdx.x >> 6), b = threadIdx.x & (kWave - 1);
-    if (i >= n) return;
-    float cf = 0.f, ls = 0.f;
-    if (b < B) {
-        const int64_t t = (int64_t)i * B + b;
-        double z = 0.0;
-        for (int32_t ch = 0; ch < chunks; ++ch) z += zpart[t * chunks + ch];
-        const int32_t r = idx[t];
-        cf = ls = __builtin_nanf("");  // label index outside [0, M): no access, NaN marks the node's gradient and loss
-        if (r >= 0 && r < M) sample_terms<PROB_LOGREG>(z, y[(int64_t)i * M + r], 1.0f / (float)B, &cf, &ls);
-        coef[t] = cf;
-        lossterm[t] = ls;
+                               float* __restrict__ coef, float* __restrict__ lossterm) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * B) return;
+    double z = 0.0;
+    for (int32_t ch = 0; ch < chunks; ++ch) z += zpart[t * chunks + ch];
+    const int i = (int)(t / B);
+    float cf, ls;
+    const int32_t r = idx[t];
+    if (r < 0 || r >= M) {  // label index outside [0, M): no access, NaN marks the node's gradient and loss
+        coef[t] = __builtin_nanf("");
+        lossterm[t] = __builtin_nanf("");
+        return;
     }
-    const double sum = wave_sum((double)cf);
-    if (b == 0) coef_sum[i] = sum;
+    sample_terms<PROB_LOGREG>(z, y[(int64_t)i * M + r], 1.0f / (float)B, &cf, &ls);
+    coef[t] = cf;
+    lossterm[t] = ls;
 }
 
 // Pass 2: one lane per column quad of node i, features regenerated.
 template <int BMAX>
 __global__ void __launch_bounds__(256) k_virtual_accum(const float* __restrict__ coef,
-                                                       const double* __restrict__ coef_sum,
                                                        const int32_t* __restrict__ idx, int32_t B,
                                                        int64_t d, uint32_t k0, uint32_t k1,
                                                        float mu_sigma, int vec_ok,
@@ -406,35 +404,25 @@ __global__ void __launch_bounds__(256) k_virtual_accum(const float* __restrict__
     const int64_t c = q * 4;
     if (c >= d) return;
     const v4f mu = mu_sigma * normals4((uint32_t)q, i, 0u, TAG_MU, k0, k1);
-    // g = sum_b coef_b h_b = mu sum_b coef_b + kNormalScale sum_b coef_b polar_b over at most 32 samples of similar size:
-    // fp32 fused multiply-adds (error <= 32 x 6e-8 of sum |coef_b h_b|, far inside 1e-5 of the row's scale).  A sample whose
+    // g = sum_b coef_b h_b over at most 32 samples of similar size: fp32 fused multiply-adds (error
+    // <= 32 x 6e-8 of sum |coef_b h_b|, far inside 1e-5 of the row's scale).  A sample whose
     // coefficient is exactly zero adds exactly nothing and its features are not regenerated:
     // once the margins of a logistic problem are large, sigma(-y z) underflows to 0 for every
     // correctly classified sample.  (NaN coefficients, which mark invalid sample indices, are
     // not zero and poison the row as before.)  The coefficient is the same for the whole
     // workgroup, so the test is a scalar branch.
-    const PhiloxQuad pq((uint32_t)q, TAG_FEAT, k1);
     v4f a = v4f(0.f);
 #pragma unroll
     for (int b = 0; b < BMAX; ++b) {
         if (b < B) {
             const float cb = coef[(int64_t)i * B + b];
             if (cb != 0.f) {
-                const PhiloxPair pp(i, (uint32_t)idx[(int64_t)i * B + b], k0, k1);
-                const PolarQuad z = polar4(pq, pp, k0, k1);
-                const float ta = cb * z.ra, tb = cb * z.rb;
-                a.x += ta * z.ca;
-                a.y += ta * z.sa;
-                a.z += tb * z.cb;
-                a.w += tb * z.sb;
+                const v4f h = virtual_quad(mu, (uint32_t)q, i, (uint32_t)idx[(int64_t)i * B + b], k0, k1);
+                a += cb * h;
             }
         }
     }
-    const double csum = coef_sum[i];
-    const float a0 = (float)(kNormalScale * (double)a.x + csum * (double)mu.x);
-    const float a1 = (float)(kNormalScale * (double)a.y + csum * (double)mu.y);
-    const float a2 = (float)(kNormalScale * (double)a.z + csum * (double)mu.z);
-    const float a3 = (float)(kNormalScale * (double)a.w + csum * (double)mu.w);
+    const float a0 = a.x, a1 = a.y, a2 = a.z, a3 = a.w;
     float* row = g + (int64_t)i * ld;
     if (vec_ok && c + 3 < d) {
         v4f out;
@@ -1123,7 +1111,7 @@ hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B,
     if (B > BMAX) return hipErrorInvalidValue;
     float* coef = c->coef;
     float* lossterm = c->coef + (size_t)c->n * B;
-    double* zpart = c->partials;  // sized by the caller: n * (B * virtual_margin_chunks + 1) doubles
+    double* zpart = c->partials;  // n*B*chunks doubles, sized by the caller (n * B * virtual_margin_chunks)
     const uint32_t k0 = (uint32_t)(c->seed & 0xffffffffu), k1 = (uint32_t)(c->seed >> 32);
     const int64_t nb = (int64_t)c->n * B;
     const int64_t d4 = (c->d + 3) / 4;
@@ -1132,9 +1120,8 @@ hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B,
     dim3 grid1((unsigned)chunks, (unsigned)c->n), block(256);
     hipLaunchKernelGGL((k_virtual_margin<BMAX>), grid1, block, 0, c->stream, c->x, c->ld, c->d, idx,
                        B, k0, k1, c->mu_sigma, qpb, zpart);
-    double* coef_sum = zpart + nb * chunks;  // n doubles behind the partial margins
-    hipLaunchKernelGGL(k_virtual_coef, dim3((unsigned)((c->n + 3) / 4)), dim3(256), 0, c->stream,
-                       zpart, (int32_t)chunks, c->tgt, idx, B, c->M, c->n, coef, lossterm, coef_sum);
+    hipLaunchKernelGGL(k_virtual_coef, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, c->stream,
+                       zpart, (int32_t)chunks, c->tgt, idx, B, c->M, c->n, coef, lossterm);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (loss_out) {
@@ -1144,7 +1131,7 @@ hipError_t launch_virtual_grad(const gpga_ctx* c, const int32_t* idx, int32_t B,
     if (!grad) return hipGetLastError();
     const int vec_ok = aligned16(c->g) && (c->ld % 4 == 0);
     dim3 grid2((unsigned)((d4 + 255) / 256), (unsigned)c->n);
-    hipLaunchKernelGGL((k_virtual_accum<BMAX>), grid2, block, 0, c->stream, coef, coef_sum, idx, B, c->d, k0,
+    hipLaunchKernelGGL((k_virtual_accum<BMAX>), grid2, block, 0, c->stream, coef, idx, B, c->d, k0,
                        k1, c->mu_sigma, vec_ok, c->g, c->ld);
     return hipGetLastError();
 }

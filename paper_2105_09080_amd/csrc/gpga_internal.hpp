@@ -247,7 +247,7 @@ GlobalOrder global_order(const gpga_ctx* c);
 // launch_small_run.  column_run_fits tells whether a gpga_run of T iterations qualifies.
 bool column_run_fits(const gpga_ctx* c, int64_t T);
 hipError_t launch_column_run(const gpga_ctx* c, int32_t T);
-// Column chunks per node of the virtual-feature margin pass; the gradient needs n * (B * chunks + 1) doubles in c->partials.
+// Column chunks per node of the virtual-feature margin pass; it needs n * B * chunks doubles in c->partials.
 int64_t virtual_margin_chunks(const gpga_ctx* c);
 
 // Reductions and fills.

@@ -69,64 +69,6 @@ __device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uin
     return z;
 }
 
-// The same generator taken apart for many draws per column quad.  Counter words (c4, a, b, tag): the first two rounds
-// leave words that depend on the quad alone (PhiloxQuad) and words that depend on (a, b) alone (PhiloxPair), and
-// what is left of them per draw is two xors.  A PhiloxPair of uniform a, b stays in scalar registers: the xors are
-// written plainly, since the three-input instruction exists for vectors only (with it the second round's product of
-// scalars took two quarter-rate vector multiplies a draw).
-struct PhiloxQuad {
-    uint32_t lo0, hi1, lo1;
-    __device__ __forceinline__ PhiloxQuad(uint32_t c4, uint32_t tag, uint32_t k1) {
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * c4;
-        lo0 = (uint32_t)p0;
-        const uint64_t p1 = (uint64_t)kPhiloxM1 * ((uint32_t)(p0 >> 32) ^ tag ^ k1);
-        hi1 = (uint32_t)(p1 >> 32);
-        lo1 = (uint32_t)p1;
-    }
-};
-struct PhiloxPair {
-    uint32_t x0, x2, x3;
-    __device__ __forceinline__ PhiloxPair(uint32_t a, uint32_t b, uint32_t k0, uint32_t k1) {
-        const uint64_t p1 = (uint64_t)kPhiloxM1 * b;
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * ((uint32_t)(p1 >> 32) ^ a ^ k0);
-        x0 = (uint32_t)p1 ^ (k0 + kPhiloxW0);
-        x2 = (uint32_t)(p0 >> 32) ^ (k1 + kPhiloxW1);
-        x3 = (uint32_t)p0 ^ (k1 + 2u * kPhiloxW1);
-    }
-};
-__device__ __forceinline__ u32x4 philox_rounds(const PhiloxQuad& q, const PhiloxPair& r, uint32_t k0, uint32_t k1) {
-    uint32_t c0 = q.hi1 ^ r.x0, c1 = q.lo1, c2 = q.lo0 ^ r.x2, c3 = 0u;  // after two rounds; c3 ^ key comes as r.x3
-#pragma unroll
-    for (int n = 2; n < 10; ++n) {
-        const uint32_t key0 = k0 + (uint32_t)n * kPhiloxW0, key1 = k1 + (uint32_t)n * kPhiloxW1;
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
-        c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, key0, 0x96);
-        c2 = n == 2 ? (uint32_t)(p0 >> 32) ^ r.x3 : __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, key1, 0x96);
-        c1 = (uint32_t)p1;
-        c3 = (uint32_t)p0;
-    }
-    return {c0, c1, c2, c3};
-}
-
-// One draw of four normals in polar form: columns 4q, 4q+1 are kNormalScale * ra * (cos, sin) of the first angle,
-// 4q+2, 4q+3 likewise of the second.  A sum over draws applies the constant once.
-constexpr double kNormalScale = 1.1774100225154747;  // sqrt(2 ln 2): sqrt(-2 ln u) = kNormalScale * sqrt(-log2 u)
-struct PolarQuad {
-    float ra, ca, sa, rb, cb, sb;
-};
-__device__ __forceinline__ PolarQuad polar4(const PhiloxQuad& q, const PhiloxPair& p, uint32_t k0, uint32_t k1) {
-    const u32x4 r = philox_rounds(q, p, k0, k1);
-    const float ub = uniform23(r.b), ud = uniform23(r.d);
-    PolarQuad z;
-    z.ra = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(uniform23(r.a)));
-    z.rb = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(uniform23(r.c)));
-    z.ca = __builtin_amdgcn_cosf(ub);
-    z.sa = __builtin_amdgcn_sinf(ub);
-    z.cb = __builtin_amdgcn_cosf(ud);
-    z.sb = __builtin_amdgcn_sinf(ud);
-    return z;
-}
-
 // The synthetic gradient of four columns: sigma * N(seed, TAG_GRAD, i, k, c).  The product is rounded here, as a
 // stored gradient is: no fused multiply-add of a later use takes it in.
 __device__ __forceinline__ v4f synth_quad(uint32_t c4, uint32_t i, uint32_t kiter, uint32_t k0, uint32_t k1, float sigma) {
