@@ -54,9 +54,7 @@ __device__ __forceinline__ float uniform23(uint32_t r) {
 // sin(2 pi u) is one instruction on u itself with no range reduction.  Measured
 // over all 2^23 possible u: |sin|, |cos| error <= 1.3e-7, ln relative error
 // <= 1.7e-7, radius error <= 4.9e-7 (radius <= 5.7).
-__device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uint32_t tag,
-                                        uint32_t k0, uint32_t k1) {
-    const u32x4 r = philox4x32_10(c4, a, b, tag, k0, k1);
+__device__ __forceinline__ v4f box_muller4(const u32x4& r) {
     constexpr float kMinus2Ln2 = -1.3862943611198906f;  // -2 ln u = (-2 ln 2) log2 u
     const float ra = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.a)));
     const float rb = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.c)));
@@ -67,6 +65,49 @@ __device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uin
     z.z = rb * __builtin_amdgcn_cosf(ud);
     z.w = rb * __builtin_amdgcn_sinf(ud);
     return z;
+}
+__device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uint32_t tag,
+                                        uint32_t k0, uint32_t k1) {
+    return box_muller4(philox4x32_10(c4, a, b, tag, k0, k1));
+}
+
+// The same generator taken apart for many draws per column quad.  Counter words (c4, a, b, tag): the first two rounds
+// leave words that depend on the quad alone (PhiloxQuad) and words that depend on (a, b) alone (PhiloxPair), and
+// what is left of them per draw is two xors.  A PhiloxPair of uniform a, b stays in scalar registers: the xors are
+// written plainly, since the three-input instruction exists for vectors only (with it the second round's product of
+// scalars took two quarter-rate vector multiplies a draw).
+struct PhiloxQuad {
+    uint32_t lo0, hi1, lo1;
+    __device__ __forceinline__ PhiloxQuad(uint32_t c4, uint32_t tag, uint32_t k1) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * c4;
+        lo0 = (uint32_t)p0;
+        const uint64_t p1 = (uint64_t)kPhiloxM1 * ((uint32_t)(p0 >> 32) ^ tag ^ k1);
+        hi1 = (uint32_t)(p1 >> 32);
+        lo1 = (uint32_t)p1;
+    }
+};
+struct PhiloxPair {
+    uint32_t x0, x2, x3;
+    __device__ __forceinline__ PhiloxPair(uint32_t a, uint32_t b, uint32_t k0, uint32_t k1) {
+        const uint64_t p1 = (uint64_t)kPhiloxM1 * b;
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * ((uint32_t)(p1 >> 32) ^ a ^ k0);
+        x0 = (uint32_t)p1 ^ (k0 + kPhiloxW0);
+        x2 = (uint32_t)(p0 >> 32) ^ (k1 + kPhiloxW1);
+        x3 = (uint32_t)p0 ^ (k1 + 2u * kPhiloxW1);
+    }
+};
+__device__ __forceinline__ u32x4 philox_rounds(const PhiloxQuad& q, const PhiloxPair& r, uint32_t k0, uint32_t k1) {
+    uint32_t c0 = q.hi1 ^ r.x0, c1 = q.lo1, c2 = q.lo0 ^ r.x2, c3 = 0u;  // after two rounds; c3 ^ key comes as r.x3
+#pragma unroll
+    for (int n = 2; n < 10; ++n) {
+        const uint32_t key0 = k0 + (uint32_t)n * kPhiloxW0, key1 = k1 + (uint32_t)n * kPhiloxW1;
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
+        c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, key0, 0x96);
+        c2 = n == 2 ? (uint32_t)(p0 >> 32) ^ r.x3 : __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, key1, 0x96);
+        c1 = (uint32_t)p1;
+        c3 = (uint32_t)p0;
+    }
+    return {c0, c1, c2, c3};
 }
 
 // The synthetic gradient of four columns: sigma * N(seed, TAG_GRAD, i, k, c).  The product is rounded here, as a
