@@ -8,23 +8,31 @@
 // Sum of splitter r0 over n rows of one column unit, `step` units apart.  `whole`: the unit lies in a whole 64-lane tile
 // of the step kernel, which, unsplit, keeps a sum of the even and one of the odd batches and adds the rows behind the last
 // full batch one by one.
-__device__ __forceinline__ v4f splitter_sum(const GlobalOrder& o, int r0, int n, bool whole, const v4f* __restrict__ y, int step) {
+// The odd batches go first and their sum waits in the place of their first row, which costs no registers.
+__device__ __forceinline__ v4f splitter_sum(const GlobalOrder& o, int r0, int n, bool whole, v4f* __restrict__ y, int step) {
     const int RS = o.RL * o.wpb;
     const bool by_parity = RS == 1 && whole;
     const int batched = by_parity ? n - n % o.U : n;
-    v4f sum = v4f(0.f), odd = v4f(0.f);
-    int base = r0;
+    const int stride = by_parity ? 2 * o.U : RS * o.U;
+    v4f sum = v4f(0.f);
 #pragma unroll 1
-    for (; base < batched; base += RS * o.U) {
-        v4f part = v4f(0.f);
+    for (int base = by_parity ? o.U : r0;;) {
 #pragma unroll 1
-        for (int u = 0; u < o.U && base + u * RS < n; ++u) part += y[(base + u * RS) * step];
-        if (by_parity && (base / o.U) & 1) odd += part;
-        else sum += part;
+        for (; base < batched; base += stride) {
+            v4f part = v4f(0.f);
+#pragma unroll 1
+            for (int u = 0; u < o.U && base + u * RS < n; ++u) part += y[(base + u * RS) * step];
+            sum += part;
+        }
+        if (!by_parity || (base / o.U) % 2 == 0) break;
+        if (o.U < batched) y[o.U * step] = sum;  // the odd batches are done; now the even ones
+        sum = v4f(0.f);
+        base = 0;
     }
+    if (!by_parity) return sum;
 #pragma unroll 1
-    for (; RS == 1 && base < n; ++base) sum += y[base * step];
-    return by_parity ? sum + odd : sum;
+    for (int base = batched; base < n; ++base) sum += y[base * step];
+    return o.U < batched ? sum + y[o.U * step] : sum;
 }
 
 // The tree as a binary counter: splitters' sums go in in order, after the last of a power of two `sum` is the total.
