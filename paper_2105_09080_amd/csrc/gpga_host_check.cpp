@@ -16,6 +16,7 @@
 
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
+#include "gpga_rows_deal.hpp"
 #include "gpga_schedule.hpp"
 
 namespace {
@@ -291,9 +292,38 @@ void schedules() {
     std::printf("\n");
 }
 
+// The lane groups of k_rows_step: every node has its share of groups, and whoever adds up partial sums finds all of
+// them inside the array (one slot a thread).
+void rows_deal() {
+    std::vector<double> sums(kRowsThreads);
+    int64_t idle = 0;
+    for (int lanes : {4, 8, 16, 32, 64}) {
+        for (int n = 1; n <= 128; ++n) {
+            for (int B : {1, 8, 9, 16, 17, 33, 50, 65, 100, 128, 500, 1000, 100000}) {
+                const RowsDeal deal(lanes, n, B);
+                expect(deal.split >= 1 && deal.nodes >= 1 && deal.nodes * deal.split <= deal.groups, "shares fit the groups");
+                std::vector<int> share((size_t)deal.nodes, 0);
+                for (int g = 0; g < deal.groups; ++g) {
+                    if (deal.dealt(g)) ++share[(size_t)deal.node(g)];
+                    else ++idle;
+                    if (!deal.adds(g)) continue;
+                    for (int q = 0; q < lanes; ++q)
+                        for (int w = 0; w < deal.split; ++w) sums.at((size_t)(g * lanes + q + w * lanes)) += 1.0;
+                }
+                for (int s : share) expect(s == deal.split, "a node's share is complete");
+            }
+        }
+    }
+    expect(idle > 0, "some of these splits leave groups idle");
+    double total = 0.0;
+    for (double s : sums) total += s;
+    std::printf("rows_deal idle %" PRId64 " added %.0f\n", idle, total);
+}
+
 }  // namespace
 
 int main() {
+    rows_deal();
     named_graphs();
     rejected_matrices();
     schedules();

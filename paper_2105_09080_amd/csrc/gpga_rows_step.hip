@@ -11,11 +11,11 @@
 // under the adaptive period 17.1 -> 11.7, 32 x 10 000 with 32 rows 27.7 -> 25.2, 16 x 39 999 with 50 rows 130 -> 59.
 #include "gpga_internal.hpp"
 #include "gpga_order.hpp"
+#include "gpga_rows_deal.hpp"
 #include "gpga_unit.hpp"
 
 namespace {
 
-constexpr int kRowsThreads = 1024;
 constexpr int kRowsMaxNodes = 128;
 constexpr int64_t kRowsMaxStaged = 4096;       // (node, sample) pairs whose row numbers and coefficients go to LDS first
 // Larger states are bound by their rows, which the separate kernels read in longer pieces (64 x 40 000: 1102 us a run
@@ -40,11 +40,6 @@ struct RowsStepArgs {
 };
 constexpr int kModeSparse = 8, kModeGlobal = 9;
 
-__host__ __device__ __forceinline__ int rows_split(int groups, int n, int B) {
-    const int most = groups > n ? groups / n : 1, want = (B + 7) / 8;
-    return want < most ? want : most;
-}
-
 template <int MOM, int QT>
 __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a) {
     constexpr int NG = kRowsThreads / QT;
@@ -68,12 +63,11 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a
     }
     __syncthreads();
 
-    // SG groups share the samples of a node, at least eight each; NG / SG nodes at a time
-    const int SG = rows_split(NG, n, B);
-    const int per = NG / SG, part = grp % SG;
+    const RowsDeal deal(QT, n, B);
+    const int SG = deal.split, per = deal.nodes, part = deal.part(grp);
     for (int i0 = 0; i0 < n; i0 += per) {
-        const int i = i0 + grp / SG;
-        const bool mine = grp / SG < per && i < n && on;
+        const int i = i0 + deal.node(grp);
+        const bool mine = deal.dealt(grp) && i < n && on;
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         v4f xv = v4f(0.f), mv = v4f(0.f);
         const int64_t o = (int64_t)i * a.ge.ld + col;
@@ -116,7 +110,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a
 #pragma unroll
             for (int c = 0; c < 4; ++c) sPart[c * kRowsThreads + tid] = acc[c];
             __syncthreads();
-            if (part == 0) {
+            if (deal.adds(grp)) {
 #pragma unroll 4
                 for (int w = 1; w < SG; ++w)
 #pragma unroll
@@ -176,7 +170,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a
 template <int MOM, int QT>
 hipError_t launch_rows_tile(const gpga_ctx* c, RowsStepArgs a) {
     set_units(&a.ge, 4, QT);
-    const size_t part = rows_split(kRowsThreads / QT, a.ge.n, a.B) > 1 ? 4 * kRowsThreads * sizeof(double) : 0;
+    const size_t part = RowsDeal(QT, a.ge.n, a.B).split > 1 ? 4 * kRowsThreads * sizeof(double) : 0;
     const size_t leaves = a.mode == kModeGlobal ? (size_t)a.go.RL * a.go.wpb * QT * sizeof(v4f) : 0;
     const size_t staged = (int64_t)a.ge.n * a.B <= kRowsMaxStaged ? (size_t)a.ge.n * a.B : 0;
     const size_t lds = (size_t)a.ge.n * QT * sizeof(v4f) + 2 * ((staged + 1) & ~(size_t)1) * sizeof(int32_t) +

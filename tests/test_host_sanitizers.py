@@ -79,6 +79,13 @@ def test_schedule_arithmetic_matches_the_oracle(facts):
                           for k in (0, 50, 100, 550, 999, 1000, 5000)]
 
 
+def test_lane_groups_add_up_sums_inside_their_array_only(facts):
+    """The dealing of lane groups to nodes in the one-launch form of gpga_run on stored features; the check program
+    walks every partial sum of every split (an access past the array throws and ends it)."""
+    row, = [f for f in facts if f[0] == "rows_deal"]
+    assert int(row[2]) > 0 and float(row[4]) > 0
+
+
 def test_pacing_controller_finds_and_follows_the_edge_of_a_launch_model(facts):
     """The controller that sets the rate of paced launches, run on the CPU against a model of what a
     launch reports (keeps up below an edge rate with occasional late launches, falls behind above it):
