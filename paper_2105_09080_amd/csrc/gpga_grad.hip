@@ -883,8 +883,9 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
                 s2 += p[w * 2 * DP + DP];
             }
             const double v = s2 - s1 * s1 * inv_n;
-            ss = v > 0.0 ? v : 0.0;
+            ss = v < 0.0 ? 0.0 : v;               // a state that is not a number keeps a distance that is none
         }
+        if (n == 1 || a.shift[t] < 0) ss = 0.0;   // all rows have the same bits, whatever they are
         ss = group_sum_last(ss, kWave);
         if (lane == 0) a.trace[a.k0 + t] = sqrt(ss);
     };

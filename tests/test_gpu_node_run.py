@@ -66,6 +66,13 @@ def test_row_numbers_outside_the_data_give_nan_where_they_did(hx, B):
         assert not ok.any() or np.abs(u[ok] - v[ok]).max() <= TOL * np.abs(v[ok]).max()
 
 
+@pytest.mark.parametrize("d", [7, 20, 21])   # 21 columns: the general single-workgroup kernel
+def test_the_trace_of_a_state_that_is_not_a_number_is_not_zero(hx, d):
+    # rows outside the data at iteration 2 make two nodes NaN; it ends in a global average (H = 3), whose entry is 0
+    trace = run(hx, 12, d, 1, 5, "ring", 0.9, False, "logreg", 1, bad=True)[2]
+    assert np.isfinite(trace[:2]).all() and (trace[:2] > 0).all() and trace[2] == 0.0 and np.isnan(trace[3:]).all()
+
+
 @pytest.mark.parametrize("n,d,ld", [(1, 1, 1), (3, 3, 4), (5, 4, 5), (40, 7, 7), (33, 257, 257), (32, 1000, 1001), (200, 1031, 1031),
                                     (4, 300_002, 300_003), (64, 262_147, 262_147), (3, 1_048_577, 1_048_577)])
 def test_distance_and_mean_on_every_split(hx, n, d, ld):
