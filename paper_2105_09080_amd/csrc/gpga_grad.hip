@@ -848,14 +848,15 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
     }
 
     auto traced = [&](int t) { return a.trace && t >= 0 && t < a.T && a.k0 + t < a.trace_cap; };
-    // shifted sums of iteration t's rows, this wavefront's share of them
-    auto trace_columns = [&](int t) {
+    // shifted sums of iteration t's rows, this wavefront's share of them; after an average all rows have the same bits,
+    // whatever they are, and none is looked at
+    auto trace_columns = [&](int t, bool average) {
         const int c = lane & (LG - 1), group = tw * (kWave / LG) + lane / LG;
         double s1 = 0.0, s2 = 0.0;
         if (c < DP) {
             const float* __restrict__ X = sX + (t & 1) * n * DP + c;
             const double ref = X[0];
-            for (int r = group; r < n; r += kNodeTraceWaves * (kWave / LG)) {
+            for (int r = group; r < (average ? 0 : n); r += kNodeTraceWaves * (kWave / LG)) {
                 const double v = (double)X[r * DP] - ref;
                 s1 += v;
                 s2 += v * v;
@@ -883,9 +884,8 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
                 s2 += p[w * 2 * DP + DP];
             }
             const double v = s2 - s1 * s1 * inv_n;
-            ss = v < 0.0 ? 0.0 : v;               // a state that is not a number keeps a distance that is none
+            ss = (v > 0.0 ? v : 0.0) + 0.0 * s1;  // the last term: a state that is not finite has no distance
         }
-        if (n == 1 || a.shift[t] < 0) ss = 0.0;   // all rows have the same bits, whatever they are
         ss = group_sum_last(ss, kWave);
         if (lane == 0) a.trace[a.k0 + t] = sqrt(ss);
     };
@@ -972,6 +972,7 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
             for (int c = 0; c < C; ++c) X[c] = x[c];
         }
     };
+    bool average = false;                         // trace wavefronts: whether the latest iteration ended in one
     // The two kinds of wavefront run loops of their own that meet at the same barriers: one loop with both roles in
     // it, or one that leaves in the middle of a round, blurs the count of loads in flight.
     if (worker) {
@@ -986,14 +987,16 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
     } else {
         for (int t = 0; t < a.T; ++t) {
             __syncthreads();
-            if (a.shift[t] < 0) column_means(t);
-            if (traced(t - 1)) trace_columns(t - 1);
+            const bool now = a.shift[t] < 0;
+            if (now) column_means(t);
+            if (traced(t - 1)) trace_columns(t - 1, average);
+            average = now || n == 1;
             if (tw == 0 && traced(t - 2)) trace_entry(t - 2);
         }
     }
     __syncthreads();
     if (!worker) {
-        if (traced(a.T - 1)) trace_columns(a.T - 1);
+        if (traced(a.T - 1)) trace_columns(a.T - 1, average);
         if (tw == 0 && traced(a.T - 2)) trace_entry(a.T - 2);
     }
     __syncthreads();
