@@ -913,7 +913,11 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
         for (int b = 0; b < NB; ++b) {
             double acc = 0.0;
 #pragma unroll
-            for (int c = 0; c < C; ++c) acc += (double)s.f[b][c] * (double)x[c];
+            for (int c = 0; c < C; ++c) {
+                // lanes behind the last column repeat it: an infinite one times x = 0 would be no number
+                const float f = real[c] ? s.f[b][c] : 0.f;
+                acc += (double)f * (double)x[c];
+            }
             acc = quad_sum(acc);
             if (b == 0 || l == b) z = acc;
         }

@@ -21,10 +21,12 @@ def hx():
     return harness
 
 
-def run(hx, n, d, B, T, topology, momentum, nesterov, problem, small, bad=False):
+def run(hx, n, d, B, T, topology, momentum, nesterov, problem, small, bad=False, infinite=False):
     import torch
     M = 30 if B else 3
     feat, y, _ = inputs.logreg_problem(n, d, M, seed=n + d)
+    if infinite:
+        feat[::2, :, d - 1] = np.inf
     sim = hx.Simulation(n, d, topology=topology, H=3, lr=0.1, momentum=momentum, ld=d + 1)
     if nesterov:
         sim.set_nesterov(True)
@@ -64,6 +66,15 @@ def test_row_numbers_outside_the_data_give_nan_where_they_did(hx, B):
         assert np.array_equal(np.isnan(u), np.isnan(v)) and np.isnan(u).any()
         ok = ~np.isnan(v)
         assert not ok.any() or np.abs(u[ok] - v[ok]).max() <= TOL * np.abs(v[ok]).max()
+
+
+@pytest.mark.parametrize("d", [1, 5, 10, 12, 18])   # with and without lanes behind the last column
+@pytest.mark.parametrize("problem", ["logreg", "lsq"])
+def test_an_infinite_last_feature_reaches_its_own_column_only(hx, d, problem):
+    a = run(hx, 12, d, 2, 1, "none", 0.9, False, problem, 1, infinite=True)
+    b = run(hx, 12, d, 2, 1, "none", 0.9, False, problem, 0, infinite=True)
+    for u, v in zip(a[:2], b[:2]):
+        assert np.array_equal(u, v, equal_nan=True) or np.allclose(u, v, rtol=TOL, atol=TOL * np.abs(v[np.isfinite(v)]).max(), equal_nan=True)
 
 
 @pytest.mark.parametrize("d", [7, 20, 21])   # 21 columns: the general single-workgroup kernel
