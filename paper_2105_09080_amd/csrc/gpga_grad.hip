@@ -12,6 +12,7 @@
 //  * virtual rows logistic regression whose feature rows are regenerated from
 //                 the counter RNG inside both passes (the array would not fit).
 #include "gpga_internal.hpp"
+#include "gpga_node_run.hpp"
 #include "gpga_rng.hpp"
 #include "gpga_schedule.hpp"
 #include "gpga_unit.hpp"
@@ -740,9 +741,6 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
 //    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.
 // Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 49.6 us here
 // (71 us with loads the compiler could not count).
-constexpr int node_trace_waves(int NB) { return NB == 1 ? 8 : 4; }  // fewer leave the registers that several samples take
-constexpr int kNodeLanes = 4, kNodeSamples = 4, kNodeMaxNodes = 128, kNodeMaxCols = 20;
-
 __device__ __forceinline__ double quad_sum(double v) {
     v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
     v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
@@ -1161,37 +1159,32 @@ bool small_run_fits(const gpga_ctx* c, const int32_t* idx, int32_t B) {
 
 template <int KIND, int MOM, int C, int NB>
 static hipError_t launch_node(const gpga_ctx* c, SmallArgs a) {
-    constexpr size_t DP = kNodeLanes * C, trace_waves = node_trace_waves(NB);
     a.worker_waves = (a.n * kNodeLanes + kWave - 1) / kWave;
-    const int threads = kWave * (a.worker_waves + (a.trace ? (int)trace_waves : 0));
-    const size_t lds = (DP + 4 * trace_waves * DP) * sizeof(double) + 4 * (size_t)a.n * DP * sizeof(float) +
-                       2 * (size_t)a.nnz * sizeof(int32_t);
+    const int threads = kWave * (a.worker_waves + (a.trace ? node_trace_waves(NB) : 0));
+    const size_t lds = node_run_lds(a.n, C, NB, a.nnz);
+    if (lds > kNodeMaxLds) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_node_run<KIND, MOM, C, NB>), dim3(1), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
 }
 
 template <int KIND, int MOM, int C>
 static hipError_t launch_node_samples(const gpga_ctx* c, const SmallArgs& a) {
-    if (a.B == 1) return launch_node<KIND, MOM, C, 1>(c, a);
-    return a.B == 2 ? launch_node<KIND, MOM, C, 2>(c, a) : launch_node<KIND, MOM, C, kNodeSamples>(c, a);
+    switch (node_samples(a.B)) {
+        case 1: return launch_node<KIND, MOM, C, 1>(c, a);
+        case 2: return launch_node<KIND, MOM, C, 2>(c, a);
+        default: return launch_node<KIND, MOM, C, kNodeSamples>(c, a);
+    }
 }
 
 template <int KIND, int MOM>
 static hipError_t launch_node_cols(const gpga_ctx* c, const SmallArgs& a) {
-    return a.d <= 12 ? launch_node_samples<KIND, MOM, 3>(c, a) : launch_node_samples<KIND, MOM, 5>(c, a);
+    return node_columns(a.d) == 3 ? launch_node_samples<KIND, MOM, 3>(c, a) : launch_node_samples<KIND, MOM, 5>(c, a);
 }
 
 template <int KIND>
 static hipError_t launch_node_kind(const gpga_ctx* c, const SmallArgs& a) {
     if (c->mu == 0.f) return launch_node_cols<KIND, 0>(c, a);
     return c->nesterov ? launch_node_cols<KIND, 2>(c, a) : launch_node_cols<KIND, 1>(c, a);
-}
-
-// Which small problems run with four lanes a node: rows and batches that fit its registers, nodes that fit 512
-// threads, and a W of at most 20 entries a node in LDS (54 KiB in all).
-static bool node_run_fits(const gpga_ctx* c, int32_t Beff) {
-    return c->n <= kNodeMaxNodes && c->d <= kNodeMaxCols && Beff <= kNodeSamples &&
-           (c->csr.col.empty() || c->csr.col.size() <= (size_t)20 * kNodeMaxNodes);
 }
 
 template <int KIND>
@@ -1238,7 +1231,7 @@ hipError_t launch_small_run(const gpga_ctx* c, int32_t T, const int32_t* idx, in
         a.lr[t] = lr[t];
         a.shift[t] = is_global_iteration(c->topo, c->H, c->k + t) ? -1 : one_peer_shift(c->n, c->k + t);
     }
-    if (node_run_fits(c, a.B)) {
+    if (node_run_takes(a.n, a.d, a.B, a.nnz)) {
         return c->problem == PROB_LSQ ? launch_node_kind<PROB_LSQ>(c, a) : launch_node_kind<PROB_LOGREG>(c, a);
     }
     const size_t lds = small_run_lds(c, a.B);

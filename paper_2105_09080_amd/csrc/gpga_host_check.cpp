@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "gpga_internal.hpp"
+#include "gpga_node_run.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_rows_deal.hpp"
 #include "gpga_schedule.hpp"
@@ -320,9 +321,29 @@ void rows_deal() {
     std::printf("rows_deal idle %" PRId64 " added %.0f\n", idle, total);
 }
 
+// Small trajectories: whatever k_node_run takes fits the LDS a launch gets without an attribute.
+void node_run_sizes() {
+    size_t most = 0;
+    int64_t taken = 0;
+    for (int n = 1; n <= kNodeMaxNodes + 1; ++n)
+        for (int d = 1; d <= kNodeMaxCols + 1; ++d)
+            for (int B = 1; B <= kNodeSamples + 1; ++B)
+                for (int64_t entries = 0; entries <= 21 * (int64_t)n; entries += n) {
+                    if (!node_run_takes(n, d, B, entries)) continue;
+                    const size_t lds = node_run_lds(n, node_columns(d), node_samples(B), entries);
+                    expect(lds <= 65536, "LDS of a small trajectory");
+                    expect(n <= kNodeMaxNodes && kNodeLanes * node_columns(d) >= d && node_samples(B) >= B, "sizes of a small trajectory");
+                    if (lds > most) most = lds;
+                    ++taken;
+                }
+    expect(node_run_takes(128, 20, 1, 18 * 128) && !node_run_takes(128, 20, 1, 20 * 128), "the largest problems, by the entries of W");
+    std::printf("node_run taken %" PRId64 " most_lds %zu\n", taken, most);
+}
+
 }  // namespace
 
 int main() {
+    node_run_sizes();
     rows_deal();
     named_graphs();
     rejected_matrices();

@@ -68,6 +68,32 @@ def test_row_numbers_outside_the_data_give_nan_where_they_did(hx, B):
         assert not ok.any() or np.abs(u[ok] - v[ok]).max() <= TOL * np.abs(v[ok]).max()
 
 
+@pytest.mark.parametrize("entries", [18, 20])   # a node: within the LDS of the four-lane form, and beyond it
+def test_the_densest_mixing_matrices(hx, entries):
+    import torch
+    n, d, T = 128, 20, 6
+    W = np.zeros((n, n))
+    for off in range(entries):
+        W[np.arange(n), (np.arange(n) + off * 5) % n] = 1.0 / entries
+    feat, y, _ = inputs.logreg_problem(n, d, 30, seed=9)
+    out = []
+    for small in (1, 0):
+        sim = hx.Simulation(n, d, topology="custom", H=4, lr=0.1, momentum=0.9)
+        sim.set_mixing(W)
+        sim.set_option("small_run", small)
+        sim.problem_logreg(feat, y)
+        sim.set_state(X=inputs.random_state(n, d, seed=1)[0])
+        trace = sim.attach_trace(T)
+        sim.run(T, sim.upload_batches(inputs.batch_indices(T, n, 1, 30, seed=3)))
+        torch.cuda.synchronize()
+        assert (int(sim.query("step_path")) == 7) == bool(small)
+        out.append((sim.X.cpu().numpy().copy(), trace.cpu().numpy().copy()))
+        sim.close()
+    (xa, ta), (xb, tb) = out
+    assert np.abs(xa - xb).max() <= TOL * np.abs(xb).max()
+    assert np.abs(ta - tb).max() <= TOL * np.linalg.norm(xb)
+
+
 @pytest.mark.parametrize("d", [1, 5, 10, 12, 18])   # with and without lanes behind the last column
 @pytest.mark.parametrize("problem", ["logreg", "lsq"])
 def test_an_infinite_last_feature_reaches_its_own_column_only(hx, d, problem):

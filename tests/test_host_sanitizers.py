@@ -86,6 +86,12 @@ def test_lane_groups_add_up_sums_inside_their_array_only(facts):
     assert int(row[2]) > 0 and float(row[4]) > 0
 
 
+def test_small_trajectories_fit_the_lds_of_a_plain_launch(facts):
+    """Every size that the four-lanes-a-node form of gpga_run takes, with up to 20 entries of W a node."""
+    row, = [f for f in facts if f[0] == "node_run"]
+    assert int(row[2]) > 0 and 60_000 < int(row[4]) <= 65_536
+
+
 def test_pacing_controller_finds_and_follows_the_edge_of_a_launch_model(facts):
     """The controller that sets the rate of paced launches, run on the CPU against a model of what a
     launch reports (keeps up below an edge rate with occasional late launches, falls behind above it):
