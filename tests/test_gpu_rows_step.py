@@ -67,6 +67,24 @@ def test_one_launch_matches_separate_calls(hx, n, d, M, B, topology, H, momentum
     a.close(), b.close()
 
 
+@pytest.mark.parametrize("n,d,M,one_launch", [
+    (100, 10, 8000, False), (128, 40, 300, False), (128, 40, 32, True), (32, 256, 200, False), (8, 1000, 1000, True), (8, 5000, 1000, False)])
+def test_large_batches_on_many_nodes_keep_a_workgroup_per_node(hx, n, d, M, one_launch):
+    # full batches: one launch would leave the samples of all nodes to the few workgroups that the columns make
+    import torch
+    sim, _ = make(hx, n, d, M, 0, 2, "ring", 0, 0.9, "lsq", d)
+    ref, _ = make(hx, n, d, M, 0, 2, "ring", 0, 0.9, "lsq", d)
+    sim.run(2)
+    assert (int(sim.query("step_path")) == 9) == one_launch
+    for _ in range(2):
+        ref.local_grad()
+        ref.step()
+    torch.cuda.synchronize()
+    for u, v in zip(results(sim, 0.9)[0], results(ref, 0.9)[0]):
+        assert np.abs(u - v).max() <= TOL * np.abs(v).max()
+    sim.close(), ref.close()
+
+
 def test_rows_outside_the_data_poison_their_node_only(hx):
     import torch
     a, idx = make(hx, 8, 1000, 50, 9, 1, "none", 0, 0.9, "logreg", 1000, bad=True)
