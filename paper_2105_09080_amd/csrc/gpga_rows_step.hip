@@ -17,7 +17,7 @@
 namespace {
 
 constexpr int kRowsMaxNodes = 128;
-constexpr int64_t kRowsMaxStaged = 5120;       // (node, sample) pairs whose row numbers and coefficients go to LDS first
+constexpr int64_t kRowsMaxStaged = 4352;       // (node, sample) pairs whose row numbers and coefficients go to LDS first
 // Larger states are bound by their rows, which the separate kernels read in longer pieces (64 x 40 000: 1102 us a run
 // of 8 iterations here, 1025 there; 50 x 20 000: 660 here, 721 there).
 constexpr int64_t kRowsMaxElements = 1 << 21;
@@ -205,14 +205,14 @@ bool rows_step_fits(const gpga_ctx* c, int32_t Beff) {
     if (!c->default_geometry() || (c->problem != PROB_LSQ && c->problem != PROB_LOGREG)) return false;
     const bool sparse = c->topo == GPGA_TOPO_GRID || c->topo == GPGA_TOPO_EXPO || c->topo == GPGA_TOPO_CUSTOM;
     if (sparse && (!c->csr_ready || !c->csr_off_d)) return false;
-    // at most 64 KiB of x^(k+1/2), 32 KiB of sums and 40 KiB of samples in LDS
-    if (c->d < 4 || c->n > kRowsMaxNodes || (int64_t)c->n * c->d > kRowsMaxElements || c->max_lds_block < 136 * 1024) return false;
+    // at most 64 KiB of x^(k+1/2), 32 KiB of sums and 34 KiB of samples in LDS
+    if (c->d < 4 || c->n > kRowsMaxNodes || (int64_t)c->n * c->d > kRowsMaxElements || c->max_lds_block < 130 * 1024) return false;
     // Batches: a workgroup here takes the samples of all nodes for its columns, the separate accumulate pass has a workgroup
     // per node and 256 columns.  Up to as many samples as are staged this form wins or is even (n = 128, 32 samples: d = 64
-    // 19.7 -> 13.8 us an iteration, d = 2000 30.7 -> 23.9; n = 32, 128 samples, d = 20 000 121 -> 115); beyond them only where
-    // the separate pass leaves most of the chip idle (n = 8, d = 1000, 1000 samples 55.5 -> 34.0; n = 16, d = 1000, 2000
-    // samples 104 -> 99; against n = 16, d = 2500 75 -> 92; n = 32, d = 256, 4000 samples 238 -> 309; n = 100, d = 10, 8000
-    // samples 281 -> 1740).
+    // 19.7 -> 13.8 us an iteration, d = 2000 30.7 -> 23.9; n = 32, 128 samples, d = 20 000 121 -> 115, d = 3000 27.3 -> 28.3;
+    // with 160 samples d = 1500 24.8 -> 27.5); beyond them only where the separate pass leaves most of the chip idle (n = 8,
+    // d = 1000, 1000 samples 55.5 -> 34.0; n = 16, d = 1000, 2000 samples 104 -> 99; against n = 16, d = 2500 75 -> 92; n = 32,
+    // d = 256, 4000 samples 238 -> 309; n = 100, d = 10, 8000 samples 281 -> 1740).
     return (int64_t)c->n * Beff <= kRowsMaxStaged || (c->n <= 16 && (int64_t)c->n * ((c->d + 255) / 256) <= 128);
 }
 
