@@ -189,6 +189,10 @@ __global__ void __launch_bounds__(256) k_rows_margin_short(const float* __restri
 // wavefront order, so a minibatch of 32 rows is four chains of eight dependent loads instead of one of 32
 // and a small problem still fills the chip (cfg2: 1280 -> 5120 wavefronts, 15 -> 9 us).  W = 4
 // wavefronts per workgroup, 16 for minibatches of 64 rows and more.
+// Rows of up to 256 columns that are no whole quads keep one column a lane: such rows are bound by the chain of samples of
+// a wavefront, and a quad brings four chains of fp64 sums to a lane and fewer workgroups (gradient over 8000 rows of 10 on
+// 8 nodes 226 us with quads, 156 without, on 100 nodes 311 / 195; over 4000 rows of 255 on 8 nodes 154 / 103).
+__host__ __device__ __forceinline__ bool accum_quads(int64_t d) { return d > 256 || (d >= 4 && d % 4 == 0); }
 template <int W>
 __global__ void __launch_bounds__(kWave* W) k_rows_accum(const float* __restrict__ feat,
                                                     const float* __restrict__ coef,
@@ -204,9 +208,8 @@ __global__ void __launch_bounds__(kWave* W) k_rows_accum(const float* __restrict
     const int32_t* __restrict__ ii = idx ? idx + (int64_t)i * B : nullptr;
     float* __restrict__ gi = g + (int64_t)i * ld;
     // column quad; the last one of a ragged width is moved left and overlaps its neighbour (both store the same sums).
-    // Rows of fewer than four columns: one column a lane.
     const int64_t t = (int64_t)blockIdx.x * kWave + lane;
-    const bool quads = d >= 4, on = quads ? t * 4 < d : t < d;
+    const bool quads = accum_quads(d), on = quads ? t * 4 < d : t < d;
     const int64_t col = !quads ? t : t * 4 > d - 4 ? d - 4 : t * 4;
     double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
     if (on) {
@@ -1090,7 +1093,7 @@ hipError_t launch_rows_grad(const gpga_ctx* c, const int32_t* idx, int32_t B, fl
     if (!grad && c->d <= 32) return launch_rows_loss_short(c, idx, Beff, loss_out);
     const hipError_t e = launch_rows_margin(c, idx, B, loss_out);
     if (e != hipSuccess || !grad) return e;
-    const int64_t cols = c->d >= 4 ? (c->d + 3) / 4 : c->d;
+    const int64_t cols = accum_quads(c->d) ? (c->d + 3) / 4 : c->d;
     dim3 grid2((unsigned)((cols + kWave - 1) / kWave), (unsigned)c->n);
     if (Beff >= 64) {
         hipLaunchKernelGGL(k_rows_accum<16>, grid2, dim3(kWave * 16), 0, c->stream, c->feat, c->coef, idx, Beff, c->M,

@@ -106,3 +106,25 @@ def test_launch_overrides_and_large_states_keep_the_step_kernels(hx):
     a.run(2, idx)
     assert int(a.query("step_path")) == 1
     a.close()
+
+
+@pytest.mark.parametrize("d", [3, 5, 63, 65, 130, 255, 256, 257, 258])   # one column or four a lane of the accumulate pass
+@pytest.mark.parametrize("M", [7, 64])                                   # 4 or 16 wavefronts
+def test_gradients_of_ragged_rows(hx, d, M):
+    import torch
+    n = 3
+    feat, y, _ = inputs.logreg_problem(n, d, M, seed=d)
+    X = inputs.random_state(n, d, seed=1)[0]
+    sim = hx.Simulation(n, d, topology="ring", H=0, lr=0.1, ld=d + 1)
+    sim.problem_lsq(feat, y)
+    sim.g.fill_(7.0)
+    sim.set_state(X=X)
+    sim.local_grad()
+    torch.cuda.synchronize()
+    F, t = feat.astype(np.float64), y.astype(np.float64)
+    res = np.einsum("nmd,nd->nm", F, X.astype(np.float32).astype(np.float64)) - t
+    ref = np.einsum("nm,nmd->nd", res, F) / M
+    # a coefficient and a sum are rounded to fp32 once each
+    bound = 2 * 6e-8 * np.einsum("nm,nmd->nd", np.abs(res), np.abs(F)) / M + 6e-8 * np.abs(ref)
+    assert (np.abs(sim.G.cpu().numpy() - ref) <= bound).all() and (sim.g[:, d:].cpu().numpy() == 7.0).all()
+    sim.close()
