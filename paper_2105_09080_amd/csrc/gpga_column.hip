@@ -57,9 +57,11 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
     const int skew = (int)(col & 3);  // the last unit of a ragged width starts inside an RNG quad
     const float mu = a.ge.mu;
     const float third = 1.0f / 3.0f;
-    // whether the 64-lane tile of the step kernels that this unit lies in is a whole one (decides their row order)
-    const int64_t unit = tile * QT + q - a.ge.lead;
-    const bool whole = (((unit < 0 ? 0 : unit) + a.lead64) / kWave + 1) * kWave - a.lead64 <= a.ge.ncols;
+    // whether the 64-lane tile of the step kernels that unit number u of this tile lies in is a whole one (decides their row order)
+    auto whole_tile = [&](int u) {
+        const int64_t unit = tile * QT + u - a.ge.lead;
+        return (((unit < 0 ? 0 : unit) + a.lead64) / kWave + 1) * kWave - a.lead64 <= a.ge.ncols;
+    };
 
     v4f x[R], m[R], y[R];
 #pragma unroll
@@ -97,16 +99,24 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
         }
         __syncthreads();
         if (shift < 0) {
-            v4f mean = v4f(0.f);
-            if (rs == 0) {
-                SplitterTree tree;
-                for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0) tree.add(r0, splitter_sum(a.go, r0, n, whole, sy + q, QT));
-                mean = tree.sum * a.inv_n;
+            // Narrow tiles have many rows: a column a thread, of the first ones (with a whole unit a lane, 256 x 2M averaged
+            // in every iteration took 4920 us an iteration, 128 x 4M 2705, against 1260 and 892).  Wide tiles, of up to 32
+            // rows, leave it to the lanes of one wavefront.
+            if (QT < kWave) {
+                float* const sf = reinterpret_cast<float*>(sy);
+                for (int e = threadIdx.x; e < 4 * QT; e += blockDim.x) {
+                    SplitterTree<float> tree;
+                    for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0)
+                        tree.add(r0, splitter_column_sum(a.go, r0, n, whole_tile(e / 4), sf + e, 4 * QT));
+                    sf[e] = tree.sum * a.inv_n;  // nobody else reads this column meanwhile
+                }
+            } else if (rs == 0) {
+                SplitterTree<v4f> tree;
+                for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0) tree.add(r0, splitter_sum(a.go, r0, n, whole_tile(q), sy + q, QT));
+                sy[q] = tree.sum * a.inv_n;
             }
             __syncthreads();
-            if (rs == 0) sy[q] = mean;
-            __syncthreads();
-            mean = sy[q];
+            const v4f mean = sy[q];
 #pragma unroll
             for (int j = 0; j < R; ++j) x[j] = mean;
         } else if (a.mode == MIX_RING) {

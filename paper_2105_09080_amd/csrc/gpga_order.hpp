@@ -3,6 +3,8 @@
 // splitters' sums meet in a binary tree (a butterfly over lanes, then a tree over wavefronts).
 #pragma once
 
+#include <type_traits>
+
 #include "gpga_internal.hpp"
 
 // Sum of splitter r0 over n rows of one column unit, `step` units apart.  `whole`: the unit lies in a whole 64-lane tile
@@ -35,15 +37,58 @@ __device__ __forceinline__ v4f splitter_sum(const GlobalOrder& o, int r0, int n,
     return o.U < batched ? sum + y[o.U * step] : sum;
 }
 
-// The tree as a binary counter: splitters' sums go in in order, after the last of a power of two `sum` is the total.
-struct SplitterTree {
-    v4f level[5], sum;
-    __device__ __forceinline__ SplitterTree() {
-        sum = v4f(0.f);
+// The same sum of one column, rows `step` floats apart, for many columns at a time: a chain of LDS reads that a few lanes run
+// while the others wait, so eight rows are read ahead of the additions.
+__device__ __forceinline__ float splitter_column_sum(const GlobalOrder& o, int r0, int n, bool whole, const float* __restrict__ y, int step) {
+    const int RS = o.RL * o.wpb;
+    const bool by_parity = RS == 1 && whole;
+    const int batched = by_parity ? n - n % o.U : n;
+    const int stride = by_parity ? 2 * o.U : RS * o.U;
+    auto batches = [&](int base, auto batch_rows) {  // base, base + stride, ...
+        constexpr int U = decltype(batch_rows)::value, per = 8 / U;
+        float sum = 0.f;
+#pragma unroll 1
+        for (; base < batched; base += per * stride) {
+            float v[per][U];
 #pragma unroll
-        for (int l = 0; l < 5; ++l) level[l] = v4f(0.f);
+            for (int b = 0; b < per; ++b)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int row = base + b * stride + u * RS;
+                    v[b][u] = y[(row < n ? row : n - 1) * step];
+                }
+#pragma unroll
+            for (int b = 0; b < per; ++b) {
+                float part = 0.f;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (base + b * stride + u * RS < n) part += v[b][u];
+                if (base + b * stride < batched) sum += part;
+            }
+        }
+        return sum;
+    };
+    auto from = [&](int base) {  // batches of 1 or 4 rows (global_order)
+        return o.U == 1 ? batches(base, std::integral_constant<int, 1>{}) : batches(base, std::integral_constant<int, 4>{});
+    };
+    if (!by_parity) return from(r0);
+    const float odd = from(o.U);
+    float sum = from(0);
+#pragma unroll 1
+    for (int base = batched; base < n; ++base) sum += y[base * step];
+    return sum + odd;
+}
+
+// The tree as a binary counter: splitters' sums go in in order, after the last of a power of two `sum` is the total.
+template <typename T>
+struct SplitterTree {
+    T level[5], sum;
+    __device__ __forceinline__ SplitterTree() {
+        sum = T(0);
+#pragma unroll
+        for (int l = 0; l < 5; ++l) level[l] = T(0);
     }
-    __device__ __forceinline__ void add(int r0, const v4f& leaf) {
+    __device__ __forceinline__ void add(int r0, const T& leaf) {
         sum = leaf;
         bool carry = true;
 #pragma unroll

@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a
             if (on) leaf[r0 * QT + q] = splitter_sum(a.go, r0, n, whole, sy + q, QT);
         __syncthreads();
         if (!on) return;
-        SplitterTree tree;
+        SplitterTree<v4f> tree;
         for (int r0 = 0; r0 < RS; ++r0) tree.add(r0, leaf[r0 * QT + q]);
         const v4f mean = tree.sum * a.inv_n;
         for (int i = grp; i < n; i += NG) *reinterpret_cast<v4u*>(a.ge.x_new + (int64_t)i * a.ge.ld + col) = mean;

@@ -47,6 +47,9 @@ CASES = [(n, d, topology, H, 0.9, False, 5, d + pad)
 CASES += [(64, 1000, "full", 0, 0.0, False, 4, 1000), (64, 130, "ring", 4, 0.0, False, 64, 130), (20, 515, "expo1", 4, 0.9, True, 65, 515),
           (40, 129, "grid", 7, 0.9, True, 130, 129), (8, 600_001, "expo1", 4, 0.9, False, 8, 600_001),
           (64, 2_200_000, "ring", 4, 0.9, False, 8, 2_200_000)]   # the wide, paced step kernels on the other side
+# averages on narrow tiles, a column a thread: every order of the step kernel's sums, remainders of its batches
+CASES += [(33, 1031, "full", 0, 0.9, False, 3, 1031), (70, 130_003, "ring", 1, 0.9, False, 3, 130_004), (101, 600_001, "full", 0, 0.0, False, 2, 600_001),
+          (130, 8, "full", 0, 0.9, False, 3, 8), (199, 300_002, "full", 0, 0.9, False, 2, 300_003), (256, 550_000, "ring", 2, 0.9, True, 4, 550_000)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
