@@ -797,6 +797,8 @@ constexpr int64_t kPacedWaves = 2048;
 // n = 64 34.9 / 39.0, n = 256 111 / 128).
 constexpr int64_t kSplitWaves = 1280;
 
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
 // Default policy: large launches whose wavefronts each walk many rows run
 // persistent and paced, at the rate the controller of their kind has found;
 // everything else is a one-shot launch.
@@ -841,8 +843,10 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     const int64_t tiles = unit_tiles(ge, kWave);
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
-    // persistent and paced.
-    if (mode == MODE_PEER && vec == 4 && ge.d % 4 == 0 && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
+    // persistent and paced.  Forced ("always"), it takes rows of whole lanes or on 16-byte boundaries.
+    const bool takes_rows = c->opt_cycle_kernel != 1 || ge.d % 4 == 0 || (ge.ld % 4 == 0 && aligned16(ge.x) && aligned16(ge.x_new) &&
+                                                                         aligned16(ge.g) && (!ge.m || aligned16(ge.m)));
+    if (mode == MODE_PEER && vec == 4 && takes_rows && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
         c->opt_cycle_kernel != 0 && (tiles >= kPacedWaves || c->opt_cycle_kernel == 1)) {
         CycleArgs ca;
         ca.ge = ge;

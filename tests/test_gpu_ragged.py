@@ -56,3 +56,29 @@ def test_step_on_ragged_rows(hx, n, topology, opts, d, ld):
     for buf in (*sim._bufs, sim.m, sim.g):   # nothing beyond a row's d columns is written
         assert (host(buf)[:, d:] == 7.0).all()
     sim.close()
+
+
+@pytest.mark.parametrize("n,d,ld,k,opts,momentum,path", [
+    (64, 30_003, 30_004, 4, {"cycle_kernel": 1}, 0.9, 2), (64, 30_001, 30_004, 5, {"cycle_kernel": 1}, 0.0, 2),
+    (16, 257, 260, 1, {"cycle_kernel": 1, "blocks_per_cu": 1, "pace_gbs": 4000}, 0.9, 2),   # cycles of 8, a lone unit behind whole tiles
+    (64, 30_003, 30_003, 4, {"cycle_kernel": 1}, 0.9, 1),                                    # forced: rows on 16-byte boundaries only
+    (4, 600_001, 600_001, 1, {}, 0.9, 2), (8, 600_002, 600_007, 1, {}, 0.9, 2)])             # wide: whatever the alignment
+def test_row_streaming_kernel_on_ragged_rows(hx, n, d, ld, k, opts, momentum, path):
+    X, M, G = inputs.random_state(n, d, seed=d + n)
+    sim = hx.Simulation(n, d, topology="expo1", H=0, lr=0.1, momentum=momentum, ld=ld)
+    for name, v in opts.items():
+        sim.set_option(name, v)
+    for buf in (*sim._bufs, *([sim.m] if momentum else [])):
+        buf.fill_(7.0)
+    sim.set_state(X=X, M=M, G=G, k=k)
+    trace = sim.attach_trace(k + 1)
+    sim.step()
+    assert int(sim.query("step_path")) == path
+    X, M = orc.gossip_pga_step(X, M if momentum else np.zeros_like(M), G, k, topology="expo1", H=0, lr=0.1, momentum=momentum)
+    assert np.abs(host(sim.X) - X).max() <= TOL * np.abs(X).max()
+    if momentum:
+        assert np.abs(host(sim.M) - M).max() <= TOL * np.abs(M).max()
+    assert float(trace[k]) == pytest.approx(orc.consensus_error(X), rel=TOL)
+    for buf in sim._bufs:   # nothing beyond a row's d columns is written
+        assert (host(buf)[:, d:] == 7.0).all()
+    sim.close()
