@@ -791,11 +791,11 @@ hipError_t launch_global_u(int U, const LaunchPlan& plan, hipStream_t st, const 
 // all its rows, which is the shape the paced launch needs; below it the rows
 // are split over lanes / wavefronts of a workgroup instead.
 constexpr int64_t kPacedWaves = 2048;
-// Walks along cycles of 32 rows and more keep one wavefront per cycle and column tile down to five of them a compute unit
-// (shorter cycles are as fast either way: n = 16, 1563 tiles 25.4 us split, 25.7 whole): split rows have every
-// row open at once (ring, 1832 tiles: n = 64 157 us split, 126 whole; n = 32, 1954 tiles 58.2 / 55.7; with 489 tiles
-// n = 64 34.9 / 39.0, n = 256 111 / 128).
-constexpr int64_t kSplitWaves = 1280;
+// Walks along cycles of 32 rows and more keep one wavefront per cycle and column tile down to five and three quarters of them
+// a compute unit (shorter cycles are as fast either way: n = 16, 1563 tiles 25.4 us split, 25.7 whole), very long ones down to
+// five: split rows have every row open at once.  Ring, us split / whole: 1454 tiles n = 64 91 / 94, n = 256 375 / 385; 1504
+// tiles n = 32 54.5 / 52, n = 64 108 / 103, n = 256 441 / 428; 1290 tiles n = 256 364 / 376, n = 1000 1445 / 1400.
+inline int64_t split_waves(int64_t cycle) { return cycle >= 512 ? 1280 : cycle >= 32 ? 1472 : kPacedWaves; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -872,7 +872,7 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     if (mode != MODE_SELF && mode != MODE_INPLACE) {
         if (c->opt_row_split) {
             Q = c->opt_row_split;
-        } else if (tiles * a.C < (a.L >= 32 ? kSplitWaves : kPacedWaves)) {
+        } else if (tiles * a.C < split_waves(a.L)) {
             // too few column tiles to occupy the chip with one walker per cycle:
             // split each cycle over the wavefronts of a workgroup (LDS exchange)
             Q = pow2_floor(a.L / 4 > 0 ? a.L / 4 : 1);  // keep segments of >= 4 rows
