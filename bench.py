@@ -62,8 +62,8 @@ PAPER_CONTEXT = {
 
 # gpga_query "step_path" -> kernel
 PATH_NAMES = {1: "k_step_walk", 2: "k_step_cycles", 3: "k_step_global", 4: "k_step_tile", 5: "k_step_band",
-              6: "W = I walk + k_spmm_rows (k_step_circ if W is circulant)", 7: "k_small_run / k_node_run",
-              8: "k_column_run", 9: "k_rows_step"}
+              6: "W = I walk + k_spmm_rows", 7: "k_small_run / k_node_run", 8: "k_column_run", 9: "k_rows_step",
+              10: "k_step_circ"}
 
 
 def parse_args():

@@ -51,7 +51,8 @@ struct PaceState;  // gpga_pace.hpp
 constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
-                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9 };
+                      PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9,
+                      PATH_CIRCULANT = 10 };
 
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
@@ -199,8 +200,8 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& ge, int vec);
 hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, double* spread_partials = nullptr,
                            int64_t* spread_count = nullptr);
 
-// Circulant W on up to 1024 nodes, more than the tile kernel takes with wide lanes: the whole column tile in LDS, the next one loaded meanwhile.  circulant_fits tells
-// whether the context qualifies.
+// Circulant W on up to 1024 nodes, more than the tile kernel takes with wide lanes: the whole column tile in LDS, the next
+// one loaded meanwhile.  circulant_fits tells whether the context qualifies.
 bool circulant_fits(const gpga_ctx* c);
 hipError_t launch_step_circulant(const gpga_ctx* c, const StepGeom& geom);
 

@@ -732,6 +732,7 @@ hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, doubl
     //    consensus trace;
     //  * banded W on more rows: the sliding-window kernel (grid, n = 256 / 512 / 1024: 5.7 / 5.2 / 5.8 TB/s;
     //    the whole tile with 4-byte lanes 5.3 / 4.0 / -);
+    //  * circulant W on 225 to 1024 nodes that fills the chip (circulant_fits): the whole tile, pipelined;
     //  * any other W whose tile fits with 4-byte lanes (n <= 640): the whole tile, 16 wavefronts (static
     //    exponential graph, n = 256 / 512: 4.6 / 3.6 TB/s; 8-byte lanes are no faster; two passes 3.4 / 3.4);
     //  * else two passes.
@@ -747,7 +748,7 @@ hipError_t launch_step_csr(const gpga_ctx* c, const StepGeom& ge, int vec, doubl
         return launch_band<float>(c, ge, mom, band_waves, spread_partials, spread_count);
     }
     if (!wide_tile_fits && c->default_geometry() && circulant_fits(c)) {
-        c->note_path(ge.n <= 640 ? PATH_TILE : PATH_TWO_PASS, 16);
+        c->note_path(PATH_CIRCULANT, 16);
         return launch_step_circulant(c, ge);
     }
     // 8-byte lanes only on request ("mix_lane_bytes" = 8): they were the slowest of the three wherever two of them fit.

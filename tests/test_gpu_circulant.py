@@ -46,7 +46,7 @@ def test_circulant_steps_match_the_oracle(hx, n, d, pad, momentum, nesterov, cus
     X_ref, M_ref = X, (M if momentum else np.zeros_like(M))
     for k in range(2):   # both directions of the ping-pong
         sim.step()
-        assert int(sim.query("step_lane_bytes")) == 16
+        assert (int(sim.query("step_path")), int(sim.query("step_lane_bytes"))) == (10, 16)
         X_ref, M_ref = orc.gossip_pga_step(X_ref, M_ref, G, k, topology=topology, H=0, lr=0.1, momentum=momentum,
                                            nesterov=nesterov, W=W)
     assert np.abs(host(sim.X) - X_ref).max() <= TOL * np.abs(X_ref).max()

@@ -210,22 +210,27 @@ def test_cfg3_every_element_of_one_step_with_nesterov_momentum(hx, topology, k, 
     torch.cuda.empty_cache()
 
 
-SPARSE_AT_SIZE = [   # the last entry: (step_path, step_paced): 4 whole tile, 5 sliding window, 6 two passes
-    (64, 25_600_000, "grid", "whole-tile kernel, 16-byte lanes, paced", (4, 1)),
-    (64, 25_600_000, "expo", "whole-tile kernel, 16-byte lanes, paced", (4, 1)),
-    (128, 12_800_000, "expo", "whole-tile kernel, 128 KiB tile, 16 wavefronts", (4, 1)),
-    (256, 6_400_000, "expo", "whole-tile kernel, 4-byte lanes, 16 wavefronts", (4, 0)),
-    (256, 6_400_000, "grid", "sliding-window kernel, paced", (5, 1)),
-    (1024, 1_000_000, "grid", "sliding-window kernel, 8-byte lanes, paced", (5, 1)),
-    (1024, 1_000_000, "expo", "two passes", (6, 0)),
+SPARSE_AT_SIZE = [   # the last entry: (step_path, step_paced): 4 whole tile, 5 sliding window, 6 two passes, 10 circulant W
+    (64, 25_600_000, "grid", {}, "whole-tile kernel, 16-byte lanes, paced", (4, 1)),
+    (64, 25_600_000, "expo", {}, "whole-tile kernel, 16-byte lanes, paced", (4, 1)),
+    (128, 12_800_000, "expo", {}, "whole-tile kernel, 128 KiB tile, 16 wavefronts", (4, 1)),
+    (256, 6_400_000, "expo", {"mix_lane_bytes": 4}, "whole-tile kernel, 4-byte lanes, 16 wavefronts", (4, 0)),
+    (256, 6_400_000, "expo", {}, "circulant W, 512-byte row pieces", (10, 0)),
+    (256, 6_400_000, "grid", {}, "sliding-window kernel, paced", (5, 1)),
+    (1024, 1_000_000, "grid", {}, "sliding-window kernel, 8-byte lanes, paced", (5, 1)),
+    (1024, 1_000_000, "expo", {"mix_two_pass": 1}, "two passes", (6, 0)),
+    (1024, 1_000_000, "expo", {}, "circulant W, 128-byte row pieces", (10, 0)),
 ]
 
 
-@pytest.mark.parametrize("n,d,topology,what,expect", SPARSE_AT_SIZE, ids=[f"{n}x{d}-{t}" for n, d, t, _, _ in SPARSE_AT_SIZE])
-def test_sparse_W_every_element_of_one_step_at_full_size(hx, n, d, topology, what, expect):
+@pytest.mark.parametrize("n,d,topology,opts,what,expect", SPARSE_AT_SIZE,
+                         ids=["-".join([f"{n}x{d}", t, *o]) for n, d, t, o, _, _ in SPARSE_AT_SIZE])
+def test_sparse_W_every_element_of_one_step_at_full_size(hx, n, d, topology, opts, what, expect):
     # the sparse-W kernels in the launch configurations large problems get (synthetic gradients)
     kw = dict(topology=topology, H=0, lr=0.1, momentum=0.9)
     sim = hx.Simulation(n, d, **kw)
+    for name, v in opts.items():
+        sim.set_option(name, v)
     sim.problem_synthetic(7, 1e-3)
     _random_resident_state(sim, 400)
     sim.set_state(k=0)
