@@ -251,9 +251,8 @@ gpga_status gpga_consensus_error(gpga_ctx* ctx, double* out_host);
  * DEVICE pointer, 8-byte aligned, caller-owned) on the bound stream.  The call
  * allocates and frees nothing and does not synchronise: the per-workgroup partial sums
  * live in a static device array of 1 MiB (131072 doubles) that every GPU the library runs
- * on holds until the process ends.  Limit: one partial per 1024 columns on 16-byte
- * aligned rows with ld % 4 == 0 (d <= 134 216 704), per 256 columns otherwise
- * (d <= 33 554 432); a larger d gives EINVAL with the limit in gpga_last_error.  All
+ * on holds until the process ends.  Limit: one partial per 1024 columns
+ * (d <= 134 217 728); a larger d gives EINVAL with the limit in gpga_last_error.  All
  * calls on one GPU share that GPU's array: calls that overlap there (other streams or
  * threads) race; calls queued on one stream do not.  ESTATE before gpga_bind. */
 gpga_status gpga_consensus_error_static(gpga_ctx* ctx, double* out_dev);

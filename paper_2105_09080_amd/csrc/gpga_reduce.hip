@@ -291,17 +291,21 @@ hipError_t launch_probe_stream(int kind, const float* src, float* dst, const flo
     return hipGetLastError();
 }
 
-size_t consensus_partials_used(const gpga_ctx* c) {
-    const bool vec = aligned16(c->x) && (c->ld % 4 == 0);
-    const int64_t nv = vec ? c->d / 4 : 0;
-    return (size_t)((nv + 255) / 256 + (c->d - nv * 4 + 255) / 256);
-}
-
 // Row groups per workgroup of the two reductions over `units` column units: as few as give the chip (256 compute
 // units) about a thousand lanes each, and rows enough for every group to keep its loads in flight.
 static int reduce_split(int64_t units, int32_t n) {
     constexpr int64_t kLanes = 256 * 1024;
     return units >= kLanes ? 1 : units * 4 >= kLanes || n <= 32 ? 4 : 16;
+}
+
+static int64_t reduce_blocks(int64_t units, int split) {
+    const int lanes = split == 1 ? reduce_lanes(1) : kWave;
+    return (units + lanes - 1) / lanes;
+}
+
+size_t consensus_partials_used(const gpga_ctx* c) {
+    const int64_t units = c->d < 4 ? c->d : (c->d + 3) / 4;
+    return (size_t)reduce_blocks(units, c->d < 4 ? 16 : reduce_split(units, c->n));
 }
 
 size_t consensus_partials_needed(const gpga_ctx* c) {
@@ -327,7 +331,7 @@ hipError_t launch_fill_rows(const gpga_ctx* c, float* dst, const float* src) {
 
 template <typename T, int RS>
 static hipError_t launch_mean_split(const gpga_ctx* c, int64_t units, float* xbar) {
-    const int64_t blocks = (units + reduce_lanes(RS) - 1) / reduce_lanes(RS);
+    const int64_t blocks = reduce_blocks(units, RS);
     hipLaunchKernelGGL((k_col_mean<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, xbar);
     return hipGetLastError();
@@ -343,7 +347,7 @@ hipError_t launch_col_mean(const gpga_ctx* c, float* xbar) {
 
 template <typename T, int RS>
 static hipError_t launch_consensus_split(const gpga_ctx* c, int64_t units, double* parts, size_t cap, int64_t* count) {
-    const int64_t blocks = (units + reduce_lanes(RS) - 1) / reduce_lanes(RS);
+    const int64_t blocks = reduce_blocks(units, RS);
     if ((size_t)blocks > cap) return hipErrorOutOfMemory;
     hipLaunchKernelGGL((k_consensus<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, parts);

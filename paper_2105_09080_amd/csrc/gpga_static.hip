@@ -18,8 +18,8 @@
 
 namespace {
 
-// 1 MiB: one double per 256-lane workgroup of the reduction pass, i.e. d up to
-// 131072 x 1024 = 1.34e8 columns on the 128-bit path (3.3e7 on the scalar path).
+// 1 MiB: one double per workgroup of the reduction pass.  Wide rows have one per 256 lanes of four columns, whatever
+// their alignment: d up to 131072 x 1024 = 1.34e8 columns.
 constexpr size_t kStaticScratchDoubles = 131072;
 
 // No `used` attribute here: the compiler gives a static device variable that host code
@@ -69,9 +69,8 @@ extern "C" gpga_status gpga_consensus_error_static(gpga_ctx* c, double* out_dev)
     const size_t need = consensus_partials_used(c);
     if (need > kStaticScratchDoubles) {
         snprintf(c->err, sizeof(c->err),
-                 "d = %lld needs %zu partial sums, the static scratch holds %zu (d <= %zu on 16-byte aligned rows, "
-                 "%zu otherwise): use gpga_consensus_error",
-                 (long long)c->d, need, kStaticScratchDoubles, (kStaticScratchDoubles - 1) * 1024, kStaticScratchDoubles * 256);
+                 "d = %lld needs %zu partial sums, the static scratch holds %zu (d <= %zu): use gpga_consensus_error",
+                 (long long)c->d, need, kStaticScratchDoubles, kStaticScratchDoubles * 1024);
         return GPGA_EINVAL;
     }
     double* ptr = nullptr;

@@ -77,3 +77,15 @@ def test_static_scratch_after_steps_and_size_limit(hx):
     assert e.value.status == B.GPGA_EINVAL and "static scratch" in str(e.value)
     B.gpga_destroy(ctx)
     del t
+
+
+@pytest.mark.parametrize("n,d,ld", [(2, 34_000_001, 34_000_001), (2, 1_048_580, 1_048_583), (40, 1_048_576, 1_048_577), (3, 300_002, 300_003)])
+def test_static_scratch_holds_what_the_launch_uses_on_unaligned_rows(hx, n, d, ld):
+    # the guard counts the workgroups that are launched: the same ones whatever the alignment
+    sim = hx.Simulation(n, d, topology="ring", H=0, lr=0.1, momentum=0.0, ld=ld)
+    for buf in sim._bufs:
+        buf.normal_()
+    out = torch.zeros(1, dtype=torch.float64, device="cuda")
+    sim.consensus_error_static(out)
+    assert float(out.item()) == pytest.approx(sim.consensus_error(), rel=1e-12) and float(out.item()) > 0.0
+    sim.close()
