@@ -31,8 +31,9 @@ struct RowsStepArgs {
     int32_t B, M;
     int32_t mode;          // StencilMode, or one of the two below
     int32_t shift;         // one-peer offset
-    const int32_t* off;    // sparse W: K (signed circular offset, weight) entries a node, padded with weight 0
+    const int32_t* off;    // sparse W: (signed circular offset, weight) entries, K a node at most
     const float* val;
+    const int32_t* wptr;   // node i has wptr[i + 1] - wptr[i] of them
     int32_t K;
     GlobalOrder go;
     int32_t lead64;
@@ -156,11 +157,11 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_step(const RowsStepArgs a
             v = (y + sy[(i + a.shift >= n ? i + a.shift - n : i + a.shift) * QT + q]) * 0.5f;
         } else if (a.mode == kModeSparse) {
             v = v4f(0.f);
-            for (int p = 0; p < a.K; ++p) {
-                const float w = a.val[i * a.K + p];
+            const int entries = a.wptr[i + 1] - a.wptr[i];
+            for (int p = 0; p < entries; ++p) {
                 int j = i + a.off[i * a.K + p];
                 j = j < 0 ? j + n : j >= n ? j - n : j;
-                if (w != 0.f) v += w * sy[j * QT + q];
+                v += a.val[i * a.K + p] * sy[j * QT + q];
             }
         }
         *reinterpret_cast<v4u*>(a.ge.x_new + (int64_t)i * a.ge.ld + col) = v;
@@ -230,6 +231,7 @@ hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32
     a.shift = shift;
     a.off = c->csr_off_d;
     a.val = c->csr_ellval_d;
+    a.wptr = c->csr_ptr_d;
     a.K = c->csr_max_row;
     a.go = global_order(c);
     set_units(&a.ge, 4, kWave);

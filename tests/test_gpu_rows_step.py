@@ -96,6 +96,33 @@ def test_rows_outside_the_data_poison_their_node_only(hx):
     a.close()
 
 
+def test_an_explicit_zero_weight_carries_what_is_not_a_number(hx):
+    # entries of W that are there with weight 0: one launch multiplies them as the step kernels do, and no padding besides
+    import torch
+    from paper_2105_09080_amd import binding
+    n, d, M = 6, 40, 12
+    rows = [[(i, 0.75), ((i + 1) % n, 0.25)] + ([((i + 3) % n, 0.0)] if i == 2 else []) for i in range(n)]
+    ptr = np.cumsum([0] + [len(r) for r in rows])
+    col, val = [j for r in rows for j, _ in r], [w for r in rows for _, w in r]
+    out = []
+    for fused in (True, False):
+        sim, idx = make(hx, n, d, M, 4, 1, "custom", 0, 0.9, "lsq", d)
+        binding.gpga_set_mixing_csr(sim.ctx, ptr, col, val)
+        x = inputs.random_state(n, d, seed=1)[0]
+        x[5, 7] = np.nan
+        sim.set_state(X=x)
+        if fused:
+            sim.run(1, idx)
+        else:
+            sim.local_grad(idx[0])
+            sim.step()
+        torch.cuda.synchronize()
+        assert (int(sim.query("step_path")) == 9) == fused
+        out.append(torch.isnan(sim.X).cpu().numpy())
+        sim.close()
+    assert np.array_equal(out[0], out[1]) and out[0][2].any() and not out[0][1].any()
+
+
 def test_launch_overrides_and_large_states_keep_the_step_kernels(hx):
     a, idx = make(hx, 8, 1000, 50, 9, 2, "ring", 0, 0.9, "logreg", 1000)
     a.set_option("unroll", 2)
