@@ -340,9 +340,50 @@ void node_run_sizes() {
     std::printf("node_run taken %" PRId64 " most_lds %zu\n", taken, most);
 }
 
+// Recognising circulant matrices: the named graphs that are, whatever the order of a row's entries, and near misses that are not.
+void circulant_matrices() {
+    int32_t k, off[kMaxCirculant];
+    float val[kMaxCirculant];
+    std::mt19937 rng(7);
+    for (int32_t n : {1, 2, 3, 5, 8, 16, 31, 100, 225, 256, 1000, 1024}) {
+        HostCsr w;
+        build_static_expo_csr(n, &w);
+        expect(circulant_rows(n, w, kMaxCirculant, &k, off, val), "the static exponential graph is circulant");
+        expect(k == w.ptr[1], "entries a row");
+        std::vector<double> row((size_t)n, 0.0), want((size_t)n, 0.0);
+        for (int32_t p = 0; p < k; ++p) {
+            expect(off[p] >= 0 && off[p] < n && (p == 0 || off[p] > off[p - 1]), "offsets ascend in [0, n)");
+            row[(size_t)off[p]] += val[p];
+        }
+        for (int32_t p = 0; p < w.ptr[1]; ++p) want[(size_t)w.col[p]] += w.val[p];
+        expect(row == want, "offsets and weights are those of row 0");
+        std::printf("circulant %d %d\n", n, k);
+        if (n < 5) continue;
+        HostCsr shuffled = w;
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t p = w.ptr[i + 1] - 1; p > w.ptr[i]; --p) {
+                const int32_t o = w.ptr[i] + (int32_t)(rng() % (uint32_t)(p - w.ptr[i] + 1));
+                std::swap(shuffled.col[(size_t)p], shuffled.col[(size_t)o]);
+                std::swap(shuffled.val[(size_t)p], shuffled.val[(size_t)o]);
+            }
+        expect(circulant_rows(n, shuffled, kMaxCirculant, &k, off, val), "the order of a row's entries does not matter");
+        HostCsr other = w;
+        other.val[(size_t)w.ptr[n - 1]] += 1e-3f;
+        expect(!circulant_rows(n, other, kMaxCirculant, &k, off, val), "another weight in the last row");
+        other = w;
+        other.col[(size_t)w.ptr[n - 1]] = (w.col[(size_t)w.ptr[n - 1]] + 3) % n;
+        expect(!circulant_rows(n, other, kMaxCirculant, &k, off, val), "another neighbour in the last row");
+        expect(!circulant_rows(n, w, w.ptr[1] - 1, &k, off, val), "more entries than asked for");
+        HostCsr grid;
+        build_grid_csr(n, &grid);
+        if (n == 100) expect(!circulant_rows(n, grid, kMaxCirculant, &k, off, val), "a torus of 10 x 10 is not circulant");
+    }
+}
+
 }  // namespace
 
 int main() {
+    circulant_matrices();
     node_run_sizes();
     rows_deal();
     named_graphs();

@@ -92,6 +92,15 @@ def test_small_trajectories_fit_the_lds_of_a_plain_launch(facts):
     assert int(row[2]) > 0 and 60_000 < int(row[4]) <= 65_536
 
 
+def test_circulant_matrices_are_recognised(facts):
+    """Offsets and weights of the static exponential graph against the oracle's matrix; the near misses are the check program's own."""
+    rows = {int(f[1]): int(f[2]) for f in facts if f[0] == "circulant"}
+    for n in (3, 8, 31, 225, 1024):
+        W = orc.mixing_matrix("expo", n, 0)
+        assert rows[n] == np.count_nonzero(W[0])
+        assert all(np.array_equal(np.roll(W[0], i), W[i]) for i in (1, n // 2, n - 1))
+
+
 def test_pacing_controller_finds_and_follows_the_edge_of_a_launch_model(facts):
     """The controller that sets the rate of paced launches, run on the CPU against a model of what a
     launch reports (keeps up below an edge rate with occasional late launches, falls behind above it):
