@@ -95,7 +95,15 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
             s_val[p] = a.w.val[p];
         }
     }
-    const int64_t ld = a.ge.ld;
+    // Scalar registers: with more than 80 (a granule of 16 and the trap handler's 16 come on top) only seven wavefronts fit a
+    // SIMD, and the second of two workgroups of 16 wavefronts does not start (4-byte lanes, 225 to 300 nodes, 84 registers:
+    // n = 256, d = 976 544 1414 us instead of 1120).  Single columns need neither shift nor a count of units of their own.
+    StepGeom ge = a.ge;
+    if (V == 1) {
+        ge.lead = 0;
+        ge.ncols = ge.d;
+    }
+    const int64_t ld = ge.ld;
     const float lr = a.ge.lr, mu = a.ge.mu;
     // Pacing counts rows of the WORKGROUP, so that all its wavefronts have the same deadlines whatever the remainder of
     // n by the wavefronts: counted per wavefront, those with a row less measured themselves as late at every rate, and
@@ -108,9 +116,9 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
     // Workgroups stride over the column tiles (one tile each in the default one-shot launch).
     // A paced launch has exactly the resident workgroups: they then read the same row group
     // of their tiles at the same time and later store the same output rows.
-    for (int64_t tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
-        const int64_t col = unit_column<T>(a.ge, tile, kWave, lane);
-        const bool on = unit_on(a.ge, tile, kWave, lane);
+    for (uint32_t tile = blockIdx.x; tile < (uint32_t)a.tiles; tile += gridDim.x) {  // fewer than 2^31 tiles
+        const int64_t col = unit_column<T>(ge, tile, kWave, lane);
+        const bool on = unit_on(ge, tile, kWave, lane);
 
         const float* __restrict__ xp = a.ge.x + col;
         const float* __restrict__ gp = a.ge.g + col;
@@ -122,7 +130,7 @@ __global__ void __launch_bounds__(kWave* kTileWavesMax) k_step_tile(const TileAr
         // predicates: all the loads of a group are issued back to back before the first use,
         // and nothing makes them wait for the stores of the group before.
         int base = wave;
-        if (whole_units(a.ge, tile, kWave)) {  // every lane has a column
+        if (whole_units(ge, tile, kWave)) {  // every lane has a column
             for (; base + (kTileUnroll - 1) * kTileWaves < n; base += kTileWaves * kTileUnroll) {
                 T xv[kTileUnroll], mv[kTileUnroll], gv[kTileUnroll];
                 pace_wait(run, tile_units + (uint32_t)(base - wave) * kLoadUnits);
