@@ -294,8 +294,7 @@ hipError_t launch_probe_stream(int kind, const float* src, float* dst, const flo
 // Row groups per workgroup of the two reductions over `units` column units: as few as give the chip (256 compute
 // units) about a thousand lanes each, and rows enough for every group to keep its loads in flight.
 static int reduce_split(int64_t units, int32_t n) {
-    constexpr int64_t kLanes = 256 * 1024;
-    return units >= kLanes ? 1 : units * 4 >= kLanes || n <= 32 ? 4 : 16;
+    return units >= 98304 ? 1 : n <= 32 || units >= (n <= 48 ? 24576 : 49152) ? 4 : 16;
 }
 
 static int64_t reduce_blocks(int64_t units, int split) {
