@@ -475,15 +475,16 @@ def test_cfg3_sized_slabs_sparse_W_and_nesterov(hx, topology, nesterov):
                      gossip_path=(1,) if topology == "ring" else (4,))
 
 
-@pytest.mark.parametrize("topology,path", [("grid", 5), ("expo", 6)])
-def test_cfg5_sized_slabs_sparse_W(hx, topology, path):
+@pytest.mark.parametrize("topology,path,opts", [("grid", 5, {}), ("expo", 6, {"mix_two_pass": 1}), ("expo", 10, {})])
+def test_cfg5_sized_slabs_sparse_W(hx, topology, path, opts):
     # n = 1024 rows (synthetic gradients on the cfg5 shape so that the oracle can follow column slabs): the
-    # 32 x 32 grid is banded and takes the sliding-window kernel, the static exponential graph the two passes
-    # (local update written over the old iterate, then the sparse product)
+    # 32 x 32 grid is banded and takes the sliding-window kernel, the static exponential graph is circulant and
+    # takes the kernel made for that; forced, the two passes (local update written over the old iterate, then the
+    # sparse product)
     c = dict(inputs.CONFIGS["cfg5"], problem="synthetic", grad_var=1e-3)
     inputs.CONFIGS["cfg5_synth"] = c
     try:
-        _slab_trajectory(hx, "cfg5_synth", topology, n_slabs=16, width=256, T=10, H=8, gossip_path=(path,))
+        _slab_trajectory(hx, "cfg5_synth", topology, n_slabs=16, width=256, T=10, H=8, opts=opts, gossip_path=(path,))
     finally:
         del inputs.CONFIGS["cfg5_synth"]
 
