@@ -520,11 +520,7 @@ static gpga_status run_step(gpga_ctx* c, bool global, int32_t rows_B = 0, const 
     ge.n = c->n;
     ge.lr = scheduled_lr(c, c->k);
     ge.mu = c->mu;
-    // 16-byte lanes whatever the alignment of the rows; only rows of fewer than 4 columns take 4-byte lanes.
-    // Rows that are not 16-byte aligned, 4-byte lanes and a pass of their own for the last columns against
-    // this: ring n = 64, d = 25 000 001 10.7 -> 5.9 ms (4-byte lanes are not paced); n = 16, d = 1 000 003
-    // 85 -> 65 us; grid n = 64, d = 4 100 001 2.60 -> 1.23 ms; W = I n = 64, d = 1 000 001 447 -> 219 us.
-    const int vec = c->d >= 4 ? 4 : 1;
+    const int vec = step_lane_columns(c);
     // Consensus trace of this iteration: 0 after a global average (all rows get the same
     // bits); sums produced by the fused kernel itself when it stores whole columns once
     // (no unit overlaps another: d is a multiple of the lane width); else one reduction

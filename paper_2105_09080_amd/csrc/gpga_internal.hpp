@@ -238,6 +238,8 @@ hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32
 // small_run_fits tells whether the context's problem and sizes qualify.
 bool small_run_fits(const gpga_ctx* c, const int32_t* idx, int32_t B);
 hipError_t launch_small_run(const gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, const float* lr);
+// Columns a lane of the step kernels takes: 4 (16-byte lanes) or 1.
+int step_lane_columns(const gpga_ctx* c);
 // How the global-average kernel adds the rows of a column on this context: RL row lanes x wpb wavefronts share the
 // rows, each in batches of U.
 struct GlobalOrder {

@@ -291,8 +291,10 @@ hipError_t launch_probe_stream(int kind, const float* src, float* dst, const flo
     return hipGetLastError();
 }
 
-// Row groups per workgroup of the two reductions over `units` column units: as few as give the chip (256 compute
-// units) about a thousand lanes each, and rows enough for every group to keep its loads in flight.
+// Row groups per workgroup of the two reductions over `units` column units: as few as give the chip lanes enough, for the sum
+// of the partials follows in one workgroup, and rows enough for every group to keep its loads in flight.  Consensus distance
+// with 1 / 4 groups: 4 x 900 000 8.9 / 11.5 us, 16 x 520 000 8.1 / 9.5, 256 x 400 000 (mean) 60 / 64; with 4 / 16 groups:
+// 33 x 150 000 8.0 / 10.0; with 1 / 16: 64 x 250 000 18.9 / 15.8, 64 x 50 000 11.8 / 7.2.
 static int reduce_split(int64_t units, int32_t n) {
     return units >= 98304 ? 1 : n <= 32 || units >= (n <= 48 ? 24576 : 49152) ? 4 : 16;
 }

@@ -822,6 +822,10 @@ LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool w
 
 }  // namespace
 
+static bool rows_on_16_bytes(const gpga_ctx* c) {
+    return c->ld % 4 == 0 && aligned16(c->x) && aligned16(c->x_new) && aligned16(c->g) && (!c->m || aligned16(c->m));
+}
+
 hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, int32_t S, int vec,
                             double* spread_partials, int64_t* spread_count) {
     if (spread_count) *spread_count = 0;
@@ -844,8 +848,7 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
     // persistent and paced.  Forced ("always"), it takes rows of whole lanes or on 16-byte boundaries.
-    const bool takes_rows = c->opt_cycle_kernel != 1 || ge.d % 4 == 0 || (ge.ld % 4 == 0 && aligned16(ge.x) && aligned16(ge.x_new) &&
-                                                                         aligned16(ge.g) && (!ge.m || aligned16(ge.m)));
+    const bool takes_rows = c->opt_cycle_kernel != 1 || ge.d % 4 == 0 || rows_on_16_bytes(c);
     if (mode == MODE_PEER && vec == 4 && takes_rows && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
         c->opt_cycle_kernel != 0 && (tiles >= kPacedWaves || c->opt_cycle_kernel == 1)) {
         CycleArgs ca;
@@ -940,9 +943,22 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
                : launch_walk_mode<float, 0>(mode, U, lp, c->stream, a);
 }
 
+// 16-byte lanes on rows on 16-byte boundaries, and on wide rows whatever their alignment (4-byte lanes there: ring n = 64,
+// d = 25 000 001 10.7 -> 5.9 ms, they are not paced; n = 16, d = 1 000 003 85 -> 65 us; grid n = 64, d = 4 100 001 2.60 ->
+// 1.23 ms; W = I n = 64, d = 1 000 001 447 -> 219 us).  Narrow rows of another alignment keep 4-byte lanes: their steps are
+// bound by the chain of rows of a wavefront, and a quarter of the columns a lane makes four times the wavefronts (16 / 4
+// bytes: ring n = 1000, d = 201 79 / 48 us, d = 4001 104 / 58, n = 100, d = 17 001 16.5 / 15.1, n = 20, d = 17 001 6.7 / 6.2;
+// n = 230, d = 20 001 even).
+constexpr int64_t kWideRagged = 36864;
+int step_lane_columns(const gpga_ctx* c) {
+    if (c->d < 4) return 1;
+    const bool wide = c->d >= kWideRagged || (c->d >= kWideRagged / 2 && (int64_t)c->n * c->d >= 64 * kWideRagged);
+    return wide || rows_on_16_bytes(c) ? 4 : 1;
+}
+
 GlobalOrder global_order(const gpga_ctx* c) {
     const int n = c->n, waves = c->opt_waves ? c->opt_waves : 4;
-    const int vec = c->d >= 4 ? 4 : 1;
+    const int vec = step_lane_columns(c);
     // Spread rows over lanes and waves only when columns alone cannot fill the chip.
     const int64_t tiles64 = ((c->d + vec - 1) / vec + kWave - 1) / kWave;
     int RL = 1, wpb = 1;

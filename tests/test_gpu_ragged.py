@@ -82,3 +82,18 @@ def test_row_streaming_kernel_on_ragged_rows(hx, n, d, ld, k, opts, momentum, pa
     for buf in sim._bufs:   # nothing beyond a row's d columns is written
         assert (host(buf)[:, d:] == 7.0).all()
     sim.close()
+
+
+@pytest.mark.parametrize("n,d,ld,lane_bytes", [
+    (400, 501, 501, 4), (400, 504, 505, 4), (400, 501, 504, 16), (8, 36_863, 36_863, 4), (8, 36_865, 36_865, 16), (128, 18_431, 18_431, 4), (130, 18_433, 18_434, 16)])
+@pytest.mark.parametrize("topology", ["ring", "full", "none"])
+def test_narrow_rows_of_another_alignment_keep_four_byte_lanes(hx, n, d, ld, lane_bytes, topology):
+    X, M, G = inputs.random_state(n, d, seed=d + n)
+    sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=0.9, ld=ld)
+    sim.set_state(X=X, M=M, G=G, k=0)
+    sim.step()
+    assert int(sim.query("step_lane_bytes")) == lane_bytes
+    X, M = orc.gossip_pga_step(X, M, G, 0, topology=topology, H=0, lr=0.1, momentum=0.9)
+    for got, want in ((host(sim.X), X), (host(sim.M), M)):
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    sim.close()
