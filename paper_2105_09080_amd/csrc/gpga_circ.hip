@@ -171,10 +171,24 @@ hipError_t launch_circ_rows(const gpga_ctx* c, const CircArgs& a) {
 
 }  // namespace
 
+// Row pieces of 128 bytes (more than 512 nodes) want whole cache lines: a piece that straddles two moves twice the bytes, and
+// the two lines of a row are fetched by workgroups far apart.  Us this kernel / the others, n = 700: rows on 128 bytes, 250M
+// elements 963 / 1544; on 64 bytes 1419 / 1625, with 6M 54 / 45; on 32 bytes 1642 / 1711 and 526 / 404 (60M), on 16 bytes 2551
+// / 1676; other rows 2652 / 1788, but where those have 4-byte lanes 29 / 56 (3M).  (Wider pieces lose less: 512-byte ones win
+// at any alignment, 256-byte ones win or are even up to 60M elements and are within a fifth either way beyond.)
+static bool pieces_pay(const gpga_ctx* c) {
+    if (c->n <= 512) return true;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(c->x) | reinterpret_cast<uintptr_t>(c->x_new) | reinterpret_cast<uintptr_t>(c->g) |
+                         reinterpret_cast<uintptr_t>(c->m) | (uintptr_t)(c->ld * 4);
+    const int64_t elements = (int64_t)c->n * c->d;
+    if (at % 16 == 0) return at % 128 == 0 || (at % 64 == 0 && elements >= 1 << 24);
+    return elements < (c->n <= 640 ? 1 << 22 : 3 << 22);
+}
+
 bool circulant_fits(const gpga_ctx* c) {
     // From 225 nodes on: with fewer the tile kernel's 4-byte lanes are as fast or faster (n = 200, d = 1M 790 us against 836;
     // n = 250 1111 against 1028).
-    if (c->csr_circ_k == 0 || c->n <= 224 || c->n > 1024 || c->d < 4 || c->max_lds_block < 128 * 1024) return false;
+    if (c->csr_circ_k == 0 || c->n <= 224 || c->n > 1024 || c->d < 4 || c->max_lds_block < 128 * 1024 || !pieces_pay(c)) return false;
     // Tiles for half the compute units: below, the kernels that split rows over more workgroups are faster (n = 1024,
     // 38 tiles 26 us against 16, 157 tiles 38.4 against 40.4; n = 600, 188 tiles 22 against 55).
     return (c->d + 3) / 4 >= (int64_t)circ_lanes(c->n) * c->num_cus / 2;

@@ -67,3 +67,18 @@ def test_the_pacing_rate_holds_where_rows_do_not_divide_among_wavefronts(hx, n, 
     assert int(sim.query("step_paced")) == 1
     assert min(sim.query("pace_rate_gbs:tile"), sim.query("pace_rate_gbs:tile/1")) > 2500.0
     sim.close()
+
+
+@pytest.mark.parametrize("n,d,path", [
+    (700, 16_640, 10), (700, 16_656, 6), (700, 16_644, 6), (700, 24_016, 10), (700, 24_001, 6), (600, 24_001, 4), (400, 50_001, 10), (240, 70_002, 10)])
+def test_rows_that_straddle_cache_lines_keep_the_other_kernels(hx, n, d, path):
+    # 128-byte row pieces (more than 512 nodes) on 128-, 64-, 16- and 4-byte boundaries; wider pieces at any
+    X, M, G = inputs.random_state(n, d, seed=n + d)
+    sim = hx.Simulation(n, d, topology="expo", H=0, lr=0.1, momentum=0.9)
+    sim.set_state(X=X, M=M, G=G, k=0)
+    sim.step()
+    assert int(sim.query("step_path")) == path
+    X_ref, M_ref = orc.gossip_pga_step(X, M, G, 0, topology="expo", H=0, lr=0.1, momentum=0.9)
+    assert np.abs(host(sim.X) - X_ref).max() <= TOL * np.abs(X_ref).max()
+    assert np.abs(host(sim.M) - M_ref).max() <= TOL * np.abs(M_ref).max()
+    sim.close()
