@@ -83,8 +83,9 @@ gpga_status gpga_destroy(gpga_ctx* ctx);
  *             caller itself (e.g. a real backward pass) before gpga_step
  * After each gpga_step the roles of x_dev and x_new_dev swap (gpga_current_x).
  * No two of the four arrays may overlap (EINVAL).
- * Pointers must be 4-byte aligned; 16-byte aligned pointers with ld % 4 == 0
- * take the 128-bit path.  hip_stream is a hipStream_t (NULL = default stream). */
+ * Pointers must be 4-byte aligned.  Every kernel has 128-bit lanes for 16-byte aligned
+ * pointers with ld % 4 == 0, and for wide rows (from some 20 000 columns on) whatever their
+ * alignment.  hip_stream is a hipStream_t (NULL = default stream). */
 gpga_status gpga_bind(gpga_ctx* ctx, float* x_dev, float* x_new_dev, float* m_dev,
                       float* g_dev, int64_t ld, void* hip_stream);
 
@@ -189,6 +190,10 @@ gpga_status gpga_step(gpga_ctx* ctx);
  * of the same loop unless option "small_run" is 0: whole iterations - gradients,
  * momentum and local update, gossip step or global average, consensus trace - run
  * inside single-workgroup launches of up to 256 iterations with the state in LDS.
+ * Other problems with stored features on up to 128 nodes (n*d <= 2^21, up to 4352 samples
+ * an iteration over all nodes, more on up to 16 narrow nodes) run gradient sums, update and
+ * mixing in one launch; synthetic gradients on up to 256 nodes run several iterations a launch
+ * (option "column_run").
  * The results are the same to rounding and land where T separate steps leave them:
  * the live X (gpga_current_x) in the same one of the two bound arrays, m updated,
  * g holding the gradients of the last iteration. */
@@ -206,8 +211,11 @@ gpga_status gpga_run(gpga_ctx* ctx, int64_t T, const int32_t* batch_table_dev, i
  * (n <= 256).  Above that, a W whose neighbours all lie within a circular distance
  * band <= 32 of their node (n >= 4 band; the grid is one: band = its width) runs, on
  * large problems, as a fused sliding-window kernel that keeps 4 band + 16 rows in LDS
- * (still 20 B per element); any other W runs as a local-update pass followed by a
- * sparse product (28 B per element).  On
+ * (still 20 B per element); a circulant W of up to 16 entries a row (EXPO is one) on 225 to
+ * 1024 nodes runs, where its column tiles fill the chip, as a fused kernel that loads one tile
+ * while it mixes another (20 B; more than 512 nodes: rows on 128-byte boundaries, or 64 on
+ * large problems); any other W runs as a local-update pass followed by a sparse product
+ * (28 B per element).  On
  * every path g_dev is only read, and the array that held X^(k) holds unspecified
  * values after the step (as after any step: it is the target of the next one). */
 gpga_status gpga_set_mixing_csr(gpga_ctx* ctx, const int64_t* row_ptr_host, const int32_t* col_host,
@@ -282,13 +290,13 @@ gpga_status gpga_node_mean(gpga_ctx* ctx, const float* v_dev, double* out_dev);
 gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
 
 /* Launch-geometry overrides for measurement sweeps; values outside the
- * documented range give EINVAL.  Names: "unroll" (rows in flight per lane: 1, 2,
+ * documented range give EINVAL.  Any of them that is set also keeps gpga_run and circulant
+ * W on the step kernels the overrides are for.  Names: "unroll" (rows in flight per lane: 1, 2,
  * 4, 8), "waves" (wavefronts per workgroup: 1, 2, 4, 8), "row_split" (wavefronts
  * sharing one column tile along the node axis, 0 = automatic, else 1, 2, 4, 8;
  * must not exceed "waves"), "row_lanes" (global-average kernel: lanes of a
  * wavefront spread over rows: 0 = automatic, 1, 2, 4), "xcd_swizzle" (0/1),
- * "mix_two_pass" (1 = sparse-W gossip steps always take the two-pass path; any override that is set
- * also keeps gpga_run and circulant W on the step kernels the overrides are for),
+ * "mix_two_pass" (1 = sparse-W gossip steps always take the two-pass path),
  * "mix_spmm_lanes" (two-pass path, second pass: lanes per column tile, 0 = automatic
  * (narrower as n grows, so that a tile's rows stay in one L2), 64, 128, 256),
  * "mix_band" (sliding-window kernel for banded W: -1 = automatic (large problems whose
@@ -304,7 +312,8 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * the stream is being captured), 0 = one iteration at a time),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
- * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always),
+ * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always, on rows
+ * of whole 16-byte lanes or on 16-byte boundaries),
  * "pace_min_cycle" (shortest row cycle whose walk is paced, 0 = automatic (4)),
  * "blocks_per_cu" (persistent launch of the fused step: -1 = automatic, 0 = one
  * workgroup per column-tile group, k = 1..32 resident workgroups per compute unit,

@@ -8,8 +8,9 @@
 // loads the same rows of its next tile, updates them and keeps their x^(k+1/2) in registers (8 x 16 bytes a thread);
 // between two tiles they move to LDS.  Being circulant is what makes the mixing cheap: offsets and weights are scalars,
 // a neighbour's address is one add and one wrap.
-// Bound: memory with n rows open at once.  Static exponential graph, momentum 0.9: n = 1024, d = 1M 6.20 -> 4.03 ms
-// (5.1 TB/s of 20 bytes an element), n = 700, d = 500k 2.23 -> 1.43 ms; against the tile kernel with 4-byte lanes n = 512,
+// (y and two rows of x, m and g in flight fill 128 registers: 32 a lane spill, 18 without momentum.)
+// Bound: memory with n rows open at once.  Static exponential graph, momentum 0.9: n = 1024, d = 1M 6.20 -> 3.7 - 4.0 ms
+// (5.1 to 5.5 TB/s of 20 bytes an element), n = 700, d = 500k 2.23 -> 1.43 ms; against the tile kernel with 4-byte lanes n = 512,
 // d = 2M 5.68 -> 4.19 ms, n = 256, d = 4M 4.77 -> 4.16 ms, n = 300, d = 1M without momentum 1.18 -> 0.75 ms.
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"

@@ -6,13 +6,13 @@
 // LDS - and stores x, m and the last gradient once: 20 bytes per element for the whole trajectory, where one
 // iteration at a time takes 24 (g written, then read by the step) per iteration.
 //
-// Bound: the vector ALUs, ~75 instructions per four elements and iteration (eight Philox rounds - the first two
-// depend on the column and on uniform values only - Box-Muller, update, mix); memory for very few iterations.
-// Measured on 64 x 25.6M elements, momentum 0.9: 0.65 ms an iteration on top of 5.9 ms for the load and the store
-// (33 GB, 5.6 TB/s); 6 iterations 37.8 -> 9.7 ms, 2 iterations 12.5 -> 7.2 ms.  One iteration would take the 6.2 ms
-// that the gradient kernel and a paced step take, so a run of one iteration stays with those.
-// A thread owns R consecutive rows of one 16-byte column unit: with R = 2 the state takes 24 registers, so that
-// two workgroups of 16 wavefronts fit on a compute unit and one loads or stores while the other computes.
+// Bound: the vector ALUs, some 75 instructions per four elements and iteration (ten Philox rounds, Box-Muller, update, mix);
+// memory for very few iterations.  Measured on 64 x 25.6M elements, momentum 0.9: 0.5 ms an iteration on top of 5.9 ms for
+// the load and the store (33 GB, 5.6 TB/s); 6 iterations 37.8 -> 8.5 ms, 2 iterations 12.5 -> 7.2 ms.  One iteration would
+// take the 6.2 ms that the gradient kernel and a paced step take, so a run of one iteration stays with those.
+// A thread owns R consecutive rows of one 16-byte column unit: with R = 2 the state takes 24 registers, and 64 in all let two
+// workgroups of 16 wavefronts fit on a compute unit, so that one loads or stores while the other computes.  That cap is
+// tight: 33 to 128 nodes spill 10 registers a lane (4 without momentum), up to 32 nodes 5 (none), more than 128 none.
 #include "gpga_internal.hpp"
 #include "gpga_order.hpp"
 #include "gpga_rng.hpp"
@@ -171,8 +171,8 @@ hipError_t launch_column(const gpga_ctx* c, ColumnArgs a) {
 }
 
 // Tile width: all rows in 1024 threads and 64 KiB of LDS at most.  (n = 64: row pieces of 256 bytes instead of 512 in
-// workgroups of half the size run 2 iterations in 7.35 instead of 7.18 ms and 6 in 9.33 instead of 9.61; a persistent
-// launch that loads the next tile while it computes - half the wavefronts for twice the registers - takes 8.6 and 11.5.)
+// workgroups of half the size ran 2 iterations in 7.35 instead of 7.18 ms and 6 in 9.33 instead of 9.61; a persistent
+// launch that loads the next tile while it computes - half the wavefronts for twice the registers - took 8.6 and 11.5.)
 template <int MOM>
 hipError_t launch_column_rows(const gpga_ctx* c, const ColumnArgs& a) {
     if (a.ge.n <= 32) return launch_column<MOM, 2, 64>(c, a);

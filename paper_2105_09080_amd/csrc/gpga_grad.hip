@@ -742,8 +742,10 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
 //  * x^(k+1/2) is exchanged through two LDS arrays in turn, so an iteration has ONE barrier;
 //  * the consensus distance of iteration t is formed by wavefronts of its own while the nodes do iteration
 //    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.
-// Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 49.6 us here
-// (71 us with loads the compiler could not count).
+// Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 50.5 us here
+// (71 us with loads the compiler could not count).  Rows of 13 to 20 columns spill registers, 5 to 16 a lane with
+// one sample of a logistic problem and 25 to 67 with four, and still take a third of k_small_run's time (n = 128, d = 20, four
+// samples 18.9 -> 5.3 us an iteration).
 __device__ __forceinline__ double quad_sum(double v) {
     v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
     v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
