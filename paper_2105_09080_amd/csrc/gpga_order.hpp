@@ -68,7 +68,7 @@ __device__ __forceinline__ float splitter_column_sum(const GlobalOrder& o, int r
         }
         return sum;
     };
-    auto from = [&](int base) {  // batches of 1 or 4 rows (global_order)
+    auto from = [&](int base) {  // batches of 1 or 4 rows (global_order, more than three rows)
         return o.U == 1 ? batches(base, std::integral_constant<int, 1>{}) : batches(base, std::integral_constant<int, 4>{});
     };
     if (!by_parity) return from(r0);

@@ -798,11 +798,46 @@ constexpr int64_t kPacedWaves = 2048;
 inline int64_t split_waves(int64_t cycle) { return cycle >= 512 ? 1280 : cycle >= 32 ? 1472 : kPacedWaves; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+bool rows_on_16_bytes(const gpga_ctx* c) {
+    return c->ld % 4 == 0 && aligned16(c->x) && aligned16(c->x_new) && aligned16(c->g) && (!c->m || aligned16(c->m));
+}
 
 // Default policy: large launches whose wavefronts each walk many rows run
 // persistent and paced, at the rate the controller of their kind has found;
 // everything else is a one-shot launch.
 constexpr int kAutoBlocksPerCu = 4;
+
+// One-shot walks of few rows.  Pacing buys the rate of one open row (6.2 TB/s) and costs some 100 us at the end of the
+// launch; a free-running launch of n rows loses 7 % (n = 8) to 16 % (n = 64) of that rate and ends with its last
+// tile.  So the fewer rows, the longer a step must be before pacing pays: up to this many bytes of a step free-running
+// wins.  Us paced / free, momentum 0.9: 8 x 25.6M full 809 / 753, ring 827 / 706, 8 x 60M 1706 / 1666, 8 x 70M 1939 / 2000;
+// 12 x 17M 792 / 742; 16 x 14M 854 / 816, 16 x 20M 1150 / 1170; 20 x 7M 580 / 516; 32 x 5M ring 661 / 624, 32 x 8M 965 / 996;
+// 64 x 3M 730 / 750; without momentum 6 x 40M ring 617 / 469, 20 x 8M 438 / 342, 64 x 3M 478 / 432, 64 x 8M 1093 / 1134.
+constexpr double kFreeRowBytes = 80e9;  // divided by the rows, and at least / at most
+constexpr double kFreeMinBytes = 3.2e9, kFreeMaxBytes = 10e9;
+constexpr int kFreeRows = 64;
+bool free_running_pays(const gpga_ctx* c) {
+    if (c->n > kFreeRows) return false;
+    const double most = kFreeRowBytes / c->n, bytes = 4.0 * (c->mu != 0.f ? 5 : 3) * c->n * (double)c->d;
+    return bytes <= (most < kFreeMinBytes ? kFreeMinBytes : most > kFreeMaxBytes ? kFreeMaxBytes : most);
+}
+// Wavefronts per workgroup of a walk.  One where a launch of few rows streams past the caches on 16-byte rows: tiles are then
+// handed out one by one, in order, and fewer of them are open at once (8 x 25.6M ring 728 -> 706 us, full 758 -> 753, 16 x 8M
+// one-peer 482 -> 461; 8 x 25 600 001, where neighbouring tiles share cache lines, ring 813 -> 900; 16 x 2M, 32 x 2M even;
+// 64 x 1.1M without momentum 158 -> 162).
+constexpr int64_t kLoneWaveElements = 1 << 26;
+int walk_waves(const gpga_ctx* c, int64_t tiles) {
+    if (c->opt_waves) return c->opt_waves;
+    const bool lone = free_running_pays(c) && !c->opt_row_split && c->opt_blocks_per_cu < 0 && c->opt_pace_gbs < 0 &&
+                      (int64_t)c->n * c->d >= (c->n <= 32 ? 1 : 2) * kLoneWaveElements && tiles >= kPacedWaves && rows_on_16_bytes(c);
+    return lone ? 1 : 4;
+}
+// Rows per batch of a free-running walk along a cycle (us with 2 / 4 / 8, four wavefronts: 8 x 25.6M ring 778 / 762 / 731,
+// 16 x 14M without momentum 481 / 483 / 451; 4 x 51.2M 736 / 717 / 725; long columns of few tiles keep 2).
+int walk_unroll(const gpga_ctx* c, int64_t tiles, int64_t cycle) {
+    if (!free_running_pays(c) || (int64_t)c->n * c->d < kLoneWaveElements || tiles < kPacedWaves) return kDefaultUnroll;
+    return cycle >= 8 ? 8 : cycle >= 4 ? 4 : kDefaultUnroll;
+}
 
 LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool walks_rows, int pace_key) {
     LaunchPlan p;
@@ -813,7 +848,7 @@ LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool w
     p.ctx = c;
     p.clock_hz = c->clock_hz;
     p.pace_key = pace_key;
-    const bool big = walks_rows && vec == 4 && (int64_t)c->n * c->d * 4 >= kPaceMinBytes;
+    const bool big = walks_rows && vec == 4 && (int64_t)c->n * c->d * 4 >= kPaceMinBytes && !free_running_pays(c);
     p.bpc = c->opt_blocks_per_cu < 0 ? (big ? kAutoBlocksPerCu : 0) : c->opt_blocks_per_cu;
     p.pace_gbs = c->opt_pace_gbs < 0 ? (big ? -1.0 : 0.0) : (double)c->opt_pace_gbs;
     if (!walks_rows) p.pace_gbs = 0.0;
@@ -821,10 +856,6 @@ LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool w
 }
 
 }  // namespace
-
-static bool rows_on_16_bytes(const gpga_ctx* c) {
-    return c->ld % 4 == 0 && aligned16(c->x) && aligned16(c->x_new) && aligned16(c->g) && (!c->m || aligned16(c->m));
-}
 
 hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, int32_t S, int vec,
                             double* spread_partials, int64_t* spread_count) {
@@ -843,8 +874,9 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
         a.C = gcd_i(S, n);
         a.L = n / a.C;
     }
-    const int waves = c->opt_waves ? c->opt_waves : 4;
     const int64_t tiles = unit_tiles(ge, kWave);
+    // (a ring of two or three rows has nothing to stream: 2 x 60M without momentum 238 us with four wavefronts, 273 with one)
+    const int waves = vec == 4 && !(mode == MODE_RING && n < 4) ? walk_waves(c, tiles) : c->opt_waves ? c->opt_waves : 4;
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
     // persistent and paced.  Forced ("always"), it takes rows of whole lanes or on 16-byte boundaries.
@@ -858,7 +890,8 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
         ca.gx = (tiles + waves - 1) / waves;
         LaunchPlan plan = make_plan(c, ca.gx, waves, vec, true,
                                     a.L == 2 ? PACE_CYCLES : a.L == 4 ? PACE_PEER_4 : a.L == 8 ? PACE_PEER_8 : PACE_PEER_16);
-        if (c->opt_blocks_per_cu < 0 && plan.bpc == 0) plan.bpc = kAutoBlocksPerCu;  // forced on a small problem
+        // forced on a small problem
+        if (c->opt_cycle_kernel == 1 && c->opt_blocks_per_cu < 0 && plan.bpc == 0) plan.bpc = kAutoBlocksPerCu;
         const int momk = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
         ca.spread_partials = nullptr;
         const bool traced = spread_partials && spread_count;  // every lane stores whole columns: the consensus sums ride along
@@ -911,7 +944,10 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
                          : a.L <= 4 ? PACE_PEER_4 : a.L <= 8 ? PACE_PEER_8 : PACE_PEER_LONG;
     const LaunchPlan plan = make_plan(c, gx * gy, waves, vec, uniform && a.L >= min_cycle, pace_key);
     // paced wavefronts advance one row per batch (two rows in flight); free-running ones two
-    const int U = c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : kDefaultUnroll);
+    const int U = c->opt_unroll                                 ? c->opt_unroll
+                  : plan.pace_gbs != 0.0                        ? 1
+                  : spread_partials || vec != 4 || a.Q > 1      ? kDefaultUnroll
+                                                                : walk_unroll(c, tiles, a.L);
     const int mom = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
     a.spread_partials = nullptr;
     a.cpi = 1;
@@ -979,7 +1015,8 @@ GlobalOrder global_order(const gpga_ctx* c) {
     if (wpb > waves) wpb = waves;
     while (wpb > 1 && RL * wpb > n) wpb >>= 1;
     const LaunchPlan plan = make_plan(c, 1, waves, vec, RL == 1 && wpb == 1 && n >= 8, PACE_GLOBAL);
-    return {RL, wpb, c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : 4)};
+    // (2 x 60M: 376 us with two rows a batch, 415 with four)
+    return {RL, wpb, c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : n < 4 ? 2 : 4)};
 }
 
 hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& geom, int vec) {
@@ -988,9 +1025,9 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& geom, int vec) 
     a.ge = geom;
     const int n = a.ge.n;
     const GlobalOrder go = global_order(c);
-    const int waves = c->opt_waves ? c->opt_waves : 4;
     const int CL = kWave / go.RL;
     set_units(&a.ge, vec, CL);
+    const int waves = go.wpb == 1 && vec == 4 ? walk_waves(c, unit_tiles(a.ge, CL)) : c->opt_waves ? c->opt_waves : 4;
     a.inv_n = 1.0f / (float)n;
     a.RL = go.RL;
     a.tpb = waves / go.wpb;

@@ -452,3 +452,21 @@ def test_cfg5_replica_gossip_aga_lockstep(hx, topology):
     assert len(ref.history) >= 3 and len(set(periods)) > 1, (ref.history, "the period never adapted")
     print(f"cfg5 replica Gossip-AGA {topology}: periods {sorted(set(periods))}, averages at {[h[0] for h in ref.history]}, worst {worst:.2e}")
     sim.close()
+
+
+# Free-running walks of few rows: one wavefront a workgroup on 16-byte rows, four on others, batches of 2, 4 and 8 rows with
+# and without rows behind the last batch; the last case is the first size of its row count that is paced again.
+@pytest.mark.parametrize("n,d,topology,k,momentum,expect", [
+    (8, 8_400_004, "ring", 0, 0.9, (1, 0)), (8, 8_400_004, "full", 0, 0.9, (3, 0)), (8, 8_400_004, "expo1", 0, 0.9, (2, 0)),
+    (8, 8_400_004, "none", 0, 0.9, (1, 0)), (11, 6_200_000, "ring", 0, 0.9, (1, 0)), (3, 22_400_000, "ring", 0, 0.9, (1, 0)),
+    (3, 22_400_000, "full", 0, 0.9, (3, 0)), (5, 13_500_001, "ring", 0, 0.9, (1, 0)), (20, 3_400_000, "expo1", 0, 0.9, (1, 0)),
+    (32, 2_200_003, "ring", 0, 0.9, (1, 0)), (32, 2_200_000, "expo1", 1, 0.9, (2, 0)), (64, 2_560_000, "ring", 0, 0.9, (1, 1))])
+def test_free_running_walks_of_few_rows(hx, n, d, topology, k, momentum, expect):
+    sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=momentum)
+    sim.problem_synthetic(5, 1e-3)
+    _random_resident_state(sim, seed=n + d)
+    sim.local_grad()
+    kw = dict(topology=topology, H=0, lr=0.1, momentum=momentum)
+    _full_width_lockstep(sim, k, kw, f"free-running {topology} {n} x {d}", expect=expect)
+    sim.close()
+    torch.cuda.empty_cache()
