@@ -352,7 +352,8 @@ gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
  *       7 whole iterations in one workgroup (small problems, gpga_run),
  *       8 several iterations with the columns on chip (synthetic gradients, gpga_run),
  *       9 gradient sums, update and mixing in one launch (stored features, small problems, gpga_run),
- *       10 circulant sparse W on 225 to 1024 nodes, the whole column tile in LDS and the next one loaded meanwhile;
+ *       10 circulant sparse W on 225 to 1024 nodes, the whole column tile in LDS and the next one loaded meanwhile,
+ *       11 gradient sums, update and mixing in one launch (virtual features, gpga_run);
  *   "step_paced" (1 = that launch was a paced persistent launch), "step_lane_bytes" (16, 8 or 4),
  *   "trace_fused" (1 = the consensus-trace entry of that step came from the step kernel's own
  *       sums, 0 = a reduction pass followed or no trace is attached).  These four do not synchronise.

@@ -490,7 +490,7 @@ gpga_status gpga_local_loss(gpga_ctx* c, const int32_t* batch_idx, int32_t B, fl
 
 // One fused iteration; `global` selects the all-node mean instead of the gossip mix.
 // With rows_B > 0 the gradients are not in g yet: the step also forms them, from the coefficients of rows_B samples a node
-// (row numbers rows_idx), and stores them if want_g.
+// (row numbers rows_idx) of stored or virtual features, and stores them if want_g.
 static gpga_status run_step(gpga_ctx* c, bool global, int32_t rows_B = 0, const int32_t* rows_idx = nullptr, bool want_g = true) {
     int mode = MODE_SELF;
     int32_t S = 0;
@@ -530,10 +530,12 @@ static gpga_status run_step(gpga_ctx* c, bool global, int32_t rows_B = 0, const 
     c->last_path = PATH_NONE;
     c->last_paced = 0;
     c->last_trace_fused = 0;
-    const bool fuse = trace && !global && c->d % 4 == 0 && rows_B == 0;
+    const bool virtual_rows = rows_B > 0 && c->problem == PROB_LOGREG_VIRTUAL;
+    const bool fuse = trace && !global && c->d % 4 == 0 && (rows_B == 0 || virtual_rows);
     double* const spread = fuse ? c->partials + 1 : nullptr;
     int64_t* const count = fuse ? &spread_count : nullptr;
-    hipError_t e = rows_B > 0 ? launch_rows_step(c, ge, rows_idx, rows_B, global, mode, S, csr, want_g)
+    hipError_t e = virtual_rows ? launch_virtual_step(c, ge, rows_idx, rows_B, mode, S, want_g, spread, count)
+                   : rows_B > 0 ? launch_rows_step(c, ge, rows_idx, rows_B, global, mode, S, csr, want_g)
                    : global ? launch_step_global(c, ge, vec)
                           : csr ? launch_step_csr(c, ge, vec, spread, count)
                                 : launch_step_walk(c, ge, mode, S, vec, spread, count);
@@ -640,6 +642,10 @@ static gpga_status run_iteration(gpga_ctx* c, const int32_t* idx, int32_t B, boo
     int32_t Beff = 0;
     gpga_status s = check_batch(c, idx, B, &Beff);
     if (s != GPGA_OK) return s;
+    if (!global && virtual_step_fits(c, Beff)) {
+        s = run_grad(c, idx, B, loss_out, false);  // margins, coefficients, losses
+        return s == GPGA_OK ? run_step(c, false, Beff, idx, want_g) : s;
+    }
     if (!rows_step_fits(c, Beff)) {
         s = run_grad(c, idx, B, loss_out, true);
         return s == GPGA_OK ? run_step(c, global) : s;

@@ -321,11 +321,6 @@ __global__ void __launch_bounds__(kWave) k_loss_chunks(const double* __restrict_
 
 // Virtual features are bound by vector issue.  Splitting off what the first two Philox rounds share between draws of a
 // quad and between quads of a draw: n = 1024, d = 1M, B = 16 a new state's iteration 19.5 -> 18.2 ms (gradient and step).
-// Feature quad h_{i,m} of four columns = mu_i + zeta_{i,m}, rounded to fp32 like a stored feature would be.
-__device__ __forceinline__ v4f virtual_quad(const v4f& mu, const PhiloxQuad& quad, uint32_t i, uint32_t m, uint32_t k0, uint32_t k1) {
-    return mu + box_muller4(philox_rounds(quad, PhiloxPair(i, m, k0, k1), k0, k1));
-}
-
 // Pass 1: grid (column chunks, node).  Each lane owns column quads and keeps B
 // partial margins; the node shift mu_i is generated once per quad and reused for
 // all B samples.  Partial margins are combined per workgroup and stored as

@@ -52,7 +52,7 @@ constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
                       PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9,
-                      PATH_CIRCULANT = 10 };
+                      PATH_CIRCULANT = 10, PATH_VIRTUAL_STEP = 11 };
 
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
@@ -231,6 +231,11 @@ bool rows_step_fits(const gpga_ctx* c, int32_t Beff);
 hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
 hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32_t* idx, int32_t Beff, bool global, int mode,
                             int32_t shift, bool csr, bool want_g);
+// Virtual features: what follows the margin pass of a gossip iteration in one launch, same conventions (spread_* as for
+// launch_step_walk).
+bool virtual_step_fits(const gpga_ctx* c, int32_t B);
+hipError_t launch_virtual_step(const gpga_ctx* c, const StepGeom& geom, const int32_t* idx, int32_t B, int mode, int32_t S, bool want_g,
+                               double* spread_partials, int64_t* spread_count);
 // Small problems: T <= kSmallRunMaxIters whole iterations (stored-feature gradients, update,
 // mix or average, consensus trace) in one single-workgroup launch; the final iterates go to the
 // array T separate steps would leave them in (c->x for even T, c->x_new for odd T: the caller

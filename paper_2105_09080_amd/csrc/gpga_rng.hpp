@@ -117,3 +117,8 @@ __device__ __forceinline__ v4f synth_quad(uint32_t c4, uint32_t i, uint32_t kite
     const v4f z = normals4(c4, i, kiter, TAG_GRAD, k0, k1);
     return sigma * z;
 }
+
+// Feature quad h_{i,m} of four columns = mu_i + zeta_{i,m}, rounded to fp32 like a stored feature would be.
+__device__ __forceinline__ v4f virtual_quad(const v4f& mu, const PhiloxQuad& quad, uint32_t i, uint32_t m, uint32_t k0, uint32_t k1) {
+    return mu + box_muller4(philox_rounds(quad, PhiloxPair(i, m, k0, k1), k0, k1));
+}

@@ -1,0 +1,65 @@
+"""gpga_run on virtual features with gradient sums, update and gossip step in one launch, against separate calls: tiles shared
+among wavefronts by rows and by cycles, ragged widths and strides, every offset of the one-peer graph, averages, the trace,
+samples without weight and row numbers outside the data."""
+import numpy as np
+import pytest
+
+from paper_2105_09080_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_09080_amd import harness
+    return harness
+
+
+# Both sides round the same operations in the same order, so x, m and g are the same bits; the trace adds its columns in
+# another order in fp64.
+@pytest.mark.parametrize("n,d,B,T,topology,H,momentum,nesterov,pad,scale", [
+    (1, 524_287, 3, 2, "ring", 0, 0.9, False, 0, 1.0), (2, 524_288, 4, 2, "ring", 0, 0.9, False, 0, 1.0),
+    (15, 720_897, 5, 5, "expo1", 4, 0.9, False, 4, 1.0), (24, 262_144, 1, 5, "expo1", 0, 0.0, False, 1, 1.0),
+    (128, 32_767, 7, 7, "expo1", 0, 0.9, True, 0, 1.0), (130, 32_765, 16, 3, "ring", 2, 0.9, False, 2, 1.0),
+    (130, 32_768, 16, 2, "none", 0, 0.9, False, 0, 1.0), (96, 65_500, 8, 7, "expo1", 0, 0.9, False, 0, 1.0),
+    (16, 524_284, 16, 3, "ring", 0, 0.9, False, 0, 4000.0)])   # margins so large that most coefficients are exactly zero
+def test_one_launch_matches_separate_calls(hx, n, d, B, T, topology, H, momentum, nesterov, pad, scale):
+    import torch
+    M, runs = 50, []
+    y, idx = inputs.virtual_labels(n, M, seed=n), inputs.batch_indices(T, n, B, M, seed=d)
+    if T > 2:
+        idx[T - 1, 0, 0], idx[T - 1, n - 1, B - 1] = M, -1
+    for fused in (True, False):
+        sim = hx.Simulation(n, d, topology=topology, H=H, lr=0.05 / np.sqrt(d), momentum=momentum, ld=d + pad)
+        if nesterov:
+            sim.set_nesterov(True)
+        sim.problem_logreg_virtual(7, y, 0.5)
+        for buf in (*sim._bufs, sim.g):
+            buf.fill_(7.0)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n + d)
+        sim.X.normal_(0.0, scale / np.sqrt(1.5 * d), generator=gen)
+        batches, trace = sim.upload_batches(idx), sim.attach_trace(T)
+        if fused:
+            sim.run(T, batches)
+            assert int(sim.query("step_path")) == (11 if T % (H or T + 1) else 3)
+        else:
+            for k in range(T):
+                sim.local_grad(batches[k])
+                sim.step()
+        torch.cuda.synchronize()
+        runs.append((sim, trace))
+    (a, ta), (b, tb) = runs
+    for got, want in ((a.X, b.X), (a.G, b.G)) + (((a.M, b.M),) if momentum else ()):
+        assert torch.equal(got.nan_to_num(nan=3e38), want.nan_to_num(nan=3e38))
+    if T > 2:
+        assert bool(a.G[0].isnan().all()) and bool(a.G[n - 1].isnan().all())
+    ta, tb = ta.cpu().numpy()[:T - 1], tb.cpu().numpy()[:T - 1]   # the last entry of a state that is not a number is none
+    assert np.abs(ta - tb).max() <= 1e-9 * np.abs(tb).max()
+    for buf in (*a._bufs, a.g):   # nothing beyond a row's d columns is written
+        assert bool((buf[:, d:] == 7.0).all())
+    a.close()
+    b.close()
