@@ -28,7 +28,7 @@ __global__ void __launch_bounds__(256) k_synth_grad(float* __restrict__ g, int64
     const int64_t c = c4 * 4;
     if (c >= d) return;
     const uint32_t i = blockIdx.y;
-    const v4f z = sigma * normals4((uint32_t)c4, i, kiter, TAG_GRAD, k0, k1);
+    const v4f z = synth_quad((uint32_t)c4, i, kiter, k0, k1, sigma);
     float* row = g + (int64_t)i * ld;
     if (vec_ok && c + 3 < d) {
         __builtin_nontemporal_store(z, reinterpret_cast<v4f*>(row + c));

@@ -54,18 +54,31 @@ __device__ __forceinline__ float uniform23(uint32_t r) {
 // sin(2 pi u) is one instruction on u itself with no range reduction.  Measured
 // over all 2^23 possible u: |sin|, |cos| error <= 1.3e-7, ln relative error
 // <= 1.7e-7, radius error <= 4.9e-7 (radius <= 5.7).
-__device__ __forceinline__ v4f box_muller4(const u32x4& r) {
+// kScaled: times `scale`, a factor of the radii, with every product rounded.
+template <bool kScaled>
+__device__ __forceinline__ v4f box_muller4_of(const u32x4& r, float scale) {
     constexpr float kMinus2Ln2 = -1.3862943611198906f;  // -2 ln u = (-2 ln 2) log2 u
-    const float ra = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.a)));
-    const float rb = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.c)));
+    float ra = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.a)));
+    float rb = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(uniform23(r.c)));
     const float ub = uniform23(r.b), ud = uniform23(r.d);
     v4f z;
+    if (kScaled) {
+#pragma clang fp contract(off)
+        ra *= scale;
+        rb *= scale;
+        z.x = ra * __builtin_amdgcn_cosf(ub);
+        z.y = ra * __builtin_amdgcn_sinf(ub);
+        z.z = rb * __builtin_amdgcn_cosf(ud);
+        z.w = rb * __builtin_amdgcn_sinf(ud);
+        return z;
+    }
     z.x = ra * __builtin_amdgcn_cosf(ub);
     z.y = ra * __builtin_amdgcn_sinf(ub);
     z.z = rb * __builtin_amdgcn_cosf(ud);
     z.w = rb * __builtin_amdgcn_sinf(ud);
     return z;
 }
+__device__ __forceinline__ v4f box_muller4(const u32x4& r) { return box_muller4_of<false>(r, 1.f); }
 __device__ __forceinline__ v4f normals4(uint32_t c4, uint32_t a, uint32_t b, uint32_t tag,
                                         uint32_t k0, uint32_t k1) {
     return box_muller4(philox4x32_10(c4, a, b, tag, k0, k1));
@@ -110,13 +123,40 @@ __device__ __forceinline__ u32x4 philox_rounds(const PhiloxQuad& q, const Philox
     return {c0, c1, c2, c3};
 }
 
-// The synthetic gradient of four columns: sigma * N(seed, TAG_GRAD, i, k, c).  The product is rounded here, as a
-// stored gradient is: no fused multiply-add of a later use takes it in.
+// The synthetic gradient of four columns: sigma * N(seed, TAG_GRAD, i, k, c), with sigma in the two radii.  The products are
+// rounded here, as a stored gradient is: no fused multiply-add of a later use takes them in.
 __device__ __forceinline__ v4f synth_quad(uint32_t c4, uint32_t i, uint32_t kiter, uint32_t k0, uint32_t k1, float sigma) {
-#pragma clang fp contract(off)
-    const v4f z = normals4(c4, i, kiter, TAG_GRAD, k0, k1);
-    return sigma * z;
+    return box_muller4_of<true>(philox4x32_10(c4, i, kiter, TAG_GRAD, k0, k1), sigma);
 }
+
+// The same for many rows and iterations of one column quad: words of the first two rounds that depend on the quad alone are
+// kept, those of the iteration (uniform) are scalar, and four vector instructions are left of the eight.
+struct SynthQuad {
+    uint32_t lo0, hi1, lo1;
+    __device__ __forceinline__ SynthQuad(uint32_t c4, uint32_t k1) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * c4;
+        lo0 = (uint32_t)p0;
+        const uint64_t p1 = (uint64_t)kPhiloxM1 * ((uint32_t)(p0 >> 32) ^ TAG_GRAD ^ k1);
+        hi1 = (uint32_t)(p1 >> 32);
+        lo1 = (uint32_t)p1;
+    }
+    __device__ __forceinline__ v4f gradient(uint32_t i, uint32_t kiter, uint32_t k0, uint32_t k1, float sigma) const {
+        const uint64_t pk = (uint64_t)kPhiloxM1 * kiter;
+        const uint64_t pi = (uint64_t)kPhiloxM0 * (i ^ ((uint32_t)(pk >> 32) ^ k0));
+        uint32_t c0 = hi1 ^ ((uint32_t)pk ^ (k0 + kPhiloxW0)), c1 = lo1;
+        uint32_t c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pi >> 32), lo0, k1 + kPhiloxW1, 0x96), c3 = (uint32_t)pi;
+#pragma unroll
+        for (int n = 2; n < 10; ++n) {
+            const uint32_t key0 = k0 + (uint32_t)n * kPhiloxW0, key1 = k1 + (uint32_t)n * kPhiloxW1;
+            const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
+            c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, key0, 0x96);
+            c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, key1, 0x96);
+            c1 = (uint32_t)p1;
+            c3 = (uint32_t)p0;
+        }
+        return box_muller4_of<true>({c0, c1, c2, c3}, sigma);
+    }
+};
 
 // Feature quad h_{i,m} of four columns = mu_i + zeta_{i,m}, rounded to fp32 like a stored feature would be.
 __device__ __forceinline__ v4f virtual_quad(const v4f& mu, const PhiloxQuad& quad, uint32_t i, uint32_t m, uint32_t k0, uint32_t k1) {
