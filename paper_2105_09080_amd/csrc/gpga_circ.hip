@@ -8,10 +8,11 @@
 // loads the same rows of its next tile, updates them and keeps their x^(k+1/2) in registers (8 x 16 bytes a thread);
 // between two tiles they move to LDS.  Being circulant is what makes the mixing cheap: offsets and weights are scalars,
 // a neighbour's address is one add and one wrap.
-// (y and two rows of x, m and g in flight fill 128 registers: 32 a lane spill, 18 without momentum.)
-// Bound: memory with n rows open at once.  Static exponential graph, momentum 0.9: n = 1024, d = 1M 6.20 -> 3.7 - 4.0 ms
-// (5.1 to 5.5 TB/s of 20 bytes an element), n = 700, d = 500k 2.23 -> 1.43 ms; against the tile kernel with 4-byte lanes n = 512,
-// d = 2M 5.68 -> 4.19 ms, n = 256, d = 4M 4.77 -> 4.16 ms, n = 300, d = 1M without momentum 1.18 -> 0.75 ms.
+// (y and two rows of x, m and g in flight fill 108 of 128 registers.  Row addresses of all passes kept over the tiles put 32 a
+// lane into scratch memory, 300 x 1M 1267 us against 994; four rows in flight, 16 of them again, are no faster.)
+// Bound: memory with n rows open at once.  Static exponential graph, momentum 0.9: n = 1024, d = 1M 6.20 -> 3.6 - 4.1 ms
+// (5.0 to 5.7 TB/s of 20 bytes an element), n = 700, d = 500k 2.23 -> 1.39 ms; against the tile kernel with 4-byte lanes n = 512,
+// d = 2M 5.68 -> 3.95 ms, n = 256, d = 4M 4.77 -> 3.4 - 3.9 ms, n = 300, d = 1M without momentum 1.18 -> 0.71 ms.
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_unit.hpp"
@@ -37,7 +38,7 @@ __global__ void __launch_bounds__(kCircThreads) k_step_circ(const CircArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     v4f* __restrict__ sy = reinterpret_cast<v4f*>(s_raw);  // [n][LN]
     const int n = a.ge.n, total = n * LN;
-    const int q = threadIdx.x % LN, r0 = threadIdx.x / LN;
+    const int q = threadIdx.x % LN, first = threadIdx.x / LN;
     const float lr = a.ge.lr, mu = a.ge.mu;
     const int64_t ld = a.ge.ld;
     struct Row {
@@ -45,17 +46,23 @@ __global__ void __launch_bounds__(kCircThreads) k_step_circ(const CircArgs a) {
     };
     Row rows[kCircAhead];
     v4f y[kCircPasses];
+    // Addresses are formed anew at every use: those of all passes, kept, would not fit the registers beside y and the rows.
+    auto row_of = [&](int p) -> int {
+        int r = first;
+        asm volatile("" : "+v"(r));
+        return p * RP + r;
+    };
     // Rows behind the last one are loaded as that row and dropped; whole passes behind it are skipped.
     const int passes = a.passes;
     auto load = [&](Row& w, int64_t tile, int p) {
-        const int row = p * RP + r0;
+        const int row = row_of(p);
         const int64_t o = (int64_t)(row < n ? row : n - 1) * ld + unit_column<v4f>(a.ge, tile, LN, q);
         w.x = ld_unit<v4f>(a.ge.x + o);
         if (MOM) w.m = ld_unit<v4f>(a.ge.m + o);
         w.g = ld_unit<v4f>(a.ge.g + o);
     };
     auto update = [&](const Row& w, int64_t tile, int p) -> v4f {
-        const int row = p * RP + r0;
+        const int row = row_of(p);
         v4f mom = w.g;
         if (MOM) {
             mom = mu * w.m + w.g;
@@ -64,7 +71,7 @@ __global__ void __launch_bounds__(kCircThreads) k_step_circ(const CircArgs a) {
         return MOM == 2 ? w.x - lr * (w.g + mu * mom) : w.x - lr * mom;
     };
     auto mix = [&](int64_t tile, int p) {
-        const int row = p * RP + r0;
+        const int row = row_of(p);
         const uint32_t at = (uint32_t)(row * LN + q);
         if (row >= n) return;
         v4f acc = v4f(0.f);
@@ -83,8 +90,10 @@ __global__ void __launch_bounds__(kCircThreads) k_step_circ(const CircArgs a) {
     auto to_lds = [&]() {
         __syncthreads();  // the tile before has been mixed
 #pragma unroll
-        for (int p = 0; p < kCircPasses; ++p)
-            if (p * RP + r0 < n) sy[(p * RP + r0) * LN + q] = y[p];
+        for (int p = 0; p < kCircPasses; ++p) {
+            const int row = row_of(p);
+            if (row < n) sy[row * LN + q] = y[p];
+        }
         __syncthreads();
     };
     int64_t tile = blockIdx.x;
