@@ -264,7 +264,7 @@ hipError_t launch_col_mean(const gpga_ctx* c, float* xbar);
 // Sum of squared deviations into c->partials[0] (device double).
 hipError_t launch_consensus_sq(gpga_ctx* c, size_t* partials_needed);
 size_t consensus_partials_needed(const gpga_ctx* c);
-// Partials the reduction pass over the bound X really writes (depends on its alignment).
+// Upper bound of the partials that the reduction pass over the bound X writes.
 size_t consensus_partials_used(const gpga_ctx* c);
 // slot[0] = consensus distance of the live X (reduction pass + one final kernel).
 hipError_t launch_consensus_trace(gpga_ctx* c, double* slot);

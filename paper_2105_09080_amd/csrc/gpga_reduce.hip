@@ -103,12 +103,13 @@ __device__ __forceinline__ void acc_add(d4& a, const d4& b) {
 // a wavefront each (64 units a workgroup).  Consensus distance + mean,
 // against one lane a column throughout: n = 256, d = 1172 62.5 -> 26.5 us, n = 100, d = 50 000 56.7 -> 27.7, n = 64,
 // d = 100 000 44.9 -> 29.1; rows without 16-byte alignment (n = 64, d = 5 000 001) 517 -> 466.
-constexpr int reduce_lanes(int RS) { return RS == 1 ? 256 : kWave; }
-template <typename T, int RS>
-__global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_col_mean(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
+// CL column units a workgroup: 64 with shared rows, else 256, or 1024 on arrays wide enough to keep every compute unit at it
+// (kWideReduce): the 16 KiB of a row that such a workgroup reads at a time keep fewer memory pages open (64 x 25.6M
+// distance and mean 2113 -> 2065 us, 16 x 30M 666 -> 642, 256 x 1M 349 -> 337; 64 x 400 000 52 -> 65).
+template <typename T, int RS, int CL>
+__global__ void __launch_bounds__(CL * RS) k_col_mean(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
                                                   int32_t n, float* __restrict__ xbar) {
     typedef typename AccOf<T>::type Acc;
-    constexpr int CL = reduce_lanes(RS);
     __shared__ Acc s_acc[RS > 1 ? RS - 1 : 1][CL];
     const int lane = threadIdx.x % CL, grp = threadIdx.x / CL;
     const int64_t u = (int64_t)blockIdx.x * CL + lane;
@@ -136,13 +137,12 @@ __global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_col_mean(const float*
     if (on) *reinterpret_cast<typename Unit<T>::mem*>(xbar + c) = to_mean(acc, 1.0 / (double)n);
 }
 
-template <typename T, int RS>
-__global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_consensus(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
+template <typename T, int RS, int CL>
+__global__ void __launch_bounds__(CL * RS) k_consensus(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
                                                    int32_t n, double* __restrict__ partials) {
     typedef typename AccOf<T>::type Acc;
-    constexpr int CL = reduce_lanes(RS);
     __shared__ Acc s_acc[2][RS > 1 ? RS - 1 : 1][CL];
-    __shared__ double s_buf[4];
+    __shared__ double s_buf[CL / kWave];
     const int lane = threadIdx.x % CL, grp = threadIdx.x / CL;
     const int64_t u = (int64_t)blockIdx.x * CL + lane;
     const bool on = u < units;
@@ -186,7 +186,12 @@ __global__ void __launch_bounds__(reduce_lanes(RS) * RS) k_consensus(const float
     const int wl = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     if (wl == 0) s_buf[wave] = ss;
     __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = (s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3]);
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < CL / kWave; ++w) t += s_buf[w];
+        partials[blockIdx.x] = t;
+    }
 }
 
 // out[0] = sum of `count` partials, one workgroup, fixed order.
@@ -299,14 +304,20 @@ static int reduce_split(int64_t units, int32_t n) {
     return units >= 98304 ? 1 : n <= 32 || units >= (n <= 48 ? 24576 : 49152) ? 4 : 16;
 }
 
+constexpr int64_t kWideReduce = 245760;  // column units: 240 workgroups of 1024
+static int reduce_lanes(int64_t units, int split) { return split > 1 ? kWave : units >= kWideReduce ? 1024 : 256; }
+
 static int64_t reduce_blocks(int64_t units, int split) {
-    const int lanes = split == 1 ? reduce_lanes(1) : kWave;
+    const int lanes = reduce_lanes(units, split);
     return (units + lanes - 1) / lanes;
 }
 
+// One per 256 units on wide arrays although the launch may write a quarter of that: the width that
+// gpga_consensus_error_static refuses does not move with the launch shape.
 size_t consensus_partials_used(const gpga_ctx* c) {
     const int64_t units = c->d < 4 ? c->d : (c->d + 3) / 4;
-    return (size_t)reduce_blocks(units, c->d < 4 ? 16 : reduce_split(units, c->n));
+    const int lanes = (c->d < 4 ? 16 : reduce_split(units, c->n)) > 1 ? kWave : 256;
+    return (size_t)((units + lanes - 1) / lanes);
 }
 
 size_t consensus_partials_needed(const gpga_ctx* c) {
@@ -330,27 +341,28 @@ hipError_t launch_fill_rows(const gpga_ctx* c, float* dst, const float* src) {
     return c->d >= 4 ? launch_fill<v4f>(c, dst, src) : launch_fill<float>(c, dst, src);
 }
 
-template <typename T, int RS>
+template <typename T, int RS, int CL>
 static hipError_t launch_mean_split(const gpga_ctx* c, int64_t units, float* xbar) {
     const int64_t blocks = reduce_blocks(units, RS);
-    hipLaunchKernelGGL((k_col_mean<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
+    hipLaunchKernelGGL((k_col_mean<T, RS, CL>), dim3((unsigned)blocks), dim3(CL * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, xbar);
     return hipGetLastError();
 }
 
 hipError_t launch_col_mean(const gpga_ctx* c, float* xbar) {
-    if (c->d < 4) return launch_mean_split<float, 16>(c, c->d, xbar);
+    if (c->d < 4) return launch_mean_split<float, 16, kWave>(c, c->d, xbar);
     const int64_t units = (c->d + 3) / 4;
     const int split = reduce_split(units, c->n);
-    if (split == 1) return launch_mean_split<v4f, 1>(c, units, xbar);
-    return split == 4 ? launch_mean_split<v4f, 4>(c, units, xbar) : launch_mean_split<v4f, 16>(c, units, xbar);
+    if (split == 1 && reduce_lanes(units, 1) == 1024) return launch_mean_split<v4f, 1, 1024>(c, units, xbar);
+    if (split == 1) return launch_mean_split<v4f, 1, 256>(c, units, xbar);
+    return split == 4 ? launch_mean_split<v4f, 4, kWave>(c, units, xbar) : launch_mean_split<v4f, 16, kWave>(c, units, xbar);
 }
 
-template <typename T, int RS>
+template <typename T, int RS, int CL>
 static hipError_t launch_consensus_split(const gpga_ctx* c, int64_t units, double* parts, size_t cap, int64_t* count) {
     const int64_t blocks = reduce_blocks(units, RS);
     if ((size_t)blocks > cap) return hipErrorOutOfMemory;
-    hipLaunchKernelGGL((k_consensus<T, RS>), dim3((unsigned)blocks), dim3(reduce_lanes(RS) * RS), 0, c->stream, c->x, c->ld, c->d, units,
+    hipLaunchKernelGGL((k_consensus<T, RS, CL>), dim3((unsigned)blocks), dim3(CL * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, parts);
     *count = blocks;
     return hipGetLastError();
@@ -360,12 +372,13 @@ static hipError_t launch_consensus_split(const gpga_ctx* c, int64_t units, doubl
 // `cap` doubles); *count receives their number.
 static hipError_t launch_consensus_partials(const gpga_ctx* c, double* parts, size_t cap, int64_t* count) {
     *count = 0;
-    if (c->d < 4) return launch_consensus_split<float, 16>(c, c->d, parts, cap, count);
+    if (c->d < 4) return launch_consensus_split<float, 16, kWave>(c, c->d, parts, cap, count);
     const int64_t units = (c->d + 3) / 4;
     const int split = reduce_split(units, c->n);
-    if (split == 1) return launch_consensus_split<v4f, 1>(c, units, parts, cap, count);
-    return split == 4 ? launch_consensus_split<v4f, 4>(c, units, parts, cap, count)
-                      : launch_consensus_split<v4f, 16>(c, units, parts, cap, count);
+    if (split == 1 && reduce_lanes(units, 1) == 1024) return launch_consensus_split<v4f, 1, 1024>(c, units, parts, cap, count);
+    if (split == 1) return launch_consensus_split<v4f, 1, 256>(c, units, parts, cap, count);
+    return split == 4 ? launch_consensus_split<v4f, 4, kWave>(c, units, parts, cap, count)
+                      : launch_consensus_split<v4f, 16, kWave>(c, units, parts, cap, count);
 }
 
 hipError_t launch_consensus_sq(gpga_ctx* c, size_t* partials_needed) {
