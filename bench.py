@@ -63,7 +63,7 @@ PAPER_CONTEXT = {
 # gpga_query "step_path" -> kernel
 PATH_NAMES = {1: "k_step_walk", 2: "k_step_cycles", 3: "k_step_global", 4: "k_step_tile", 5: "k_step_band",
               6: "W = I walk + k_spmm_rows", 7: "k_small_run / k_node_run", 8: "k_column_run", 9: "k_rows_step",
-              10: "k_step_circ"}
+              10: "k_step_circ", 11: "k_virtual_step"}
 
 
 def parse_args():

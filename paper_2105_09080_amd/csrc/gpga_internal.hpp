@@ -47,7 +47,8 @@ struct PaceState;  // gpga_pace.hpp
 
 // Arrays of at least this many bytes (n x d x 4) run the fused step as paced persistent launches.  Measured on
 // the ring walk with n = 64: 281 MB (0.3 ms) 4.1 TB/s paced against 4.9 one-shot, 563 MB equal, 1.1 GB 5.3
-// against 4.9: a paced launch ends about 100 us after its plan whatever its length.
+// against 4.9: a paced launch ends about 100 us after its plan whatever its length.  Walks and averages of up to 64 rows
+// wait longer (free_running_pays in gpga_step.hip).
 constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
