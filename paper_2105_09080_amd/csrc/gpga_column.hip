@@ -16,6 +16,7 @@
 // of 16 wavefronts fit on a compute unit, so that one loads or stores while the other computes.  That cap and the 78 scalar
 // registers that go with it are tight: addresses, round keys and lane masks kept over the loop end up in scratch memory and in
 // vector lanes, 70 moves per two rows (ring, 24 iterations 24.6 ms); formed anew in each iteration they are scalar additions.
+#include "gpga_exchange.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_order.hpp"
 #include "gpga_rng.hpp"
@@ -43,7 +44,7 @@ struct ColumnArgs {
 
 enum ColumnMix : int { MIX_SELF = 0, MIX_RING = 1, MIX_PEER = 2, MIX_CSR = 3 };
 
-// Two exchange buffers are used in turn, so that an iteration has one barrier.
+// Two exchange buffers are used in turn, so that an exchange has one barrier (an average two): gpga_exchange.hpp.
 template <int MIX, int MOM, int R, int QT>
 __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const ColumnArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
@@ -98,10 +99,13 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
     };
     if (whole) load_state(true); else load_state(false);
     const SynthQuad quad(c4, a.k1);
+    constexpr bool kOwn = MIX == MIX_SELF;
+    int exchanges = 0;
     for (int t = 0; t < a.T; ++t) {
-        v4f* __restrict__ sy = reinterpret_cast<v4f*>(s_raw) + (t & 1) * n * QT;  // [n][QT]
+        v4f* __restrict__ sy = reinterpret_cast<v4f*>(s_raw) + exchange_buffer<kOwn>(t, exchanges) * n * QT;  // [n][QT]
         const float lr = a.lr[t];
         const int shift = a.shift[t];
+        const bool meets = exchanges_rows<kOwn>(n, shift);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int row = row0 + j;
@@ -113,18 +117,19 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
             if (MOM) m[j] = mom = mu * m[j] + g;
             y[j] = MOM == 2 ? x[j] - lr * (g + mu * mom) : x[j] - lr * mom;
             if (row < n) {
-                sy[row * QT + q] = y[j];
+                if (!kOwn || meets) sy[row * QT + q] = y[j];
                 if (t == a.T - 1) {
                     float* const to = a.g_out + (int64_t)(once(row0) + j) * a.ge.ld + col;
                     if (whole) store(to, g, true); else store(to, g, false);
                 }
             }
         }
-        if (n == 1 || (MIX == MIX_SELF && shift >= 0)) {
+        if (!meets) {
 #pragma unroll
             for (int j = 0; j < R; ++j) x[j] = y[j];
             continue;
         }
+        ++exchanges;
         __syncthreads();
         if (shift < 0) {
             // A column a thread, of the first ones (with a whole unit a lane, 256 x 2M averaged in every iteration took 4920 us

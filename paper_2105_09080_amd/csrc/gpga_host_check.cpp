@@ -14,6 +14,7 @@
 #include <random>
 #include <vector>
 
+#include "gpga_exchange.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_node_run.hpp"
 #include "gpga_pace.hpp"
@@ -340,6 +341,56 @@ void node_run_sizes() {
     std::printf("node_run taken %" PRId64 " most_lds %zu\n", taken, most);
 }
 
+// The exchange buffers of k_column_run.  What wavefronts do between two barriers is in no order, so a buffer must not be read by
+// one iteration and written by another there.  Returns how often that happens in T iterations with an average in every
+// H-th; `buffer(t, exchanges before)` and `writes(t)` are the rule.
+template <bool kOwn, typename Buffer, typename Writes>
+int64_t exchange_hazards(int n, int T, int H, Buffer buffer, Writes writes) {
+    struct Use {
+        int64_t phase;   // barriers passed
+        int t, buf;
+        bool write;
+    };
+    std::vector<Use> uses;
+    int64_t phase = 0, hazards = 0;
+    int exchanges = 0;
+    for (int t = 0; t < T; ++t) {
+        const int shift = H > 0 && (t + 1) % H == 0 ? -1 : kOwn ? 0 : 1;
+        const int b = buffer(t, exchanges);
+        expect(b == 0 || b == 1, "two exchange buffers");
+        if (writes(t, shift)) uses.push_back({phase, t, b, true});
+        if (!exchanges_rows<kOwn>(n, shift)) continue;
+        ++exchanges;
+        uses.push_back({++phase, t, b, false});
+        if (shift < 0) uses.push_back({++phase, t, b, false});  // the mean, behind the second barrier
+    }
+    for (const Use& u : uses)
+        for (const Use& v : uses)
+            if (u.write && !v.write && u.t != v.t && u.phase == v.phase && u.buf == v.buf) ++hazards;
+    return hazards;
+}
+
+template <bool kOwn>
+int64_t exchange_rule_hazards(int n, int T, int H) {
+    return exchange_hazards<kOwn>(n, T, H, [](int t, int before) { return exchange_buffer<kOwn>(t, before); },
+                                  [n](int, int shift) { return !kOwn || exchanges_rows<kOwn>(n, shift); });
+}
+
+void exchange_buffers() {
+    int64_t schedules = 0, by_iteration = 0;
+    for (int n : {1, 2, 3, 40, 256})
+        for (int H = 0; H <= 9; ++H) {
+            expect(exchange_rule_hazards<true>(n, kColumnRunMaxIters, H) == 0, "exchange buffers, W = I");
+            expect(exchange_rule_hazards<false>(n, kColumnRunMaxIters, H) == 0, "exchange buffers, other graphs");
+            schedules += 2;
+            // buffers in turn by iteration, written whether or not an exchange follows: what the walk has to find
+            if (n > 1 && H >= 2)
+                by_iteration += exchange_hazards<true>(n, kColumnRunMaxIters, H, [](int t, int) { return t & 1; },
+                                                       [](int, int) { return true; }) > 0;
+        }
+    std::printf("exchange schedules %" PRId64 " found_by_iteration %" PRId64 "\n", schedules, by_iteration);
+}
+
 // Recognising circulant matrices: the named graphs that are, whatever the order of a row's entries, and near misses that are not.
 void circulant_matrices() {
     int32_t k, off[kMaxCirculant];
@@ -383,6 +434,7 @@ void circulant_matrices() {
 }  // namespace
 
 int main() {
+    exchange_buffers();
     circulant_matrices();
     node_run_sizes();
     rows_deal();

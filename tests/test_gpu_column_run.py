@@ -51,6 +51,9 @@ CASES += [(64, 1000, "full", 0, 0.0, False, 4, 1000), (64, 130, "ring", 4, 0.0, 
 CASES += [(33, 1031, "full", 0, 0.9, False, 3, 1031), (70, 130_003, "ring", 1, 0.9, False, 3, 130_004), (101, 600_001, "full", 0, 0.0, False, 2, 600_001),
           (130, 8, "full", 0, 0.9, False, 3, 8), (199, 300_002, "full", 0, 0.9, False, 2, 300_003), (256, 550_000, "ring", 2, 0.9, True, 4, 550_000)]
 
+# local SGD: iterations without an exchange between the averages, over the tile sizes
+CASES += [(n, 1031, "none", H, 0.9, False, 64, 1031) for n in (3, 40, 128, 200) for H in (2, 3, 4)]
+
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
 def test_columns_on_chip_give_the_bits_of_separate_steps(hx, case):

@@ -92,6 +92,13 @@ def test_small_trajectories_fit_the_lds_of_a_plain_launch(facts):
     assert int(row[2]) > 0 and 60_000 < int(row[4]) <= 65_536
 
 
+def test_no_iteration_writes_an_exchange_buffer_that_another_reads(facts):
+    """Local SGD and gossip with averages in every H-th of 64 iterations; turns by iteration, which W = I has no barriers for,
+    are found in every schedule with iterations between its averages."""
+    row, = [f for f in facts if f[0] == "exchange"]
+    assert int(row[2]) == 100 and int(row[4]) == 4 * 8
+
+
 def test_circulant_matrices_are_recognised(facts):
     """Offsets and weights of the static exponential graph against the oracle's matrix; the near misses are the check program's own."""
     rows = {int(f[1]): int(f[2]) for f in facts if f[0] == "circulant"}
