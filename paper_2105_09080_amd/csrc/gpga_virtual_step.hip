@@ -46,7 +46,8 @@ __global__ void __launch_bounds__(kWave* kVirtualStepWaves) k_virtual_step(const
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_tile = a.Qc * a.Qs, tile_l = wave / per_tile;
     const int cw = (wave - tile_l * per_tile) / a.Qs, seg = wave % a.Qs;
-    const int64_t tile_i = (int64_t)blockIdx.x * (blockDim.x / kWave / per_tile) + tile_l;
+    const int tiles_wg = blockDim.x / kWave / per_tile;
+    const int64_t tile_i = (int64_t)blockIdx.x * tiles_wg + tile_l;
     const int n = a.ge.n;
     const int64_t ld = a.ge.ld, d = a.ge.d;
     const float lr = a.ge.lr, mu = a.ge.mu;
@@ -54,13 +55,15 @@ __global__ void __launch_bounds__(kWave* kVirtualStepWaves) k_virtual_step(const
     // Quads of the counter RNG start at multiples of four, whatever the width: the last one of a ragged width is a part.
     const uint32_t q = (uint32_t)tile_i * kWave + lane;
     const int64_t col = (int64_t)q * 4;
-    const bool whole = (tile_i + 1) * kWave * 4 <= d;  // uniform: every lane has a whole quad
+    // Every lane of the workgroup has a whole quad: one answer for all its tiles, since their wavefronts meet at the barriers of
+    // the body that it chooses.
+    const bool whole = ((int64_t)blockIdx.x + 1) * tiles_wg * kWave * 4 <= d;
     const int have = whole || col + 4 <= d ? 4 : col < d ? (int)(d - col) : 0;
     const PhiloxQuad quad(q, TAG_FEAT, a.k1);
     ColumnSpread<v4f> spread;
     if (TRACE) spread.reset(whole || have == 4 ? ld_unit_cached<v4f>(a.ge.x + col) : v4f(0.f));
 
-    auto tile = [&](auto all) {  // a body of its own for tiles of whole quads: no branches around its loads and stores
+    auto tile = [&](auto all) {  // a body of its own for workgroups of whole quads: no branches around its loads and stores
     constexpr bool kAll = decltype(all)::value;
     auto load = [&](const float* p) -> v4f {
         if (kAll || have == 4) return ld_unit<v4f>(p);

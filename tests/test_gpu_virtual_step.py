@@ -25,6 +25,9 @@ def hx():
     (15, 720_897, 5, 5, "expo1", 4, 0.9, False, 4, 1.0), (24, 262_144, 1, 5, "expo1", 0, 0.0, False, 1, 1.0),
     (128, 32_767, 7, 7, "expo1", 0, 0.9, True, 0, 1.0), (130, 32_765, 16, 3, "ring", 2, 0.9, False, 2, 1.0),
     (130, 32_768, 16, 2, "none", 0, 0.9, False, 0, 1.0), (96, 65_500, 8, 7, "expo1", 0, 0.9, False, 0, 1.0),
+    # two tiles a workgroup that share their barriers: the last one a part, and one without a partner
+    (24, 300_001, 4, 3, "ring", 0, 0.9, False, 0, 1.0), (24, 300_280, 4, 3, "ring", 2, 0.9, False, 0, 1.0),
+    (24, 300_288, 4, 5, "expo1", 0, 0.9, True, 0, 1.0),
     (16, 524_284, 16, 3, "ring", 0, 0.9, False, 0, 4000.0)])   # margins so large that most coefficients are exactly zero
 def test_one_launch_matches_separate_calls(hx, n, d, B, T, topology, H, momentum, nesterov, pad, scale):
     import torch
