@@ -813,33 +813,36 @@ constexpr int kAutoBlocksPerCu = 4;
 // wins.  Us paced / free, momentum 0.9: 8 x 25.6M full 809 / 753, ring 827 / 706, 8 x 60M 1706 / 1666, 8 x 70M 1939 / 2000;
 // 12 x 17M 792 / 742; 16 x 14M 854 / 816, 16 x 20M 1150 / 1170; 20 x 7M 580 / 516; 32 x 5M ring 661 / 624, 32 x 8M 965 / 996;
 // 64 x 3M 730 / 750; without momentum 6 x 40M ring 617 / 469, 20 x 8M 438 / 342, 64 x 3M 478 / 432, 64 x 8M 1093 / 1134.
+// A caller who sets a rate or the workgroups of a compute unit asks for a persistent launch and gets it.
 constexpr double kFreeRowBytes = 80e9;  // divided by the rows, and at least / at most
 constexpr double kFreeMinBytes = 3.2e9, kFreeMaxBytes = 10e9;
 constexpr int kFreeRows = 64;
 bool free_running_pays(const gpga_ctx* c) {
-    if (c->n > kFreeRows) return false;
+    if (c->n > kFreeRows || c->opt_blocks_per_cu >= 0 || c->opt_pace_gbs >= 0) return false;
     const double most = kFreeRowBytes / c->n, bytes = 4.0 * (c->mu != 0.f ? 5 : 3) * c->n * (double)c->d;
     return bytes <= (most < kFreeMinBytes ? kFreeMinBytes : most > kFreeMaxBytes ? kFreeMaxBytes : most);
 }
-// Wavefronts per workgroup of a walk.  One where a launch of few rows streams past the caches on 16-byte rows: tiles are then
+// A walk: nor were paced cycles or the persistent one-peer kernel asked for.
+bool walk_runs_free(const gpga_ctx* c) { return free_running_pays(c) && c->opt_pace_min_cycle <= 0 && c->opt_cycle_kernel != 1; }
+// Wavefronts per workgroup.  One where a launch of few rows streams past the caches on 16-byte rows: tiles are then
 // handed out one by one, in order, and fewer of them are open at once (8 x 25.6M ring 728 -> 706 us, full 758 -> 753, 16 x 8M
 // one-peer 482 -> 461; 8 x 25 600 001, where neighbouring tiles share cache lines, ring 813 -> 900; 16 x 2M, 32 x 2M even;
 // 64 x 1.1M without momentum 158 -> 162).
 constexpr int64_t kLoneWaveElements = 1 << 26;
-int walk_waves(const gpga_ctx* c, int64_t tiles) {
+int walk_waves(const gpga_ctx* c, int64_t tiles, bool runs_free) {
     if (c->opt_waves) return c->opt_waves;
-    const bool lone = free_running_pays(c) && !c->opt_row_split && c->opt_blocks_per_cu < 0 && c->opt_pace_gbs < 0 &&
-                      (int64_t)c->n * c->d >= (c->n <= 32 ? 1 : 2) * kLoneWaveElements && tiles >= kPacedWaves && rows_on_16_bytes(c);
+    const bool lone = runs_free && !c->opt_row_split && (int64_t)c->n * c->d >= (c->n <= 32 ? 1 : 2) * kLoneWaveElements &&
+                      tiles >= kPacedWaves && rows_on_16_bytes(c);
     return lone ? 1 : 4;
 }
 // Rows per batch of a free-running walk along a cycle (us with 2 / 4 / 8, four wavefronts: 8 x 25.6M ring 778 / 762 / 731,
 // 16 x 14M without momentum 481 / 483 / 451; 4 x 51.2M 736 / 717 / 725; long columns of few tiles keep 2).
-int walk_unroll(const gpga_ctx* c, int64_t tiles, int64_t cycle) {
-    if (!free_running_pays(c) || (int64_t)c->n * c->d < kLoneWaveElements || tiles < kPacedWaves) return kDefaultUnroll;
+int walk_unroll(const gpga_ctx* c, int64_t tiles, int64_t cycle, bool runs_free) {
+    if (!runs_free || (int64_t)c->n * c->d < kLoneWaveElements || tiles < kPacedWaves) return kDefaultUnroll;
     return cycle >= 8 ? 8 : cycle >= 4 ? 4 : kDefaultUnroll;
 }
 
-LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool walks_rows, int pace_key) {
+LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool walks_rows, bool runs_free, int pace_key) {
     LaunchPlan p;
     p.work = work;
     p.num_cus = c->num_cus;
@@ -848,7 +851,7 @@ LaunchPlan make_plan(const gpga_ctx* c, int64_t work, int waves, int vec, bool w
     p.ctx = c;
     p.clock_hz = c->clock_hz;
     p.pace_key = pace_key;
-    const bool big = walks_rows && vec == 4 && (int64_t)c->n * c->d * 4 >= kPaceMinBytes && !free_running_pays(c);
+    const bool big = walks_rows && vec == 4 && (int64_t)c->n * c->d * 4 >= kPaceMinBytes && !runs_free;
     p.bpc = c->opt_blocks_per_cu < 0 ? (big ? kAutoBlocksPerCu : 0) : c->opt_blocks_per_cu;
     p.pace_gbs = c->opt_pace_gbs < 0 ? (big ? -1.0 : 0.0) : (double)c->opt_pace_gbs;
     if (!walks_rows) p.pace_gbs = 0.0;
@@ -876,10 +879,13 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     }
     const int64_t tiles = unit_tiles(ge, kWave);
     // (a ring of two or three rows has nothing to stream: 2 x 60M without momentum 238 us with four wavefronts, 273 with one)
-    const int waves = vec == 4 && !(mode == MODE_RING && n < 4) ? walk_waves(c, tiles) : c->opt_waves ? c->opt_waves : 4;
+    const bool runs_free = walk_runs_free(c);
+    const int waves = walk_waves(c, tiles, runs_free && vec == 4 && !(mode == MODE_RING && n < 4));
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
-    // persistent and paced.  Forced ("always"), it takes rows of whole lanes or on 16-byte boundaries.
+    // persistent where it does not run free, and paced from kPaceMinBytes on (below, us persistent / free: 2 x 30M 222 / 194,
+    // 8 x 14M 427 / 393, 16 x 8M 499 / 465, 16 x 2M 115 / 116, 64 x 2M 494 / 498; 128 x 1M even, persistent).  Forced ("always"), it takes rows of whole lanes
+    // or on 16-byte boundaries.
     const bool takes_rows = c->opt_cycle_kernel != 1 || ge.d % 4 == 0 || rows_on_16_bytes(c);
     if (mode == MODE_PEER && vec == 4 && takes_rows && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
         c->opt_cycle_kernel != 0 && (tiles >= kPacedWaves || c->opt_cycle_kernel == 1)) {
@@ -888,10 +894,9 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
         ca.S = S;
         ca.C = a.C;
         ca.gx = (tiles + waves - 1) / waves;
-        LaunchPlan plan = make_plan(c, ca.gx, waves, vec, true,
+        LaunchPlan plan = make_plan(c, ca.gx, waves, vec, true, runs_free,
                                     a.L == 2 ? PACE_CYCLES : a.L == 4 ? PACE_PEER_4 : a.L == 8 ? PACE_PEER_8 : PACE_PEER_16);
-        // forced on a small problem
-        if (c->opt_cycle_kernel == 1 && c->opt_blocks_per_cu < 0 && plan.bpc == 0) plan.bpc = kAutoBlocksPerCu;
+        if (!runs_free && c->opt_blocks_per_cu < 0 && plan.bpc == 0) plan.bpc = kAutoBlocksPerCu;
         const int momk = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
         ca.spread_partials = nullptr;
         const bool traced = spread_partials && spread_count;  // every lane stores whole columns: the consensus sums ride along
@@ -942,12 +947,12 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     const int pace_key = mode == MODE_RING ? PACE_RING
                          : mode != MODE_PEER ? PACE_SELF
                          : a.L <= 4 ? PACE_PEER_4 : a.L <= 8 ? PACE_PEER_8 : PACE_PEER_LONG;
-    const LaunchPlan plan = make_plan(c, gx * gy, waves, vec, uniform && a.L >= min_cycle, pace_key);
-    // paced wavefronts advance one row per batch (two rows in flight); free-running ones two
+    const LaunchPlan plan = make_plan(c, gx * gy, waves, vec, uniform && a.L >= min_cycle, runs_free, pace_key);
+    // paced wavefronts advance one row per batch (two rows in flight)
     const int U = c->opt_unroll                                 ? c->opt_unroll
                   : plan.pace_gbs != 0.0                        ? 1
                   : spread_partials || vec != 4 || a.Q > 1      ? kDefaultUnroll
-                                                                : walk_unroll(c, tiles, a.L);
+                                                                : walk_unroll(c, tiles, a.L, runs_free);
     const int mom = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
     a.spread_partials = nullptr;
     a.cpi = 1;
@@ -1014,7 +1019,7 @@ GlobalOrder global_order(const gpga_ctx* c) {
     }
     if (wpb > waves) wpb = waves;
     while (wpb > 1 && RL * wpb > n) wpb >>= 1;
-    const LaunchPlan plan = make_plan(c, 1, waves, vec, RL == 1 && wpb == 1 && n >= 8, PACE_GLOBAL);
+    const LaunchPlan plan = make_plan(c, 1, waves, vec, RL == 1 && wpb == 1 && n >= 8, free_running_pays(c), PACE_GLOBAL);
     // (2 x 60M: 376 us with two rows a batch, 415 with four)
     return {RL, wpb, c->opt_unroll ? c->opt_unroll : (plan.pace_gbs != 0.0 ? 1 : n < 4 ? 2 : 4)};
 }
@@ -1027,7 +1032,8 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& geom, int vec) 
     const GlobalOrder go = global_order(c);
     const int CL = kWave / go.RL;
     set_units(&a.ge, vec, CL);
-    const int waves = go.wpb == 1 && vec == 4 ? walk_waves(c, unit_tiles(a.ge, CL)) : c->opt_waves ? c->opt_waves : 4;
+    const bool runs_free = free_running_pays(c);
+    const int waves = walk_waves(c, unit_tiles(a.ge, CL), runs_free && go.wpb == 1 && vec == 4);
     a.inv_n = 1.0f / (float)n;
     a.RL = go.RL;
     a.tpb = waves / go.wpb;
@@ -1036,7 +1042,7 @@ hipError_t launch_step_global(const gpga_ctx* c, const StepGeom& geom, int vec) 
     if (gx > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.gx = gx;
     a.xcd = c->opt_xcd_swizzle;
-    const LaunchPlan plan = make_plan(c, gx, waves, vec, go.RL == 1 && go.wpb == 1 && n >= 8, PACE_GLOBAL);
+    const LaunchPlan plan = make_plan(c, gx, waves, vec, go.RL == 1 && go.wpb == 1 && n >= 8, runs_free, PACE_GLOBAL);
     const int U = go.U;
     const int mom = c->mu != 0.f ? (c->nesterov ? 2 : 1) : 0;
     if (vec == 4) {

@@ -470,3 +470,24 @@ def test_free_running_walks_of_few_rows(hx, n, d, topology, k, momentum, expect)
     _full_width_lockstep(sim, k, kw, f"free-running {topology} {n} x {d}", expect=expect)
     sim.close()
     torch.cuda.empty_cache()
+
+
+# Sizes that run free by themselves: a rate, a residency, the shortest paced cycle or the persistent one-peer kernel asked for
+# by itself is what the step gets; expect = (step_path, step_paced).
+@pytest.mark.parametrize("n,d,topology,k,opts,expect", [
+    (8, 16_800_000, "ring", 0, {}, (1, 0)), (8, 16_800_000, "ring", 0, {"pace_gbs": 5000}, (1, 1)),
+    (8, 16_800_000, "full", 0, {"pace_gbs": 5000}, (3, 1)), (8, 16_800_000, "expo1", 0, {"pace_gbs": 5000}, (2, 1)),
+    (20, 6_800_000, "expo1", 2, {"pace_gbs": 5000}, (1, 1)), (8, 16_800_000, "ring", 0, {"blocks_per_cu": 2}, (1, 1)),
+    (8, 16_800_000, "full", 0, {"blocks_per_cu": 2}, (3, 1)), (8, 16_800_000, "ring", 0, {"pace_min_cycle": 8}, (1, 1)),
+    (8, 16_800_000, "expo1", 1, {"cycle_kernel": 1}, (2, 1)), (16, 600_000, "expo1", 0, {"pace_gbs": 4000}, (2, 1)),
+    (8, 16_800_000, "ring", 0, {"pace_gbs": 0}, (1, 0))])
+def test_launches_asked_for_on_few_rows(hx, n, d, topology, k, opts, expect):
+    sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=0.9)
+    for name, value in opts.items():
+        sim.set_option(name, value)
+    sim.problem_synthetic(5, 1e-3)
+    _random_resident_state(sim, seed=n + d)
+    sim.local_grad()
+    _full_width_lockstep(sim, k, dict(topology=topology, H=0, lr=0.1, momentum=0.9), f"{topology} {n} x {d} {opts}", expect=expect)
+    sim.close()
+    torch.cuda.empty_cache()
