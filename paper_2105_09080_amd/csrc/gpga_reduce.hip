@@ -207,17 +207,31 @@ __global__ void __launch_bounds__(256) k_final_sum(const double* __restrict__ pa
     if (threadIdx.x == 0) out[0] = (s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3]);
 }
 
-// slot[0] = sqrt(sum of `count` partials), one workgroup, fixed order.
-__global__ void __launch_bounds__(256) k_trace_store(const double* __restrict__ partials, int64_t count,
-                                                     double* __restrict__ slot) {
-    __shared__ double s_buf[4];
+// slot[0] = sqrt(sum of `count` partials), one workgroup, fixed order.  One-shot launches leave a partial a workgroup, and lone
+// wavefronts one for every 256 columns: 1024 threads with eight loads in flight from 1025 partials on (a traced step of
+// 8 x 25.6M on the ring 824 -> 748 us, 4 x 100M 1677 -> 1340, 2 x 200M one-peer 2345 -> 1455).
+template <int TH>
+__global__ void __launch_bounds__(TH) k_trace_store(const double* __restrict__ partials, int64_t count, double* __restrict__ slot) {
+    __shared__ double s_buf[TH / kWave];
+    constexpr int kAhead = TH > 256 ? 8 : 1;
     double acc = 0.0;
-    for (int64_t t = threadIdx.x; t < count; t += blockDim.x) acc += partials[t];
+    for (int64_t t = threadIdx.x; t < count; t += TH * kAhead) {
+        double v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = t + u * TH < count ? partials[t + u * TH] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) acc += v[u];
+    }
     acc = wave_sum(acc);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     if (lane == 0) s_buf[wave] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) slot[0] = sqrt((s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3]));
+    if (threadIdx.x == 0) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < TH / kWave; ++w) sum += s_buf[w];
+        slot[0] = sqrt(sum);
+    }
 }
 
 // out[0] = (1/count) sum v[i], one workgroup, fixed order.
@@ -403,7 +417,8 @@ hipError_t launch_consensus_distance(const gpga_ctx* c, double* scratch, size_t 
 }
 
 hipError_t launch_trace_store(const gpga_ctx* c, const double* partials, int64_t count, double* slot) {
-    hipLaunchKernelGGL(k_trace_store, dim3(1), dim3(256), 0, c->stream, partials, count, slot);
+    if (count > 1024) hipLaunchKernelGGL(k_trace_store<1024>, dim3(1), dim3(1024), 0, c->stream, partials, count, slot);
+    else hipLaunchKernelGGL(k_trace_store<256>, dim3(1), dim3(256), 0, c->stream, partials, count, slot);
     return hipGetLastError();
 }
 
