@@ -884,8 +884,8 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
     // persistent where it does not run free, and paced from kPaceMinBytes on (below, us persistent / free: 2 x 30M 222 / 194,
-    // 8 x 14M 427 / 393, 16 x 8M 499 / 465, 16 x 2M 115 / 116, 64 x 2M 494 / 498; 128 x 1M even, persistent).  Forced ("always"), it takes rows of whole lanes
-    // or on 16-byte boundaries.
+    // 8 x 14M 427 / 393, 16 x 8M 499 / 465, 16 x 2M 115 / 116, 64 x 2M 494 / 498; 128 x 1M even, persistent).
+    // Forced ("always"), it takes rows of whole lanes or on 16-byte boundaries.
     const bool takes_rows = c->opt_cycle_kernel != 1 || ge.d % 4 == 0 || rows_on_16_bytes(c);
     if (mode == MODE_PEER && vec == 4 && takes_rows && (a.L == 2 || a.L == 4 || a.L == 8 || a.L == 16) && !c->opt_row_split &&
         c->opt_cycle_kernel != 0 && (tiles >= kPacedWaves || c->opt_cycle_kernel == 1)) {
@@ -959,8 +959,11 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
     LaunchPlan lp = plan;
     // Paced launches with one cycle per workgroup: a work item takes ALL cycles of its column tile
     // in turn instead of one (measured 3.41 -> 3.33 ms on n = 1024, d = 1M); its lanes then store
-    // whole columns, as they do when there is a single cycle.
-    if (a.C > 1 && Q == 1 && wpb == 1 && plan.pace_gbs != 0.0 && plan.bpc > 0 && mode == MODE_PEER) {
+    // whole columns, as they do when there is a single cycle.  So do free-running ones that would else be paced, if the
+    // trace is to ride along (one-peer steps, us with a reduction pass / without: 20 x 7M 580 / 545, 12 x 27M 1306 / 1254,
+    // 20 x 10M without momentum 513 / 441; paced 587, 1274, 520).
+    const bool traced_free = runs_free && spread_partials && uniform && a.L >= min_cycle && (int64_t)n * ge.d * 4 >= kPaceMinBytes;
+    if (a.C > 1 && Q == 1 && wpb == 1 && ((plan.pace_gbs != 0.0 && plan.bpc > 0) || traced_free) && mode == MODE_PEER) {
         a.cpi = a.C;
         a.gy = 1;
         lp.work = a.gx;

@@ -493,14 +493,16 @@ def test_launches_asked_for_on_few_rows(hx, n, d, topology, k, opts, expect):
     torch.cuda.empty_cache()
 
 
-# The consensus trace on free-running steps: lone wavefronts and workgroups of four, no momentum, Nesterov momentum; expect = (step_path, step_paced, trace_fused).  X and
+# The consensus trace on free-running steps: lone wavefronts and workgroups of four, one-peer offsets with several cycles a tile
+# (12 rows: two cycles of 6; 20: four of 5), no momentum, Nesterov momentum; expect = (step_path, step_paced, trace_fused).  X and
 # M are checked against the step in float64; the trace sums the stored fp32 values in fp64, so only rounding of some 1e8
 # additions (about 1e-12 for pairwise orders) stands between it and torch's figure.
 @pytest.mark.parametrize("n,d,topology,k,momentum,nesterov,expect", [
     (8, 8_400_004, "ring", 0, 0.0, False, (1, 0, 1)), (8, 8_400_004, "ring", 0, 0.9, True, (1, 0, 1)),
     (8, 8_400_004, "full", 0, 0.0, False, (3, 0, 0)), (8, 8_400_004, "full", 0, 0.9, True, (3, 0, 0)),
     (8, 8_400_004, "expo1", 1, 0.0, False, (2, 0, 1)), (16, 4_200_004, "expo1", 0, 0.9, True, (2, 0, 1)),
-    (4, 33_600_000, "ring", 0, 0.9, False, (1, 0, 1)),
+    (20, 6_800_000, "expo1", 2, 0.9, False, (1, 0, 1)), (12, 11_200_004, "expo1", 1, 0.0, False, (1, 0, 1)),
+    (20, 6_800_000, "expo1", 3, 0.9, True, (1, 0, 1)), (4, 33_600_000, "ring", 0, 0.9, False, (1, 0, 1)),
     (8, 2_000_000, "expo1", 0, 0.9, False, (2, 0, 1)), (2, 67_200_000, "expo1", 0, 0.9, False, (2, 0, 1))])
 def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, expect):
     sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=momentum)
