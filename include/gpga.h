@@ -331,9 +331,9 @@ gpga_status gpga_set_option(gpga_ctx* ctx, const char* name, int64_t value);
  * kind of launch (gossip step per one-peer offset class, global average) finds for itself,
  * each launch setting the rate of the next; a controller needs about a dozen launches.
  * gpga_tune runs `launches` (1..4096) fused steps of every kind the context's schedule
- * contains on the bound buffers.  The iteration counter is restored; the CONTENTS of x,
+ * contains, if that kind is paced, on the bound buffers.  The iteration counter is restored; the CONTENTS of x,
  * x_new and m afterwards are unspecified (call gpga_reset or set them), g is only read.
- * Does nothing when the launches of this context are not paced.  Asynchronous. */
+ * Does nothing when no launch of this context is paced.  Asynchronous. */
 gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
 
 /* Read-only facts about the context as doubles.  Names:

@@ -540,6 +540,7 @@ static gpga_status run_step(gpga_ctx* c, bool global, int32_t rows_B = 0, const 
                           : csr ? launch_step_csr(c, ge, vec, spread, count)
                                 : launch_step_walk(c, ge, mode, S, vec, spread, count);
     if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
+    if (c->plan_only) return GPGA_OK;
     float* t = c->x;
     c->x = c->x_new;
     c->x_new = t;
@@ -918,6 +919,20 @@ gpga_status gpga_probe_stream(int32_t kind, const float* src_dev, float* dst_dev
     return e == hipSuccess ? GPGA_OK : GPGA_EDEVICE;
 }
 
+// Whether the next step would be a paced launch.
+static gpga_status step_is_paced(gpga_ctx* c, bool global, bool* paced) {
+    const int path = c->last_path, was = c->last_paced, lane_bytes = c->last_lane_bytes, fused = c->last_trace_fused;
+    c->plan_only = true;
+    const gpga_status s = run_step(c, global);
+    c->plan_only = false;
+    *paced = c->last_paced != 0;
+    c->last_path = path;
+    c->last_paced = was;
+    c->last_lane_bytes = lane_bytes;
+    c->last_trace_fused = fused;
+    return s;
+}
+
 gpga_status gpga_tune(gpga_ctx* c, int32_t launches) {
     if (!c) return GPGA_EINVAL;
     if (launches < 1 || launches > 4096) return fail(c, GPGA_EINVAL, "launches must be 1..4096");
@@ -936,6 +951,10 @@ gpga_status gpga_tune(gpga_ctx* c, int32_t launches) {
         const bool global = kind == kinds;
         if (global && c->H == 0 && c->topo != GPGA_TOPO_FULL) break;
         if (!global && c->topo == GPGA_TOPO_FULL) continue;
+        c->k = kind;
+        bool paced = false;
+        s = step_is_paced(c, global, &paced);
+        if (!paced) continue;
         for (int32_t j = 0; j < launches && s == GPGA_OK; ++j) {
             c->k = kind;  // the offset of a one-peer step follows k mod tau
             s = run_step(c, global);

@@ -163,6 +163,7 @@ hipError_t launch_circ_lanes(const gpga_ctx* c, CircArgs a) {
         attr_set[dev] = true;
     }
     const int64_t blocks = balanced_blocks(a.tiles, (int64_t)c->num_cus * resident_per_cu(c, k_step_circ<MOM, LN>, threads, lds, 2));
+    if (c->plan_only) return hipSuccess;
     hipLaunchKernelGGL((k_step_circ<MOM, LN>), dim3((unsigned)blocks), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
 }

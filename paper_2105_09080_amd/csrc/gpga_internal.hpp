@@ -115,6 +115,7 @@ struct gpga_ctx {
     mutable int last_path = 0;        // StepPath; the first kernel of a step decides (the second pass of a two-pass step does not overwrite it)
     mutable int last_paced = 0;       // 1 = that launch was paced
     mutable int last_lane_bytes = 0;  // bytes per lane of that launch (16, 8, 4)
+    bool plan_only = false;           // the launchers of a step choose and note their launch and stop before it (gpga_tune)
     int last_trace_fused = 0;         // 1 = the step kernel itself produced the consensus sums of the trace entry
     int opt_mix_spmm_lanes = 0;  // two-pass sparse W, pass 2: lanes per column tile (0 = automatic, 64, 128, 256)
     int opt_mix_tile_kb = 0;     // sparse-W tile kernel: largest tile in KiB of LDS (0 = automatic)

@@ -539,6 +539,7 @@ hipError_t launch_spmm(const gpga_ctx* c, const StepGeom& geom, const CsrDev& w)
     const int64_t tiles = unit_tiles(ge, LANES);
     const int64_t ng = ((int64_t)ge.n + 256 / LANES - 1) / (256 / LANES);
     if (tiles * ng > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (c->plan_only) return hipSuccess;
     hipLaunchKernelGGL((k_spmm_rows<T, LANES>), dim3((unsigned)(tiles * ng)), dim3(256), 0, c->stream, ge, tiles, w);
     return hipGetLastError();
 }
@@ -580,6 +581,7 @@ hipError_t launch_tile_mom(const gpga_ctx* c, TileArgs a, int waves, size_t lds,
         if (spread_count && a.spread_partials && spread_slots_fit(c, blocks)) *spread_count = blocks;
         else a.spread_partials = nullptr;
     }
+    if (c->plan_only) return hipSuccess;
     hipLaunchKernelGGL((k_step_tile<T, MOM, LCSR, TRACE>), dim3((unsigned)blocks), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
 }
@@ -674,6 +676,7 @@ hipError_t launch_band_mom(const gpga_ctx* c, BandArgs a, int waves, size_t lds,
         if (spread_count && a.spread_partials && spread_slots_fit(c, blocks)) *spread_count = blocks;
         else a.spread_partials = nullptr;
     }
+    if (c->plan_only) return hipSuccess;
     hipLaunchKernelGGL((k_step_band<T, MOM, TRACE>), dim3((unsigned)blocks), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
 }

@@ -724,6 +724,7 @@ hipError_t launch_planned(Kernel kernel, LaunchPlan plan, Args a, hipStream_t st
     }
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     if (plan.blocks_out) *plan.blocks_out = blocks;
+    if (plan.ctx->plan_only) return hipSuccess;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, st, a);
     return hipGetLastError();
 }

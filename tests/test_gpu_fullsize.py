@@ -537,3 +537,25 @@ def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, 
     assert abs(float(trace[k]) - dist) <= 1e-9 * dist
     sim.close()
     torch.cuda.empty_cache()
+
+
+# gpga_tune runs the kinds of step that are paced; where none is, the caller's arrays and what gpga_query reports stay as they were.
+@pytest.mark.parametrize("n,d,topology,H,kinds", [
+    (8, 25_600_000, "ring", 4, ()), (8, 16_800_000, "full", 0, ()), (20, 6_800_000, "expo1", 6, ()), (8, 16_800_000, "none", 4, ()),
+    (300, 450_000, "expo", 0, ()), (64, 2_560_000, "ring", 4, ("ring", "global")), (64, 2_560_000, "none", 4, ("global",))])
+def test_tune_runs_paced_steps_only(hx, n, d, topology, H, kinds):
+    sim = hx.Simulation(n, d, topology=topology, H=H, lr=0.1, momentum=0.9)
+    gen = torch.Generator(device=sim.device)
+    gen.manual_seed(n + d)
+    arrays = (*sim._bufs, sim.M, sim.G)
+    for t in arrays:
+        t.normal_(0.0, 1.0, generator=gen)
+    kept = [t.clone() for t in arrays]
+    sim.tune(4)
+    torch.cuda.synchronize()
+    assert all(torch.equal(t, u) for t, u in zip(arrays, kept)) == (not kinds)
+    assert sim.k == 0 and int(sim.query("step_path")) == (3 if kinds else 0)
+    ran = {name: sum(sim.query(f"pace_launches:{name}{way}") for way in ("", "/1")) for name in ("global", "ring", "self", "tile")}
+    assert ran == {name: 4 * (name in kinds) for name in ran}
+    sim.close()
+    torch.cuda.empty_cache()
