@@ -45,7 +45,8 @@ struct ColumnArgs {
 enum ColumnMix : int { MIX_SELF = 0, MIX_RING = 1, MIX_PEER = 2, MIX_CSR = 3 };
 
 // Two exchange buffers are used in turn, so that an exchange has one barrier (an average two): gpga_exchange.hpp.
-template <int MIX, int MOM, int R, int QT>
+// QUADS: an average is formed a quad a lane by the first wavefront, else a column a thread.
+template <int MIX, int MOM, int R, int QT, bool QUADS>
 __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const ColumnArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     const int n = a.ge.n;
@@ -132,17 +133,23 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
         ++exchanges;
         __syncthreads();
         if (shift < 0) {
-            // A column a thread, of the first ones (with a whole unit a lane, 256 x 2M averaged in every iteration took 4920 us
-            // an iteration, 128 x 4M 2705, against 1260 and 892).
-            float* const sf = reinterpret_cast<float*>(sy);
-            for (int e = threadIdx.x; e < 4 * QT; e += blockDim.x) {
-                // whether the 64-lane tile of the step kernels that this unit lies in is a whole one (decides their row order)
-                const int64_t unit = (int64_t)blockIdx.x * QT + e / 4;
+            // whether the 64-lane tile of the step kernels that a unit lies in is a whole one decides their row order
+            if (!QUADS) {
+                float* const sf = reinterpret_cast<float*>(sy);
+                for (int e = threadIdx.x; e < 4 * QT; e += blockDim.x) {
+                    const int64_t unit = (int64_t)blockIdx.x * QT + e / 4;
+                    const bool whole64 = ((unit + a.lead64) / kWave + 1) * kWave - a.lead64 <= a.ge.ncols;
+                    SplitterTree<float> tree;
+                    for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0)
+                        tree.add(r0, splitter_column_sum(a.go, r0, n, whole64, sf + e, 4 * QT));
+                    sf[e] = tree.sum * a.inv_n;  // nobody else reads this column meanwhile
+                }
+            } else if (rs == 0) {
+                const int64_t unit = (int64_t)blockIdx.x * QT + q;
                 const bool whole64 = ((unit + a.lead64) / kWave + 1) * kWave - a.lead64 <= a.ge.ncols;
-                SplitterTree<float> tree;
-                for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0)
-                    tree.add(r0, splitter_column_sum(a.go, r0, n, whole64, sf + e, 4 * QT));
-                sf[e] = tree.sum * a.inv_n;  // nobody else reads this column meanwhile
+                SplitterTree<v4f> tree;
+                for (int r0 = 0; r0 < a.go.RL * a.go.wpb; ++r0) tree.add(r0, splitter_sum(a.go, r0, n, whole64, sy + q, QT));
+                sy[q] = tree.sum * a.inv_n;
             }
             __syncthreads();
             const v4f mean = sy[q];
@@ -196,7 +203,7 @@ __global__ void __launch_bounds__(1024, R == 2 ? 8 : 4) k_column_run(const Colum
 
 size_t column_lds(int n, int lanes) { return (size_t)2 * n * lanes * sizeof(v4f); }  // 64 KiB at most, 128 beyond 128 rows
 
-template <int MIX, int MOM, int R, int QT>
+template <int MIX, int MOM, int R, int QT, bool QUADS = false>
 hipError_t launch_column(const gpga_ctx* c, const ColumnArgs& a) {
     const int threads = ((a.ge.n + R - 1) / R * QT + kWave - 1) / kWave * kWave;
     const size_t lds = column_lds(a.ge.n, QT);
@@ -204,7 +211,7 @@ hipError_t launch_column(const gpga_ctx* c, const ColumnArgs& a) {
         static bool attr_set[64] = {false};
         const int dev = c->device >= 0 && c->device < 64 ? c->device : 0;
         if (!attr_set[dev]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_column_run<MIX, MOM, R, QT>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_column_run<MIX, MOM, R, QT, QUADS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->max_lds_block);
             if (e != hipSuccess) return e;
             attr_set[dev] = true;
@@ -212,8 +219,20 @@ hipError_t launch_column(const gpga_ctx* c, const ColumnArgs& a) {
     }
     const int64_t blocks = (a.ge.ncols + QT - 1) / QT;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_column_run<MIX, MOM, R, QT>), dim3((unsigned)blocks), dim3(threads), lds, c->stream, a);
+    hipLaunchKernelGGL((k_column_run<MIX, MOM, R, QT, QUADS>), dim3((unsigned)blocks), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
+}
+
+// How averages are formed on 64-lane tiles.  A thread adds a column, eight rows read ahead: where rows are few, and dealt to
+// splitters besides, most of what it reads is not used, and the workgroup has fewer threads than columns.  Us of four averages,
+// a column a thread / a quad a lane of the first wavefront: n = 2, d = 50 000 19.2 / 9.0, n = 4, d = 291 188 25.2 / 16.1,
+// d = 3M 58.7 / 49.3, n = 7, d = 50 000 13.2 / 13.6, d = 1.5M 48.3 / 45.6; n = 8, d = 50 000 13.4 / 14.0, d = 400 000 27.2 / 21.6,
+// d = 600 000 25.9 / 28.8; n = 12, d = 100 000 16.9 / 17.9, d = 150 000 20.0 / 19.4, d = 291 188 27.5 / 25.1, d = 600 000
+// 37.4 / 44.0; n = 13, d = 291 188 30.7 / 34.7; n = 32, d = 3M 404 / 586.  (Narrow tiles have more rows: a column a thread;
+// 256 x 2M averaged in every iteration 4920 us an iteration a quad a lane, 1260 a column a thread, 128 x 4M 2705 and 892.)
+bool quad_averages(const gpga_ctx* c) {
+    const int64_t tiles = ((c->d + 3) / 4 + kWave - 1) / kWave;
+    return c->n < 8 || (c->n <= 12 && tiles >= 512 && tiles < 2048);
 }
 
 // Tile width: all rows in 1024 threads, and two workgroups of up to 128 rows in a compute unit's LDS.  (n = 64, before: row
@@ -222,7 +241,7 @@ hipError_t launch_column(const gpga_ctx* c, const ColumnArgs& a) {
 // registers - took 8.6 and 11.5.)
 template <int MIX, int MOM>
 hipError_t launch_column_rows(const gpga_ctx* c, const ColumnArgs& a) {
-    if (a.ge.n <= 32) return launch_column<MIX, MOM, 2, 64>(c, a);
+    if (a.ge.n <= 32) return quad_averages(c) ? launch_column<MIX, MOM, 2, 64, true>(c, a) : launch_column<MIX, MOM, 2, 64>(c, a);
     if (a.ge.n <= 64) return launch_column<MIX, MOM, 2, 32>(c, a);
     if (a.ge.n <= 128) return launch_column<MIX, MOM, 2, 16>(c, a);
     return launch_column<MIX, MOM, 4, 16>(c, a);

@@ -68,10 +68,8 @@ __device__ __forceinline__ float splitter_column_sum(const GlobalOrder& o, int r
         }
         return sum;
     };
-    auto from = [&](int base) {  // batches of 1, 2 or 4 rows (global_order)
-        return o.U == 1   ? batches(base, std::integral_constant<int, 1>{})
-               : o.U == 2 ? batches(base, std::integral_constant<int, 2>{})
-                          : batches(base, std::integral_constant<int, 4>{});
+    auto from = [&](int base) {  // batches of 1 or 4 rows (global_order, four nodes and more)
+        return o.U == 1 ? batches(base, std::integral_constant<int, 1>{}) : batches(base, std::integral_constant<int, 4>{});
     };
     if (!by_parity) return from(r0);
     const float odd = from(o.U);

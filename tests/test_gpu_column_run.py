@@ -51,6 +51,9 @@ CASES += [(64, 1000, "full", 0, 0.0, False, 4, 1000), (64, 130, "ring", 4, 0.0, 
 CASES += [(33, 1031, "full", 0, 0.9, False, 3, 1031), (70, 130_003, "ring", 1, 0.9, False, 3, 130_004), (101, 600_001, "full", 0, 0.0, False, 2, 600_001),
           (130, 8, "full", 0, 0.9, False, 3, 8), (199, 300_002, "full", 0, 0.9, False, 2, 300_003), (256, 550_000, "ring", 2, 0.9, True, 4, 550_000)]
 
+# averages on wide tiles: a quad a lane (fewer than 8 nodes, up to 12 on 512 to 2047 tiles), else a column a thread
+CASES += [(n, d, "full", 0, 0.9, False, 3, d) for n, d in ((2, 1031), (3, 524_289), (7, 1031), (7, 600_001), (8, 131_000), (8, 131_073), (12, 140_001),
+                                                            (12, 524_290), (13, 140_001), (32, 4099))]
 # local SGD: iterations without an exchange between the averages, over the tile sizes
 CASES += [(n, 1031, "none", H, 0.9, False, 64, 1031) for n in (3, 40, 128, 200) for H in (2, 3, 4)]
 
