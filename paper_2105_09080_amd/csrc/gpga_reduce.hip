@@ -103,8 +103,8 @@ __device__ __forceinline__ void acc_add(d4& a, const d4& b) {
 // a wavefront each (64 units a workgroup).  Consensus distance + mean,
 // against one lane a column throughout: n = 256, d = 1172 62.5 -> 26.5 us, n = 100, d = 50 000 56.7 -> 27.7, n = 64,
 // d = 100 000 44.9 -> 29.1; rows without 16-byte alignment (n = 64, d = 5 000 001) 517 -> 466.
-// CL column units a workgroup: 64 with shared rows, else 256, or 1024 on arrays wide enough to keep every compute unit at it
-// (kWideReduce): the 16 KiB of a row that such a workgroup reads at a time keep fewer memory pages open (64 x 25.6M
+// CL column units a workgroup: 64 with shared rows, else 256, or 1024 on arrays that keep every compute unit at it to the end
+// (wide_reduce): the 16 KiB of a row that such a workgroup reads at a time keep fewer memory pages open (64 x 25.6M
 // distance and mean 2113 -> 2065 us, 16 x 30M 666 -> 642, 256 x 1M 349 -> 337; 64 x 400 000 52 -> 65).
 template <typename T, int RS, int CL>
 __global__ void __launch_bounds__(CL * RS) k_col_mean(const float* __restrict__ x, int64_t ld, int64_t d, int64_t units,
@@ -318,12 +318,15 @@ static int reduce_split(int64_t units, int32_t n) {
     return units >= 98304 ? 1 : n <= 32 || units >= (n <= 48 ? 24576 : 49152) ? 4 : 16;
 }
 
-constexpr int64_t kWideReduce = 245760;  // column units: 240 workgroups of 1024
-static int reduce_lanes(int64_t units, int split) { return split > 1 ? kWave : units >= kWideReduce ? 1024 : 256; }
-
-static int64_t reduce_blocks(int64_t units, int split) {
-    const int lanes = reduce_lanes(units, split);
-    return (units + lanes - 1) / lanes;
+// Whether unsplit reductions take workgroups of 1024 units.  Large ones end in a round of their own, so the last round of a
+// workgroup a compute unit is to be half full, unless it is one of many: three on up to 24 rows, ten on more.  Distance and
+// mean, us with 256 / 1024, by workgroups of 1024: 263 64 rows 116 / 134, 8 rows 28 / 31, 16 rows 385 49.1 / 50.6; 64 rows 451
+// 172 / 161, 521 213 / 223, 701 255 / 250, 801 299 / 311, 941 344 / 338, 1046 392 / 406, 3101 1209 / 1149; 8 rows 801 56 / 54,
+// 1046 71 / 65.
+static bool wide_reduce(const gpga_ctx* c, int64_t units) {
+    if (units < 245760) return false;
+    const int64_t blocks = (units + 1023) / 1024, cus = c->num_cus, rounds = blocks / cus, last = blocks % cus;
+    return last == 0 || last * 100 >= cus * 52 || rounds >= (c->n <= 24 ? 3 : 10);
 }
 
 // One per 256 units on wide arrays although the launch may write a quarter of that: the width that
@@ -357,7 +360,7 @@ hipError_t launch_fill_rows(const gpga_ctx* c, float* dst, const float* src) {
 
 template <typename T, int RS, int CL>
 static hipError_t launch_mean_split(const gpga_ctx* c, int64_t units, float* xbar) {
-    const int64_t blocks = reduce_blocks(units, RS);
+    const int64_t blocks = (units + CL - 1) / CL;
     hipLaunchKernelGGL((k_col_mean<T, RS, CL>), dim3((unsigned)blocks), dim3(CL * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, xbar);
     return hipGetLastError();
@@ -367,14 +370,14 @@ hipError_t launch_col_mean(const gpga_ctx* c, float* xbar) {
     if (c->d < 4) return launch_mean_split<float, 16, kWave>(c, c->d, xbar);
     const int64_t units = (c->d + 3) / 4;
     const int split = reduce_split(units, c->n);
-    if (split == 1 && reduce_lanes(units, 1) == 1024) return launch_mean_split<v4f, 1, 1024>(c, units, xbar);
+    if (split == 1 && wide_reduce(c, units)) return launch_mean_split<v4f, 1, 1024>(c, units, xbar);
     if (split == 1) return launch_mean_split<v4f, 1, 256>(c, units, xbar);
     return split == 4 ? launch_mean_split<v4f, 4, kWave>(c, units, xbar) : launch_mean_split<v4f, 16, kWave>(c, units, xbar);
 }
 
 template <typename T, int RS, int CL>
 static hipError_t launch_consensus_split(const gpga_ctx* c, int64_t units, double* parts, size_t cap, int64_t* count) {
-    const int64_t blocks = reduce_blocks(units, RS);
+    const int64_t blocks = (units + CL - 1) / CL;
     if ((size_t)blocks > cap) return hipErrorOutOfMemory;
     hipLaunchKernelGGL((k_consensus<T, RS, CL>), dim3((unsigned)blocks), dim3(CL * RS), 0, c->stream, c->x, c->ld, c->d, units,
                        c->n, parts);
@@ -389,7 +392,7 @@ static hipError_t launch_consensus_partials(const gpga_ctx* c, double* parts, si
     if (c->d < 4) return launch_consensus_split<float, 16, kWave>(c, c->d, parts, cap, count);
     const int64_t units = (c->d + 3) / 4;
     const int split = reduce_split(units, c->n);
-    if (split == 1 && reduce_lanes(units, 1) == 1024) return launch_consensus_split<v4f, 1, 1024>(c, units, parts, cap, count);
+    if (split == 1 && wide_reduce(c, units)) return launch_consensus_split<v4f, 1, 1024>(c, units, parts, cap, count);
     if (split == 1) return launch_consensus_split<v4f, 1, 256>(c, units, parts, cap, count);
     return split == 4 ? launch_consensus_split<v4f, 4, kWave>(c, units, parts, cap, count)
                       : launch_consensus_split<v4f, 16, kWave>(c, units, parts, cap, count);

@@ -16,8 +16,10 @@ def hx():
     return harness
 
 
-# 245 760 units of four columns are the first width with 1024 units a workgroup
-@pytest.mark.parametrize("n,d,pad", [(1, 983_037, 0), (3, 983_036, 0), (5, 983_041, 3), (2, 1_048_576, 0), (6, 1_048_577, 0), (9, 983_100, 1)])
+# 245 760 units of four columns are the first width with 1024 units a workgroup; the last ones fill little more or less than half
+# of a second round and a fourth part of a fourth
+@pytest.mark.parametrize("n,d,pad", [(1, 983_037, 0), (3, 983_036, 0), (5, 983_041, 3), (2, 1_048_576, 0), (6, 1_048_577, 0), (9, 983_100, 1),
+                                     (4, 1_593_345, 0), (4, 1_593_341, 1), (24, 3_200_003, 0)])
 def test_distance_and_mean_of_wide_arrays(hx, n, d, pad):
     import torch
     sim = hx.Simulation(n, d, topology="ring", H=0, lr=0.1, momentum=0.0, ld=d + pad)
