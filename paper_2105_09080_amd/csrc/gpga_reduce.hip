@@ -207,7 +207,8 @@ __global__ void __launch_bounds__(256) k_final_sum(const double* __restrict__ pa
     if (threadIdx.x == 0) out[0] = (s_buf[0] + s_buf[1]) + (s_buf[2] + s_buf[3]);
 }
 
-// slot[0] = sqrt(sum of `count` partials), one workgroup, fixed order.  One-shot launches leave a partial a workgroup, and lone
+// slot[0] = sqrt(sum of `count` partials), one workgroup, fixed order: with 256 threads that of k_final_sum, so that a reduction
+// pass gives the same bits whichever entry point asks.  One-shot steps leave a partial a workgroup, and lone
 // wavefronts one for every 256 columns: 1024 threads with eight loads in flight from 1025 partials on (a traced step of
 // 8 x 25.6M on the ring 824 -> 748 us, 4 x 100M 1677 -> 1340, 2 x 200M one-peer 2345 -> 1455).
 template <int TH>
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(TH) k_trace_store(const double* __restrict__ p
     if (threadIdx.x == 0) {
         double sum = 0.0;
 #pragma unroll
-        for (int w = 0; w < TH / kWave; ++w) sum += s_buf[w];
+        for (int w = 0; w < TH / kWave; w += 4) sum += (s_buf[w] + s_buf[w + 1]) + (s_buf[w + 2] + s_buf[w + 3]);
         slot[0] = sqrt(sum);
     }
 }
@@ -416,9 +417,11 @@ hipError_t launch_consensus_distance(const gpga_ctx* c, double* scratch, size_t 
     int64_t count = 0;
     const hipError_t e = launch_consensus_partials(c, scratch, scratch_cap, &count);
     if (e != hipSuccess) return e;
-    return launch_trace_store(c, scratch, count, slot);
+    hipLaunchKernelGGL(k_trace_store<256>, dim3(1), dim3(256), 0, c->stream, scratch, count, slot);
+    return hipGetLastError();
 }
 
+// The partial sums that a step kernel left.
 hipError_t launch_trace_store(const gpga_ctx* c, const double* partials, int64_t count, double* slot) {
     if (count > 1024) hipLaunchKernelGGL(k_trace_store<1024>, dim3(1), dim3(1024), 0, c->stream, partials, count, slot);
     else hipLaunchKernelGGL(k_trace_store<256>, dim3(1), dim3(256), 0, c->stream, partials, count, slot);

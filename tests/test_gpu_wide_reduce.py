@@ -30,5 +30,8 @@ def test_distance_and_mean_of_wide_arrays(hx, n, d, pad):
     want, mean = orc.consensus_error(X), X.mean(0)
     # deviations are formed in fp32 (half an ulp of 1e-3 each, of random sign), sums are fp64
     assert abs(sim.consensus_error() - want) <= 1e-7 * want
+    out = torch.zeros(1, dtype=torch.float64, device="cuda")
+    sim.consensus_error_static(out)   # the same partial sums, added in the same order
+    assert float(out.item()) == sim.consensus_error()
     assert np.abs(sim.mean().cpu().numpy() - mean).max() <= 6.0e-8 * np.abs(mean).max()   # one rounding to fp32
     sim.close()
