@@ -493,9 +493,9 @@ def test_launches_asked_for_on_few_rows(hx, n, d, topology, k, opts, expect):
     torch.cuda.empty_cache()
 
 
-# The consensus trace on free-running steps: lone wavefronts and workgroups of four, one-peer offsets with several cycles a tile
-# (12 rows: two cycles of 6; 20: four of 5), no momentum, Nesterov momentum; expect = (step_path, step_paced, trace_fused).  X and
-# M are checked against the step in float64; the trace sums the stored fp32 values in fp64, so only rounding of some 1e8
+# Free-running steps with the consensus trace and, in the batches of rows that untraced walks take, without: lone wavefronts and
+# workgroups of four, one-peer offsets with several cycles a tile (12 rows: two cycles of 6; 20: four of 5), no momentum, Nesterov
+# momentum; expect = (step_path, step_paced, trace_fused if traced).  X and M are checked against the step in float64; the trace sums the stored fp32 values in fp64, so only rounding of some 1e8
 # additions (about 1e-12 for pairwise orders) stands between it and torch's figure.
 @pytest.mark.parametrize("n,d,topology,k,momentum,nesterov,expect", [
     (8, 8_400_004, "ring", 0, 0.0, False, (1, 0, 1)), (8, 8_400_004, "ring", 0, 0.9, True, (1, 0, 1)),
@@ -504,7 +504,8 @@ def test_launches_asked_for_on_few_rows(hx, n, d, topology, k, opts, expect):
     (20, 6_800_000, "expo1", 2, 0.9, False, (1, 0, 1)), (12, 11_200_004, "expo1", 1, 0.0, False, (1, 0, 1)),
     (20, 6_800_000, "expo1", 3, 0.9, True, (1, 0, 1)), (4, 33_600_000, "ring", 0, 0.9, False, (1, 0, 1)),
     (8, 2_000_000, "expo1", 0, 0.9, False, (2, 0, 1)), (2, 67_200_000, "expo1", 0, 0.9, False, (2, 0, 1))])
-def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, expect):
+@pytest.mark.parametrize("traced", [True, False])
+def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, expect, traced):
     sim = hx.Simulation(n, d, topology=topology, H=0, lr=0.1, momentum=momentum)
     if nesterov:
         sim.set_nesterov(True)
@@ -515,11 +516,11 @@ def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, 
             t.normal_(0.0, 1.0, generator=gen)
     x, g = sim.X, sim.G
     m = sim.M.double() if momentum else None
-    trace = sim.attach_trace(k + 1)
+    trace = sim.attach_trace(k + 1) if traced else None
     sim.set_state(k=k)
     sim.step()
     torch.cuda.synchronize()
-    assert (int(sim.query("step_path")), int(sim.query("step_paced")), int(sim.query("trace_fused"))) == expect
+    assert (int(sim.query("step_path")), int(sim.query("step_paced")), int(sim.query("trace_fused"))) == (*expect[:2], expect[2] * traced)
     lr, mu = float(np.float32(0.1)), float(np.float32(momentum))
     mom = mu * m + g if momentum else g
     y = x - lr * (g + mu * mom if nesterov else mom).double()
@@ -533,8 +534,9 @@ def test_trace_of_free_running_steps(hx, n, d, topology, k, momentum, nesterov, 
     if momentum:
         assert float((sim.M - mom).abs().max()) <= TOL_STEP * float(mom.abs().max())
     del y, want, mom, m
-    dist = 0.0 if topology == "full" else float((sim.X - sim.X.double().mean(dim=0)).norm())
-    assert abs(float(trace[k]) - dist) <= 1e-9 * dist
+    if traced:
+        dist = 0.0 if topology == "full" else float((sim.X - sim.X.double().mean(dim=0)).norm())
+        assert abs(float(trace[k]) - dist) <= 1e-9 * dist
     sim.close()
     torch.cuda.empty_cache()
 

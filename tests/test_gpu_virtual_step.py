@@ -28,6 +28,8 @@ def hx():
     # two tiles a workgroup that share their barriers: the last one a part, and one without a partner
     (24, 300_001, 4, 3, "ring", 0, 0.9, False, 0, 1.0), (24, 300_280, 4, 3, "ring", 2, 0.9, False, 0, 1.0),
     (24, 300_288, 4, 5, "expo1", 0, 0.9, True, 0, 1.0),
+    # one wavefront a tile keeps the trace's sums: one-peer offsets of one to four cycles, W = I
+    (12, 524_288, 4, 5, "expo1", 0, 0.9, False, 0, 1.0), (6, 524_288, 2, 4, "none", 3, 0.0, False, 4, 1.0),
     (16, 524_284, 16, 3, "ring", 0, 0.9, False, 0, 4000.0)])   # margins so large that most coefficients are exactly zero
 def test_one_launch_matches_separate_calls(hx, n, d, B, T, topology, H, momentum, nesterov, pad, scale):
     import torch
@@ -48,7 +50,9 @@ def test_one_launch_matches_separate_calls(hx, n, d, B, T, topology, H, momentum
         batches, trace = sim.upload_batches(idx), sim.attach_trace(T)
         if fused:
             sim.run(T, batches)
-            assert int(sim.query("step_path")) == (11 if T % (H or T + 1) else 3)
+            gossip = T % (H or T + 1) != 0
+            assert int(sim.query("step_path")) == (11 if gossip else 3)
+            assert int(sim.query("trace_fused")) == (gossip and d % 4 == 0 and d > 2047 * 256)
         else:
             for k in range(T):
                 sim.local_grad(batches[k])
