@@ -321,6 +321,7 @@ __global__ void __launch_bounds__(kWave) k_loss_chunks(const double* __restrict_
 
 // Virtual features are bound by vector issue.  Splitting off what the first two Philox rounds share between draws of a
 // quad and between quads of a draw: n = 1024, d = 1M, B = 16 a new state's iteration 19.5 -> 18.2 ms (gradient and step).
+
 // Pass 1: grid (column chunks, node).  Each lane owns column quads and keeps B
 // partial margins; the node shift mu_i is generated once per quad and reused for
 // all B samples.  Partial margins are combined per workgroup and stored as

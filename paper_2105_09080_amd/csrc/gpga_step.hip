@@ -837,7 +837,8 @@ int walk_waves(const gpga_ctx* c, int64_t tiles, bool runs_free) {
     return lone ? 1 : 4;
 }
 // Rows per batch of a free-running walk along a cycle (us with 2 / 4 / 8, four wavefronts: 8 x 25.6M ring 778 / 762 / 731,
-// 16 x 14M without momentum 481 / 483 / 451; 4 x 51.2M 736 / 717 / 725; long columns of few tiles keep 2).
+// 16 x 14M without momentum 481 / 483 / 451; 4 x 51.2M 736 / 717 / 725; long columns of few tiles keep 2).  Eight rows of x, m
+// and g fill the registers of two wavefronts a SIMD, and on the ring five more spill, 24 bytes of scratch memory a lane.
 int walk_unroll(const gpga_ctx* c, int64_t tiles, int64_t cycle, bool runs_free) {
     if (!runs_free || (int64_t)c->n * c->d < kLoneWaveElements || tiles < kPacedWaves) return kDefaultUnroll;
     return cycle >= 8 ? 8 : cycle >= 4 ? 4 : kDefaultUnroll;
@@ -879,8 +880,8 @@ hipError_t launch_step_walk(const gpga_ctx* c, const StepGeom& geom, int mode, i
         a.L = n / a.C;
     }
     const int64_t tiles = unit_tiles(ge, kWave);
-    // (a ring of two or three rows has nothing to stream: 2 x 60M without momentum 238 us with four wavefronts, 273 with one)
     const bool runs_free = walk_runs_free(c);
+    // (a ring of two or three rows has nothing to stream: 2 x 60M without momentum 238 us with four wavefronts, 273 with one)
     const int waves = walk_waves(c, tiles, runs_free && vec == 4 && !(mode == MODE_RING && n < 4));
 
     // One-peer steps over short cycles (2, 4, 8 or 16 rows) on large problems: the row-streaming kernel,
