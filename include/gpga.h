@@ -242,8 +242,8 @@ gpga_status gpga_check_mixing_csr(int32_t n, const int64_t* row_ptr_host, const 
  * estimate F_init <- (F_init + F)/2 is refreshed (iteration k < warmup_iters;
  * F_init starts at 0) or H <- ceil(F_init / F * H_init), kept in [1, H_max].
  * loss_dev: n floats on the device, the minibatch losses F_i(x_i^(k); xi_i) of
- * this iteration (gpga_local_loss, called before the step).  Averaging steps
- * synchronise the stream (one scalar is read back).  1 <= H_init <= H_max. */
+ * this iteration (gpga_local_loss, called before the step).  Averaging steps, and
+ * gpga_run, synchronise the stream (the scalar, or the period, is read back).  1 <= H_init <= H_max. */
 gpga_status gpga_aga_enable(gpga_ctx* ctx, int64_t H_init, int64_t warmup_iters, int64_t H_max);
 gpga_status gpga_aga_step(gpga_ctx* ctx, const float* loss_dev);
 /* Current averaging period H. */
@@ -310,6 +310,11 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * "column_run" (gpga_run on synthetic gradients with up to 256 nodes: 1 = several iterations a
  * launch with the columns on chip (default; not while a trace is being recorded, and not while
  * the stream is being captured), 0 = one iteration at a time),
+ * "rows_run" (gpga_run on stored features, 4 to 128 nodes: 1 = several iterations a launch whose workgroups exchange
+ * margins and iterates (default; from three iterations on, not while a trace is being recorded, and not while the
+ * stream is being captured), 0 = one iteration at a time), "run_wait_us" (how long a workgroup of such a launch waits
+ * for another, in microseconds, before the launch is given up and its last workgroup does the work alone, 0..10000000,
+ * default 100000; launches of this kind never overlap within a process),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
  * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always, on rows
@@ -353,7 +358,8 @@ gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
  *       8 several iterations with the columns on chip (synthetic gradients, gpga_run),
  *       9 gradient sums, update and mixing in one launch (stored features, small problems, gpga_run),
  *       10 circulant sparse W on 225 to 1024 nodes, the whole column tile in LDS and the next one loaded meanwhile,
- *       11 gradient sums, update and mixing in one launch (virtual features, gpga_run);
+ *       11 gradient sums, update and mixing in one launch (virtual features, gpga_run),
+ *       12 several iterations in one launch (stored features, gpga_run);
  *   "step_paced" (1 = that launch was a paced persistent launch), "step_lane_bytes" (16, 8 or 4),
  *   "trace_fused" (1 = the consensus-trace entry of that step came from the step kernel's own
  *       sums, 0 = a reduction pass followed or no trace is attached).  These four do not synchronise.

@@ -14,7 +14,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libgpga.so")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 SOURCES = ["gpga_api.hip", "gpga_step.hip", "gpga_mix.hip", "gpga_graph.hip", "gpga_grad.hip", "gpga_reduce.hip",
            "gpga_column.hip", "gpga_rows_step.hip", "gpga_circ.hip", "gpga_virtual_step.hip",
-           "gpga_static.hip"]
+           "gpga_rows_run.hip", "gpga_gang.hip", "gpga_static.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <new>
 
+#include "gpga_gang.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_schedule.hpp"
@@ -297,12 +298,15 @@ gpga_status gpga_destroy(gpga_ctx* c) {
     DeviceGuard guard(c->device);
     gpga_status s = GPGA_OK;
     if (c->bound && hipStreamSynchronize(c->stream) != hipSuccess) s = GPGA_EDEVICE;
+    gang_forget(c);
     if (c->coef) (void)hipFree(c->coef);
     if (c->aga_loss) (void)hipFree(c->aga_loss);
     if (c->partials) (void)hipFree(c->partials);
     if (c->pace_states) (void)hipFree(c->pace_states);
+    if (c->run_space) (void)hipFree(c->run_space);
     free_csr_device(c);
     if (c->host_scalar) (void)hipHostFree(c->host_scalar);
+    if (c->aga_state) (void)hipHostFree(c->aga_state);
     delete c;
     return s;
 }
@@ -326,6 +330,10 @@ gpga_status gpga_bind(gpga_ctx* c, float* x, float* x_new, float* m, float* g, i
                 if ((lo <= hi ? hi - lo : lo - hi) < span)
                     return fail(c, GPGA_EINVAL, "%s and %s overlap", names[p], names[q]);
             }
+    }
+    if (c->bound && c->stream != static_cast<hipStream_t>(hip_stream)) {
+        DeviceGuard guard(c->device);
+        gang_forget(c);
     }
     c->x = x;
     c->x_first = x;
@@ -658,6 +666,27 @@ static gpga_status run_iteration(gpga_ctx* c, const int32_t* idx, int32_t B, boo
     return run_step(c, global, Beff, idx, want_g);
 }
 
+// Several iterations of gpga_run in one launch; *done is false if it cannot be launched now.
+static gpga_status run_chunk(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g, bool* done) {
+    hipError_t e = launch_rows_run(c, T, idx, B, want_g);
+    *done = e != hipErrorNotReady;
+    if (!*done) return GPGA_OK;
+    if (e != hipSuccess) return hip_fail(c, e, "trajectory kernel launch");
+    c->last_path = PATH_ROWS_RUN;
+    c->last_paced = 0;
+    c->last_lane_bytes = 16;
+    c->last_trace_fused = 0;
+    if (T % 2) std::swap(c->x, c->x_new);  // X is where T separate steps would have left it
+    c->k += T;
+    if (!c->aga) return GPGA_OK;
+    e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    c->aga_C = c->aga_state->since;
+    c->H = c->aga_state->period;
+    c->aga_F_init = c->aga_state->first_loss;
+    return GPGA_OK;
+}
+
 // Algorithm 2 after the global average of iteration k: the period that follows from that iteration's minibatch losses.
 static gpga_status aga_average(gpga_ctx* c, int64_t k, const float* loss_dev) {
     c->aga_C = 0;
@@ -667,18 +696,10 @@ static gpga_status aga_average(gpga_ctx* c, int64_t k, const float* loss_dev) {
         e = hipMemcpyAsync(c->host_scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "loss average");
-    const double F = *c->host_scalar;
-    if (k < c->aga_warmup) {
-        c->aga_F_init = 0.5 * (c->aga_F_init + F);
-    } else {
-        int64_t H_new = c->aga_H_max;
-        if (F > 0.0) {
-            const double h = std::ceil(c->aga_F_init / F * (double)c->aga_H_init);
-            if (std::isfinite(h) && h < (double)c->aga_H_max) H_new = (int64_t)h;
-        }
-        if (H_new < 1) H_new = 1;
-        c->H = H_new;
-    }
+    RowsRunAga state = aga_begin(c);
+    state.step(k, *c->host_scalar);
+    c->aga_F_init = state.first_loss;
+    c->H = state.period;
     return GPGA_OK;
 }
 
@@ -689,13 +710,30 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
     if (c->problem == PROB_NONE) return fail(c, GPGA_ESTATE, "no problem attached (gpga_problem_*)");
     DeviceGuard guard(c->device);
     const int64_t stride = batch_table_dev ? (int64_t)c->n * B : 0;
+    int32_t checked_B = 0;
+    const bool checked = T > 1 && check_batch(c, batch_table_dev, B, &checked_B) == GPGA_OK;  // else the first iteration reports it
+    const int32_t most = checked ? rows_run_iterations(c, T, batch_table_dev, B) : 0;  // iterations a launch
     if (c->aga) {
         // Algorithm 2: the minibatch losses are needed only in iterations that end in a global
         // average, which the counter tells beforehand
         gpga_status s = grow_f32(c, &c->aga_loss, &c->aga_loss_cap, (size_t)c->n);
         if (s != GPGA_OK) return s;
+        if (!c->aga_state && hipHostMalloc(reinterpret_cast<void**>(&c->aga_state), sizeof(RowsRunAga), hipHostMallocDefault) != hipSuccess) {
+            c->aga_state = nullptr;
+            return fail(c, GPGA_ENOMEM, "hipHostMalloc(adaptive period)");
+        }
         for (int64_t j = 0; j < T; ++j) {
             const int32_t* idx = batch_table_dev ? batch_table_dev + j * stride : nullptr;
+            const int32_t chunk = (int32_t)(T - j < most ? T - j : most);
+            if (chunk > 1) {
+                bool done = false;
+                s = run_chunk(c, chunk, idx, B, j + chunk == T, &done);
+                if (s != GPGA_OK) return s;
+                if (done) {
+                    j += chunk - 1;
+                    continue;
+                }
+            }
             const int64_t k = c->k;
             const bool global = c->aga_C + 1 == c->H;
             s = run_iteration(c, idx, B, global, global ? c->aga_loss : nullptr, j == T - 1);
@@ -706,7 +744,7 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         }
         return GPGA_OK;
     }
-    if (small_run_fits(c, batch_table_dev, B)) {
+    if (most == 0 && small_run_fits(c, batch_table_dev, B)) {
         // the whole loop inside single-workgroup launches of up to kSmallRunMaxIters iterations
         int32_t Beff = 0;
         gpga_status s = check_batch(c, batch_table_dev, B, &Beff);
@@ -748,6 +786,16 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         return GPGA_OK;
     }
     for (int64_t j = 0; j < T; ++j) {
+        const int32_t chunk = (int32_t)(T - j < most ? T - j : most);
+        if (chunk > 1) {
+            bool done = false;
+            const gpga_status s = run_chunk(c, chunk, batch_table_dev ? batch_table_dev + j * stride : nullptr, B, j + chunk == T, &done);
+            if (s != GPGA_OK) return s;
+            if (done) {
+                j += chunk - 1;
+                continue;
+            }
+        }
         const gpga_status s = run_iteration(c, batch_table_dev ? batch_table_dev + j * stride : nullptr, B,
                                             is_global_iteration(c->topo, c->H, c->k), nullptr, j == T - 1);
         if (s != GPGA_OK) return s;
@@ -875,6 +923,12 @@ gpga_status gpga_set_option(gpga_ctx* c, const char* name, int64_t value) {
     } else if (!strcmp(name, "small_run")) {
         if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "small_run must be 0 or 1");
         c->opt_small_run = (int)value;
+    } else if (!strcmp(name, "rows_run")) {
+        if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "rows_run must be 0 or 1");
+        c->opt_rows_run = (int)value;
+    } else if (!strcmp(name, "run_wait_us")) {
+        if (value < 0 || value > 10000000) return fail(c, GPGA_EINVAL, "run_wait_us must be 0..10000000");
+        c->opt_run_wait_us = (int)value;
     } else if (!strcmp(name, "mix_csr_lds")) {
         if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "mix_csr_lds must be 0 or 1");
         c->opt_mix_csr_lds = (int)value;

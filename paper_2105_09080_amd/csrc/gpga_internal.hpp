@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <vector>
@@ -38,12 +39,33 @@ constexpr int kSmallRunPasses = 4;     // (node, sample) pairs a lane group keep
 constexpr int kSmallRunMaxIters = 256;   // iterations per launch (their step sizes travel in the kernel arguments)
 
 constexpr int kMaxCirculant = 16;        // entries a row of a circulant W may have for the kernel made for it
+constexpr int kRowsRunMaxIters = 32;     // iterations per launch of the trajectory kernel on stored features
 constexpr int kColumnRunMaxIters = 64;   // iterations per launch of the column-resident trajectory kernel
 
 enum LrSchedule : int { SCHED_NONE = 0, SCHED_STEP, SCHED_MILESTONES, SCHED_POLY };
 constexpr int kMaxMilestones = 16;
 
 struct PaceState;  // gpga_pace.hpp
+
+// Adaptive averaging period (Algorithm 2): iterations since the last average, period, estimate of the first loss; the rule that
+// follows a global average in iteration k with mean minibatch loss F.  One place for host and device.
+struct RowsRunAga {
+    int64_t since, period;
+    double first_loss;
+    int64_t k0, warmup, initial, most;
+    __host__ __device__ void step(int64_t k, double F) {
+        if (k < warmup) {
+            first_loss = 0.5 * (first_loss + F);
+            return;
+        }
+        int64_t next = most;
+        if (F > 0.0) {
+            const double h = ceil(first_loss / F * (double)initial);
+            if (h - h == 0.0 && h < (double)most) next = (int64_t)h;  // finite
+        }
+        period = next < 1 ? 1 : next;
+    }
+};
 
 // Arrays of at least this many bytes (n x d x 4) run the fused step as paced persistent launches.  Measured on
 // the ring walk with n = 64: 281 MB (0.3 ms) 4.1 TB/s paced against 4.9 one-shot, 563 MB equal, 1.1 GB 5.3
@@ -53,7 +75,7 @@ constexpr int64_t kPaceMinBytes = 512ll << 20;
 
 enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL = 3, PATH_TILE = 4, PATH_BAND = 5,
                       PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9,
-                      PATH_CIRCULANT = 10, PATH_VIRTUAL_STEP = 11 };
+                      PATH_CIRCULANT = 10, PATH_VIRTUAL_STEP = 11, PATH_ROWS_RUN = 12 };
 
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
@@ -103,6 +125,9 @@ struct gpga_ctx {
     double* partials = nullptr;
     size_t partials_cap = 0;  // in doubles
     double* host_scalar = nullptr;  // pinned, 1 double
+    unsigned char* run_space = nullptr;  // what the workgroups of k_rows_run exchange
+    size_t run_space_cap = 0;            // in bytes
+    uint32_t run_number = 0;             // of the last such launch, 0: run_space is not cleared yet
 
     // launch geometry overrides (0 = automatic)
     int opt_unroll = 0;
@@ -124,6 +149,8 @@ struct gpga_ctx {
     int opt_mix_band = -1;     // sliding-window kernel for banded W: -1 = automatic (large problems), 0 = never, 1 = whenever W qualifies
     int opt_mix_csr_lds = 1;   // 0 = the tile kernel reads W from global memory even when it fits in LDS
     int opt_column_run = 1;    // 0 = gpga_run takes synthetic gradients one iteration at a time
+    int opt_rows_run = 1;      // 0 = gpga_run takes stored features one iteration at a time
+    int opt_run_wait_us = 100000;  // how long a workgroup of such a launch waits for another before one does the work alone
     int opt_small_run = 1;     // 0 = gpga_run never takes the single-workgroup path for small problems
     int opt_blocks_per_cu = -1;  // -1 = automatic, 0 = one workgroup per tile group, k = persistent
     int num_cus = 256;
@@ -165,9 +192,14 @@ struct gpga_ctx {
     double aga_F_init = 0.0;
     float* aga_loss = nullptr;  // n minibatch losses (library-owned; used by gpga_run)
     size_t aga_loss_cap = 0;
+    RowsRunAga* aga_state = nullptr;  // pinned: what a launch of several iterations leaves
 
     char err[256] = {0};
 };
+
+inline RowsRunAga aga_begin(const gpga_ctx* c) {
+    return {c->aga_C, c->H, c->aga_F_init, c->k, c->aga_warmup, c->aga_H_init, c->aga_H_max};
+}
 
 // Description of one fused step launch over all d columns (column units: gpga_unit.hpp).
 struct StepGeom {
@@ -233,6 +265,11 @@ bool rows_step_fits(const gpga_ctx* c, int32_t Beff);
 hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
 hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32_t* idx, int32_t Beff, bool global, int mode,
                             int32_t shift, bool csr, bool want_g);
+// Several iterations on stored features in one launch, T <= rows_run_iterations of the `wanted` ones (0: not for this context and
+// batch).  Under an
+// adaptive period the launch decides itself which iterations average and leaves the period's state in c->aga_state.
+int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B);
+hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g);
 // Virtual features: what follows the margin pass of a gossip iteration in one launch, same conventions (spread_* as for
 // launch_step_walk).
 bool virtual_step_fits(const gpga_ctx* c, int32_t B);

@@ -1,0 +1,229 @@
+"""gpga_run on stored features with several iterations a launch, against separate calls: slices and samples around the
+registers that hold them, ragged rows, every graph, adaptive periods, launches that are given up, streams and threads."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_2105_09080_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# Margins and g are fp64 sums rounded to fp32 on both sides; another order of a sum turns a rounding now and then: one ulp,
+# carried through a few contractive iterations (features of unit length, step size 0.1).
+TOL = 4 * 1.2e-7
+
+
+@pytest.fixture(scope="module")
+def hx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_09080_amd import harness
+    return harness
+
+
+def make(hx, n, d, M, batch, T, topology, H, momentum, problem="logreg", pad=0, nesterov=False, lr=0.1, stream=None, feat=None):
+    rng = np.random.default_rng([n, d, M])
+    if feat is None:
+        feat = (rng.standard_normal((n, M, d)) / np.sqrt(d)).astype(np.float32)
+    y = np.where(rng.random((n, M)) < 0.5, 1.0, -1.0).astype(np.float32)
+    sim = hx.Simulation(n, d, topology=topology, H=H, lr=lr, momentum=momentum, ld=d + pad, stream=stream)
+    if nesterov:
+        sim.set_nesterov(True)
+    sim.set_option("small_run", 0)
+    (sim.problem_logreg if problem == "logreg" else sim.problem_lsq)(feat, y)
+    idx = sim.upload_batches(inputs.batch_indices(T, n, batch, M, seed=3)) if batch else None
+    for buf in (*sim._bufs, sim.g):
+        buf.fill_(7.0)
+    sim.set_state(X=inputs.random_state(n, d, seed=1)[0], M=inputs.random_state(n, d, seed=2)[0] if momentum else None)
+    return sim, idx
+
+
+def separate(sim, idx, T):
+    for k in range(T):
+        sim.local_grad(None if idx is None else idx[k])
+        sim.step()
+
+
+def results(sim, momentum):
+    torch.cuda.synchronize()
+    return [t.cpu().numpy().astype(np.float64) for t in (sim.X, sim.G, *((sim.M,) if momentum else ()))]
+
+
+def assert_alike(ra, rb):
+    for u, v in zip(ra, rb):
+        assert np.abs(u - v).max() <= TOL * np.abs(v).max()
+
+
+SHAPES = [  # rows of a thread and what holds them; slices of a node
+    (4, 36, 6, 1, 5, "ring", 2, 0.9, "logreg", 0),        # one row, part of a wavefront
+    (16, 257, 40, 9, 6, "expo1", 4, 0.9, "logreg", 1),    # a ragged last quad of one column
+    (12, 1022, 40, 33, 4, "grid", 3, 0.9, "lsq", 0),      # ... of two
+    (9, 3003, 40, 24, 5, "expo", 4, 0.0, "logreg", 3),    # ... of three; slices that are no power of two
+    (128, 515, 30, 8, 3, "expo", 2, 0.9, "logreg", 0),    # most nodes, eight neighbours
+    (32, 5121, 20, 32, 3, "ring", 0, 0.9, "logreg", 0),   # a column more than the wavefronts of a slice
+    (20, 9999, 24, 40, 3, "expo1", 3, 0.9, "lsq", 0),     # many rows a thread
+    (32, 5120, 20, 50, 3, "ring", 2, 0.9, "logreg", 0),   # the most
+    (8, 1000, 100, 0, 7, "ring", 4, 0.0, "lsq", 0),       # full batches in double precision
+    (30, 1002, 130, 0, 4, "none", 3, 0.9, "lsq", 0),      # full batches in single precision
+    (64, 130, 12, 0, 40, "ring", 16, 0.9, "logreg", 0),   # more than one launch
+    (5, 64, 30, 20, 6, "full", 0, 0.9, "logreg", 0),
+]
+
+
+@pytest.mark.parametrize("given_up", [False, True])
+@pytest.mark.parametrize("n,d,M,batch,T,topology,H,momentum,problem,pad", SHAPES)
+def test_several_iterations_a_launch_match_separate_calls(hx, n, d, M, batch, T, topology, H, momentum, problem, pad, given_up):
+    a, idx_a = make(hx, n, d, M, batch, T, topology, H, momentum, problem, pad, nesterov=n == 16)
+    b, idx_b = make(hx, n, d, M, batch, T, topology, H, momentum, problem, pad, nesterov=n == 16)
+    if given_up:
+        a.set_option("run_wait_us", 0)   # the first wait that is not met at once ends the launch; one workgroup does it again
+    a.run(T, idx_a)
+    assert int(a.query("step_path")) == 12 and a.k == T
+    separate(b, idx_b, T)
+    assert_alike(results(a, momentum), results(b, momentum))
+    for e in (*a._bufs, a.g):
+        assert (e[:, d:].cpu().numpy() == 7.0).all()   # nothing beyond a row's d columns is written
+    assert [t.data_ptr() for t in a._bufs].index(a.X.data_ptr()) == T % 2
+    a.close(), b.close()
+
+
+@pytest.mark.parametrize("given_up", [False, True])
+@pytest.mark.parametrize("n,d,M,batch,T,topology,H,warmup,most", [
+    (16, 512, 64, 8, 60, "expo1", 2, 8, 12), (9, 1203, 33, 0, 41, "expo", 2, 6, 20), (70, 301, 40, 5, 50, "grid", 3, 4, 9)])
+def test_adaptive_period_decided_in_the_launch(hx, n, d, M, batch, T, topology, H, warmup, most, given_up):
+    out = []
+    for fused in (True, False):
+        sim, idx = make(hx, n, d, M, batch, T, topology, 0, 0.9, "lsq" if not batch else "logreg", lr=0.5)
+        sim.aga_enable(H, warmup, most)
+        if given_up:
+            sim.set_option("run_wait_us", 0)
+        if fused:
+            sim.run(T // 2, idx)
+            periods = [sim.period]
+            sim.run(T - T // 2, None if idx is None else idx[T // 2:])
+            assert int(sim.query("step_path")) == 12
+        else:
+            for k in range(T):
+                i = None if idx is None else idx[k]
+                loss = sim.local_loss(i)
+                sim.local_grad(i)
+                sim.aga_step(loss)
+                if k == T // 2 - 1:
+                    periods = [sim.period]
+        out.append((results(sim, 0.9), periods + [sim.period]))
+        sim.close()
+    assert out[0][1] == out[1][1]
+    # sums of losses decide nothing here but the period: the same bound, over more iterations
+    for u, v in zip(out[0][0], out[1][0]):
+        assert np.abs(u - v).max() <= 4 * TOL * np.abs(v).max()
+
+
+def test_rows_outside_the_data_poison_their_node_only(hx):
+    n, d, T = 8, 1001, 3
+    sim, _ = make(hx, n, d, 50, 9, T, "none", 0, 0.9)
+    idx = inputs.batch_indices(T, n, 9, 50, seed=3)
+    idx[0, 0, 0], idx[T - 1, n - 1, 8] = 50, -1
+    sim.run(T, sim.upload_batches(idx))
+    torch.cuda.synchronize()
+    assert int(sim.query("step_path")) == 12
+    nan = torch.isnan(sim.G).cpu().numpy()
+    assert nan[0].all() and nan[7].all() and not nan[1:7].any()
+    sim.close()
+
+
+def test_infinite_features_and_iterates_as_in_separate_calls(hx):
+    n, d, M, T = 6, 331, 12, 3
+    rng = np.random.default_rng(5)
+    feat = (rng.standard_normal((n, M, d)) / np.sqrt(d)).astype(np.float32)
+    feat[1, :, d - 1] = np.inf      # the last column of a ragged width
+    feat[3, 2, 170] = -np.inf
+    out = []
+    for fused in (True, False):
+        sim, idx = make(hx, n, d, M, 5, T, "none", 0, 0.0, feat=feat)
+        x = inputs.random_state(n, d, seed=1)[0]
+        x[4, 7] = np.inf
+        sim.set_state(X=x)
+        if fused:
+            sim.run(T, idx)
+            assert int(sim.query("step_path")) == 12
+        else:
+            separate(sim, idx, T)
+        torch.cuda.synchronize()
+        out.append((sim.X.cpu().numpy(), sim.G.cpu().numpy()))
+        sim.close()
+    for u, v in zip(*out):
+        assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isinf(u), np.isinf(v))
+
+
+def test_two_streams_and_threads(hx):
+    # launches of this kind follow each other across streams; each keeps its own order and results
+    T, rounds = 6, 12
+    sims = []
+    for s in range(2):
+        sim, idx = make(hx, 32, 4000, 40, 16, T, ("ring", "expo1")[s], 4, 0.9, stream=torch.cuda.Stream())
+        ref, ref_idx = make(hx, 32, 4000, 40, 16, T, ("ring", "expo1")[s], 4, 0.9)
+        sims.append((sim, idx, ref, ref_idx))
+    torch.cuda.synchronize()
+
+    def work(sim, idx):
+        for _ in range(rounds):
+            sim.run(T, idx)
+
+    threads = [threading.Thread(target=work, args=s[:2]) for s in sims]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for sim, _, ref, ref_idx in sims:
+        assert int(sim.query("step_path")) == 12
+        ref.set_option("rows_run", 0)
+        for _ in range(rounds):
+            ref.run(T, ref_idx)
+        assert int(ref.query("step_path")) == 9
+        ra, rb = results(sim, 0.9), results(ref, 0.9)
+        for u, v in zip(ra, rb):
+            assert np.abs(u - v).max() <= rounds * TOL * np.abs(v).max()
+        sim.close(), ref.close()
+
+
+def test_a_captured_run_keeps_its_launches_per_iteration(hx):
+    stream = torch.cuda.Stream()
+    sim, idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9, stream=stream)
+    ref, ref_idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
+    with torch.cuda.stream(stream):
+        sim.run(4, idx)                      # sizes the scratch
+        assert int(sim.query("step_path")) == 12
+        sim.set_option("rows_run", 0)
+        sim.run(4, idx)
+        sim.set_option("rows_run", 1)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            sim.run(4, idx)
+        assert int(sim.query("step_path")) == 9
+        for _ in range(3):
+            graph.replay()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        ref.run(4, ref_idx)
+    assert_alike(results(sim, 0.9), results(ref, 0.9))
+    sim.close(), ref.close()
+
+
+def test_options_and_traces_keep_one_iteration_a_launch(hx):
+    sim, idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
+    sim.set_option("rows_run", 0)
+    sim.run(4, idx)
+    assert int(sim.query("step_path")) == 9
+    sim.set_option("rows_run", 1)
+    sim.attach_trace(8)
+    sim.run(4, idx)
+    assert int(sim.query("step_path")) == 9
+    from paper_2105_09080_amd import binding as B
+    for name, value in (("rows_run", 2), ("run_wait_us", -1)):
+        with pytest.raises(B.GpgaError):
+            sim.set_option(name, value)
+    sim.close()
