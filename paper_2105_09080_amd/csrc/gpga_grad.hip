@@ -693,13 +693,17 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
 //    multiply-adds and two lane exchanges within the quad, lane b of the quad evaluates the sigmoid of sample b;
 //  * rows and labels are fetched three iterations ahead, two with several samples a node, and their row numbers as
 //    many again (both lie in HBM: about 1 us away, more than an iteration takes), and the gradient uses the registers the margin used;
+//  * a lane's columns are neighbours in its row and come in one wide load (the last lanes' overlap the one before): the loads
+//    are scattered, some 20 lines each, and a compute unit takes one line a clock.  50 iterations and the five launches of a
+//    loss evaluation (16 us), 100 nodes, us with a load a column -> wide: d = 10, one sample 63.4 -> 63.0, two 82 -> 67, four
+//    133 -> 76; d = 20 75 -> 70, 117 -> 90, 209 -> 109.  Two lanes a node (half the wavefronts, one sigmoid less a SIMD, but
+//    registers for the double) took 66, 74, 93 and 74, 94, 123;
 //  * x^(k+1/2) is exchanged through two LDS arrays in turn, so an iteration has ONE barrier;
 //  * the consensus distance of iteration t is formed by wavefronts of its own while the nodes do iteration
 //    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.
 // Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 50.5 us here
-// (71 us with loads the compiler could not count).  Rows of 13 to 20 columns spill registers, 5 to 16 a lane with
-// one sample of a logistic problem and 25 to 67 with four, and still take a third of k_small_run's time (n = 128, d = 20, four
-// samples 18.9 -> 5.3 us an iteration).
+// (71 us with loads the compiler could not count).  Rows of 13 to 20 columns with four samples spill 10 to 51 registers a lane
+// and still take a seventh of k_small_run's time (n = 128, d = 20 18.9 us an iteration, 2.3 here).
 __device__ __forceinline__ double quad_sum(double v) {
     v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
     v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
@@ -734,14 +738,16 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
     const double inv_n = 1.0 / (double)n;
     const bool sparse = a.topo == GPGA_TOPO_GRID || a.topo == GPGA_TOPO_EXPO || a.topo == GPGA_TOPO_CUSTOM;
 
+    // Columns of a lane: C neighbouring ones from `first` on, one wide load; those that the lane before has too are padding.
+    const int first = l * C + C <= d ? l * C : d - C;
     float x[C], m[C];
-    bool real[C];                                 // columns below d; the padding stays 0
+    bool real[C];                                 // the padding stays 0
     int w0 = 0, w1 = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        real[c] = have && l * C + c < d;
-        x[c] = real[c] ? a.x[(int64_t)i * a.ld + l * C + c] : 0.f;
-        m[c] = MOM && real[c] ? a.m[(int64_t)i * a.ld + l * C + c] : 0.f;
+        real[c] = have && first + c >= l * C;
+        x[c] = real[c] ? a.x[(int64_t)i * a.ld + first + c] : 0.f;
+        m[c] = MOM && real[c] ? a.m[(int64_t)i * a.ld + first + c] : 0.f;
     }
     if (sparse) {
         for (int p = tid; p < a.nnz; p += blockDim.x) {
@@ -764,20 +770,19 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
     };
     Slot slots[kNodeDepth];
     const int in = i < n ? i : n - 1;
-    const float* __restrict__ feat_i = a.feat + (int64_t)in * a.M * d;
+    const char* __restrict__ feat_i = reinterpret_cast<const char*>(a.feat + (int64_t)in * a.M * d + first);
+    const uint32_t row_bytes = 4u * (uint32_t)d;
     const float* __restrict__ tgt_i = a.tgt + (int64_t)in * a.M;
     const int32_t* __restrict__ idx = a.idx ? a.idx : reinterpret_cast<const int32_t*>(a.tgt);  // full batch: not used
-    int cols[C];
+    auto valid = [&](int32_t r) { return (uint32_t)r < (uint32_t)a.M; };
+    const int64_t idx_bytes = a.idx ? 4ll * n * B : 0;
+    uint32_t pick[NB];                            // a lane's offsets in a table of row numbers
 #pragma unroll
-    for (int c = 0; c < C; ++c) cols[c] = l * C + c < d ? l * C + c : d - 1;
-    auto valid = [&](int32_t r) { return r >= 0 && r < a.M; };
+    for (int b = 0; b < NB; ++b) pick[b] = a.idx ? 4u * (uint32_t)(in * B + (b < B ? b : 0)) : 0u;
     auto fetch_rows = [&](Slot& s, int t) {
-        const int tc = t < a.T ? t : a.T - 1;
+        const char* __restrict__ p = reinterpret_cast<const char*>(idx) + (t < a.T ? t : a.T - 1) * idx_bytes;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int bc = b < B ? b : 0;
-            s.rows[b] = idx[a.idx ? ((int64_t)tc * n + in) * B + bc : 0];
-        }
+        for (int b = 0; b < NB; ++b) s.rows[b] = *reinterpret_cast<const int32_t*>(p + pick[b]);
     };
     auto fetch = [&](Slot& s) {
         if (!a.idx) {
@@ -787,12 +792,13 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
         s.r = s.rows[0];
 #pragma unroll
         for (int b = 1; b < NB; ++b) s.r = l == b ? s.rows[b] : s.r;
-        s.y = tgt_i[valid(s.r) ? s.r : 0];
+        s.y = tgt_i[valid(s.r) ? (uint32_t)s.r : 0u];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const float* __restrict__ f = feat_i + (int64_t)(valid(s.rows[b]) ? s.rows[b] : 0) * d;
+            const uint32_t r = valid(s.rows[b]) ? (uint32_t)s.rows[b] : 0u;
+            const float* __restrict__ f = reinterpret_cast<const float*>(feat_i + (uint64_t)r * row_bytes);
 #pragma unroll
-            for (int c = 0; c < C; ++c) s.f[b][c] = f[cols[c]];
+            for (int c = 0; c < C; ++c) s.f[b][c] = f[c];
         }
     };
     if (worker) {
@@ -849,7 +855,7 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
 
     auto column_means = [&](int t) {              // every wavefront takes columns, lanes over rows
         const float* __restrict__ Y = sY + (t & 1) * n * DP;
-        for (int c = wave; c < d; c += nw) {
+        for (int c = wave; c < DP; c += nw) {
             double v = 0.0;
             for (int r = lane; r < n; r += kWave) v += (double)Y[r * DP + c];
             v = group_sum_last(v, kWave);
@@ -860,9 +866,13 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
     float g[C];                                   // gradient of the latest iteration
 #pragma unroll
     for (int c = 0; c < C; ++c) g[c] = 0.f;
+    float lr = a.lr[0];                           // of the coming iteration, read ahead of its use
+    int shift_of = a.shift[0];
     auto iteration = [&](int t, Slot& s) {
-        const float lr = a.lr[t];
-        const int shift = a.shift[t];
+        const int shift = shift_of;
+        const int tn = t + 1 < a.T ? t + 1 : t;
+        float lr_next = a.lr[tn];
+        int shift_next = a.shift[tn];
         float y[C];
         float* __restrict__ Y = sY + (t & 1) * n * DP;
         double z = 0.0;                           // margin of this lane's sample
@@ -871,7 +881,7 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
             double acc = 0.0;
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                // lanes behind the last column repeat it: an infinite one times x = 0 would be no number
+                // padding: an infinite column of another lane times x = 0 would be no number
                 const float f = real[c] ? s.f[b][c] : 0.f;
                 acc += (double)f * (double)x[c];
             }
@@ -880,6 +890,7 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
         }
         float cf = __builtin_nanf(""), ls;        // no valid sample: the node's gradient becomes NaN
         if (valid(s.r)) sample_terms<KIND>(z, s.y, invB, &cf, &ls);
+        asm volatile("" : "+s"(lr_next), "+s"(shift_next));
         const float cb[4] = {quad_bcast<0>(cf), quad_bcast<1>(cf), quad_bcast<2>(cf), quad_bcast<3>(cf)};
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -891,10 +902,15 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
             float mom = g[c];
             if (MOM) m[c] = mom = mu * m[c] + g[c];
             y[c] = MOM == 2 ? x[c] - lr * (g[c] + mu * mom) : x[c] - lr * mom;
-            if (have) Y[i * DP + l * C + c] = y[c];
+        }
+        if (have) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) Y[i * DP + l * C + c] = y[c];
         }
         fetch(s);                                 // for iteration t + kNodeDepth
         fetch_rows(s, t + 2 * kNodeDepth);
+        lr = lr_next;
+        shift_of = shift_next;
         __syncthreads();
         if (shift < 0) column_means(t);
         if (!have) return;
@@ -965,9 +981,9 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         if (real[c]) {
-            a.x_out[(int64_t)i * a.ld + l * C + c] = x[c];
-            a.g[(int64_t)i * a.ld + l * C + c] = g[c];
-            if (MOM) a.m[(int64_t)i * a.ld + l * C + c] = m[c];
+            a.x_out[(int64_t)i * a.ld + first + c] = x[c];
+            a.g[(int64_t)i * a.ld + first + c] = g[c];
+            if (MOM) a.m[(int64_t)i * a.ld + first + c] = m[c];
         }
     }
 }
@@ -1137,7 +1153,11 @@ static hipError_t launch_node_samples(const gpga_ctx* c, const SmallArgs& a) {
 
 template <int KIND, int MOM>
 static hipError_t launch_node_cols(const gpga_ctx* c, const SmallArgs& a) {
-    return node_columns(a.d) == 3 ? launch_node_samples<KIND, MOM, 3>(c, a) : launch_node_samples<KIND, MOM, 5>(c, a);
+    switch (node_columns(a.d)) {
+        case 1: return launch_node_samples<KIND, MOM, 1>(c, a);
+        case 3: return launch_node_samples<KIND, MOM, 3>(c, a);
+        default: return launch_node_samples<KIND, MOM, 5>(c, a);
+    }
 }
 
 template <int KIND>

@@ -103,6 +103,16 @@ def test_an_infinite_last_feature_reaches_its_own_column_only(hx, d, problem):
         assert np.array_equal(u, v, equal_nan=True) or np.allclose(u, v, rtol=TOL, atol=TOL * np.abs(v[np.isfinite(v)]).max(), equal_nan=True)
 
 
+@pytest.mark.parametrize("d", [2, 4, 6, 8, 11, 14, 16, 17, 19])   # lanes whose columns overlap the lane before by none, some, all
+@pytest.mark.parametrize("B,topology", [(1, "ring"), (2, "full"), (3, "expo1")])
+def test_rows_that_the_lanes_columns_do_not_divide(hx, d, B, topology):
+    a = run(hx, 20, d, B, 5, topology, 0.9, False, "logreg", 1)
+    b = run(hx, 20, d, B, 5, topology, 0.9, False, "logreg", 0)
+    for u, v in zip(a, b):
+        scale = np.abs(v).max() if v is not b[2] else np.linalg.norm(b[0])
+        assert np.abs(u - v).max() <= TOL * max(scale, 1e-30)
+
+
 @pytest.mark.parametrize("d", [7, 20, 21])   # 21 columns: the general single-workgroup kernel
 def test_the_trace_of_a_state_that_is_not_a_number_is_not_zero(hx, d):
     # rows outside the data at iteration 2 make two nodes NaN; it ends in a global average (H = 3), whose entry is 0
