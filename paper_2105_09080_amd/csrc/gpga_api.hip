@@ -266,11 +266,14 @@ gpga_status gpga_create(gpga_ctx** out, int32_t n, int64_t d, int32_t topology, 
         return GPGA_ENOMEM;
     }
     c->partials_cap = need;
-    if (hipMalloc(reinterpret_cast<void**>(&c->pace_states), kPaceKeys * sizeof(PaceState)) == hipSuccess) {
-        (void)hipMemset(c->pace_states, 0, kPaceKeys * sizeof(PaceState));
+    // pacing states, and behind them the counters of the loss kernel (more nodes than these have no losses)
+    const size_t states = kPaceKeys * sizeof(PaceState), left = sizeof(uint32_t) * kLossLeftStride * (size_t)(n < 65535 ? n : 65535);
+    if (hipMalloc(reinterpret_cast<void**>(&c->pace_states), states + left) == hipSuccess) {
+        (void)hipMemset(c->pace_states, 0, states + left);
         (void)hipDeviceSynchronize();
+        c->loss_left = reinterpret_cast<uint32_t*>(c->pace_states + kPaceKeys);
     } else {
-        c->pace_states = nullptr;  // launches simply run unpaced
+        c->pace_states = nullptr;  // launches simply run unpaced, sums of losses in launches of their own
     }
     {   // set-up of gpga_consensus_error_static on this device, so that its calls find the address ready
         double* static_ptr = nullptr;

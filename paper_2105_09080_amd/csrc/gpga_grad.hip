@@ -226,45 +226,86 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float* __restrict__ loss
 }
 
 // Losses alone on short rows (d <= 32): one thread per sample, the 256 rows of a workgroup staged through LDS with
-// coalesced loads when they are consecutive (full batch), one fp64 partial sum per workgroup; k_loss_chunks adds
-// them.  Bound: reading the rows and two double-precision transcendentals a sample.  n = 100, M = 8000, d = 10 (35 MB):
-// 12.0 + 4.6 us, where a coefficient and a loss term stored per sample and summed by one workgroup a node took
-// 18.3 + 9.7; with room for the widest rows in every workgroup (32 KiB instead of 10) the first kernel takes 22.
-template <int KIND>
+// coalesced loads when they are consecutive (full batch) and read back V columns at a time, x as doubles; one fp64
+// partial sum per workgroup, and the node's last workgroup to end adds them in their order (many workgroups: k_loss_chunks).
+// Bound: reading the rows, and an exponential and a logarithm in fp64 a sample.  Us, two launches and a column at a time
+// -> this form: 100 x 8000 x 10 13.3 -> 13.1, 20 x 8000 x 10 7.1 -> 5.6, 100 x 4000 x 16 14.1 -> 8.8, 64 x 2000 x 20 8.1 -> 5.5, 50 x
+// 4000 x 32 23.4 -> 9.5 (rows of 32 columns: every lane on the same LDS bank), 10 x 200 x 10 6.0 -> 3.9.  Workgroups of several
+// times 256 rows, the next ones loaded ahead, took 13.3 - 16 on the first.
+template <int KIND, int V>
 __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict__ feat, const float* __restrict__ tgt,
                                                          const float* __restrict__ x, int64_t ld,
                                                          const int32_t* __restrict__ idx, int32_t B, int32_t M,
-                                                         int32_t d, double* __restrict__ partials) {
+                                                         int32_t d, int cached, double* __restrict__ partials,
+                                                         uint32_t* __restrict__ left, float* __restrict__ loss) {
     extern __shared__ __align__(16) unsigned char s_raw[];  // 256 rows (full batch)
     float* __restrict__ s_rows = reinterpret_cast<float*>(s_raw);
+    __shared__ __align__(16) double s_x[32];
     __shared__ double s_buf[4];
+    __shared__ int s_last;
     const int64_t i = blockIdx.y;
     const int32_t b0 = blockIdx.x * 256, b = b0 + (int32_t)threadIdx.x;
-    const float* __restrict__ xi = x + i * ld;
     const int32_t r = idx ? (b < B ? idx[i * B + b] : 0) : b;
     const bool ok = b < B && r >= 0 && r < M;
     const float target = ok ? tgt[i * M + r] : 0.f;
+    if ((int32_t)threadIdx.x < d) s_x[threadIdx.x] = (double)x[i * ld + threadIdx.x];
     if (!idx) {
         const float* __restrict__ rows = feat + (i * M + b0) * d;
         const int32_t count = (B - b0 < 256 ? B - b0 : 256) * d;
-        for (int32_t e = threadIdx.x * 4; e + 4 <= count; e += 1024)
-            *reinterpret_cast<v4f*>(s_rows + e) = ld_unit<v4f>(rows + e);
+        if (cached) {
+            for (int32_t e = threadIdx.x * 4; e + 4 <= count; e += 1024)
+                *reinterpret_cast<v4f*>(s_rows + e) = ld_unit_cached<v4f>(rows + e);
+        } else {
+            for (int32_t e = threadIdx.x * 4; e + 4 <= count; e += 1024)
+                *reinterpret_cast<v4f*>(s_rows + e) = ld_unit<v4f>(rows + e);
+        }
         for (int32_t e = (count & ~3) + (int32_t)threadIdx.x; e < count; e += 256) s_rows[e] = rows[e];
-        __syncthreads();
     }
+    __syncthreads();
     double term = 0.0;
     if (ok) {
-        const float* __restrict__ f = idx ? feat + (i * M + r) * d : s_rows + threadIdx.x * d;
         double z = 0.0;
-        for (int c = 0; c < d; ++c) z += (double)f[c] * xi[c];
-        float cf, ls;
-        sample_terms<KIND>(z, target, 1.0f / (float)B, &cf, &ls);
-        term = ls;
+        if (idx) {
+            const float* __restrict__ f = feat + (i * M + r) * d;
+            for (int c = 0; c < d; ++c) z += (double)f[c] * s_x[c];
+        } else {
+            typedef float vec __attribute__((ext_vector_type(V)));
+            const float* __restrict__ f = s_rows + threadIdx.x * d;
+            for (int c = 0; c < d; c += V) {
+                const vec v = *reinterpret_cast<const vec*>(f + c);
+#pragma unroll
+                for (int u = 0; u < V; ++u) z += (double)v[u] * s_x[c + u];
+            }
+        }
+        term = sample_loss<KIND>(z, target, 1.0f / (float)B);
     } else if (b < B) {
         term = __builtin_nan("");  // a sample index outside [0, M): no access, the node's loss becomes NaN
     }
     const double t = block_sum(term, s_buf);
-    if (threadIdx.x == 0) partials[i * gridDim.x + blockIdx.x] = t;
+    if (threadIdx.x == 0) {
+        s_last = 0;
+        if (gridDim.x == 1) {
+            loss[i] = (float)t;
+        } else if (!left) {
+            partials[i * gridDim.x + blockIdx.x] = t;  // for k_loss_chunks
+        } else {
+            // The sum past the caches that are not shared, waited for, and only then the count: a release would write back the
+            // whole L2, once a workgroup (44 us instead of 11 at 100 x 8000 x 10).
+            __hip_atomic_store(partials + i * gridDim.x + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+            s_last = __hip_atomic_fetch_add(left + i * kLossLeftStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        }
+    }
+    __syncthreads();
+    if (!s_last || threadIdx.x >= kWave) return;
+    double v = 0.0;
+    for (uint32_t ch = threadIdx.x; ch < gridDim.x; ch += kWave)
+        v += __hip_atomic_load(partials + i * gridDim.x + ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = wave_sum(v);
+    if (threadIdx.x == 0) {
+        loss[i] = (float)v;
+        left[i * kLossLeftStride] = 0;  // for the next launch
+    }
 }
 
 __global__ void __launch_bounds__(kWave) k_loss_chunks(const double* __restrict__ partials, int32_t chunks,
@@ -1044,19 +1085,35 @@ hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, 
     return hipGetLastError();
 }
 
-static hipError_t launch_rows_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
+// Data that the L2s hold is read through them (100 x 8000 x 10, 32 MB, 13.3 us, past them 13.8; 64 x 2000 x 20 6.7 / 8.4; 120 x
+// 8000 x 20, 77 MB, 23.0 / 22.2).
+constexpr int64_t kLossCachedBytes = 32 << 20;
+// The sums of a node's workgroups ride along (a launch less, 3 us) while their counts on one word, some 15 ns each, take less
+// time, and while most workgroups are resident at once, since each stays until its sum has arrived (us along / apart: 235
+// workgroups a node, 8 x 60 000 x 30 21.9 / 19.6; 7560 in all, 120 x 16 000 x 10 26.9 / 24.5; 3840, 120 x 8000 x 20 21.4 / 22.0).
+constexpr unsigned kLossLastMost = 64;
+template <int V>
+static void launch_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
     // the partial sums (one double per 256 samples) take the place of the per-sample terms
     double* partials = reinterpret_cast<double*>(c->coef);
     const dim3 grid((unsigned)((Beff + 255) / 256), (unsigned)c->n), block(256);
     const size_t lds = idx ? 0 : (size_t)256 * c->d * sizeof(float);
+    const int cached = (int64_t)c->n * c->M * c->d * 4 <= kLossCachedBytes;
+    uint32_t* const left = grid.x <= kLossLastMost && (int64_t)grid.x * grid.y <= 16 * c->num_cus ? c->loss_left : nullptr;
     if (c->problem == PROB_LSQ) {
-        hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx,
-                           Beff, c->M, (int32_t)c->d, partials);
+        hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ, V>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx,
+                           Beff, c->M, (int32_t)c->d, cached, partials, left, loss_out);
     } else {
-        hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld,
-                           idx, Beff, c->M, (int32_t)c->d, partials);
+        hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG, V>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld,
+                           idx, Beff, c->M, (int32_t)c->d, cached, partials, left, loss_out);
     }
-    hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials, (int32_t)grid.x, loss_out);
+    if (!left && grid.x > 1)
+        hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials, (int32_t)grid.x, loss_out);
+}
+static hipError_t launch_rows_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
+    if (c->d % 4 == 0) launch_loss_short<4>(c, idx, Beff, loss_out);
+    else if (c->d % 2 == 0) launch_loss_short<2>(c, idx, Beff, loss_out);
+    else launch_loss_short<1>(c, idx, Beff, loss_out);
     return hipGetLastError();
 }
 

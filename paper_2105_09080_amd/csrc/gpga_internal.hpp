@@ -77,6 +77,8 @@ enum StepPath : int { PATH_NONE = 0, PATH_WALK = 1, PATH_CYCLES = 2, PATH_GLOBAL
                       PATH_TWO_PASS = 6, PATH_SMALL_RUN = 7, PATH_COLUMN_RUN = 8, PATH_ROWS_STEP = 9,
                       PATH_CIRCULANT = 10, PATH_VIRTUAL_STEP = 11, PATH_ROWS_RUN = 12 };
 
+constexpr int kLossLeftStride = 32;  // counters of gpga_ctx::loss_left, a line each
+
 struct gpga_ctx {
     void note_path(int path, int lane_bytes) const {
         if (last_path == PATH_NONE) {
@@ -125,6 +127,7 @@ struct gpga_ctx {
     double* partials = nullptr;
     size_t partials_cap = 0;  // in doubles
     double* host_scalar = nullptr;  // pinned, 1 double
+    uint32_t* loss_left = nullptr;       // k_rows_loss_short: workgroups of a node that have ended, 0 between launches; not its own allocation
     unsigned char* run_space = nullptr;  // what the workgroups of k_rows_run exchange
     size_t run_space_cap = 0;            // in bytes
     uint32_t run_number = 0;             // of the last such launch, 0: run_space is not cleared yet
