@@ -741,7 +741,9 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
 //    registers for the double) took 66, 74, 93 and 74, 94, 123;
 //  * x^(k+1/2) is exchanged through two LDS arrays in turn, so an iteration has ONE barrier;
 //  * the consensus distance of iteration t is formed by wavefronts of its own while the nodes do iteration
-//    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.
+//    t + 1: shifted sums per column (row 0 is the shift), then the columns one iteration later.  They share the SIMDs with the
+//    nodes, so their reads go ahead four rows at a time and rows of lanes are added by exchanges of registers (one row at a
+//    time and through LDS 100 x 10 63.4 -> 56.2 us, 64 x 20 65.3 -> 54.9; one, two or all rows by a runtime count 58 - 66).
 // Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 50.5 us here
 // (71 us with loads the compiler could not count).  Rows of 13 to 20 columns with four samples spill 10 to 51 registers a lane
 // and still take a seventh of k_small_run's time (n = 128, d = 20 18.9 us an iteration, 2.3 here).
@@ -755,11 +757,11 @@ __device__ __forceinline__ float quad_bcast(float v) {  // the value of lane B o
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), B * 0x55, 0xf, 0xf, true));
 }
 
-template <int KIND, int MOM, int C, int NB>
+template <int KIND, int MOM, int C, int NB, int TW>
 __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trace_waves(NB)) k_node_run(const SmallArgs a) {
     constexpr int DP = kNodeLanes * C;            // padded row
     constexpr int LG = DP <= 16 ? 16 : 32;        // lanes over columns in the trace wavefronts
-    constexpr int kNodeTraceWaves = node_trace_waves(NB);
+    constexpr int kNodeTraceWaves = TW;
     constexpr int kNodeDepth = NB == 1 ? 3 : 2;   // iterations the samples are fetched ahead
     extern __shared__ __align__(16) unsigned char s_raw[];
     const int n = a.n, d = a.d, B = a.B;
@@ -860,22 +862,25 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
         if (c < DP) {
             const float* __restrict__ X = sX + (t & 1) * n * DP + c;
             const double ref = X[0];
-            for (int r = group; r < (average ? 0 : n); r += kNodeTraceWaves * (kWave / LG)) {
-                const double v = (double)X[r * DP] - ref;
-                s1 += v;
-                s2 += v * v;
+            constexpr int step = kNodeTraceWaves * (kWave / LG);
+            for (int r = group; r < (average ? 0 : n); r += kNodeTraceRows * step) {
+                float v[kNodeTraceRows];
+#pragma unroll
+                for (int u = 0; u < kNodeTraceRows; ++u) v[u] = X[(r + u * step < n ? r + u * step : 0) * DP];  // row 0 adds nothing
+#pragma unroll
+                for (int u = 0; u < kNodeTraceRows; ++u) {
+                    const double dv = (double)v[u] - ref;
+                    s1 += dv;
+                    s2 += dv * dv;
+                }
             }
         }
-#pragma unroll
-        for (int o = LG; o < kWave; o <<= 1) {
-            s1 += __shfl_xor(s1, o, kWave);
-            s2 += __shfl_xor(s2, o, kWave);
+        if (LG == 16) {
+            s1 = swap_add(s1, s1, false);
+            s2 = swap_add(s2, s2, false);
         }
-        if (lane < DP) {
-            double* __restrict__ p = sP + ((t & 1) * kNodeTraceWaves + tw) * 2 * DP + lane;
-            p[0] = s1;
-            p[DP] = s2;
-        }
+        s1 = swap_add(s1, s2, true);
+        if ((lane & 31) < DP) sP[((t & 1) * kNodeTraceWaves + tw) * 2 * DP + (lane >> 5) * DP + (lane & 31)] = s1;
     };
     auto trace_entry = [&](int t) {
         double ss = 0.0;
@@ -1189,22 +1194,26 @@ bool small_run_fits(const gpga_ctx* c, const int32_t* idx, int32_t B) {
     return small_run_lds(c, (int32_t)Beff) <= 100 * 1024 && small_run_lds(c, (int32_t)Beff) <= (size_t)c->max_lds_block;
 }
 
-template <int KIND, int MOM, int C, int NB>
+template <int KIND, int MOM, int C, int NB, int TW>
 static hipError_t launch_node(const gpga_ctx* c, SmallArgs a) {
     a.worker_waves = (a.n * kNodeLanes + kWave - 1) / kWave;
-    const int threads = kWave * (a.worker_waves + (a.trace ? node_trace_waves(NB) : 0));
+    const int threads = kWave * (a.worker_waves + (a.trace ? TW : 0));
     const size_t lds = node_run_lds(a.n, C, NB, a.nnz);
     if (lds > kNodeMaxLds) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_node_run<KIND, MOM, C, NB>), dim3(1), dim3(threads), lds, c->stream, a);
+    hipLaunchKernelGGL((k_node_run<KIND, MOM, C, NB, TW>), dim3(1), dim3(threads), lds, c->stream, a);
     return hipGetLastError();
 }
 
 template <int KIND, int MOM, int C>
 static hipError_t launch_node_samples(const gpga_ctx* c, const SmallArgs& a) {
     switch (node_samples(a.B)) {
-        case 1: return launch_node<KIND, MOM, C, 1>(c, a);
-        case 2: return launch_node<KIND, MOM, C, 2>(c, a);
-        default: return launch_node<KIND, MOM, C, kNodeSamples>(c, a);
+        case 1:
+            // Four wavefronts where they have all rows at once, eight where they would need a second batch (us a pass with the
+            // trace, four / eight: 20 x 10 43.7 / 47.1, 64 x 10 51.0 / 54.5, 100 x 10 58.1 / 56.2, 64 x 20 59.2 / 54.9).
+            return a.n <= 4 * kNodeTraceRows * (kNodeLanes * C <= 16 ? 4 : 2) ? launch_node<KIND, MOM, C, 1, 4>(c, a)
+                                                                            : launch_node<KIND, MOM, C, 1, node_trace_waves(1)>(c, a);
+        case 2: return launch_node<KIND, MOM, C, 2, node_trace_waves(2)>(c, a);
+        default: return launch_node<KIND, MOM, C, kNodeSamples, node_trace_waves(kNodeSamples)>(c, a);
     }
 }
 

@@ -8,7 +8,8 @@ constexpr int kNodeLanes = 4, kNodeSamples = 4, kNodeMaxNodes = 128, kNodeMaxCol
 constexpr int64_t kNodeMaxEntries = 20 * kNodeMaxNodes;  // of W
 constexpr size_t kNodeMaxLds = 64 * 1024;                // what a launch may have unless the kernel's attribute says otherwise
 
-constexpr int node_trace_waves(int samples) { return samples == 1 ? 8 : 4; }  // fewer leave the registers that several samples take
+constexpr int node_trace_waves(int samples) { return samples == 1 ? 8 : 4; }  // at most; fewer leave the registers that several samples take
+constexpr int kNodeTraceRows = 4;                                                // of a lane read at a time
 constexpr int node_columns(int64_t d) { return d <= 4 ? 1 : d <= 12 ? 3 : 5; }  // of a lane; never more than d
 constexpr int node_samples(int B) { return B <= 2 ? B : kNodeSamples; }       // rows a node's lanes hold
 

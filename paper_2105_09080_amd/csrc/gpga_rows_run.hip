@@ -77,18 +77,6 @@ struct RowsRunArgs {
 constexpr int kRunSparse = 8, kRunMean = 9;
 
 // Sums over the 64 lanes of four values; the lanes 15, 31, 47 and 63 hold those of v0, v2, v1 and v3.
-__device__ __forceinline__ double swap_add(double a, double b, bool halves) {
-    const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
-    uint32_t a0 = (uint32_t)ua, a1 = (uint32_t)(ua >> 32), b0 = (uint32_t)ub, b1 = (uint32_t)(ub >> 32);
-    if (halves) {
-        const auto lo = __builtin_amdgcn_permlane32_swap(a0, b0, false, false), hi = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-        a0 = lo[0], b0 = lo[1], a1 = hi[0], b1 = hi[1];
-    } else {
-        const auto lo = __builtin_amdgcn_permlane16_swap(a0, b0, false, false), hi = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
-        a0 = lo[0], b0 = lo[1], a1 = hi[0], b1 = hi[1];
-    }
-    return __longlong_as_double((long long)(((uint64_t)a1 << 32) | a0)) + __longlong_as_double((long long)(((uint64_t)b1 << 32) | b0));
-}
 __device__ __forceinline__ double four_sums(double v0, double v1, double v2, double v3) {
     return row16_sum_last(swap_add(swap_add(v0, v1, true), swap_add(v2, v3, true), false));
 }

@@ -27,6 +27,20 @@ __device__ __forceinline__ double row16_sum_last(double v) {
     v += dpp_f64<0x118>(v);  // row_shr:8
     return v;
 }
+// Halves (rows of 16 otherwise) exchanged between two values and added: with halves, lanes 0 to 31 hold a[l] + a[l + 32] and
+// the others b[l - 32] + b[l]; without, rows 0 and 2 the sums of a's rows 0, 1 and 2, 3, rows 1 and 3 those of b's.
+__device__ __forceinline__ double swap_add(double a, double b, bool halves) {
+    const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+    uint32_t a0 = (uint32_t)ua, a1 = (uint32_t)(ua >> 32), b0 = (uint32_t)ub, b1 = (uint32_t)(ub >> 32);
+    if (halves) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(a0, b0, false, false), hi = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+        a0 = lo[0], b0 = lo[1], a1 = hi[0], b1 = hi[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(a0, b0, false, false), hi = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+        a0 = lo[0], b0 = lo[1], a1 = hi[0], b1 = hi[1];
+    }
+    return __longlong_as_double((long long)(((uint64_t)a1 << 32) | a0)) + __longlong_as_double((long long)(((uint64_t)b1 << 32) | b0));
+}
 // Per-sample coefficient and loss term from the margin z.
 //   least squares: r = z - b          coef = r / B           loss = r^2 / (2B)
 //   logistic     : t = y z            coef = -y s(-t) / B    loss = ln(1 + e^{-t}) / B

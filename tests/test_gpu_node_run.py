@@ -113,6 +113,13 @@ def test_rows_that_the_lanes_columns_do_not_divide(hx, d, B, topology):
         assert np.abs(u - v).max() <= TOL * max(scale, 1e-30)
 
 
+@pytest.mark.parametrize("n,d", [(1, 3), (15, 4), (16, 10), (17, 16), (32, 20), (33, 13), (63, 12), (64, 4), (65, 10), (128, 12), (128, 20)])
+def test_the_trace_on_every_number_of_row_batches(hx, n, d):
+    a = run(hx, n, d, 1, 7, "ring", 0.0, False, "logreg", 1)
+    b = run(hx, n, d, 1, 7, "ring", 0.0, False, "logreg", 0)
+    assert np.abs(a[2] - b[2]).max() <= TOL * np.linalg.norm(b[0]) and np.abs(a[0] - b[0]).max() <= TOL * np.abs(b[0]).max()
+
+
 @pytest.mark.parametrize("d", [7, 20, 21])   # 21 columns: the general single-workgroup kernel
 def test_the_trace_of_a_state_that_is_not_a_number_is_not_zero(hx, d):
     # rows outside the data at iteration 2 make two nodes NaN; it ends in a global average (H = 3), whose entry is 0
