@@ -226,11 +226,12 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float* __restrict__ loss
 }
 
 // Losses alone on short rows (d <= 32): one thread per sample, the 256 rows of a workgroup staged through LDS with
-// coalesced loads when they are consecutive (full batch) and read back V columns at a time, x as doubles; one fp64
-// partial sum per workgroup, and the node's last workgroup to end adds them in their order (many workgroups: k_loss_chunks).
+// coalesced loads when they are consecutive (full batch) and read back V columns at a time; one fp64 partial sum per
+// workgroup, and the node's last workgroup to end adds them in their order (many workgroups: k_loss_chunks).
 // Bound: reading the rows, and an exponential and a logarithm in fp64 a sample.  Us, two launches and a column at a time
-// -> this form: 100 x 8000 x 10 13.3 -> 13.1, 20 x 8000 x 10 7.1 -> 5.6, 100 x 4000 x 16 14.1 -> 8.8, 64 x 2000 x 20 8.1 -> 5.5, 50 x
-// 4000 x 32 23.4 -> 9.5 (rows of 32 columns: every lane on the same LDS bank), 10 x 200 x 10 6.0 -> 3.9.  Workgroups of several
+// -> this form: 100 x 8000 x 10 13.5 -> 13.0, 20 x 8000 x 10 7.2 -> 5.6, 100 x 4000 x 16 14.1 -> 8.7, 64 x 2000 x 20 8.2 -> 5.6, 50 x
+// 4000 x 32 23.4 -> 8.8 (rows of 32 columns: every lane on the same LDS bank), 10 x 200 x 10 6.3 -> 3.9, 120 x 16 000 x 10 23.6 both
+// (26.8 with x in LDS too).  Workgroups of several
 // times 256 rows, the next ones loaded ahead, took 13.3 - 16 on the first.
 template <int KIND, int V>
 __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict__ feat, const float* __restrict__ tgt,
@@ -240,7 +241,6 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
                                                          uint32_t* __restrict__ left, float* __restrict__ loss) {
     extern __shared__ __align__(16) unsigned char s_raw[];  // 256 rows (full batch)
     float* __restrict__ s_rows = reinterpret_cast<float*>(s_raw);
-    __shared__ __align__(16) double s_x[32];
     __shared__ double s_buf[4];
     __shared__ int s_last;
     const int64_t i = blockIdx.y;
@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
     const int32_t r = idx ? (b < B ? idx[i * B + b] : 0) : b;
     const bool ok = b < B && r >= 0 && r < M;
     const float target = ok ? tgt[i * M + r] : 0.f;
-    if ((int32_t)threadIdx.x < d) s_x[threadIdx.x] = (double)x[i * ld + threadIdx.x];
+    const float* __restrict__ xi = x + i * ld;
     if (!idx) {
         const float* __restrict__ rows = feat + (i * M + b0) * d;
         const int32_t count = (B - b0 < 256 ? B - b0 : 256) * d;
@@ -260,21 +260,21 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
                 *reinterpret_cast<v4f*>(s_rows + e) = ld_unit<v4f>(rows + e);
         }
         for (int32_t e = (count & ~3) + (int32_t)threadIdx.x; e < count; e += 256) s_rows[e] = rows[e];
+        __syncthreads();
     }
-    __syncthreads();
     double term = 0.0;
     if (ok) {
         double z = 0.0;
         if (idx) {
             const float* __restrict__ f = feat + (i * M + r) * d;
-            for (int c = 0; c < d; ++c) z += (double)f[c] * s_x[c];
+            for (int c = 0; c < d; ++c) z += (double)f[c] * xi[c];
         } else {
             typedef float vec __attribute__((ext_vector_type(V)));
             const float* __restrict__ f = s_rows + threadIdx.x * d;
             for (int c = 0; c < d; c += V) {
                 const vec v = *reinterpret_cast<const vec*>(f + c);
 #pragma unroll
-                for (int u = 0; u < V; ++u) z += (double)v[u] * s_x[c + u];
+                for (int u = 0; u < V; ++u) z += (double)v[u] * xi[c + u];
             }
         }
         term = sample_loss<KIND>(z, target, 1.0f / (float)B);
@@ -282,19 +282,19 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
         term = __builtin_nan("");  // a sample index outside [0, M): no access, the node's loss becomes NaN
     }
     const double t = block_sum(term, s_buf);
-    if (threadIdx.x == 0) {
-        s_last = 0;
-        if (gridDim.x == 1) {
-            loss[i] = (float)t;
-        } else if (!left) {
-            partials[i * gridDim.x + blockIdx.x] = t;  // for k_loss_chunks
-        } else {
-            // The sum past the caches that are not shared, waited for, and only then the count: a release would write back the
-            // whole L2, once a workgroup (44 us instead of 11 at 100 x 8000 x 10).
-            __hip_atomic_store(partials + i * gridDim.x + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-            s_last = __hip_atomic_fetch_add(left + i * kLossLeftStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    if (gridDim.x == 1 || !left) {
+        if (threadIdx.x == 0) {
+            if (gridDim.x == 1) loss[i] = (float)t;
+            else partials[i * gridDim.x + blockIdx.x] = t;  // for k_loss_chunks
         }
+        return;
+    }
+    if (threadIdx.x == 0) {
+        // The sum past the caches that are not shared, waited for, and only then the count: a release would write back the
+        // whole L2, once a workgroup (44 us instead of 11 at 100 x 8000 x 10).
+        __hip_atomic_store(partials + i * gridDim.x + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        s_last = __hip_atomic_fetch_add(left + i * kLossLeftStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();
     if (!s_last || threadIdx.x >= kWave) return;
@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
     v = wave_sum(v);
     if (threadIdx.x == 0) {
         loss[i] = (float)v;
-        left[i * kLossLeftStride] = 0;  // for the next launch
+        __hip_atomic_store(left + i * kLossLeftStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
     }
 }
 
@@ -1095,7 +1095,7 @@ hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, 
 constexpr int64_t kLossCachedBytes = 32 << 20;
 // The sums of a node's workgroups ride along (a launch less, 3 us) while their counts on one word, some 15 ns each, take less
 // time, and while most workgroups are resident at once, since each stays until its sum has arrived (us along / apart: 235
-// workgroups a node, 8 x 60 000 x 30 21.9 / 19.6; 7560 in all, 120 x 16 000 x 10 26.9 / 24.5; 3840, 120 x 8000 x 20 21.4 / 22.0).
+// workgroups a node, 8 x 60 000 x 30 21.9 / 19.6; 3840, 120 x 8000 x 20 21.4 / 22.0).
 constexpr unsigned kLossLastMost = 64;
 template <int V>
 static void launch_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
