@@ -19,6 +19,7 @@
 #include "gpga_node_run.hpp"
 #include "gpga_pace.hpp"
 #include "gpga_rows_deal.hpp"
+#include "gpga_rows_run.hpp"
 #include "gpga_schedule.hpp"
 
 namespace {
@@ -341,6 +342,32 @@ void node_run_sizes() {
     std::printf("node_run taken %" PRId64 " most_lds %zu\n", taken, most);
 }
 
+// The arrays of a trajectory on stored features in LDS: in bounds, in order, and on the boundaries that their accesses need.
+void rows_run_lds() {
+    int64_t plans = 0;
+    int most = 0;
+    for (int n : {4, 5, 6, 7, 8, 9, 16, 20, 31, 32, 64, 70, 100, 128})
+        for (int64_t d : {32, 33, 200, 257, 301, 331, 512, 1000, 1001, 2048, 3003, 5121, 9999, 25000, 163840})
+            for (int B : {1, 2, 3, 5, 8, 9, 15, 16, 21, 32, 33, 50, 99, 100, 255, 320})
+                for (bool batches : {false, true}) {
+                    const RunPlan p = plan_run(n, d, 256, B, batches);
+                    if (!p.P) continue;
+                    ++plans;
+                    expect((int64_t)n * p.P <= 256 && (int64_t)4 * p.w * p.P >= d && p.w <= kWave * p.QW && p.QW * p.RG <= kRowWaves, "sharing of a trajectory");
+                    const int slots = slots_for(p.slots, !batches), staged = batches ? std::max(2048 / B, 3) * B : B;
+                    expect(slots >= p.slots && slots * p.RG >= B, "rows of a trajectory fit their slots");
+                    for (int K : {0, 1, 5, 64}) {
+                        const RunLds l(n, B, p.w, p.QW, p.RG, slots, staged, K);
+                        expect(l.z % 8 == 0 && l.sum % 8 == 0, "margins of a trajectory lie on 8 bytes");
+                        expect(l.x % 16 == 0 && l.m % 16 == 0, "columns of a trajectory lie on 16 bytes");
+                        expect(l.x >= l.sum + 8 * B && l.val + 4 * K == l.bytes, "arrays of a trajectory do not overlap");
+                        most = std::max(most, l.bytes);
+                    }
+                }
+    expect(most <= 129 * 1024, "LDS of a trajectory");
+    std::printf("rows_run plans %" PRId64 " most_lds %d\n", plans, most);
+}
+
 // The exchange buffers of k_column_run.  What wavefronts do between two barriers is in no order, so a buffer must not be read by
 // one iteration and written by another there.  Returns how often that happens in T iterations with an average in every
 // H-th; `buffer(t, exchanges before)` and `writes(t)` are the rule.
@@ -438,6 +465,7 @@ int main() {
     circulant_matrices();
     node_run_sizes();
     rows_deal();
+    rows_run_lds();
     named_graphs();
     rejected_matrices();
     schedules();

@@ -22,18 +22,13 @@
 #include "gpga_gang.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_order.hpp"
+#include "gpga_rows_run.hpp"
 #include "gpga_samples.hpp"
 #include "gpga_schedule.hpp"
 #include "gpga_unit.hpp"
 
 namespace {
 
-constexpr int kRowsRunWaves = 12;                    // of a workgroup: three a SIMD, 168 registers each
-constexpr int kRowsRunThreads = kRowsRunWaves * kWave;
-constexpr int kRowWaves = 10;                        // those that may hold rows; the others exchange
-constexpr int kFixedSlots = 12;                      // ... in double precision: four conversions a row and use cost as much as the sums
-constexpr int kAheadSlots = 20;                      // ... with registers for half of the next iteration's rows besides
-constexpr int kRowsRunMaxSlots = 32;                 // rows a thread holds
 constexpr int kRowsRunFewest = 3;                    // iterations that are worth a launch of this kind
 constexpr int64_t kRowsRunStaged = 2048;             // (iteration, sample) pairs whose row numbers and targets go to LDS first
 constexpr int64_t kRowsRunMaxWords = 8ll << 20;      // of x^(k+1/2) a launch may exchange (64 MiB)
@@ -180,18 +175,19 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
     const int n = a.n, B = a.B, P = a.P, RG = a.RG, nthr = a.threads;
     const int wcols = 4 * a.w, held = 4 * kWave * a.QW;  // columns of a slice; of its lanes
     const int share = (wcols + n - 1) / n;               // columns whose mean this workgroup forms
-    double* __restrict__ sAcc = reinterpret_cast<double*>(s_raw);                 // [RG][held]
-    double* __restrict__ sZ = sAcc + RG * held;                                   // [QW][B]
-    double* __restrict__ sSum = sZ + a.QW * B;                                    // [B] whole margins
-    float* __restrict__ sX = reinterpret_cast<float*>(sSum + B);                  // [held]
-    float* __restrict__ sM = sX + held;                                           // [held]
-    float* __restrict__ sY = sM + held;                                           // [n][share]
-    float* __restrict__ sCoef = sY + n * share;                                   // [RG S], zeros behind B
-    float* __restrict__ sTgt = sCoef + RG * S;                                    // [staged]
     const int staged = HELD != ROWS_FIXED ? a.T * B : B;
-    int32_t* __restrict__ sRow = reinterpret_cast<int32_t*>(sTgt + staged);                    // [staged]
-    int32_t* __restrict__ sOff = sRow + staged;                                   // [K] this node's entries of a sparse W
-    float* __restrict__ sVal = reinterpret_cast<float*>(sOff + (a.mode == kRunSparse ? a.K : 0));
+    const RunLds lds(n, B, a.w, a.QW, RG, S, staged, a.mode == kRunSparse ? a.K : 0);
+    double* __restrict__ sAcc = reinterpret_cast<double*>(s_raw);                 // [RG][held]
+    double* __restrict__ sZ = reinterpret_cast<double*>(s_raw + lds.z);           // [QW][B]
+    double* __restrict__ sSum = reinterpret_cast<double*>(s_raw + lds.sum);       // [B] whole margins
+    float* __restrict__ sX = reinterpret_cast<float*>(s_raw + lds.x);             // [held]
+    float* __restrict__ sM = reinterpret_cast<float*>(s_raw + lds.m);             // [held]
+    float* __restrict__ sY = reinterpret_cast<float*>(s_raw + lds.y);             // [n][share]
+    float* __restrict__ sCoef = reinterpret_cast<float*>(s_raw + lds.coef);       // [RG S], zeros behind B
+    float* __restrict__ sTgt = reinterpret_cast<float*>(s_raw + lds.tgt);         // [staged]
+    int32_t* __restrict__ sRow = reinterpret_cast<int32_t*>(s_raw + lds.row);     // [staged]
+    int32_t* __restrict__ sOff = reinterpret_cast<int32_t*>(s_raw + lds.off);     // [K] this node's entries of a sparse W
+    float* __restrict__ sVal = reinterpret_cast<float*>(s_raw + lds.val);
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -696,13 +692,6 @@ hipError_t launch_slots(const gpga_ctx* c, const RowsRunArgs& a, int threads, si
     return hipGetLastError();
 }
 
-// Rows a thread has room for.
-int slots_for(int rows, bool fixed) {
-    if (rows <= 8) return rows <= 4 ? 4 : 8;
-    if (fixed) return rows <= kFixedSlots ? kFixedSlots : kRowsRunMaxSlots;
-    return rows <= 12 ? 12 : rows <= 16 ? 16 : kAheadSlots;
-}
-
 hipError_t launch_run(const gpga_ctx* c, const RowsRunArgs& a, int slots, int threads, size_t lds) {
     if (!a.idx) {
         if (slots == 4) return launch_slots<4, ROWS_FIXED>(c, a, threads, lds);
@@ -715,47 +704,6 @@ hipError_t launch_run(const gpga_ctx* c, const RowsRunArgs& a, int slots, int th
     if (slots == 12) return launch_slots<12, ROWS_AHEAD>(c, a, threads, lds);
     if (slots == 16) return launch_slots<16, ROWS_AHEAD>(c, a, threads, lds);
     return launch_slots<kAheadSlots, ROWS_AHEAD>(c, a, threads, lds);
-}
-
-int log2_ceil(int v) {
-    int l = 0;
-    while ((1 << l) < v) ++l;
-    return l;
-}
-
-// How the workgroups of a launch share nodes, columns and rows, and what an iteration is then expected to take.
-struct RunPlan {
-    int P = 0, w = 0, QW = 0, RG = 0, slots = 0;
-    double us = 0.0;
-};
-
-// More slices are fewer rows and columns a workgroup but more words of margins to exchange.  Measured, us an iteration
-// (ring or one-peer graph): 20 x 1001 with 16 samples P = 1 / 2 / 4 / 8 5.9 / 6.0 / 4.9 / 5.3; 8 x 845 with 50 15.7 / 7.4 / 5.6 /
-// 6.3; 9 x 222 with 32 4.1 / 4.7 / 4.8 / 5.0; 8 x 1000 full batches of 100 - / 9.2 / 7.0 / 7.8; 6 x 5164 with 16 P = 4 / 8 / 12 / 24
-// 9.7 / 7.5 / 7.0 / 7.3.  The terms: 3.5 us for barriers, update and y; a row of a wavefront, by how many of them share a SIMD;
-// the words of the margins a thread has to look at; half of the time the rows take from memory.
-RunPlan plan_run(const gpga_ctx* c, int32_t B, bool batches) {
-    RunPlan best;
-    const int64_t d4 = (c->d + 3) / 4;
-    for (int P = 1; P <= kWave && (int64_t)P * c->n <= c->num_cus; ++P) {
-        const int64_t w = (d4 + P - 1) / P;
-        if (w > kRowWaves * kWave || (d4 + w - 1) / w != P) continue;
-        RunPlan p;
-        p.P = P;
-        p.w = (int)w;
-        p.QW = (p.w + kWave - 1) / kWave;
-        for (int rg = 1; rg * p.QW <= kRowWaves && rg <= B; ++rg) {
-            const int slots = (B + rg - 1) / rg, waves = p.QW * rg, threads = kWave * std::min(kRowsRunWaves - waves, 4);
-            if (slots > (batches ? kAheadSlots : kRowsRunMaxSlots)) continue;
-            const double row = batches ? 0.22 : slots <= kFixedSlots ? 0.08 : 0.2;
-            double us = 3.5 + row * slots * ((waves + 3) / 4);  // wavefronts are dealt to the four SIMDs in turn
-            if (P > 1) us += 1.2 + 0.5 * (((B << log2_ceil(P)) + threads - 1) / threads) + 0.02 * P;
-            if (batches) us += 0.5 * B * p.w * 16.0 / 25e3;  // 25 bytes a ns and compute unit
-            if (!p.RG || us <= p.us) p.RG = rg, p.slots = slots, p.us = us;
-        }
-        if (p.RG && (!best.P || p.us < best.us)) best = p;
-    }
-    return best;
 }
 
 // An iteration in two launches (k_rows_margin, k_rows_step), measured: 20 x 1001 with 16 samples 8.8 us, 30 x 3000 with 32 13.0,
@@ -792,7 +740,7 @@ int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* id
     // launch (16 iterations, us, one workgroup / this: 4 x 32 with one sample 38 / 52, 10 x 40 44 / 52, 20 x 33 with two 68 / 55,
     // 12 x 100 with 8 151 / 61, 9 x 222 with 32 531 / 65; 8 x 100 with 4, 4 iterations 21.9 / 21.7).
     if (small_run_fits(c, idx, B) && (wanted < 4 || (int64_t)c->n * Beff * c->d < 1280)) return 0;
-    const RunPlan plan = plan_run(c, Beff, idx != nullptr);
+    const RunPlan plan = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
     if (!plan.P || plan.us > two_launches_us(c, Beff)) return 0;
     int64_t T = kRowsRunMaxWords / ((int64_t)c->n * c->d);
     if (T > kRowsRunMaxIters) T = kRowsRunMaxIters;
@@ -809,7 +757,7 @@ int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* id
 
 hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g) {
     const int32_t Beff = idx ? B : c->M;
-    const RunPlan p = plan_run(c, Beff, idx != nullptr);
+    const RunPlan p = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
     if (!p.P || T < 1 || T > kRowsRunMaxIters) return hipErrorInvalidValue;
     const RunSpace at(c, p, Beff, T);
     if (c->run_space_cap < at.total) {
@@ -884,12 +832,10 @@ hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B
         a.lr[t] = scheduled_lr(c, c->k + t);
         a.shift[t] = !c->aga && is_global_iteration(c->topo, c->H, c->k + t) ? -1 : one_peer_shift(c->n, c->k + t);
     }
-    const int held = 4 * kWave * p.QW, share = (4 * p.w + c->n - 1) / c->n, slots = slots_for(p.slots, !idx);
-    const size_t staged = idx ? (size_t)T * Beff : (size_t)Beff;
-    const size_t lds = 8 * ((size_t)p.RG * held + (size_t)(p.QW + 1) * Beff) +
-                       4 * ((size_t)2 * held + (size_t)c->n * share + (size_t)p.RG * slots + 2 * staged + (sparse ? 2 * (size_t)c->csr_max_row : 0));
+    const int slots = slots_for(p.slots, !idx);
+    const RunLds lds(c->n, Beff, p.w, p.QW, p.RG, slots, idx ? T * Beff : Beff, sparse ? c->csr_max_row : 0);
     if (!gang_begin(c)) return hipErrorNotReady;
-    const hipError_t e = launch_run(c, a, slots, a.threads, lds);
+    const hipError_t e = launch_run(c, a, slots, a.threads, (size_t)lds.bytes);
     gang_end(c, e == hipSuccess);
     return e;
 }

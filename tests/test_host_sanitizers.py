@@ -92,6 +92,12 @@ def test_small_trajectories_fit_the_lds_of_a_plain_launch(facts):
     assert int(row[2]) > 0 and 60_000 < int(row[4]) <= 65_536
 
 
+def test_arrays_of_a_trajectory_on_stored_features_lie_on_their_boundaries(facts):
+    """Odd numbers of samples and of wavefronts across a slice among them: x is read four columns at a time."""
+    row, = [f for f in facts if f[0] == "rows_run"]
+    assert int(row[2]) > 3000 and 40_000 < int(row[4]) <= 129 * 1024
+
+
 def test_no_iteration_writes_an_exchange_buffer_that_another_reads(facts):
     """Local SGD and gossip with averages in every H-th of 64 iterations; turns by iteration, which W = I has no barriers for,
     are found in every schedule with iterations between its averages."""
