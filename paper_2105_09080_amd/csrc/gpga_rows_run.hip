@@ -66,6 +66,7 @@ struct RowsRunArgs {
     int32_t lead64;
     int64_t ncols;
     float inv_n, mu;
+    int32_t mean64;      // averages are formed in double precision
     float lr[kRowsRunMaxIters];
     int32_t shift[kRowsRunMaxIters];  // one-peer offset; -1: the iteration ends in a global average (fixed period)
 };
@@ -125,9 +126,15 @@ __device__ __forceinline__ bool column_in_whole_tile(const RowsRunArgs& a, int64
 }
 
 // The mean of one column, rows `step` floats apart, added as k_step_global adds them (gpga_order.hpp) with batches of one or
-// four rows.  One copy of the loop: the code of an iteration is to stay in the instruction cache.
+// four rows; in double precision on the problems that k_small_run, which adds so, takes in launches of other lengths.  One copy of the loop: the code of an iteration is to stay in the instruction cache.
 __device__ __forceinline__ float column_mean(const RowsRunArgs& a, const float* y, int step, int64_t col) {
     const int n = a.n, U = a.go.U, RS = a.go.RL * a.go.wpb;
+    if (a.mean64) {
+        double sum = 0.0;
+#pragma unroll 4
+        for (int i = 0; i < n; ++i) sum += (double)y[i * step];
+        return (float)(sum * (1.0 / (double)n));
+    }
     const bool by_parity = RS == 1 && column_in_whole_tile(a, col);
     const int batched = by_parity ? n - n % U : n, stride = by_parity ? 2 * U : RS * U;
     const int next = U == 1 ? stride : RS, ahead = U == 1 ? 4 * stride : stride;  // between the four rows read together, and behind them
@@ -826,6 +833,7 @@ hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B
     a.ncols = ge.ncols;
     a.inv_n = 1.0f / (float)c->n;
     a.mu = c->mu;
+    a.mean64 = small_run_fits(c, idx, B);
     a.problem = c->problem;
     a.mom = c->mu == 0.f ? 0 : c->nesterov ? 2 : 1;
     for (int t = 0; t < T; ++t) {

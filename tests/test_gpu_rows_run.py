@@ -120,6 +120,31 @@ def test_adaptive_period_decided_in_the_launch(hx, n, d, M, batch, T, topology, 
         assert np.abs(u - v).max() <= 4 * TOL * np.abs(v).max()
 
 
+@pytest.mark.parametrize("given_up", [False, True])
+@pytest.mark.parametrize("n,d,batch", [(100, 64, 1), (9, 222, 32), (12, 33, 7), (64, 128, 2)])
+def test_averages_of_small_problems_are_formed_in_double_precision(hx, n, d, batch, given_up):
+    """Without a step every iterate stays as it is until the average: columns whose rows cancel to 1e-6 of their size.  What
+    remains is one rounding to single precision, and the rounding of fp64 sums of up to 100 rows 1e6 times the mean: 1e-8."""
+    sim, idx = make(hx, n, d, 40, batch, 4, "none", 4, 0.0, lr=0.0)
+    sim.set_option("small_run", 1)
+    if given_up:
+        sim.set_option("run_wait_us", 0)
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, d)).astype(np.float32) * 1e4
+    x[n // 2:2 * (n // 2)] = -x[:n // 2]
+    x[n - 1] += rng.standard_normal(d).astype(np.float32)
+    if n % 2:
+        x[n - 1] *= 1e-4
+    sim.set_state(X=x)
+    sim.run(4, idx)
+    torch.cuda.synchronize()
+    assert int(sim.query("step_path")) == 12
+    want = x.astype(np.float64).mean(0)
+    got = sim.X.cpu().numpy().astype(np.float64)
+    assert (np.abs(got - want) <= (2.0 ** -24 + 1e-8) * np.abs(want)).all()
+    sim.close()
+
+
 def test_rows_outside_the_data_poison_their_node_only(hx):
     n, d, T = 8, 1001, 3
     sim, _ = make(hx, n, d, 50, 9, T, "none", 0, 0.9)
