@@ -62,9 +62,7 @@ struct RowsRunArgs {
     const float* val;
     const int32_t* wptr;
     int32_t K;
-    GlobalOrder go;
-    int32_t lead64;
-    int64_t ncols;
+    int32_t splitters;   // of an average
     float inv_n, mu;
     int32_t mean64;      // averages are formed in double precision
     float lr[kRowsRunMaxIters];
@@ -121,58 +119,40 @@ __device__ __forceinline__ void aga_store(RowsRunAga* to, const RowsRunAga& s) {
     __hip_atomic_store(&to->first_loss, s.first_loss, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__device__ __forceinline__ bool column_in_whole_tile(const RowsRunArgs& a, int64_t col) {
-    return ((col >> 2) + a.lead64) / kWave * kWave + kWave - a.lead64 <= a.ncols;
-}
-
-// The mean of one column, rows `step` floats apart, added as k_step_global adds them (gpga_order.hpp) with batches of one or
-// four rows; in double precision on the problems that k_small_run, which adds so, takes in launches of other lengths.  One copy of the loop: the code of an iteration is to stay in the instruction cache.
-__device__ __forceinline__ float column_mean(const RowsRunArgs& a, const float* y, int step, int64_t col) {
-    const int n = a.n, U = a.go.U, RS = a.go.RL * a.go.wpb;
+// The mean of one column, rows `step` floats apart, added as k_step_global adds them (gpga_order.hpp) with batches of four rows
+// dealt to two splitters or more; in double precision on the problems that k_small_run, which adds so, takes in launches of
+// other lengths.
+__device__ __forceinline__ float column_mean(const RowsRunArgs& a, const float* y, int step) {
+    const int n = a.n, splitters = a.splitters;
     if (a.mean64) {
         double sum = 0.0;
 #pragma unroll 4
         for (int i = 0; i < n; ++i) sum += (double)y[i * step];
         return (float)(sum * (1.0 / (double)n));
     }
-    const bool by_parity = RS == 1 && column_in_whole_tile(a, col);
-    const int batched = by_parity ? n - n % U : n, stride = by_parity ? 2 * U : RS * U;
-    const int next = U == 1 ? stride : RS, ahead = U == 1 ? 4 * stride : stride;  // between the four rows read together, and behind them
     SplitterTree<float> tree;
-    float odd = 0.f;
 #pragma unroll 1
-    for (int pass = by_parity ? 0 : 1; pass <= RS; ++pass) {  // the odd batches, then the even ones, or the splitters
+    for (int s = 0; s < splitters; ++s) {
         float sum = 0.f;
 #pragma unroll 1
-        for (int base = pass == 0 ? U : pass - 1; base < batched; base += ahead) {
+        for (int base = s; base < n; base += 4 * splitters) {
             float v[4], part = 0.f;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = y[(base + k * next < n ? base + k * next : n - 1) * step];
+            for (int k = 0; k < 4; ++k) v[k] = y[(base + k * splitters < n ? base + k * splitters : n - 1) * step];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool on = base + k * next < (U == 1 ? batched : n);
-                if (U == 1) sum += on ? v[k] : 0.f;
-                else if (on) part += v[k];
-            }
-            if (U != 1) sum += part;
+            for (int k = 0; k < 4; ++k)
+                if (base + k * splitters < n) part += v[k];
+            sum += part;
         }
-        if (pass == 0) {
-            odd = sum;
-            continue;
-        }
-        if (by_parity) {
-#pragma unroll 1
-            for (int i = batched; i < n; ++i) sum += y[i * step];
-            sum += odd;
-        }
-        tree.add(pass - 1, sum);
+        tree.add(s, sum);
     }
     return tree.sum * a.inv_n;
 }
 
 enum RowsHeld : int {
     ROWS_FIXED = 0,    // full batches: the same rows in every iteration, held in double precision up to kFixedSlots of them
-    ROWS_AHEAD = 2     // ... half of them as soon as the margins are formed, into registers of their own
+    ROWS_AHEAD = 1     // minibatches: the next iteration's rows are fetched ahead, half of them as soon as the margins are formed, into
+                       // registers of their own
 };
 
 template <int S, int HELD>
@@ -257,7 +237,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
                 if (k == 1 && c + nthr >= ncol) break;
                 const float g = (float)s[k];
                 const float y = local_update(a.mom, x[k], g, lr, a.mu, &m[k]);
-                if (n > 1) gang_put(wy + cc[k], a.gang.number, __float_as_uint(y));
+                gang_put(wy + cc[k], a.gang.number, __float_as_uint(y));
                 sX[cc[k]] = y;
                 if (a.mom) sM[cc[k]] = m[k];
                 if (last && a.g) gang_put32(reinterpret_cast<uint32_t*>(a.g + (int64_t)node * a.ld + c0 + cc[k]), __float_as_uint(g));
@@ -470,7 +450,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
                 run_barrier();
                 uint64_t* const wm = a.wmean + (int64_t)t * d + c0;
                 for (int e = ct; e < count; e += NT)
-                    gang_put(wm + first + e, a.gang.number, __float_as_uint(column_mean(a, sY + e, count, c0 + first + e)));
+                    gang_put(wm + first + e, a.gang.number, __float_as_uint(column_mean(a, sY + e, count)));
             }
             // What comes from other workgroups: the means, or the y of one or more other nodes, two at a time.
             const int mode = average ? kRunMean : a.mode, shift = a.shift[t];
@@ -657,7 +637,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
         for (int64_t c = tid; c < d; c += nthr) {
             const float* const yc = y + c;
             auto at = [&](int i) { return yc[(int64_t)i * a.ld]; };
-            const float mean = average ? column_mean(a, yc, (int)a.ld, c) : 0.f;
+            const float mean = average ? column_mean(a, yc, (int)a.ld) : 0.f;
             for (int i = 0; i < n; ++i) {
                 float v = at(i);
                 if (average) {
@@ -741,6 +721,8 @@ int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* id
     const bool sparse = c->topo == GPGA_TOPO_GRID || c->topo == GPGA_TOPO_EXPO || c->topo == GPGA_TOPO_CUSTOM;
     if (sparse && (!c->csr_ready || !c->csr_off_d)) return 0;
     if (c->n < 4 || c->n > 128 || c->d < 32 || c->max_lds_block < 130 * 1024 || (int64_t)c->n * c->ld > 0x7fffffff) return 0;
+    const GlobalOrder order = global_order(c);
+    if (order.U != 4 || order.RL * order.wpb < 2) return 0;  // not on these sizes: column_mean adds in no other way
     const int32_t Beff = idx ? B : c->M;
     if (Beff < 1 || Beff > kRowWaves * kRowsRunMaxSlots) return 0;
     // One workgroup alone takes 2 us an iteration and more with every sample and column; this form takes 3 to 4 and some 5 a
@@ -820,17 +802,13 @@ hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B
     a.QW = p.QW;
     a.RG = p.RG;
     const bool sparse = c->topo == GPGA_TOPO_GRID || c->topo == GPGA_TOPO_EXPO || c->topo == GPGA_TOPO_CUSTOM;
-    a.mode = c->n == 1 ? MODE_SELF : sparse ? kRunSparse : c->topo == GPGA_TOPO_RING ? MODE_RING : c->topo == GPGA_TOPO_EXPO1 ? MODE_PEER : MODE_SELF;
+    a.mode = sparse ? kRunSparse : c->topo == GPGA_TOPO_RING ? MODE_RING : c->topo == GPGA_TOPO_EXPO1 ? MODE_PEER : MODE_SELF;
     a.off = c->csr_off_d;
     a.val = c->csr_ellval_d;
     a.wptr = c->csr_ptr_d;
     a.K = c->csr_max_row;
-    a.go = global_order(c);
-    StepGeom ge;
-    ge.d = c->d;
-    set_units(&ge, 4, kWave);
-    a.lead64 = ge.lead;
-    a.ncols = ge.ncols;
+    const GlobalOrder order = global_order(c);
+    a.splitters = order.RL * order.wpb;
     a.inv_n = 1.0f / (float)c->n;
     a.mu = c->mu;
     a.mean64 = small_run_fits(c, idx, B);
