@@ -314,7 +314,8 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * margins and iterates (default; from three iterations on, not while a trace is being recorded, and not while the
  * stream is being captured), 0 = one iteration at a time), "run_wait_us" (how long a workgroup of such a launch waits
  * for another, in microseconds, before the launch is given up and its last workgroup does the work alone, 0..10000000,
- * default 100000; launches of this kind never overlap within a process),
+ * default 100000; while a launch of this kind is under way in one stream, calls on another take one iteration at a time or
+ * the forms of small problems, and no call waits for another stream),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
  * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always, on rows

@@ -12,6 +12,7 @@
 #include "gpga_gang.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_pace.hpp"
+#include "gpga_rows_run.hpp"
 #include "gpga_schedule.hpp"
 
 namespace {
@@ -275,6 +276,7 @@ gpga_status gpga_create(gpga_ctx** out, int32_t n, int64_t d, int32_t topology, 
     } else {
         c->pace_states = nullptr;  // launches simply run unpaced, sums of losses in launches of their own
     }
+    gang_set_up(c);
     {   // set-up of gpga_consensus_error_static on this device, so that its calls find the address ready
         double* static_ptr = nullptr;
         (void)static_scratch_for_device(c->device, &static_ptr);
@@ -301,7 +303,6 @@ gpga_status gpga_destroy(gpga_ctx* c) {
     DeviceGuard guard(c->device);
     gpga_status s = GPGA_OK;
     if (c->bound && hipStreamSynchronize(c->stream) != hipSuccess) s = GPGA_EDEVICE;
-    gang_forget(c);
     if (c->coef) (void)hipFree(c->coef);
     if (c->aga_loss) (void)hipFree(c->aga_loss);
     if (c->partials) (void)hipFree(c->partials);
@@ -333,10 +334,6 @@ gpga_status gpga_bind(gpga_ctx* c, float* x, float* x_new, float* m, float* g, i
                 if ((lo <= hi ? hi - lo : lo - hi) < span)
                     return fail(c, GPGA_EINVAL, "%s and %s overlap", names[p], names[q]);
             }
-    }
-    if (c->bound && c->stream != static_cast<hipStream_t>(hip_stream)) {
-        DeviceGuard guard(c->device);
-        gang_forget(c);
     }
     c->x = x;
     c->x_first = x;
@@ -670,8 +667,8 @@ static gpga_status run_iteration(gpga_ctx* c, const int32_t* idx, int32_t B, boo
 }
 
 // Several iterations of gpga_run in one launch; *done is false if it cannot be launched now.
-static gpga_status run_chunk(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g, bool* done) {
-    hipError_t e = launch_rows_run(c, T, idx, B, want_g);
+static gpga_status run_chunk(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g, bool* done) {
+    hipError_t e = launch_rows_run(c, run, T, idx, want_g);
     *done = e != hipErrorNotReady;
     if (!*done) return GPGA_OK;
     if (e != hipSuccess) return hip_fail(c, e, "trajectory kernel launch");
@@ -713,9 +710,23 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
     if (c->problem == PROB_NONE) return fail(c, GPGA_ESTATE, "no problem attached (gpga_problem_*)");
     DeviceGuard guard(c->device);
     const int64_t stride = batch_table_dev ? (int64_t)c->n * B : 0;
+    auto batch = [&](int64_t j) { return batch_table_dev ? batch_table_dev + j * stride : nullptr; };
+    int64_t j = 0;  // iterations done
     int32_t checked_B = 0;
-    const bool checked = T > 1 && check_batch(c, batch_table_dev, B, &checked_B) == GPGA_OK;  // else the first iteration reports it
-    const int32_t most = checked ? rows_run_iterations(c, T, batch_table_dev, B) : 0;  // iterations a launch
+    RowsRun run;
+    if (T > 1 && check_batch(c, batch_table_dev, B, &checked_B) == GPGA_OK)  // else the first iteration reports it
+        run = rows_run_for(c, T, batch_table_dev, B);
+    // Several iterations a launch, as long as such launches can be made and more than one iteration is left.
+    auto run_chunks = [&]() -> gpga_status {
+        while (run.most > 0 && T - j > 1) {
+            const int32_t chunk = (int32_t)(T - j < run.most ? T - j : run.most);
+            bool done = false;
+            const gpga_status s = run_chunk(c, run, chunk, batch(j), j + chunk == T, &done);
+            if (s != GPGA_OK || !done) return s;
+            j += chunk;
+        }
+        return GPGA_OK;
+    };
     if (c->aga) {
         // Algorithm 2: the minibatch losses are needed only in iterations that end in a global
         // average, which the counter tells beforehand
@@ -725,21 +736,12 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
             c->aga_state = nullptr;
             return fail(c, GPGA_ENOMEM, "hipHostMalloc(adaptive period)");
         }
-        for (int64_t j = 0; j < T; ++j) {
-            const int32_t* idx = batch_table_dev ? batch_table_dev + j * stride : nullptr;
-            const int32_t chunk = (int32_t)(T - j < most ? T - j : most);
-            if (chunk > 1) {
-                bool done = false;
-                s = run_chunk(c, chunk, idx, B, j + chunk == T, &done);
-                if (s != GPGA_OK) return s;
-                if (done) {
-                    j += chunk - 1;
-                    continue;
-                }
-            }
+        s = run_chunks();
+        if (s != GPGA_OK) return s;
+        for (; j < T; ++j) {
             const int64_t k = c->k;
             const bool global = c->aga_C + 1 == c->H;
-            s = run_iteration(c, idx, B, global, global ? c->aga_loss : nullptr, j == T - 1);
+            s = run_iteration(c, batch(j), B, global, global ? c->aga_loss : nullptr, j == T - 1);
             if (s != GPGA_OK) return s;
             c->aga_C += 1;
             if (global) s = aga_average(c, k, c->aga_loss);
@@ -747,16 +749,20 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         }
         return GPGA_OK;
     }
-    if (most == 0 && small_run_fits(c, batch_table_dev, B)) {
+    {
+        const gpga_status s = run_chunks();
+        if (s != GPGA_OK) return s;
+    }
+    if ((j < T || T == 0) && small_run_fits(c, batch_table_dev, B)) {
         // the whole loop inside single-workgroup launches of up to kSmallRunMaxIters iterations
         int32_t Beff = 0;
         gpga_status s = check_batch(c, batch_table_dev, B, &Beff);
         if (s != GPGA_OK) return s;
         float lr[kSmallRunMaxIters];
-        for (int64_t j = 0; j < T;) {
+        while (j < T) {
             const int32_t chunk = (int32_t)(T - j < kSmallRunMaxIters ? T - j : kSmallRunMaxIters);
             for (int32_t t = 0; t < chunk; ++t) lr[t] = scheduled_lr(c, c->k + t);
-            const hipError_t e = launch_small_run(c, chunk, batch_table_dev ? batch_table_dev + j * stride : nullptr, B, lr);
+            const hipError_t e = launch_small_run(c, chunk, batch(j), B, lr);
             if (e != hipSuccess) return hip_fail(c, e, "small-problem kernel launch");
             c->last_path = PATH_SMALL_RUN;
             c->last_paced = 0;
@@ -774,7 +780,7 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
     }
     if (column_run_fits(c, T)) {
         // synthetic gradients: whole columns stay on chip for up to kColumnRunMaxIters iterations a launch
-        for (int64_t j = 0; j < T;) {
+        while (j < T) {
             const int32_t chunk = (int32_t)(T - j < kColumnRunMaxIters ? T - j : kColumnRunMaxIters);
             const hipError_t e = launch_column_run(c, chunk);
             if (e != hipSuccess) return hip_fail(c, e, "trajectory kernel launch");
@@ -788,19 +794,8 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         }
         return GPGA_OK;
     }
-    for (int64_t j = 0; j < T; ++j) {
-        const int32_t chunk = (int32_t)(T - j < most ? T - j : most);
-        if (chunk > 1) {
-            bool done = false;
-            const gpga_status s = run_chunk(c, chunk, batch_table_dev ? batch_table_dev + j * stride : nullptr, B, j + chunk == T, &done);
-            if (s != GPGA_OK) return s;
-            if (done) {
-                j += chunk - 1;
-                continue;
-            }
-        }
-        const gpga_status s = run_iteration(c, batch_table_dev ? batch_table_dev + j * stride : nullptr, B,
-                                            is_global_iteration(c->topo, c->H, c->k), nullptr, j == T - 1);
+    for (; j < T; ++j) {
+        const gpga_status s = run_iteration(c, batch(j), B, is_global_iteration(c->topo, c->H, c->k), nullptr, j == T - 1);
         if (s != GPGA_OK) return s;
     }
     return GPGA_OK;

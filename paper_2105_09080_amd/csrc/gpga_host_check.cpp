@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "gpga_exchange.hpp"
+#include "gpga_gang.hpp"
 #include "gpga_internal.hpp"
 #include "gpga_node_run.hpp"
 #include "gpga_pace.hpp"
@@ -368,6 +369,36 @@ void rows_run_lds() {
     std::printf("rows_run plans %" PRId64 " most_lds %d\n", plans, most);
 }
 
+// Turns of launches whose workgroups wait for each other: two of them are never under way in two streams.
+void gang_turns() {
+    const int a = 0, b = 0;
+    GangTurn t;
+    uint32_t ended = 0;
+    expect(t.take(&a, false, ended), "the first launch");
+    expect(t.take(&a, false, ended) && t.number == 2, "behind the last one in its stream");
+    expect(!t.take(&b, false, ended) && !t.take(&b, false, 1) && t.number == 2, "another stream while one is under way");
+    ended = 2;
+    expect(t.take(&b, false, ended), "another stream when the last one has ended");
+    expect(!t.take(&a, false, ended), "the first stream while the second is at it");
+    t.undo();
+    expect(t.take(&a, false, ended), "a launch that failed holds nobody back");
+    expect(!t.take(&a, true, ended), "a stream that every thread has its own of is another one");
+    ended = 3;
+    expect(t.take(&a, true, ended) && t.take(&a, true, ended), "... and the same in the same thread");
+    bool taken = true;
+    std::thread([&]() { taken = t.take(&a, true, ended); }).join();
+    expect(!taken, "... and another in another thread");
+    t = GangTurn();
+    t.number = 0xfffffffeu;
+    ended = 0xfffffffeu;
+    for (int j = 0; j < 4; ++j) {
+        expect(t.take(j % 2 ? &a : &b, false, ended), "numbers start again");
+        expect(!t.take(j % 2 ? &b : &a, false, ended), "numbers start again, another stream");
+        ended = t.number;
+    }
+    std::printf("gang_turns done\n");
+}
+
 // The exchange buffers of k_column_run.  What wavefronts do between two barriers is in no order, so a buffer must not be read by
 // one iteration and written by another there.  Returns how often that happens in T iterations with an average in every
 // H-th; `buffer(t, exchanges before)` and `writes(t)` are the rule.
@@ -466,6 +497,7 @@ int main() {
     node_run_sizes();
     rows_deal();
     rows_run_lds();
+    gang_turns();
     named_graphs();
     rejected_matrices();
     schedules();

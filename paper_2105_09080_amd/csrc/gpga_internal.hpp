@@ -268,11 +268,6 @@ bool rows_step_fits(const gpga_ctx* c, int32_t Beff);
 hipError_t launch_rows_margin(const gpga_ctx* c, const int32_t* idx, int32_t B, float* loss_out);
 hipError_t launch_rows_step(const gpga_ctx* c, const StepGeom& geom, const int32_t* idx, int32_t Beff, bool global, int mode,
                             int32_t shift, bool csr, bool want_g);
-// Several iterations on stored features in one launch, T <= rows_run_iterations of the `wanted` ones (0: not for this context and
-// batch).  Under an
-// adaptive period the launch decides itself which iterations average and leaves the period's state in c->aga_state.
-int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B);
-hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g);
 // Virtual features: what follows the margin pass of a gossip iteration in one launch, same conventions (spread_* as for
 // launch_step_walk).
 bool virtual_step_fits(const gpga_ctx* c, int32_t B);

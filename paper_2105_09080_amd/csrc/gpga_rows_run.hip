@@ -564,6 +564,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
         if (__hip_atomic_fetch_add(&a.gang.words->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
             gang_put32(&a.gang.words->left, 0u);
             s_last = gang_get32(&a.gang.words->given_up) == a.gang.number;
+            if (!s_last) gang_ended(a.gang);
         }
     }
     __syncthreads();
@@ -663,6 +664,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
     if (a.T % 2)
         for (int i = 0; i < n; ++i)
             for (int64_t c = tid; c < d; c += nthr) y[(int64_t)i * a.ld + c] = x[(int64_t)i * a.ld + c];
+    if (tid == 0) gang_ended(a.gang);
 }
 
 template <int S, int HELD>
@@ -715,44 +717,50 @@ struct RunSpace {  // of the context's exchange memory, in bytes
 
 }  // namespace
 
-int32_t rows_run_iterations(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B) {
-    if (wanted < kRowsRunFewest || !c->default_geometry() || !c->opt_rows_run || (c->problem != PROB_LSQ && c->problem != PROB_LOGREG)) return 0;
-    if (c->trace && c->k < c->trace_cap) return 0;  // the trace wants every iterate
+RowsRun rows_run_for(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B) {
+    const RowsRun no;
+    if (wanted < kRowsRunFewest || !c->default_geometry() || !c->opt_rows_run || (c->problem != PROB_LSQ && c->problem != PROB_LOGREG)) return no;
+    if (c->trace && c->k < c->trace_cap) return no;  // the trace wants every iterate
     const bool sparse = c->topo == GPGA_TOPO_GRID || c->topo == GPGA_TOPO_EXPO || c->topo == GPGA_TOPO_CUSTOM;
-    if (sparse && (!c->csr_ready || !c->csr_off_d)) return 0;
-    if (c->n < 4 || c->n > 128 || c->d < 32 || c->max_lds_block < 130 * 1024 || (int64_t)c->n * c->ld > 0x7fffffff) return 0;
+    if (sparse && (!c->csr_ready || !c->csr_off_d)) return no;
+    if (c->n < 4 || c->n > 128 || c->d < 32 || c->max_lds_block < 130 * 1024 || (int64_t)c->n * c->ld > 0x7fffffff) return no;
     const GlobalOrder order = global_order(c);
-    if (order.U != 4 || order.RL * order.wpb < 2) return 0;  // not on these sizes: column_mean adds in no other way
+    if (order.U != 4 || order.RL * order.wpb < 2) return no;  // not on these sizes: column_mean adds in no other way
     const int32_t Beff = idx ? B : c->M;
-    if (Beff < 1 || Beff > kRowWaves * kRowsRunMaxSlots) return 0;
+    if (Beff < 1 || Beff > kRowWaves * kRowsRunMaxSlots) return no;
     // One workgroup alone takes 2 us an iteration and more with every sample and column; this form takes 3 to 4 and some 5 a
     // launch (16 iterations, us, one workgroup / this: 4 x 32 with one sample 38 / 52, 10 x 40 44 / 52, 20 x 33 with two 68 / 55,
     // 12 x 100 with 8 151 / 61, 9 x 222 with 32 531 / 65; 8 x 100 with 4, 4 iterations 21.9 / 21.7).
-    if (small_run_fits(c, idx, B) && (wanted < 4 || (int64_t)c->n * Beff * c->d < 1280)) return 0;
-    const RunPlan plan = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
-    if (!plan.P || plan.us > two_launches_us(c, Beff)) return 0;
+    RowsRun run;
+    run.B = Beff;
+    run.splitters = order.RL * order.wpb;
+    run.mean64 = small_run_fits(c, idx, B);
+    if (run.mean64 && (wanted < 4 || (int64_t)c->n * Beff * c->d < 1280)) return no;
+    run.plan = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
+    if (!run.plan.P || run.plan.us > two_launches_us(c, Beff)) return no;
     int64_t T = kRowsRunMaxWords / ((int64_t)c->n * c->d);
     if (T > kRowsRunMaxIters) T = kRowsRunMaxIters;
     if (idx && T > kRowsRunStaged / Beff) T = kRowsRunStaged / Beff;
-    if (T < kRowsRunFewest) return 0;
+    if (T < kRowsRunFewest) return no;
     // A stream that is being captured keeps its launches per iteration: the number of a launch is the host's.
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return 0;
+        return no;
     }
-    return st == hipStreamCaptureStatusNone ? (int32_t)T : 0;
+    if (st != hipStreamCaptureStatusNone) return no;
+    run.most = (int32_t)T;
+    return run;
 }
 
-hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B, bool want_g) {
-    const int32_t Beff = idx ? B : c->M;
-    const RunPlan p = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
-    if (!p.P || T < 1 || T > kRowsRunMaxIters) return hipErrorInvalidValue;
+hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g) {
+    const int32_t Beff = run.B;
+    const RunPlan& p = run.plan;
+    if (T < 1 || T > run.most) return hipErrorInvalidValue;
     const RunSpace at(c, p, Beff, T);
     if (c->run_space_cap < at.total) {
         // room for the longest launch of these batches, so that runs of other lengths find it
-        const RunSpace all(c, p, Beff, rows_run_iterations(c, kRowsRunMaxIters, idx, B));
-        const size_t need = all.total > at.total ? all.total : at.total;
+        const size_t need = RunSpace(c, p, Beff, run.most).total;
         hipError_t e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return e;
         if (c->run_space) (void)hipFree(c->run_space);
@@ -807,11 +815,10 @@ hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B
     a.val = c->csr_ellval_d;
     a.wptr = c->csr_ptr_d;
     a.K = c->csr_max_row;
-    const GlobalOrder order = global_order(c);
-    a.splitters = order.RL * order.wpb;
+    a.splitters = run.splitters;
     a.inv_n = 1.0f / (float)c->n;
     a.mu = c->mu;
-    a.mean64 = small_run_fits(c, idx, B);
+    a.mean64 = run.mean64;
     a.problem = c->problem;
     a.mom = c->mu == 0.f ? 0 : c->nesterov ? 2 : 1;
     for (int t = 0; t < T; ++t) {
@@ -820,7 +827,7 @@ hipError_t launch_rows_run(gpga_ctx* c, int32_t T, const int32_t* idx, int32_t B
     }
     const int slots = slots_for(p.slots, !idx);
     const RunLds lds(c->n, Beff, p.w, p.QW, p.RG, slots, idx ? T * Beff : Beff, sparse ? c->csr_max_row : 0);
-    if (!gang_begin(c)) return hipErrorNotReady;
+    if (!gang_begin(c, &a.gang)) return hipErrorNotReady;
     const hipError_t e = launch_run(c, a, slots, a.threads, (size_t)lds.bytes);
     gang_end(c, e == hipSuccess);
     return e;

@@ -54,6 +54,20 @@ inline RunPlan plan_run(int n, int64_t d, int num_cus, int32_t B, bool batches) 
     return best;
 }
 
+// What the launches of one gpga_run have in common.
+struct RowsRun {
+    int32_t most = 0;     // iterations a launch, 0: none of this kind
+    int32_t B = 0;        // samples a node
+    int splitters = 0;    // of an average
+    bool mean64 = false;
+    RunPlan plan;
+};
+// Several iterations on stored features in one launch, for `wanted` iterations on this context and batch.  Under an adaptive
+// period the launch decides itself which iterations average and leaves the period's state in host memory.
+RowsRun rows_run_for(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B);
+// T <= run.most; hipErrorNotReady if it cannot be made now.
+hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g);
+
 // Rows a thread has room for.
 inline int slots_for(int rows, bool fixed) {
     if (rows <= 8) return rows <= 4 ? 4 : 8;

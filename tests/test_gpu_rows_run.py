@@ -183,7 +183,7 @@ def test_infinite_features_and_iterates_as_in_separate_calls(hx):
 
 
 def test_two_streams_and_threads(hx):
-    # launches of this kind follow each other across streams; each keeps its own order and results
+    # a launch that is under way in one stream leaves the other one iteration a launch; each keeps its own order and results
     T, rounds = 6, 12
     sims = []
     for s in range(2):
@@ -202,16 +202,101 @@ def test_two_streams_and_threads(hx):
     for t in threads:
         t.join()
     torch.cuda.synchronize()
-    for sim, _, ref, ref_idx in sims:
+    for sim, idx, ref, ref_idx in sims:
+        assert int(sim.query("step_path")) in (9, 12)
+        sim.run(T, idx)                      # nothing is under way
+        torch.cuda.synchronize()
         assert int(sim.query("step_path")) == 12
         ref.set_option("rows_run", 0)
-        for _ in range(rounds):
+        for _ in range(rounds + 1):
             ref.run(T, ref_idx)
         assert int(ref.query("step_path")) == 9
         ra, rb = results(sim, 0.9), results(ref, 0.9)
         for u, v in zip(ra, rb):
-            assert np.abs(u - v).max() <= rounds * TOL * np.abs(v).max()
+            assert np.abs(u - v).max() <= (rounds + 1) * TOL * np.abs(v).max()
         sim.close(), ref.close()
+
+
+def busy(stream):
+    """Some 100 ms of other work in the stream: one wavefront."""
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(int(1e7))
+
+
+def test_no_call_waits_for_another_streams_work(hx):
+    sims = [make(hx, 8, 1000, 40, 16, 6, ("ring", "expo1")[s], 4, 0.9, stream=torch.cuda.Stream()) for s in range(2)]
+    (a, idx_a), (b, idx_b) = sims
+    ref, ref_idx = make(hx, 8, 1000, 40, 16, 6, "expo1", 4, 0.9)
+    ref.set_option("rows_run", 0)
+    b.run(6, idx_b)
+    ref.run(6, ref_idx)
+    torch.cuda.synchronize()
+    a.run(6, idx_a)
+    busy(a.stream)
+    b.run(6, idx_b)                          # whether the other launch has ended or not
+    b.stream.synchronize()
+    assert not a.stream.query()
+    ref.run(6, ref_idx)
+    torch.cuda.synchronize()
+    a.run(6, idx_a)
+    a.stream.synchronize()
+    busy(a.stream)
+    b.run(6, idx_b)                          # it has
+    assert int(b.query("step_path")) == 12
+    b.stream.synchronize()
+    assert not a.stream.query()
+    ref.run(6, ref_idx)
+    for u, v in zip(results(b, 0.9), results(ref, 0.9)):
+        assert np.abs(u - v).max() <= 3 * TOL * np.abs(v).max()
+    ref.close(), a.close(), b.close()
+
+
+def test_a_launch_under_way_in_another_stream_leaves_one_iteration_a_launch(hx):
+    a, idx_a = make(hx, 32, 4000, 40, 16, 32, "ring", 4, 0.9, stream=torch.cuda.Stream())
+    small = [make(hx, 9, 222, 40, 16, 32, "ring", 4, 0.9, stream=torch.cuda.Stream()) for _ in range(2)]
+    large = [make(hx, 20, 1001, 40, 16, 32, "expo", 4, 0.9, stream=torch.cuda.Stream()) for _ in range(2)]
+    for sim, _ in small:
+        sim.set_option("small_run", 1)
+    torch.cuda.synchronize()
+    for (b, idx_b), (ref, ref_idx), path in ((*small, 7), (*large, 9)):
+        for _ in range(20):                  # 20 x 32 iterations: milliseconds
+            a.run(32, idx_a)
+        b.run(32, idx_b)
+        assert int(b.query("step_path")) == path and not a.stream.query()
+        torch.cuda.synchronize()
+        assert int(a.query("step_path")) == 12
+        ref.run(32, ref_idx)
+        assert int(ref.query("step_path")) == 12
+        for u, v in zip(results(b, 0.9), results(ref, 0.9)):
+            assert np.abs(u - v).max() <= 4 * TOL * np.abs(v).max()
+        b.close(), ref.close()
+    a.close()
+
+
+def test_binding_another_stream_within_a_capture(hx):
+    from paper_2105_09080_amd import binding as B
+    stream, fork = torch.cuda.Stream(), torch.cuda.Stream()
+    sim, idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9, stream=stream)
+    ref, ref_idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
+    for s, i in ((ref, ref_idx), (sim, idx)):
+        s.set_option("rows_run", 0)
+        s.run(4, i)                          # sizes the scratch
+        s.set_option("rows_run", 1)
+        s.run(4, i)
+        assert int(s.query("step_path")) == 12
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        fork.wait_stream(stream)
+        B.gpga_bind(sim.ctx, sim._bufs[0], sim._bufs[1], sim.m, sim.g, sim.ld, fork.cuda_stream)
+        sim.run(4, idx)
+        stream.wait_stream(fork)
+    for _ in range(3):
+        graph.replay()
+        ref.run(4, ref_idx)
+    torch.cuda.synchronize()
+    assert_alike(results(sim, 0.9), results(ref, 0.9))
+    sim.close(), ref.close()
 
 
 def test_a_captured_run_keeps_its_launches_per_iteration(hx):

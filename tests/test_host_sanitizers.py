@@ -98,6 +98,10 @@ def test_arrays_of_a_trajectory_on_stored_features_lie_on_their_boundaries(facts
     assert int(row[2]) > 3000 and 40_000 < int(row[4]) <= 129 * 1024
 
 
+def test_launches_that_wait_within_themselves_are_never_under_way_in_two_streams(facts):
+    assert ["gang_turns", "done"] in facts
+
+
 def test_no_iteration_writes_an_exchange_buffer_that_another_reads(facts):
     """Local SGD and gossip with averages in every H-th of 64 iterations; turns by iteration, which W = I has no barriers for,
     are found in every schedule with iterations between its averages."""
