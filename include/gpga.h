@@ -15,9 +15,11 @@
  *
  * Data layout: every state array is node-major fp32, row i = node i, with a
  * common leading dimension ld >= d (in floats).  All pointers named *_dev are
- * DEVICE pointers owned by the caller (the library never allocates or frees
- * n x d memory; it owns only the context and small scratch for reductions and
- * per-sample coefficients).  Work is enqueued on the stream given to
+ * DEVICE pointers owned by the caller.  The library owns the context, small scratch for
+ * reductions and per-sample coefficients, and, a device, the memory through which gpga_run exchanges
+ * margins and iterates on stored features (option "rows_run"; as large as the launches made so far
+ * need, n x d x 8 bytes for each of their up to 32 iterations, at most 64 MiB of these, and the margins;
+ * all contexts share it, and what is over 8 MiB of it goes with the last one).  Work is enqueued on the stream given to
  * gpga_bind and is asynchronous unless stated otherwise.
  *
  * Errors: every call returns a gpga_status; nothing aborts or throws across

@@ -276,7 +276,7 @@ gpga_status gpga_create(gpga_ctx** out, int32_t n, int64_t d, int32_t topology, 
     } else {
         c->pace_states = nullptr;  // launches simply run unpaced, sums of losses in launches of their own
     }
-    gang_set_up(c);
+    gang_join(c);
     {   // set-up of gpga_consensus_error_static on this device, so that its calls find the address ready
         double* static_ptr = nullptr;
         (void)static_scratch_for_device(c->device, &static_ptr);
@@ -307,7 +307,7 @@ gpga_status gpga_destroy(gpga_ctx* c) {
     if (c->aga_loss) (void)hipFree(c->aga_loss);
     if (c->partials) (void)hipFree(c->partials);
     if (c->pace_states) (void)hipFree(c->pace_states);
-    if (c->run_space) (void)hipFree(c->run_space);
+    gang_leave(c);
     free_csr_device(c);
     if (c->host_scalar) (void)hipHostFree(c->host_scalar);
     if (c->aga_state) (void)hipHostFree(c->aga_state);

@@ -2,8 +2,8 @@
 //
 // Words: a value travels as one 64-bit word, 32 bits of payload under the launch's number.  A reader polls the word itself, so
 // that one trip through memory (0.9 - 1.2 us between any two compute units of the chip, where a dependent launch costs 4 - 5)
-// carries both the value and the news that it is there.  Every word is written once a launch and launches on a context have
-// different numbers, so nothing is cleared in between and no reader can be overtaken.
+// carries both the value and the news that it is there.  Every word is written once a launch and launches on a device have
+// different numbers, so nothing is cleared in between, no reader can be overtaken, and one memory serves all contexts.
 //
 // Waits end: the launcher sees to it that such launches of one process do not overlap on a device (GangTurn), but others'
 // kernels may hold compute units, so a wait that is not met within `limit` clock ticks gives up and marks the launch; all
@@ -23,10 +23,9 @@ struct GangWords {
 struct GangArgs {
     GangWords* words;
     uint32_t* finished;  // [workgroups] number of the last launch in which the workgroup stored its results
-    uint32_t number;     // of this launch, never 0
+    uint32_t number;     // of this launch among those of the device, never 0
     uint32_t limit;      // clock ticks a wait may take
-    uint32_t turn;       // number among the launches of this kind on the device
-    uint32_t* ended;     // host memory: the last workgroup to leave stores `turn` there
+    uint32_t* ended;     // host memory: the last workgroup to leave stores the number there
 };
 
 // Whose launch the last one on a device was.  Two at a time might each hold compute units that the other needs, so a launch is
@@ -43,10 +42,41 @@ struct GangTurn {
         if (number != ended && (to != stream || here != thread)) return false;
         stream = to;
         thread = here;
-        ++number;
+        if (++number == 0) number = 1;  // what older launches left is to be cleared
         return true;
     }
-    void undo() { --number; }  // nothing was launched
+    void undo(uint32_t before) { number = before; }  // nothing was launched
+};
+
+// The memory that launches on a device exchange through, made when the first of them comes and grown rarely: a context of its own
+// cost the first gpga_run of every context an allocation, and a clear of what the longest launch would take (8 iterations on
+// 8 x 1000 113 us instead of 73).  Memory does what it says of its device: get, put, clear, and wait for the launches that use it.
+struct GangSpace {
+    unsigned char* at = nullptr;
+    size_t cap = 0;
+    bool clear = false;  // no word there carries the number of a launch to come
+    template <typename Memory>
+    bool room(size_t bytes, bool numbers_start_again, Memory& memory) {
+        constexpr size_t kPiece = 2 << 20;
+        if (cap < bytes) {
+            size_t size = ((bytes > 2 * cap ? bytes : 2 * cap) + kPiece - 1) / kPiece * kPiece;
+            unsigned char* more = memory.get(size);
+            if (!more && size > bytes) more = memory.get(size = bytes);
+            if (!more) return false;
+            if (at) {
+                if (!memory.wait()) {
+                    memory.put(more);
+                    return false;
+                }
+                memory.put(at);
+            }
+            at = more;
+            cap = size;
+            clear = false;
+        }
+        if (!clear || numbers_start_again) clear = memory.clear(at, cap);
+        return clear;
+    }
 };
 
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
@@ -68,7 +98,7 @@ __device__ __forceinline__ uint64_t gang_peek_at(const uint64_t* base, uint32_t 
 }
 // By the last workgroup to leave: nobody waits in this launch any more.
 __device__ __forceinline__ void gang_ended(const GangArgs& g) {
-    __hip_atomic_store(g.ended, g.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(g.ended, g.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 // Looks at N words at a time, look(v), until all of them carry the launch's number; *s_gone (LDS) is set if the wait was given up.
 template <int N, typename Look>
@@ -99,8 +129,9 @@ __device__ __forceinline__ void gang_wait(const GangArgs& g, int* s_gone, Look l
 }
 #endif
 
-// Set-up on the context's device; where it fails no such launch is made there.
-void gang_set_up(const gpga_ctx* c);
-// Around a launch; false, and nothing is held, if it cannot be made now.
-bool gang_begin(const gpga_ctx* c, GangArgs* g);
+// A context comes to its device and goes; one that did not come makes no such launch.
+void gang_join(gpga_ctx* c);
+void gang_leave(gpga_ctx* c);
+// Around a launch that exchanges through `bytes` of memory; false, and nothing is held, if it cannot be made now.
+bool gang_begin(const gpga_ctx* c, size_t bytes, GangArgs* g, unsigned char** base);
 void gang_end(const gpga_ctx* c, bool launched);

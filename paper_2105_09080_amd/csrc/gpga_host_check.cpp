@@ -380,7 +380,7 @@ void gang_turns() {
     ended = 2;
     expect(t.take(&b, false, ended), "another stream when the last one has ended");
     expect(!t.take(&a, false, ended), "the first stream while the second is at it");
-    t.undo();
+    t.undo(2);
     expect(t.take(&a, false, ended), "a launch that failed holds nobody back");
     expect(!t.take(&a, true, ended), "a stream that every thread has its own of is another one");
     ended = 3;
@@ -393,10 +393,65 @@ void gang_turns() {
     ended = 0xfffffffeu;
     for (int j = 0; j < 4; ++j) {
         expect(t.take(j % 2 ? &a : &b, false, ended), "numbers start again");
-        expect(!t.take(j % 2 ? &b : &a, false, ended), "numbers start again, another stream");
+        expect(!t.take(j % 2 ? &b : &a, false, ended) && t.number != 0, "numbers start again, another stream");
         ended = t.number;
     }
     std::printf("gang_turns done\n");
+}
+
+// The memory of such launches, of a device that refuses.
+struct FakeMemory {
+    size_t left = 0;            // bytes the device has
+    bool waits = true, clears = true;
+    int waited = 0, cleared = 0, held = 0;
+    std::vector<std::pair<unsigned char*, size_t>> blocks;
+    unsigned char* get(size_t bytes) {
+        if (bytes > left) return nullptr;
+        left -= bytes;
+        ++held;
+        blocks.push_back({new unsigned char[bytes], bytes});
+        return blocks.back().first;
+    }
+    void put(unsigned char* p) {
+        for (auto& b : blocks)
+            if (b.first == p) {
+                left += b.second;
+                --held;
+                b = {nullptr, 0};
+                delete[] p;
+                return;
+            }
+        expect(false, "exchange memory given back twice");
+    }
+    bool wait() { return ++waited, waits; }
+    bool clear(unsigned char* p, size_t bytes) {
+        for (size_t e = 0; clears && e < bytes; ++e) p[e] = 0;
+        return ++cleared, clears;
+    }
+};
+void gang_space() {
+    constexpr size_t MB = 1 << 20;
+    FakeMemory m;
+    GangSpace s;
+    expect(!s.room(3 * MB, false, m) && !s.at && m.held == 0, "no memory for the first launch");
+    m.left = 100 * MB;
+    m.clears = false;
+    expect(!s.room(3 * MB, false, m), "memory that cannot be cleared is not used");
+    m.clears = true;
+    expect(s.room(3 * MB, false, m) && s.cap == 4 * MB && m.cleared == 2 && m.waited == 0, "cleared later, waited for nobody");
+    expect(s.room(4 * MB, false, m) && s.room(1, false, m) && m.cleared == 2 && m.held == 1, "neither grown nor cleared again");
+    expect(s.room(4 * MB, true, m) && m.cleared == 3, "numbers start again");
+    expect(s.room(5 * MB, false, m) && s.cap == 8 * MB && m.waited == 1 && m.held == 1 && m.cleared == 4, "grown twofold, the old block given back");
+    m.waits = false;
+    expect(!s.room(9 * MB, false, m) && s.cap == 8 * MB && m.held == 1, "the old block may still be in use");
+    m.waits = true;
+    m.left = 11 * MB;
+    expect(s.room(10 * MB, false, m) && s.cap == 10 * MB && m.held == 1, "what is needed where twice as much is not to be had");
+    m.left = 0;
+    expect(!s.room(11 * MB, false, m) && s.cap == 10 * MB && s.room(10 * MB, false, m), "refused, and smaller launches keep what there is");
+    m.put(s.at);
+    expect(m.held == 0, "all exchange memory given back");
+    std::printf("gang_space done\n");
 }
 
 // The exchange buffers of k_column_run.  What wavefronts do between two barriers is in no order, so a buffer must not be read by
@@ -498,6 +553,7 @@ int main() {
     rows_deal();
     rows_run_lds();
     gang_turns();
+    gang_space();
     named_graphs();
     rejected_matrices();
     schedules();

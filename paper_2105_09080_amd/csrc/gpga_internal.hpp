@@ -128,9 +128,7 @@ struct gpga_ctx {
     size_t partials_cap = 0;  // in doubles
     double* host_scalar = nullptr;  // pinned, 1 double
     uint32_t* loss_left = nullptr;       // k_rows_loss_short: workgroups of a node that have ended, 0 between launches; not its own allocation
-    unsigned char* run_space = nullptr;  // what the workgroups of k_rows_run exchange
-    size_t run_space_cap = 0;            // in bytes
-    uint32_t run_number = 0;             // of the last such launch, 0: run_space is not cleared yet
+    bool in_gang = false;                // gang_join (gpga_gang.hpp)
 
     // launch geometry overrides (0 = automatic)
     int opt_unroll = 0;

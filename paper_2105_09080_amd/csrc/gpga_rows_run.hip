@@ -38,7 +38,7 @@ struct RowsRunArgs {
     float* x_other;      // the array x is not in
     float* m;
     float* g;            // NULL: the last iteration's gradients are not wanted
-    float* m_keep;       // n x d
+    uint64_t* m_keep;    // words: n x d
     const float* feat;   // n x M x d
     const float* tgt;    // n x M
     const int32_t* idx;  // T x n x B, or NULL: rows 0 .. B-1
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
             if (a.mom) m = a.m[o];
             // kept for a launch that has to be done again
             if (a.T % 2 == 0) gang_put32(reinterpret_cast<uint32_t*>(a.x_other + o), __float_as_uint(x));
-            if (a.mom) gang_put32(reinterpret_cast<uint32_t*>(a.m_keep + (int64_t)node * d + c0 + cc), __float_as_uint(m));
+            if (a.mom) gang_put(a.m_keep + (int64_t)node * d + c0 + cc, a.gang.number, __float_as_uint(m));
         }
         sX[cc] = x;
         sM[cc] = m;
@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
         for (int cc = tid; cc < wcols && from + cc < d; cc += nthr) {
             const int64_t o = (int64_t)i * a.ld + from + cc;
             if (a.T % 2 == 0) x[o] = y[o];
-            if (a.mom) a.m[o] = a.m_keep[(int64_t)i * d + from + cc];
+            if (a.mom) a.m[o] = __uint_as_float((uint32_t)gang_peek(a.m_keep + (int64_t)i * d + from + cc));
         }
     }
     __syncthreads();
@@ -701,13 +701,13 @@ double two_launches_us(const gpga_ctx* c, int32_t B) { return 8.6 + 0.38e-6 * (4
 
 size_t round64(size_t bytes) { return (bytes + 63) & ~(size_t)63; }
 
-struct RunSpace {  // of the context's exchange memory, in bytes
+struct RunSpace {  // of the exchange memory, in bytes; the device's launches agree on what is not words
     size_t words, finished, keep, wz, wy, wmean, wloss, total;
     RunSpace(const gpga_ctx* c, const RunPlan& p, int32_t B, int64_t T) {
         words = 0;
         finished = 64;
         keep = finished + round64((size_t)c->num_cus * sizeof(uint32_t));
-        wz = keep + round64((size_t)c->n * c->d * sizeof(float));
+        wz = keep + (c->mu != 0.f ? round64((size_t)c->n * c->d * 8) : 0);
         wy = wz + round64((size_t)T * c->n * B * p.P * 16);
         wmean = wy + round64((size_t)T * c->n * c->d * 8);
         wloss = wmean + round64((size_t)T * c->d * 8);
@@ -758,32 +758,14 @@ hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int
     const RunPlan& p = run.plan;
     if (T < 1 || T > run.most) return hipErrorInvalidValue;
     const RunSpace at(c, p, Beff, T);
-    if (c->run_space_cap < at.total) {
-        // room for the longest launch of these batches, so that runs of other lengths find it
-        const size_t need = RunSpace(c, p, Beff, run.most).total;
-        hipError_t e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return e;
-        if (c->run_space) (void)hipFree(c->run_space);
-        c->run_space = nullptr;
-        c->run_space_cap = 0;
-        e = hipMalloc(reinterpret_cast<void**>(&c->run_space), need);
-        if (e != hipSuccess) return e;
-        c->run_space_cap = need;
-        c->run_number = 0;
-    }
-    if (c->run_number == 0 || c->run_number == 0xffffffffu) {  // words of older launches carry smaller numbers
-        const hipError_t e = hipMemsetAsync(c->run_space, 0, c->run_space_cap, c->stream);
-        if (e != hipSuccess) return e;
-        c->run_number = 0;
-    }
-    ++c->run_number;
     RowsRunArgs a;
-    unsigned char* const base = c->run_space;
+    unsigned char* base = nullptr;
+    if (!gang_begin(c, at.total, &a.gang, &base)) return hipErrorNotReady;
     a.x = c->x;
     a.x_other = c->x_new;
     a.m = c->m;
     a.g = want_g ? c->g : nullptr;
-    a.m_keep = reinterpret_cast<float*>(base + at.keep);
+    a.m_keep = reinterpret_cast<uint64_t*>(base + at.keep);
     a.feat = c->feat;
     a.tgt = c->tgt;
     a.idx = idx;
@@ -795,7 +777,6 @@ hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int
     a.wloss = reinterpret_cast<uint64_t*>(base + at.wloss);
     a.gang.words = reinterpret_cast<GangWords*>(base);
     a.gang.finished = reinterpret_cast<uint32_t*>(base + at.finished);
-    a.gang.number = c->run_number;
     a.gang.limit = (uint32_t)(c->opt_run_wait_us * 1e-6 * c->clock_hz);
     a.ld = c->ld;
     a.d = c->d;
@@ -827,7 +808,6 @@ hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int
     }
     const int slots = slots_for(p.slots, !idx);
     const RunLds lds(c->n, Beff, p.w, p.QW, p.RG, slots, idx ? T * Beff : Beff, sparse ? c->csr_max_row : 0);
-    if (!gang_begin(c, &a.gang)) return hipErrorNotReady;
     const hipError_t e = launch_run(c, a, slots, a.threads, (size_t)lds.bytes);
     gang_end(c, e == hipSuccess);
     return e;

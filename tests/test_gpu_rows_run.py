@@ -217,6 +217,27 @@ def test_two_streams_and_threads(hx):
         sim.close(), ref.close()
 
 
+def test_contexts_in_turn_exchange_through_one_memory(hx):
+    """Nothing is waited for between calls: words of other contexts and launches lie where a launch's own go, and the memory grows
+    while launches that use it are under way."""
+    shapes = [(8, 1000, 24, 16, "ring", 0.9), (20, 333, 24, 8, "expo", 0.0), (4, 36, 24, 5, "expo1", 0.9), (64, 700, 24, 12, "grid", 0.9),
+              (32, 5120, 20, 32, "ring", 0.9), (8, 1001, 24, 0, "full", 0.0)]
+    T, rounds = 4, 3
+    sims = [make(hx, n, d, M, batch, T, topology, 2, momentum) for n, d, M, batch, topology, momentum in shapes]
+    refs = [make(hx, n, d, M, batch, T, topology, 2, momentum) for n, d, M, batch, topology, momentum in shapes]
+    for _ in range(rounds):
+        for sim, idx in sims:
+            sim.run(T, idx)
+            assert int(sim.query("step_path")) == 12
+    for (sim, _), (ref, idx), shape in zip(sims, refs, shapes):
+        ref.set_option("rows_run", 0)
+        for _ in range(rounds):
+            ref.run(T, idx)
+        for u, v in zip(results(sim, shape[-1]), results(ref, shape[-1])):
+            assert np.abs(u - v).max() <= rounds * TOL * np.abs(v).max()
+        sim.close(), ref.close()
+
+
 def busy(stream):
     """Some 100 ms of other work in the stream: one wavefront."""
     with torch.cuda.stream(stream):
@@ -284,7 +305,7 @@ def test_binding_another_stream_within_a_capture(hx):
         s.set_option("rows_run", 1)
         s.run(4, i)
         assert int(s.query("step_path")) == 12
-    torch.cuda.synchronize()
+        torch.cuda.synchronize()             # so that none is under way in the other stream
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=stream):
         fork.wait_stream(stream)

@@ -102,6 +102,10 @@ def test_launches_that_wait_within_themselves_are_never_under_way_in_two_streams
     assert ["gang_turns", "done"] in facts
 
 
+def test_exchange_memory_that_cannot_be_had_is_refused_and_leaves_what_there_is(facts):
+    assert ["gang_space", "done"] in facts
+
+
 def test_no_iteration_writes_an_exchange_buffer_that_another_reads(facts):
     """Local SGD and gossip with averages in every H-th of 64 iterations; turns by iteration, which W = I has no barriers for,
     are found in every schedule with iterations between its averages."""
