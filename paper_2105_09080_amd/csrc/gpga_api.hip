@@ -281,9 +281,9 @@ gpga_status gpga_create(gpga_ctx** out, int32_t n, int64_t d, int32_t topology, 
         double* static_ptr = nullptr;
         (void)static_scratch_for_device(c->device, &static_ptr);
     }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->host_scalar), sizeof(double), hipHostMallocDefault) !=
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->host), sizeof(HostWords), hipHostMallocDefault) !=
         hipSuccess) {
-        c->host_scalar = nullptr;
+        c->host = nullptr;
         (void)gpga_destroy(c);
         return GPGA_ENOMEM;
     }
@@ -309,8 +309,7 @@ gpga_status gpga_destroy(gpga_ctx* c) {
     if (c->pace_states) (void)hipFree(c->pace_states);
     gang_leave(c);
     free_csr_device(c);
-    if (c->host_scalar) (void)hipHostFree(c->host_scalar);
-    if (c->aga_state) (void)hipHostFree(c->aga_state);
+    if (c->host) (void)hipHostFree(c->host);
     delete c;
     return s;
 }
@@ -668,10 +667,8 @@ static gpga_status run_iteration(gpga_ctx* c, const int32_t* idx, int32_t B, boo
 
 // Several iterations of gpga_run in one launch; *done is false if it cannot be launched now.
 static gpga_status run_chunk(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g, bool* done) {
-    hipError_t e = launch_rows_run(c, run, T, idx, want_g);
-    *done = e != hipErrorNotReady;
+    *done = launch_rows_run(c, run, T, idx, want_g);
     if (!*done) return GPGA_OK;
-    if (e != hipSuccess) return hip_fail(c, e, "trajectory kernel launch");
     c->last_path = PATH_ROWS_RUN;
     c->last_paced = 0;
     c->last_lane_bytes = 16;
@@ -679,11 +676,11 @@ static gpga_status run_chunk(gpga_ctx* c, const RowsRun& run, int32_t T, const i
     if (T % 2) std::swap(c->x, c->x_new);  // X is where T separate steps would have left it
     c->k += T;
     if (!c->aga) return GPGA_OK;
-    e = hipStreamSynchronize(c->stream);
+    const hipError_t e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
-    c->aga_C = c->aga_state->since;
-    c->H = c->aga_state->period;
-    c->aga_F_init = c->aga_state->first_loss;
+    c->aga_C = c->host->aga.since;
+    c->H = c->host->aga.period;
+    c->aga_F_init = c->host->aga.first_loss;
     return GPGA_OK;
 }
 
@@ -693,11 +690,11 @@ static gpga_status aga_average(gpga_ctx* c, int64_t k, const float* loss_dev) {
     // F = (1/n) sum_i F_i of this iteration's minibatches: one scalar back to the host
     hipError_t e = launch_mean_f32(c, loss_dev, c->n, c->partials);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(c->host_scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+        e = hipMemcpyAsync(&c->host->scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "loss average");
     RowsRunAga state = aga_begin(c);
-    state.step(k, *c->host_scalar);
+    state.step(k, c->host->scalar);
     c->aga_F_init = state.first_loss;
     c->H = state.period;
     return GPGA_OK;
@@ -732,10 +729,6 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
         // average, which the counter tells beforehand
         gpga_status s = grow_f32(c, &c->aga_loss, &c->aga_loss_cap, (size_t)c->n);
         if (s != GPGA_OK) return s;
-        if (!c->aga_state && hipHostMalloc(reinterpret_cast<void**>(&c->aga_state), sizeof(RowsRunAga), hipHostMallocDefault) != hipSuccess) {
-            c->aga_state = nullptr;
-            return fail(c, GPGA_ENOMEM, "hipHostMalloc(adaptive period)");
-        }
         s = run_chunks();
         if (s != GPGA_OK) return s;
         for (; j < T; ++j) {
@@ -840,11 +833,11 @@ gpga_status gpga_consensus_error(gpga_ctx* c, double* out_host) {
     size_t need = 0;
     hipError_t e = launch_consensus_sq(c, &need);
     if (e != hipSuccess) return hip_fail(c, e, "consensus kernel launch");
-    e = hipMemcpyAsync(c->host_scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(&c->host->scalar, c->partials, sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync");
     e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
-    *out_host = std::sqrt(*c->host_scalar);
+    *out_host = std::sqrt(c->host->scalar);
     return GPGA_OK;
 }
 

@@ -67,6 +67,12 @@ struct RowsRunAga {
     }
 };
 
+// What kernels and copies leave for the host.
+struct HostWords {
+    double scalar;
+    RowsRunAga aga;  // adaptive period behind a launch of several iterations
+};
+
 // Arrays of at least this many bytes (n x d x 4) run the fused step as paced persistent launches.  Measured on
 // the ring walk with n = 64: 281 MB (0.3 ms) 4.1 TB/s paced against 4.9 one-shot, 563 MB equal, 1.1 GB 5.3
 // against 4.9: a paced launch ends about 100 us after its plan whatever its length.  Walks and averages of up to 64 rows
@@ -126,7 +132,7 @@ struct gpga_ctx {
     size_t coef_cap = 0;    // in floats
     double* partials = nullptr;
     size_t partials_cap = 0;  // in doubles
-    double* host_scalar = nullptr;  // pinned, 1 double
+    HostWords* host = nullptr;  // pinned
     uint32_t* loss_left = nullptr;       // k_rows_loss_short: workgroups of a node that have ended, 0 between launches; not its own allocation
     bool in_gang = false;                // gang_join (gpga_gang.hpp)
 
@@ -193,7 +199,6 @@ struct gpga_ctx {
     double aga_F_init = 0.0;
     float* aga_loss = nullptr;  // n minibatch losses (library-owned; used by gpga_run)
     size_t aga_loss_cap = 0;
-    RowsRunAga* aga_state = nullptr;  // pinned: what a launch of several iterations leaves
 
     char err[256] = {0};
 };

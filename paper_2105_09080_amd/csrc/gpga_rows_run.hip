@@ -667,6 +667,8 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
     if (tid == 0) gang_ended(a.gang);
 }
 
+// Success is what the launch itself returns: hipGetLastError may tell of an older call's failure, and who is told that nothing was
+// launched takes the iterations another way.
 template <int S, int HELD>
 hipError_t launch_slots(const gpga_ctx* c, const RowsRunArgs& a, int threads, size_t lds) {
     static bool attr_set[64] = {false};  // per instantiation and device: more than the default 64 KiB of dynamic LDS
@@ -677,8 +679,10 @@ hipError_t launch_slots(const gpga_ctx* c, const RowsRunArgs& a, int threads, si
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((k_rows_run<S, HELD>), dim3((unsigned)(a.n * a.P)), dim3((unsigned)threads), lds, c->stream, a);
-    return hipGetLastError();
+    RowsRunArgs args = a;
+    void* const packed[] = {&args};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&k_rows_run<S, HELD>), dim3((unsigned)(a.n * a.P)), dim3((unsigned)threads),
+                           const_cast<void**>(packed), lds, c->stream);
 }
 
 hipError_t launch_run(const gpga_ctx* c, const RowsRunArgs& a, int slots, int threads, size_t lds) {
@@ -753,14 +757,14 @@ RowsRun rows_run_for(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int3
     return run;
 }
 
-hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g) {
+bool launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g) {
     const int32_t Beff = run.B;
     const RunPlan& p = run.plan;
-    if (T < 1 || T > run.most) return hipErrorInvalidValue;
+    if (T < 1 || T > run.most) return false;
     const RunSpace at(c, p, Beff, T);
     RowsRunArgs a;
     unsigned char* base = nullptr;
-    if (!gang_begin(c, at.total, &a.gang, &base)) return hipErrorNotReady;
+    if (!gang_begin(c, at.total, &a.gang, &base)) return false;
     a.x = c->x;
     a.x_other = c->x_new;
     a.m = c->m;
@@ -769,7 +773,7 @@ hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int
     a.feat = c->feat;
     a.tgt = c->tgt;
     a.idx = idx;
-    a.aga = c->aga ? c->aga_state : nullptr;
+    a.aga = c->aga ? &c->host->aga : nullptr;
     if (c->aga) a.begin = aga_begin(c);
     a.wz = reinterpret_cast<uint64_t*>(base + at.wz);
     a.wy = reinterpret_cast<uint64_t*>(base + at.wy);
@@ -810,5 +814,6 @@ hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int
     const RunLds lds(c->n, Beff, p.w, p.QW, p.RG, slots, idx ? T * Beff : Beff, sparse ? c->csr_max_row : 0);
     const hipError_t e = launch_run(c, a, slots, a.threads, (size_t)lds.bytes);
     gang_end(c, e == hipSuccess);
-    return e;
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
 }

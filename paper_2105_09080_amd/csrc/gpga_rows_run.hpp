@@ -65,8 +65,8 @@ struct RowsRun {
 // Several iterations on stored features in one launch, for `wanted` iterations on this context and batch.  Under an adaptive
 // period the launch decides itself which iterations average and leaves the period's state in host memory.
 RowsRun rows_run_for(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int32_t B);
-// T <= run.most; hipErrorNotReady if it cannot be made now.
-hipError_t launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g);
+// T <= run.most; false if it cannot be made now, and then nothing was launched and no error is left behind.
+bool launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* idx, bool want_g);
 
 // Rows a thread has room for.
 inline int slots_for(int rows, bool fixed) {

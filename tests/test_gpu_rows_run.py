@@ -294,6 +294,37 @@ def test_a_launch_under_way_in_another_stream_leaves_one_iteration_a_launch(hx):
     a.close()
 
 
+def loaded_hip():
+    import ctypes
+    with open("/proc/self/maps") as f:
+        paths = {line.split()[-1] for line in f if "libamdhip64" in line}
+    assert len(paths) == 1
+    return ctypes.CDLL(paths.pop())
+
+
+@pytest.mark.parametrize("how", ["not ready", "invalid"])
+def test_an_error_that_another_call_left_is_not_the_launchs_own(hx, how):
+    import ctypes
+    hip = loaded_hip()
+    sim, idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
+    ref, ref_idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
+    ref.set_option("rows_run", 0)
+    ref.run(4, ref_idx)
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    if how == "not ready":
+        busy(other)
+        assert hip.hipStreamQuery(ctypes.c_void_p(other.cuda_stream)) == 600
+    else:
+        assert hip.hipSetDevice(1000) != 0
+    sim.run(4, idx)
+    hip.hipGetLastError()
+    assert int(sim.query("step_path")) == 12 and sim.k == 4
+    torch.cuda.synchronize()
+    assert_alike(results(sim, 0.9), results(ref, 0.9))
+    sim.close(), ref.close()
+
+
 def test_binding_another_stream_within_a_capture(hx):
     from paper_2105_09080_amd import binding as B
     stream, fork = torch.cuda.Stream(), torch.cuda.Stream()
