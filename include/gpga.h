@@ -244,8 +244,9 @@ gpga_status gpga_check_mixing_csr(int32_t n, const int64_t* row_ptr_host, const 
  * estimate F_init <- (F_init + F)/2 is refreshed (iteration k < warmup_iters;
  * F_init starts at 0) or H <- ceil(F_init / F * H_init), kept in [1, H_max].
  * loss_dev: n floats on the device, the minibatch losses F_i(x_i^(k); xi_i) of
- * this iteration (gpga_local_loss, called before the step).  Averaging steps, and
- * gpga_run, synchronise the stream (the scalar, or the period, is read back).  1 <= H_init <= H_max. */
+ * this iteration (gpga_local_loss, called before the step).  Averaging steps
+ * synchronise the stream (one scalar is read back; gpga_run on stored features reads the period
+ * once for up to 32 iterations that contain averages).  1 <= H_init <= H_max. */
 gpga_status gpga_aga_enable(gpga_ctx* ctx, int64_t H_init, int64_t warmup_iters, int64_t H_max);
 gpga_status gpga_aga_step(gpga_ctx* ctx, const float* loss_dev);
 /* Current averaging period H. */

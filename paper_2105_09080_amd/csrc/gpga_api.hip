@@ -676,6 +676,10 @@ static gpga_status run_chunk(gpga_ctx* c, const RowsRun& run, int32_t T, const i
     if (T % 2) std::swap(c->x, c->x_new);  // X is where T separate steps would have left it
     c->k += T;
     if (!c->aga) return GPGA_OK;
+    if (c->aga_C + T < c->H) {  // no average among them: nothing to read back
+        c->aga_C += T;
+        return GPGA_OK;
+    }
     const hipError_t e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
     c->aga_C = c->host->aga.since;

@@ -325,6 +325,35 @@ def test_an_error_that_another_call_left_is_not_the_launchs_own(hx, how):
     sim.close(), ref.close()
 
 
+def test_iterations_without_an_average_do_not_wait_under_an_adaptive_period(hx):
+    T = 6
+    out = []
+    for fused in (True, False):
+        sim, idx = make(hx, 16, 512, 64, 8, 5 * T, "expo1", 0, 0.9, stream=torch.cuda.Stream(), lr=0.5)
+        sim.set_option("rows_run", int(fused))
+        sim.aga_enable(T + 1, 4 * T, 16)
+        sim.run(T, idx)                      # sizes the scratch; the average is the next iteration
+        sim.run(T, idx[T:])                  # ... and then T - 1 without
+        torch.cuda.synchronize()
+        assert int(sim.query("step_path")) == (12 if fused else 9)
+        busy(sim.stream)
+        sim.run(1, idx[2 * T:])
+        assert not sim.stream.query()
+        sim.aga_enable(2 * T + 1, 4 * T, 16)
+        sim.run(T, idx[2 * T:])
+        sim.run(T, idx[3 * T:])
+        assert not sim.stream.query()
+        sim.run(T, idx[4 * T:])              # its first iteration averages
+        if not fused:
+            assert sim.stream.query()
+        torch.cuda.synchronize()
+        out.append((results(sim, 0.9), sim.period))
+        sim.close()
+    assert out[0][1] == out[1][1]
+    for u, v in zip(out[0][0], out[1][0]):
+        assert np.abs(u - v).max() <= 4 * TOL * np.abs(v).max()
+
+
 def test_binding_another_stream_within_a_capture(hx):
     from paper_2105_09080_amd import binding as B
     stream, fork = torch.cuda.Stream(), torch.cuda.Stream()
