@@ -317,8 +317,11 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * margins and iterates (default; from three iterations on, not while a trace is being recorded, and not while the
  * stream is being captured), 0 = one iteration at a time), "run_wait_us" (how long a workgroup of such a launch waits
  * for another, in microseconds, before the launch is given up and its last workgroup does the work alone, 0..10000000,
- * default 100000; while a launch of this kind is under way in one stream, calls on another take one iteration at a time or
- * the forms of small problems, and no call waits for another stream),
+ * default 100000; after two such launches of a context iterations go one at a time for a while, 4096 of them and twice as many
+ * with every further time, or until "rows_run" is set), "run_give_up" (a test of that: the workgroup, 0..255 modulo their
+ * number, that gives such a launch up when its share is done, -1 = none (default); while a launch of this kind is
+ * under way in one stream, calls on another take one iteration at a time or the forms of small problems, and no call
+ * waits for another stream),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
  * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always, on rows
@@ -364,9 +367,10 @@ gpga_status gpga_tune(gpga_ctx* ctx, int32_t launches);
  *       10 circulant sparse W on 225 to 1024 nodes, the whole column tile in LDS and the next one loaded meanwhile,
  *       11 gradient sums, update and mixing in one launch (virtual features, gpga_run),
  *       12 several iterations in one launch (stored features, gpga_run);
+ *   "run_given_up" (launches of the last kind that were given up, option "run_wait_us"; synchronises the stream);
  *   "step_paced" (1 = that launch was a paced persistent launch), "step_lane_bytes" (16, 8 or 4),
  *   "trace_fused" (1 = the consensus-trace entry of that step came from the step kernel's own
- *       sums, 0 = a reduction pass followed or no trace is attached).  These four do not synchronise.
+ *       sums, 0 = a reduction pass followed or no trace is attached).  These three and step_path do not synchronise.
  * EINVAL for an unknown name. */
 gpga_status gpga_query(gpga_ctx* ctx, const char* name, double* value_out);
 

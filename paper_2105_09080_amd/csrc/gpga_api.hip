@@ -287,6 +287,7 @@ gpga_status gpga_create(gpga_ctx** out, int32_t n, int64_t d, int32_t topology, 
         (void)gpga_destroy(c);
         return GPGA_ENOMEM;
     }
+    memset(c->host, 0, sizeof(*c->host));
     if (topology == GPGA_TOPO_GRID || topology == GPGA_TOPO_EXPO) {
         named_graph_csr(topology, n, 0, &c->csr);
         if (upload_csr(c) != GPGA_OK) {
@@ -715,11 +716,13 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
     int64_t j = 0;  // iterations done
     int32_t checked_B = 0;
     RowsRun run;
-    if (T > 1 && check_batch(c, batch_table_dev, B, &checked_B) == GPGA_OK)  // else the first iteration reports it
+    auto at_rest = [&]() { return c->gang_rest.at_rest(__atomic_load_n(&c->host->given_up, __ATOMIC_RELAXED)); };
+    if (T > 1 && check_batch(c, batch_table_dev, B, &checked_B) == GPGA_OK && !at_rest())  // else the first iteration reports it
         run = rows_run_for(c, T, batch_table_dev, B);
+    c->gang_rest.done(T);
     // Several iterations a launch, as long as such launches can be made and more than one iteration is left.
     auto run_chunks = [&]() -> gpga_status {
-        while (run.most > 0 && T - j > 1) {
+        while (run.most > 0 && T - j > 1 && !at_rest()) {
             const int32_t chunk = (int32_t)(T - j < run.most ? T - j : run.most);
             bool done = false;
             const gpga_status s = run_chunk(c, run, chunk, batch(j), j + chunk == T, &done);
@@ -921,6 +924,10 @@ gpga_status gpga_set_option(gpga_ctx* c, const char* name, int64_t value) {
     } else if (!strcmp(name, "rows_run")) {
         if (value != 0 && value != 1) return fail(c, GPGA_EINVAL, "rows_run must be 0 or 1");
         c->opt_rows_run = (int)value;
+        c->gang_rest.left = 0;
+    } else if (!strcmp(name, "run_give_up")) {
+        if (value < -1 || value > 255) return fail(c, GPGA_EINVAL, "run_give_up must be -1 (none) or a workgroup, 0..255");
+        c->opt_run_give_up = (int)value;
     } else if (!strcmp(name, "run_wait_us")) {
         if (value < 0 || value > 10000000) return fail(c, GPGA_EINVAL, "run_wait_us must be 0..10000000");
         c->opt_run_wait_us = (int)value;
@@ -1047,6 +1054,13 @@ gpga_status gpga_query(gpga_ctx* c, const char* name, double* value_out) {
         else if (is("pace_last_elapsed_us")) *value_out = st.last_elapsed * us;
         else if (is("pace_hold")) *value_out = st.hold;
         else return fail(c, GPGA_EINVAL, "unknown pacing field in '%s'", name);
+        return GPGA_OK;
+    }
+    if (!strcmp(name, "run_given_up")) {
+        DeviceGuard guard(c->device);
+        const hipError_t e = c->bound ? hipStreamSynchronize(c->stream) : hipSuccess;
+        if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+        *value_out = __atomic_load_n(&c->host->given_up, __ATOMIC_RELAXED);
         return GPGA_OK;
     }
     if (!strcmp(name, "step_path")) *value_out = c->last_path;

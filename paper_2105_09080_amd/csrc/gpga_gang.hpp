@@ -8,7 +8,7 @@
 // Waits end: the launcher sees to it that such launches of one process do not overlap on a device (GangTurn), but others'
 // kernels may hold compute units, so a wait that is not met within `limit` clock ticks gives up and marks the launch; all
 // other workgroups see the mark in their own waits and leave as well.  The last workgroup to leave a marked launch does the
-// launch's work alone.
+// launch's work alone.  A launch behind one that was given up waits a 64th of that: many may have been queued by then.
 #pragma once
 
 #include <thread>
@@ -26,6 +26,7 @@ struct GangArgs {
     uint32_t number;     // of this launch among those of the device, never 0
     uint32_t limit;      // clock ticks a wait may take
     uint32_t* ended;     // host memory: the last workgroup to leave stores the number there
+    uint32_t* count;     // host memory, the context's: launches that were given up
 };
 
 // Whose launch the last one on a device was.  Two at a time might each hold compute units that the other needs, so a launch is
@@ -96,6 +97,11 @@ __device__ __forceinline__ uint64_t gang_peek(const uint64_t* p) {
 __device__ __forceinline__ uint64_t gang_peek_at(const uint64_t* base, uint32_t index) {  // base uniform
     return gang_peek(reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(base) + (size_t)(index * 8u)));
 }
+// By the workgroup that has done a launch alone.
+__device__ __forceinline__ void gang_done_alone(const GangArgs& g) {
+    const uint32_t before = __hip_atomic_load(g.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(g.count, before + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // By the last workgroup to leave: nobody waits in this launch any more.
 __device__ __forceinline__ void gang_ended(const GangArgs& g) {
     __hip_atomic_store(g.ended, g.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -119,9 +125,10 @@ __device__ __forceinline__ void gang_wait(const GangArgs& g, int* s_gone, Look l
             if (polls == 0) begin = __builtin_amdgcn_s_memrealtime();
             continue;
         }
-        const bool late = __builtin_amdgcn_s_memrealtime() - begin >= g.limit;
+        const uint32_t given_up = gang_get32(&g.words->given_up);
+        const bool late = __builtin_amdgcn_s_memrealtime() - begin >= (given_up + 1 == g.number ? g.limit / 64 : g.limit);
         if (late) gang_put32(&g.words->given_up, g.number);
-        if (late || gang_get32(&g.words->given_up) == g.number) {
+        if (late || given_up == g.number) {
             *s_gone = 1;
             return;
         }

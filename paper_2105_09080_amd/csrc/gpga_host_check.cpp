@@ -396,6 +396,19 @@ void gang_turns() {
         expect(!t.take(j % 2 ? &b : &a, false, ended) && t.number != 0, "numbers start again, another stream");
         ended = t.number;
     }
+    GangRest r;
+    expect(!r.at_rest(0) && !r.at_rest(1), "one launch given up");
+    expect(r.at_rest(2), "two launches given up");
+    r.done(4095);
+    expect(r.at_rest(2), "the rest is not over");
+    r.done(10);
+    expect(!r.at_rest(2) && !r.at_rest(3), "the rest is over, and one more launch given up");
+    expect(r.at_rest(4), "a second rest");
+    r.done(8191);
+    expect(r.at_rest(4), "twice as long");
+    r.done(1);
+    expect(!r.at_rest(4), "over as well");
+    for (uint32_t given_up = 6; given_up < 80; given_up += 2) expect(r.at_rest(given_up) && r.left <= (int64_t)4096 << 10, "the longest rest");
     std::printf("gang_turns done\n");
 }
 

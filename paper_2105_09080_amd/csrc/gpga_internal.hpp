@@ -67,10 +67,29 @@ struct RowsRunAga {
     }
 };
 
+// Launches whose workgroups wait for each other are left alone for a while when two of them were given up: what holds the
+// compute units (another process, a mask, a kernel that does not end) may go on to.  A launch that is given up costs its wait, 100 ms, and the
+// work by one workgroup; 4096 iterations by themselves take some 50 ms, and each further rest is twice as long.
+struct GangRest {
+    uint32_t seen = 0;   // launches that were given up before the last rest
+    int32_t rests = 0;
+    int64_t left = 0;    // iterations of the rest
+    bool at_rest(uint32_t given_up) {
+        if (given_up - seen >= 2) {
+            seen = given_up;
+            left = (int64_t)4096 << (rests < 10 ? rests : 10);
+            ++rests;
+        }
+        return left > 0;
+    }
+    void done(int64_t iterations) { left = left > iterations ? left - iterations : 0; }
+};
+
 // What kernels and copies leave for the host.
 struct HostWords {
     double scalar;
     RowsRunAga aga;  // adaptive period behind a launch of several iterations
+    uint32_t given_up;  // such launches that one workgroup did alone
 };
 
 // Arrays of at least this many bytes (n x d x 4) run the fused step as paced persistent launches.  Measured on
@@ -135,6 +154,7 @@ struct gpga_ctx {
     HostWords* host = nullptr;  // pinned
     uint32_t* loss_left = nullptr;       // k_rows_loss_short: workgroups of a node that have ended, 0 between launches; not its own allocation
     bool in_gang = false;                // gang_join (gpga_gang.hpp)
+    GangRest gang_rest;
 
     // launch geometry overrides (0 = automatic)
     int opt_unroll = 0;
@@ -158,6 +178,7 @@ struct gpga_ctx {
     int opt_column_run = 1;    // 0 = gpga_run takes synthetic gradients one iteration at a time
     int opt_rows_run = 1;      // 0 = gpga_run takes stored features one iteration at a time
     int opt_run_wait_us = 100000;  // how long a workgroup of such a launch waits for another before one does the work alone
+    int opt_run_give_up = -1;  // workgroup that gives such a launch up when it has done its share
     int opt_small_run = 1;     // 0 = gpga_run never takes the single-workgroup path for small problems
     int opt_blocks_per_cu = -1;  // -1 = automatic, 0 = one workgroup per tile group, k = persistent
     int num_cus = 256;

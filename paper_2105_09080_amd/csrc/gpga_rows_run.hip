@@ -64,6 +64,7 @@ struct RowsRunArgs {
     int32_t K;
     int32_t splitters;   // of an average
     float inv_n, mu;
+    int32_t gives_up;    // workgroup that does not store what it has, or -1
     int32_t mean64;      // averages are formed in double precision
     float lr[kRowsRunMaxIters];
     int32_t shift[kRowsRunMaxIters];  // one-peer offset; -1: the iteration ends in a global average (fixed period)
@@ -546,6 +547,10 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
             gone = s_gone_y != 0;
             if (gone) break;
         }
+        if ((int)blockIdx.x == a.gives_up) {
+            if (ct == 0) gang_put32(&a.gang.words->given_up, a.gang.number);
+            gone = true;
+        }
         if (!gone && a.aga && blockIdx.x == 0 && ct == 0) aga_store(a.aga, aga);
         if (!gone) {
             for (int cc = ct; cc < ncol; cc += NT) {
@@ -664,7 +669,10 @@ __global__ void __launch_bounds__(kRowsRunThreads) k_rows_run(const RowsRunArgs 
     if (a.T % 2)
         for (int i = 0; i < n; ++i)
             for (int64_t c = tid; c < d; c += nthr) y[(int64_t)i * a.ld + c] = x[(int64_t)i * a.ld + c];
-    if (tid == 0) gang_ended(a.gang);
+    if (tid == 0) {
+        gang_done_alone(a.gang);
+        gang_ended(a.gang);
+    }
 }
 
 // Success is what the launch itself returns: hipGetLastError may tell of an older call's failure, and who is told that nothing was
@@ -781,6 +789,8 @@ bool launch_rows_run(gpga_ctx* c, const RowsRun& run, int32_t T, const int32_t* 
     a.wloss = reinterpret_cast<uint64_t*>(base + at.wloss);
     a.gang.words = reinterpret_cast<GangWords*>(base);
     a.gang.finished = reinterpret_cast<uint32_t*>(base + at.finished);
+    a.gang.count = &c->host->given_up;
+    a.gives_up = c->opt_run_give_up < 0 ? -1 : c->opt_run_give_up % (c->n * p.P);
     a.gang.limit = (uint32_t)(c->opt_run_wait_us * 1e-6 * c->clock_hz);
     a.ld = c->ld;
     a.d = c->d;

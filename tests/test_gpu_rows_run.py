@@ -81,6 +81,7 @@ def test_several_iterations_a_launch_match_separate_calls(hx, n, d, M, batch, T,
         a.set_option("run_wait_us", 0)   # the first wait that is not met at once ends the launch; one workgroup does it again
     a.run(T, idx_a)
     assert int(a.query("step_path")) == 12 and a.k == T
+    assert (a.query("run_given_up") > 0) == given_up
     separate(b, idx_b, T)
     assert_alike(results(a, momentum), results(b, momentum))
     for e in (*a._bufs, a.g):
@@ -104,6 +105,7 @@ def test_adaptive_period_decided_in_the_launch(hx, n, d, M, batch, T, topology, 
             periods = [sim.period]
             sim.run(T - T // 2, None if idx is None else idx[T // 2:])
             assert int(sim.query("step_path")) == 12
+            assert (sim.query("run_given_up") > 0) == given_up
         else:
             for k in range(T):
                 i = None if idx is None else idx[k]
@@ -138,11 +140,59 @@ def test_averages_of_small_problems_are_formed_in_double_precision(hx, n, d, bat
     sim.set_state(X=x)
     sim.run(4, idx)
     torch.cuda.synchronize()
-    assert int(sim.query("step_path")) == 12
+    assert int(sim.query("step_path")) == 12 and (sim.query("run_given_up") > 0) == given_up
     want = x.astype(np.float64).mean(0)
     got = sim.X.cpu().numpy().astype(np.float64)
     assert (np.abs(got - want) <= (2.0 ** -24 + 1e-8) * np.abs(want)).all()
     sim.close()
+
+
+@pytest.mark.parametrize("last", [False, True])   # workgroup 0 or 255 modulo their number, when the others have stored what they have
+@pytest.mark.parametrize("T", [5, 6])
+@pytest.mark.parametrize("n,d,M,batch,topology,H,momentum,adaptive", [
+    (16, 257, 40, 9, "ring", 4, 0.9, False), (8, 1000, 100, 0, "expo1", 3, 0.0, False), (9, 1203, 33, 8, "expo", 2, 0.9, True),
+    (20, 1001, 40, 16, "grid", 2, 0.0, True), (32, 5120, 20, 32, "ring", 0, 0.9, False)])
+def test_a_launch_given_up_at_its_end_is_done_again_from_its_beginning(hx, n, d, M, batch, topology, H, momentum, adaptive, T, last):
+    out = []
+    for fused in (True, False):
+        sim, idx = make(hx, n, d, M, batch, T, topology, 0 if adaptive else H, momentum)
+        if adaptive:
+            sim.aga_enable(H, 2, 9)
+        sim.set_option("rows_run", int(fused))
+        if fused:
+            from paper_2105_09080_amd import binding as B
+            for value in (-2, 256):
+                with pytest.raises(B.GpgaError):
+                    sim.set_option("run_give_up", value)
+            sim.set_option("run_give_up", 255 if last else 0)
+        sim.run(T, idx)
+        assert sim.query("run_given_up") == int(fused) and sim.k == T
+        assert int(sim.query("step_path")) == (12 if fused else 9)
+        out.append((results(sim, momentum), sim.period))
+        sim.close()
+    assert out[0][1] == out[1][1]
+    assert_alike(out[0][0], out[1][0])
+
+
+def test_launches_that_are_given_up_again_and_again_are_left_alone_for_a_while(hx):
+    T = 6
+    sim, idx = make(hx, 16, 1000, 40, 8, T, "ring", 4, 0.9)
+    ref, ref_idx = make(hx, 16, 1000, 40, 8, T, "ring", 4, 0.9)
+    ref.set_option("rows_run", 0)
+    sim.set_option("run_wait_us", 0)
+    paths = []
+    for call in range(6):
+        if call == 4:
+            sim.set_option("run_wait_us", 100000)
+            sim.set_option("rows_run", 1)
+        sim.run(T, idx)
+        ref.run(T, ref_idx)
+        torch.cuda.synchronize()
+        paths.append(int(sim.query("step_path")))
+    assert paths == [12, 12, 9, 9, 12, 12] and sim.query("run_given_up") == 2
+    for u, v in zip(results(sim, 0.9), results(ref, 0.9)):
+        assert np.abs(u - v).max() <= 6 * TOL * np.abs(v).max()
+    sim.close(), ref.close()
 
 
 def test_rows_outside_the_data_poison_their_node_only(hx):
