@@ -102,8 +102,9 @@ __device__ __forceinline__ void gang_done_alone(const GangArgs& g) {
     const uint32_t before = __hip_atomic_load(g.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(g.count, before + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// By the last workgroup to leave: nobody waits in this launch any more.
+// By the last workgroup to leave: nobody waits in this launch any more, and the words' counter stands at 0 for the next one.
 __device__ __forceinline__ void gang_ended(const GangArgs& g) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __hip_atomic_store(g.ended, g.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 // Looks at N words at a time, look(v), until all of them carry the launch's number; *s_gone (LDS) is set if the wait was given up.
