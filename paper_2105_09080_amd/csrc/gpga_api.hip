@@ -723,7 +723,8 @@ gpga_status gpga_run(gpga_ctx* c, int64_t T, const int32_t* batch_table_dev, int
     // Several iterations a launch, as long as such launches can be made and more than one iteration is left.
     auto run_chunks = [&]() -> gpga_status {
         while (run.most > 0 && T - j > 1 && !at_rest()) {
-            const int32_t chunk = (int32_t)(T - j < run.most ? T - j : run.most);
+            int32_t chunk = (int32_t)(T - j < run.most ? T - j : run.most);
+            if (T - j - chunk == 1) --chunk;  // no iteration is left over by itself
             bool done = false;
             const gpga_status s = run_chunk(c, run, chunk, batch(j), j + chunk == T, &done);
             if (s != GPGA_OK || !done) return s;

@@ -369,6 +369,50 @@ void rows_run_lds() {
     std::printf("rows_run plans %" PRId64 " most_lds %d\n", plans, most);
 }
 
+// Which form a gpga_run on stored features takes, against measured times (us: several iterations a launch, the other form).
+void rows_run_choice() {
+    struct Measured {
+        int n;
+        int64_t d;
+        int B;
+        bool batches;
+        int entries;
+        bool sparse;
+        int T, averages;
+        bool small;      // the other form is one workgroup
+        double run, other;
+        bool adaptive = false;
+    };
+    const Measured rows[] = {
+        {64, 5000, 2, true, 64, true, 16, 0, false, 1269.2, 258.3},  // many entries of W
+        {128, 2000, 2, true, 64, true, 3, 0, false, 168.4, 42.5},
+        {32, 2000, 2, true, 32, true, 3, 0, false, 101.0, 31.3},
+        {128, 5000, 8, true, 32, true, 16, 0, false, 1012.0, 317.1},
+        {104, 5000, 1, true, 2, false, 3, 3, false, 62.5, 44.6},     // averages in every iteration
+        {104, 2000, 1, true, 2, false, 4, 4, false, 54.6, 43.3},
+        {128, 2000, 1, true, 2, false, 3, 3, false, 44.0, 33.5},
+        {4, 2000, 2, true, 2, false, 3, 3, false, 33.4, 26.6},
+        {32, 12000, 1, true, 2, false, 3, 0, false, 35.4, 28.5},     // few iterations
+        {4, 300, 2, true, 2, false, 16, 0, true, 66.1, 56.1},        // little work in one workgroup
+        {8, 1000, 100, false, 2, false, 8, 2, false, 57.9, 76.0},
+        {20, 1001, 16, true, 1, false, 12, 1, false, 71.0, 107.0},
+        {32, 10000, 32, true, 1, false, 16, 2, false, 212.0, 362.0},
+        {32, 801, 8, true, 2, false, 16, 0, false, 76.8, 132.8},
+        {128, 801, 8, true, 5, true, 16, 0, false, 104.0, 198.4},
+        {9, 222, 32, true, 2, false, 16, 0, true, 65.0, 531.0},
+        {6, 2435, 2, true, 0, false, 8, 8, false, 163.0, 205.0, true},
+        {118, 771, 4, true, 5, true, 3, 3, false, 56.0, 80.0, true},
+        {16, 300, 8, true, 2, false, 16, 0, true, 68.8, 285.2},
+    };
+    for (const Measured& m : rows) {
+        const RunWork work{m.n, m.d, m.B, m.batches, m.entries, m.sparse, m.T, m.averages, m.adaptive};
+        const RunPlan p = plan_run(m.n, m.d, 256, m.B, m.batches);
+        const bool taken = p.P && rows_run_pays(work, p, 32, m.small ? one_workgroup_us(work) : two_launches_us(work, true));
+        expect(taken == (m.run < m.other), "the faster form of a run");
+        std::printf("rows_run_choice %d %" PRId64 " %d %d\n", m.n, m.d, m.T, taken ? 1 : 0);
+    }
+}
+
 // Turns of launches whose workgroups wait for each other: two of them are never under way in two streams.
 void gang_turns() {
     const int a = 0, b = 0;
@@ -565,6 +609,7 @@ int main() {
     node_run_sizes();
     rows_deal();
     rows_run_lds();
+    rows_run_choice();
     gang_turns();
     gang_space();
     named_graphs();

@@ -707,10 +707,6 @@ hipError_t launch_run(const gpga_ctx* c, const RowsRunArgs& a, int slots, int th
     return launch_slots<kAheadSlots, ROWS_AHEAD>(c, a, threads, lds);
 }
 
-// An iteration in two launches (k_rows_margin, k_rows_step), measured: 20 x 1001 with 16 samples 8.8 us, 30 x 3000 with 32 13.0,
-// 6 x 11 273 with 50 12.9, 32 x 10 000 with 32 22.4, 14 x 25 247 with 32 25.6.
-double two_launches_us(const gpga_ctx* c, int32_t B) { return 8.6 + 0.38e-6 * (4.0 * c->n * B * c->d); }
-
 size_t round64(size_t bytes) { return (bytes + 63) & ~(size_t)63; }
 
 struct RunSpace {  // of the exchange memory, in bytes; the device's launches agree on what is not words
@@ -740,20 +736,25 @@ RowsRun rows_run_for(const gpga_ctx* c, int64_t wanted, const int32_t* idx, int3
     if (order.U != 4 || order.RL * order.wpb < 2) return no;  // not on these sizes: column_mean adds in no other way
     const int32_t Beff = idx ? B : c->M;
     if (Beff < 1 || Beff > kRowWaves * kRowsRunMaxSlots) return no;
-    // One workgroup alone takes 2 us an iteration and more with every sample and column; this form takes 3 to 4 and some 5 a
-    // launch (16 iterations, us, one workgroup / this: 4 x 32 with one sample 38 / 52, 10 x 40 44 / 52, 20 x 33 with two 68 / 55,
-    // 12 x 100 with 8 151 / 61, 9 x 222 with 32 531 / 65; 8 x 100 with 4, 4 iterations 21.9 / 21.7).
     RowsRun run;
     run.B = Beff;
     run.splitters = order.RL * order.wpb;
     run.mean64 = small_run_fits(c, idx, B);
     if (run.mean64 && (wanted < 4 || (int64_t)c->n * Beff * c->d < 1280)) return no;
     run.plan = plan_run(c->n, c->d, c->num_cus, Beff, idx != nullptr);
-    if (!run.plan.P || run.plan.us > two_launches_us(c, Beff)) return no;
+    if (!run.plan.P) return no;
     int64_t T = kRowsRunMaxWords / ((int64_t)c->n * c->d);
     if (T > kRowsRunMaxIters) T = kRowsRunMaxIters;
     if (idx && T > kRowsRunStaged / Beff) T = kRowsRunStaged / Beff;
     if (T < kRowsRunFewest) return no;
+    RunWork work{c->n, c->d, Beff, idx != nullptr, sparse ? c->csr_max_row : c->topo == GPGA_TOPO_RING ? 2 : c->topo == GPGA_TOPO_EXPO1 ? 1 : 0, sparse, wanted, 0, c->aga};
+    if (c->aga) work.averages = wanted / c->H;
+    else if (c->topo == GPGA_TOPO_FULL) work.averages = wanted;
+    else if (c->H > 0) work.averages = (c->k + wanted) / c->H - c->k / c->H;
+    // (16 iterations, us, one workgroup / this: 4 x 32 with one sample 38 / 52, 10 x 40 44 / 52, 20 x 33 with two 68 / 55,
+    // 12 x 100 with 8 151 / 61, 9 x 222 with 32 531 / 65; 8 x 100 with 4, 4 iterations 21.9 / 21.7).
+    const double other = run.mean64 ? one_workgroup_us(work) : two_launches_us(work, rows_step_fits(c, Beff));
+    if (!rows_run_pays(work, run.plan, (int)T, other)) return no;
     // A stream that is being captured keeps its launches per iteration: the number of a launch is the host's.
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) {

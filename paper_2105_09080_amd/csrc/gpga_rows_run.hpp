@@ -54,6 +54,65 @@ inline RunPlan plan_run(int n, int64_t d, int num_cus, int32_t B, bool batches) 
     return best;
 }
 
+// What a gpga_run is expected to take, us, in this form and in the two it stands for.  Each is a sum of terms fitted to 2362 measured
+// runs (4 to 128 nodes, 64 to 12 000 columns, 1 to 100 samples, 3 to 16 iterations, with and without an average in every one, W of 0 to
+// 64 entries a row; 10 % off at one sigma).
+struct RunWork {
+    int n;
+    int64_t d;
+    int32_t B;
+    bool batches;
+    int entries;        // of W a node reads besides its own: 0, 1 (one peer), 2 (ring), or those of a sparse W's row
+    bool sparse;
+    int64_t T, averages;
+    bool adaptive;      // the host reads back: in the other forms at every average, here once a launch
+    double mb() const { return (double)n * (double)d * 4e-6; }
+};
+
+inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// This form.  A launch costs what loads and stores the state; an iteration the update, a thread's columns, the rows by how many
+// wavefronts share a SIMD, the words of the margins, and a trip for the y of one or a few nodes and columns at a time: 5000 columns
+// on 64 nodes with 64 entries of W a row are 1269 us in 16 iterations, 258 with two launches each.  An average gathers a share of the
+// columns over all nodes, forms their means and hands them on (104 x 5000 with one sample, 3 averages in 3 iterations: 62.5 and 44.6).
+inline double run_us(const RunWork& r, const RunPlan& p, int most) {
+    const int waves = p.QW * p.RG, threads = kWave * std::min(kRowsRunWaves - waves, 4), simd = (waves + 3) / 4;
+    const int cols = (int)std::min<int64_t>(4 * p.w, r.d), passes = ceil_div(cols, threads), share = ceil_div(4 * p.w, r.n);
+    double one = 2.5 + 0.09 * passes + (r.batches || p.slots <= kFixedSlots ? 0.02 : 0.06) * p.slots * simd + 0.08 * r.mb();
+    if (r.batches) one += 0.3e-3 * r.B * p.w;
+    if (p.P > 1) one += 0.94 + 0.46 * ceil_div((int64_t)r.B << log2_ceil(p.P), threads);
+    const int trips = r.entries == 0   ? 0
+                      : r.entries == 1 ? ceil_div(cols, (cols <= 2 * threads ? 2 : 10) * threads)
+                      : r.entries == 2 ? ceil_div(cols, (cols <= threads ? 1 : 5) * threads)
+                      : cols <= threads ? ceil_div(r.entries, 8)
+                                        : ceil_div(cols, 4 * threads) * ceil_div(r.entries, 4);
+    const double gossip = 1.04 * trips + 0.045 * r.entries * passes;
+    const double average = 0.34 + 0.035 * r.n + 0.19 * r.mb() + 0.89 * ceil_div(share, threads) + 0.62 * ceil_div((int64_t)r.n * share, 5 * threads) +
+                           0.34 * ceil_div(cols, (cols <= 2 * threads ? 2 : 10) * threads) + 0.13 * passes;
+    return ceil_div(r.T, most) * (8.7 + 1.6 * r.mb() + (r.adaptive ? 10.0 : 0.0)) + (double)r.T * one + (double)(r.T - r.averages) * gossip + (double)r.averages * average;
+}
+
+// k_rows_margin and k_rows_step in turn; where that does not take the problem the separate passes, at least twice that.
+inline double two_launches_us(const RunWork& r, bool step_fits) {
+    const double one = 7.7 + 0.256 * r.mb() * r.B + 1.2 * r.mb() + 1.74e-3 * r.n * r.B;
+    const double gossip = r.sparse ? 0.38 + 0.04 * r.entries + 0.0375 * r.entries * r.mb() : 0.0, average = 0.75 + 0.1 * r.mb() + (r.adaptive ? 13.0 : 0.0);
+    const double all = 2.0 + (double)r.T * one + (double)(r.T - r.averages) * gossip + (double)r.averages * average;
+    return step_fits ? all : 2.0 * all;
+}
+
+// k_small_run.
+inline double one_workgroup_us(const RunWork& r) {
+    const double nd = (double)r.n * (double)r.d;
+    const double one = 1.85 + 250e-6 * nd * r.B + 540e-6 * nd + 0.035 * r.n * r.B;
+    const double gossip = r.sparse ? 88e-6 * nd * r.entries : 0.0, average = 0.5 + 0.017 * (double)r.d;
+    return 2.0 + (double)r.T * one + (double)(r.T - r.averages) * gossip + (double)r.averages * average;
+}
+
+// This form is to be the faster one by some of what the terms are off, so that few runs lose by it: 404 of the measured ones are
+// slower with it, down to a fifth of the speed, 34 of those that are to take it, down to 0.82; 112 that are not would gain 9 % at the median.
+constexpr double kRowsRunMargin = 1.03;
+inline bool rows_run_pays(const RunWork& r, const RunPlan& p, int most, double other_us) { return kRowsRunMargin * run_us(r, p, most) <= other_us; }
+
 // What the launches of one gpga_run have in common.
 struct RowsRun {
     int32_t most = 0;     // iterations a launch, 0: none of this kind

@@ -454,6 +454,30 @@ def test_a_captured_run_keeps_its_launches_per_iteration(hx):
     sim.close(), ref.close()
 
 
+@pytest.mark.parametrize("n,d,batch,T,H,entries,path", [
+    (104, 2000, 1, 3, 1, 0, 9),       # an average in every one of three iterations
+    (104, 2000, 1, 16, 0, 0, 12),
+    (64, 2000, 2, 8, 0, 64, 9),       # W of 64 entries a row: as many words an iteration and column
+    (64, 2000, 2, 8, 0, 3, 12),
+    (20, 333, 16, 33, 4, 0, 12),      # 32 iterations a launch: none is left over by itself
+    (24, 145, 21, 33, 16, 0, 12),
+])
+def test_runs_take_the_form_that_measured_faster(hx, n, d, batch, T, H, entries, path):
+    out = []
+    for rows_run in (1, 0):
+        sim, idx = make(hx, n, d, 40, batch, T, "ring", H, 0.9)
+        sim.set_option("small_run", 1)
+        sim.set_option("rows_run", rows_run)
+        if entries:
+            sim.set_mixing(sum(np.roll(np.eye(n), o, 1) for o in range(entries)) / entries)
+        sim.run(T, idx)
+        assert int(sim.query("step_path")) == path or not rows_run
+        out.append(results(sim, 0.9))
+        sim.close()
+    for u, v in zip(*out):
+        assert np.abs(u - v).max() <= 4 * TOL * np.abs(v).max()
+
+
 def test_options_and_traces_keep_one_iteration_a_launch(hx):
     sim, idx = make(hx, 16, 1000, 40, 8, 4, "ring", 0, 0.9)
     sim.set_option("rows_run", 0)

@@ -98,6 +98,11 @@ def test_arrays_of_a_trajectory_on_stored_features_lie_on_their_boundaries(facts
     assert int(row[2]) > 3000 and 40_000 < int(row[4]) <= 129 * 1024
 
 
+def test_runs_on_stored_features_take_the_form_that_measured_faster(facts):
+    rows = [f for f in facts if f[0] == "rows_run_choice"]
+    assert len(rows) == 19 and sum(int(f[-1]) for f in rows) == 9
+
+
 def test_launches_that_wait_within_themselves_are_never_under_way_in_two_streams(facts):
     assert ["gang_turns", "done"] in facts
 
