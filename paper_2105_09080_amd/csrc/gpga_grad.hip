@@ -899,9 +899,12 @@ __global__ void __launch_bounds__(kNodeMaxNodes * kNodeLanes + kWave * node_trac
         if (lane == 0) a.trace[a.k0 + t] = sqrt(ss);
     };
 
-    auto column_means = [&](int t) {              // every wavefront takes columns, lanes over rows
+    // Every wavefront takes columns, lanes over rows; a lane with fewer than C of its own has them behind its padding.
+    const int whole = d - d % C, gap = C - d % C;
+    auto column_means = [&](int t) {
         const float* __restrict__ Y = sY + (t & 1) * n * DP;
-        for (int c = wave; c < DP; c += nw) {
+        for (int k = wave; k < d; k += nw) {
+            const int c = k < whole ? k : k + gap;
             double v = 0.0;
             for (int r = lane; r < n; r += kWave) v += (double)Y[r * DP + c];
             v = group_sum_last(v, kWave);
