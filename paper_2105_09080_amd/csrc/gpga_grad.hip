@@ -231,9 +231,10 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float* __restrict__ loss
 // Bound: reading the rows, and an exponential and a logarithm in fp64 a sample.  Us, two launches and a column at a time
 // -> this form: 100 x 8000 x 10 13.5 -> 13.0, 20 x 8000 x 10 7.2 -> 5.6, 100 x 4000 x 16 14.1 -> 8.7, 64 x 2000 x 20 8.2 -> 5.6, 50 x
 // 4000 x 32 23.4 -> 8.8 (rows of 32 columns: every lane on the same LDS bank), 10 x 200 x 10 6.3 -> 3.9, 120 x 16 000 x 10 23.6 both
-// (26.8 with x in LDS too).  Workgroups of several
-// times 256 rows, the next ones loaded ahead, took 13.3 - 16 on the first.
-template <int KIND, int V>
+// (26.8 with x in LDS too).  Workgroups of several times 256 rows, the next ones loaded ahead, took 13.3 - 16 on the first.
+// Columns are unrolled twofold and the form whose sums are a launch of their own knows nothing of counts: with eight columns and
+// both in one kernel narrow rows lost to the start of their workgroups (540 x 33 000 x 1, 69 660 workgroups, 73.8 -> 80.4, now 74.8).
+template <int KIND, int V, bool ALONG>
 __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict__ feat, const float* __restrict__ tgt,
                                                          const float* __restrict__ x, int64_t ld,
                                                          const int32_t* __restrict__ idx, int32_t B, int32_t M,
@@ -271,6 +272,7 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
         } else {
             typedef float vec __attribute__((ext_vector_type(V)));
             const float* __restrict__ f = s_rows + threadIdx.x * d;
+#pragma unroll 2
             for (int c = 0; c < d; c += V) {
                 const vec v = *reinterpret_cast<const vec*>(f + c);
 #pragma unroll
@@ -282,11 +284,12 @@ __global__ void __launch_bounds__(256) k_rows_loss_short(const float* __restrict
         term = __builtin_nan("");  // a sample index outside [0, M): no access, the node's loss becomes NaN
     }
     const double t = block_sum(term, s_buf);
-    if (gridDim.x == 1 || !left) {
-        if (threadIdx.x == 0) {
-            if (gridDim.x == 1) loss[i] = (float)t;
-            else partials[i * gridDim.x + blockIdx.x] = t;  // for k_loss_chunks
-        }
+    if (!ALONG) {
+        if (threadIdx.x == 0) partials[i * gridDim.x + blockIdx.x] = t;  // for k_loss_chunks
+        return;
+    }
+    if (gridDim.x == 1) {
+        if (threadIdx.x == 0) loss[i] = (float)t;
         return;
     }
     if (threadIdx.x == 0) {
@@ -1100,23 +1103,26 @@ constexpr int64_t kLossCachedBytes = 32 << 20;
 // time, and while most workgroups are resident at once, since each stays until its sum has arrived (us along / apart: 235
 // workgroups a node, 8 x 60 000 x 30 21.9 / 19.6; 3840, 120 x 8000 x 20 21.4 / 22.0).
 constexpr unsigned kLossLastMost = 64;
-template <int V>
-static void launch_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
+template <int KIND, int V>
+static void launch_loss_kind(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
     // the partial sums (one double per 256 samples) take the place of the per-sample terms
     double* partials = reinterpret_cast<double*>(c->coef);
     const dim3 grid((unsigned)((Beff + 255) / 256), (unsigned)c->n), block(256);
     const size_t lds = idx ? 0 : (size_t)256 * c->d * sizeof(float);
     const int cached = (int64_t)c->n * c->M * c->d * 4 <= kLossCachedBytes;
-    uint32_t* const left = grid.x <= kLossLastMost && (int64_t)grid.x * grid.y <= 16 * c->num_cus ? c->loss_left : nullptr;
-    if (c->problem == PROB_LSQ) {
-        hipLaunchKernelGGL((k_rows_loss_short<PROB_LSQ, V>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx,
-                           Beff, c->M, (int32_t)c->d, cached, partials, left, loss_out);
-    } else {
-        hipLaunchKernelGGL((k_rows_loss_short<PROB_LOGREG, V>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld,
-                           idx, Beff, c->M, (int32_t)c->d, cached, partials, left, loss_out);
+    if (grid.x == 1 || (c->loss_left && grid.x <= kLossLastMost && (int64_t)grid.x * grid.y <= 16 * c->num_cus)) {
+        hipLaunchKernelGGL((k_rows_loss_short<KIND, V, true>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx, Beff,
+                           c->M, (int32_t)c->d, cached, partials, c->loss_left, loss_out);
+        return;
     }
-    if (!left && grid.x > 1)
-        hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials, (int32_t)grid.x, loss_out);
+    hipLaunchKernelGGL((k_rows_loss_short<KIND, V, false>), grid, block, lds, c->stream, c->feat, c->tgt, c->x, c->ld, idx, Beff, c->M,
+                       (int32_t)c->d, cached, partials, nullptr, nullptr);
+    hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)c->n), dim3(kWave), 0, c->stream, partials, (int32_t)grid.x, loss_out);
+}
+template <int V>
+static void launch_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
+    if (c->problem == PROB_LSQ) launch_loss_kind<PROB_LSQ, V>(c, idx, Beff, loss_out);
+    else launch_loss_kind<PROB_LOGREG, V>(c, idx, Beff, loss_out);
 }
 static hipError_t launch_rows_loss_short(const gpga_ctx* c, const int32_t* idx, int32_t Beff, float* loss_out) {
     if (c->d % 4 == 0) launch_loss_short<4>(c, idx, Beff, loss_out);
