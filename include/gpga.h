@@ -180,16 +180,20 @@ gpga_status gpga_step(gpga_ctx* ctx);
 
 /* The loop of Algorithm 1: T iterations, each gpga_local_grad followed by
  * gpga_step, enqueued from one call (no per-iteration trip through the caller;
- * nothing synchronises).  batch_table_dev: T x n x B int32 on the device, iteration
+ * nothing synchronises, but for scratch that has to grow).  batch_table_dev: T x n x B int32 on the device, iteration
  * j of this call uses rows [j*n*B, (j+1)*n*B); NULL with B = 0 means full batches
  * (and is what the synthetic problem takes).  Stops at the first failing call and
  * returns its status; iterations before it stay enqueued.  With adaptive averaging
  * enabled (gpga_aga_enable) every iteration is a gpga_aga_step instead, the library
  * evaluating the minibatch losses itself in the iterations that end in a global
  * average (those synchronise, as gpga_aga_step does).
- * Small problems with stored features (least squares or logistic; n*d <= 8192,
- * d <= 512, B <= 32, n*B <= 4096, n*B*d <= 2^17; the simulation of Sec. 5.1 is one) take a second form
- * of the same loop unless option "small_run" is 0: whole iterations - gradients,
+ * With stored features (least squares or logistic), 4 to 128 nodes, d >= 32 and three iterations or
+ * more, up to 32 iterations run in one launch whose workgroups exchange margins and iterates (option
+ * "rows_run"), where that is expected to be faster than what follows; not while a trace is being recorded
+ * or the stream captured.
+ * Small problems with stored features (n*d <= 8192,
+ * d <= 512, B <= 32, n*B <= 4096, n*B*d <= 2^17; the simulation of Sec. 5.1 is one) that do not take
+ * a second form of the same loop unless option "small_run" is 0: whole iterations - gradients,
  * momentum and local update, gossip step or global average, consensus trace - run
  * inside single-workgroup launches of up to 256 iterations with the state in LDS.
  * Other problems with stored features on up to 128 nodes (n*d <= 2^21, up to 4352 samples
@@ -308,14 +312,14 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * 8, 16), "mix_lane_bytes" (sparse-W tile kernel: 0 = automatic (16-byte lanes where the
  * tile of all rows fits in LDS, else 4-byte lanes), 16 or 4 = at most that width, 8 = 8-byte
  * lanes where they fit, else 4), "mix_tile_kb" (sparse-W tile kernel: largest tile in KiB of
- * LDS, 0 = automatic (all a workgroup may have: 160 on this chip), 1..160), "small_run" (gpga_run on small problems: 1 = whole
- * iterations in single-workgroup launches (default), 0 = one kernel per stage),
+ * LDS, 0 = automatic (all a workgroup may have: 160 on this chip), 1..160), "small_run" (gpga_run on small problems that "rows_run"
+ * does not take: 1 = whole iterations in single-workgroup launches (default), 0 = the forms of larger problems),
  * "column_run" (gpga_run on synthetic gradients with up to 256 nodes: 1 = several iterations a
  * launch with the columns on chip (default; not while a trace is being recorded, and not while
  * the stream is being captured), 0 = one iteration at a time),
  * "rows_run" (gpga_run on stored features, 4 to 128 nodes: 1 = several iterations a launch whose workgroups exchange
- * margins and iterates (default; from three iterations on, not while a trace is being recorded, and not while the
- * stream is being captured), 0 = one iteration at a time), "run_wait_us" (how long a workgroup of such a launch waits
+ * margins and iterates, where that is expected to be the faster form (default; from three iterations on, not while a trace
+ * is being recorded, and not while the stream is being captured), 0 = the other forms), "run_wait_us" (how long a workgroup of such a launch waits
  * for another, in microseconds, before the launch is given up and its last workgroup does the work alone, 0..10000000,
  * default 100000; after two such launches of a context iterations go one at a time for a while, 4096 of them and twice as many
  * with every further time, or until "rows_run" is set), "run_give_up" (a test of that: the workgroup, 0..255 modulo their

@@ -748,8 +748,9 @@ __global__ void __launch_bounds__(kSmallRunThreads) k_small_run(const SmallArgs 
 //    nodes, so their reads go ahead four rows at a time and rows of lanes are added by exchanges of registers (one row at a
 //    time and through LDS 100 x 10 63.4 -> 56.2 us, 64 x 20 65.3 -> 54.9; one, two or all rows by a runtime count 58 - 66).
 // Measured with the trace, 50 iterations, one sample a node: n = 100, d = 10 231 us in k_small_run -> 50.5 us here
-// (71 us with loads the compiler could not count).  Rows of 13 to 20 columns with four samples spill 10 to 51 registers a lane
-// and still take a seventh of k_small_run's time (n = 128, d = 20 18.9 us an iteration, 2.3 here).
+// (71 us with loads the compiler could not count).  Rows of 13 to 20 columns with three or four samples spill 10 to 51 registers
+// a lane, logistic ones with momentum and one sample 1 to 3; the former still take a seventh of k_small_run's time (n = 128, d = 20
+// 18.9 us an iteration, 2.3 here).
 __device__ __forceinline__ double quad_sum(double v) {
     v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
     v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]

@@ -5,7 +5,7 @@
 // others exchange, a thread a column, with x and m in LDS.  What workgroups owe each other goes as words that carry their
 // launch's number (gpga_gang.hpp): the slices' shares of the margins within a node, then y = x^(k+1/2) between nodes; at a
 // global average every workgroup adds one n-th of its slice's columns over all nodes and hands the mean on.  Under an adaptive
-// period every workgroup takes the same decisions from the same losses, and the host reads the period once a launch.
+// period every workgroup takes the same decisions from the same losses, and the host reads the period once a launch that averages.
 //
 // An iteration is two trips through memory of 0.7 - 1.2 us (one where P = 1) in the place of two dependent launches of 4 - 5.
 // What bounds it then is code: the instructions between arrival and the next store (3 us an iteration on the smallest problems),
@@ -13,9 +13,11 @@
 // operations are served in order, so that the exchange waits behind rows on their way (32 x 10 000 with 32 samples: 12.5 us an
 // iteration, 6.4 of them the rows from memory).  Hence roles for wavefronts: one that has rows under way cannot look at a word
 // before they have arrived.
-// Whole calls of gpga_run, us, before -> now: 8 iterations on 8 x 1000 with full batches of 100 75.8 -> 61; 50 x 400 158 -> 63;
-// 16 iterations on 32 x 10 000 with 32 samples 389 -> 218; 8 on 35 x 3160 124 -> 57.6, 64 x 3000 with 50 216 -> 113; 12 on
-// 20 x 1001 under the adaptive period 152 -> 89; from a single workgroup: 8 on 9 x 222 with 32 277 -> 37, 28 x 201 142 -> 35.
+// Whole calls of gpga_run, us, two launches an iteration -> this: 8 iterations on 8 x 1000 with full batches of 100 75.8 -> 58; 50 x 400
+// 158 -> 63; 16 iterations on 32 x 10 000 with 32 samples 389 -> 219; 8 on 35 x 3160 124 -> 57.6, 64 x 3000 with 50 216 -> 113; 12 on
+// 20 x 1001 under the adaptive period 143.5 -> 77.3; from a single workgroup: 8 on 9 x 222 with 32 277 -> 37, 28 x 201 142 -> 35.
+// Which runs it takes: rows_run_pays.  Registers: full batches of 13 to 32 slots spill 5 a lane, minibatches of 17 to 20 two, the
+// others none.
 #include <algorithm>
 #include <type_traits>
 

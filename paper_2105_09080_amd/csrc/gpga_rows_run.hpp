@@ -29,7 +29,9 @@ struct RunPlan {
 // (ring or one-peer graph): 20 x 1001 with 16 samples P = 1 / 2 / 4 / 8 5.9 / 6.0 / 4.9 / 5.3; 8 x 845 with 50 15.7 / 7.4 / 5.6 /
 // 6.3; 9 x 222 with 32 4.1 / 4.7 / 4.8 / 5.0; 8 x 1000 full batches of 100 - / 9.2 / 7.0 / 7.8; 6 x 5164 with 16 P = 4 / 8 / 12 / 24
 // 9.7 / 7.5 / 7.0 / 7.3.  The terms: 3.5 us for barriers, update and y; a row of a wavefront, by how many of them share a SIMD;
-// the words of the margins a thread has to look at; half of the time the rows take from memory.
+// the words of the margins a thread has to look at; half of the time the rows take from memory.  They rank plans and no more: there
+// is nothing for an average's share and little for more slices, so that P = 9 is taken on 20 x 1001 and 21 on 6 x 5164, some 8 and 4 %
+// off the best of these; what a run takes in all is run_us.
 inline RunPlan plan_run(int n, int64_t d, int num_cus, int32_t B, bool batches) {
     RunPlan best;
     const int64_t d4 = (d + 3) / 4;
