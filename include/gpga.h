@@ -324,8 +324,8 @@ gpga_status gpga_current_x(const gpga_ctx* ctx, float** x_dev_out);
  * default 100000; after two such launches of a context iterations go one at a time for a while, 4096 of them and twice as many
  * with every further time, or until "rows_run" is set), "run_give_up" (a test of that: the workgroup, 0..255 modulo their
  * number, that gives such a launch up when its share is done, -1 = none (default); while a launch of this kind is
- * under way in one stream, calls on another take one iteration at a time or the forms of small problems, and no call
- * waits for another stream),
+ * under way in one stream, calls on another take one iteration at a time or the forms of small problems, without
+ * waiting for it),
  * "mix_csr_lds" (sparse-W tile kernel: 1 = copy a small W
  * into LDS (default), 0 = read it from global memory), "cycle_kernel" (row-streaming kernel for one-peer
  * steps whose cycles have 2, 4, 8 or 16 rows: -1 = automatic (large problems), 0 = never, 1 = always, on rows

@@ -330,7 +330,7 @@ def test_a_launch_under_way_in_another_stream_leaves_one_iteration_a_launch(hx):
         sim.set_option("small_run", 1)
     torch.cuda.synchronize()
     for (b, idx_b), (ref, ref_idx), path in ((*small, 7), (*large, 9)):
-        for _ in range(20):                  # 20 x 32 iterations: milliseconds
+        for _ in range(80):                  # 80 x 32 iterations: some 20 ms
             a.run(32, idx_a)
         b.run(32, idx_b)
         assert int(b.query("step_path")) == path and not a.stream.query()
